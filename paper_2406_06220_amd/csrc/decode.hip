@@ -59,14 +59,6 @@
 #include "exchange.h"
 #include "tile_gemm.h"
 
-#if TDT_TRACE
-// profiling builds only: copies the recorded time line (see TR in decode_state.h) to the host
-extern "C" int tdt_debug_trace(long long *out, int n)
-{
-    return (int)hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
-}
-#endif
-
 #ifndef TDT_TIMER_GROUP
 #define TDT_TIMER_GROUP 0   // the hypothesis group whose phase timers a build with TDT_PHASE_TIMERS reports
 #endif
@@ -288,25 +280,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
         __syncthreads();
         if (tid == 0) S.pend_n = 0;
     };
-    // Automatic window: as many rows as give every workgroup at most one joint work item of at
-    // most `tiles_per_item` column tiles (then one round, all wavefronts busy).  Unless the
-    // caller fixes it, a work item takes 8 column tiles, one a wavefront, in groups of five
-    // hypotheses or more (the longer windows save more joint passes than the longer items cost:
-    // measured 2 to 5 % at 6 to 13 hypotheses a group) and 4 in smaller groups (1 to 2 % the
-    // other way), more (up to 8) where the group's hypotheses with the smallest window of 4
-    // frames would otherwise make more items than there are workgroups.
-    int auto_rows;
-    {
-        const int NT = (O + CT - 1) / CT;
-        int tiles_per_item = p.joint_tiles;
-        if (tiles_per_item <= 0) {
-            const int row_tiles_min = (G * 4 + RT - 1) / RT;
-            const int groups_fit = max(1, C / row_tiles_min);
-            tiles_per_item = G >= 5 ? 8 : min(8, max(4, (NT + groups_fit - 1) / groups_fit));
-        }
-        const int groups = (NT + tiles_per_item - 1) / tiles_per_item;
-        auto_rows = max(1, C / groups) * RT;
-    }
+    const int auto_rows = auto_joint_rows(C, (O + CT - 1) / CT, p.joint_tiles);
     // streaming joint pass: dies the group's workgroups are spread over, workgroups per die, this
     // one's die and place on it, column tiles per die and this die's first
     const int wide_ndie = C >= kXcds ? kXcds : C, wide_per = C / wide_ndie;
@@ -318,16 +292,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
     // thread per count, so that a pass looks it up instead of dividing.
     for (int n = tid + 1; n <= G; n += kThreads) {
         const int NT = (O + CT - 1) / CT;
-        int Kw = FRAMELOOP ? 1 : p.window;   // Alg. 2 looks at one frame per step
-        if (Kw <= 0) {
-            Kw = auto_rows / n;
-            if (Kw < 3) Kw = 3;   // (2, 4 and 5 measured no better on any benchmark model)
-            // the row tiles this window needs are paid for whole: as many frames as fill them
-            const int fill = (n * Kw + RT - 1) / RT * RT / n;
-            if (fill > Kw) Kw = fill;
-        }
-        if (Kw > kMaxWindow) Kw = kMaxWindow;
-        if (Kw * n > rows_cap) Kw = rows_cap / n;
+        const int Kw = joint_window(n, FRAMELOOP ? 1 : p.window, auto_rows, rows_cap);   // (Alg. 2 looks at one frame per step)
         const int n_tiles = (n * Kw + RT - 1) / RT;
         int n_cg, tpg;
         split_tiles(C, n_tiles, NT, max_cg, n_cg, tpg);
@@ -1274,11 +1239,11 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
     }
 }
 
-__global__ void init_kernel(uint4 *zero, size_t n16, long long *out_stats)
+__global__ void init_kernel(uint4 *zero, size_t n16, uint4 *ones, size_t n16_ones, long long *out_stats)
 {
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += stride)
-        zero[i] = make_uint4(0, 0, 0, 0);
+    const size_t stride = (size_t)gridDim.x * blockDim.x, at = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (size_t i = at; i < n16; i += stride) zero[i] = make_uint4(0, 0, 0, 0);
+    for (size_t i = at; i < n16_ones; i += stride) ones[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
     if (out_stats && blockIdx.x == 0 && threadIdx.x < TDT_STAT_COUNT) out_stats[threadIdx.x] = 0;
 }
 
@@ -1302,14 +1267,14 @@ size_t lds_bytes_for(const tdt_weights_t *w, bool on_the_fly)
 
 }  // namespace
 
-hipError_t launch_init(void *zero_begin, size_t zero_bytes, long long *out_stats, hipStream_t stream)
+hipError_t launch_init(const ClearRanges &clear, long long *out_stats, hipStream_t stream)
 {
-    const size_t n16 = zero_bytes / 16;
-    int blocks = (int)((n16 + 255) / 256);
+    const size_t n16 = clear.zero_bytes / 16, n16_ones = clear.ones_bytes / 16;
+    int blocks = (int)(((n16 > n16_ones ? n16 : n16_ones) + 255) / 256);
     if (blocks > 1024) blocks = 1024;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL(init_kernel, dim3(blocks), dim3(256), 0, stream,
-                       static_cast<uint4 *>(zero_begin), n16, out_stats);
+                       static_cast<uint4 *>(clear.zero), n16, static_cast<uint4 *>(clear.ones), n16_ones, out_stats);
     return hipGetLastError();
 }
 

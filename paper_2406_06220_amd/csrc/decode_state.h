@@ -26,7 +26,7 @@
 #endif
 
 #if TDT_TRACE
-__device__ long long g_trace[8192];   // [0]: events recorded; then (id << 48) | ticks
+static __device__ long long g_trace[8192];   // [0]: events recorded; then (id << 48) | ticks
 namespace tdt {
 namespace {
 __shared__ int g_tr_n, g_tr_on;

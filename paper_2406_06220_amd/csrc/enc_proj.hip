@@ -624,7 +624,7 @@ unsigned pack_blocks_for(const PackBatch &b)
 // is a multiple of the number of dies, so each keeps its die-aware order of tiles.
 __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_bf16_kernel(LinearBatch batch, PackBatch pack,
                                                                    unsigned pack_blocks, uint4 *zero, size_t n16,
-                                                                   long long *out_stats)
+                                                                   uint4 *ones, size_t n16_ones, long long *out_stats)
 {
     unsigned b = blockIdx.x, used = 0;
 #pragma unroll
@@ -645,6 +645,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_bf16_kernel(LinearBat
     const unsigned zb = b, nzb = gridDim.x - used;
     for (size_t i = (size_t)zb * GEMM_THREADS + threadIdx.x; i < n16; i += (size_t)nzb * GEMM_THREADS)
         zero[i] = make_uint4(0, 0, 0, 0);
+    for (size_t i = (size_t)zb * GEMM_THREADS + threadIdx.x; i < n16_ones; i += (size_t)nzb * GEMM_THREADS)
+        ones[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
     if (out_stats && zb == 0 && threadIdx.x < TDT_STAT_COUNT) out_stats[threadIdx.x] = 0;
 }
 
@@ -759,8 +761,8 @@ static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
 
 hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
                                float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
-                               bool on_the_fly, void *packed, void *zero_begin, size_t zero_bytes,
-                               long long *out_stats, hipStream_t stream)
+                               bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
+                               hipStream_t stream)
 {
     LinearBatch batch{};
     int n = 0;
@@ -788,14 +790,14 @@ hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, i
     }
     unsigned blocks = 0;
     for (int i = 0; i < n; ++i) blocks += batch.q[i].blocks;
-    const size_t n16 = zero_bytes / 16;
-    size_t zb = (n16 + GEMM_THREADS - 1) / GEMM_THREADS;
+    const size_t n16 = clear.zero_bytes / 16, n16_ones = clear.ones_bytes / 16;
+    size_t zb = ((n16 > n16_ones ? n16 : n16_ones) + GEMM_THREADS - 1) / GEMM_THREADS;
     if (zb > 256) zb = 256;
     if (zb < 1) zb = 1;
     const PackBatch pack = pack_batch(w, pl, on_the_fly, packed);
     const unsigned pb = pack.pieces > 0 ? pack_blocks_for(pack) : 0;
     hipLaunchKernelGGL(prepare_bf16_kernel, dim3(blocks + pb + (unsigned)zb), dim3(GEMM_THREADS), 0, stream, batch,
-                       pack, pb, static_cast<uint4 *>(zero_begin), n16, out_stats);
+                       pack, pb, static_cast<uint4 *>(clear.zero), n16, static_cast<uint4 *>(clear.ones), n16_ones, out_stats);
     return hipGetLastError();
 }
 

@@ -275,6 +275,36 @@ __device__ inline void split_tiles(int C, int n_row_tiles, int n_units, int max_
     n_groups = (n_units + per_group - 1) / per_group;
 }
 
+// Automatic window of a joint pass: as many rows as give every workgroup at most one joint work
+// item of at most `tiles_per_item` column tiles.  Unless the caller fixes it, an item takes four
+// column tiles -- one round of label_loop.hip -- where the group has workgroups for three row tiles
+// of such items (config 2 at B = 32, five groups of 51: 1.40 ms against 1.57 ms with eight), else
+// eight, two rounds: there the longer windows save more passes than the second round costs (B = 128,
+// eight groups of 32: 2.71 ms against 3.21 ms with four); twelve in groups too small for two row tiles
+// of those (B = 256, 16 groups of 16: 4.59 ms against 4.99 ms with eight).
+// C workgroups, NT column tiles of the output layer.
+__device__ inline int auto_joint_rows(int C, int NT, int joint_tiles)
+{
+    const int four = C / ((NT + 3) / 4), eight = C / ((NT + 7) / 8);
+    const int tiles_per_item = joint_tiles > 0 ? joint_tiles : four >= 3 ? 4 : eight >= 2 ? 8 : 12;
+    return max(1, C / ((NT + tiles_per_item - 1) / tiles_per_item)) * RT;
+}
+// frames per hypothesis when n of them search (window: the caller's, 0 = automatic)
+__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap)
+{
+    int Kw = window;
+    if (Kw <= 0) {
+        Kw = auto_rows / n;
+        if (Kw < 3) Kw = 3;   // (2, 4 and 5 measured no better on any benchmark model)
+        // the row tiles this window needs are paid for whole: as many frames as fill them
+        const int fill = (n * Kw + RT - 1) / RT * RT / n;
+        if (fill > Kw) Kw = fill;
+    }
+    if (Kw > kMaxWindow) Kw = kMaxWindow;
+    if (Kw * n > rows_cap) Kw = rows_cap / n;
+    return Kw;
+}
+
 }  // namespace
 }  // namespace tdt
 

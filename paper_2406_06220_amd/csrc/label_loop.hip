@@ -1,0 +1,1561 @@
+// The label-looping decoder (paper Algorithm 3, Sec. 3.2; TDT Sec. 3.3) as a chain of three
+// exchanges per label.  decode.hip holds the general kernel and explains the phases P (predictor
+// step), Q (products with the new predictor state), J (joint pass) and D (decision); this one runs
+// the same phases for the default loops (label-looping, precomputed projections) of groups of at
+// most kLabelMaxHyps hypotheses whose rows fit one staging tile, and is built for the length of
+// the chain: at the benchmark sizes a label costs two exchanges between workgroups that are
+// about 1.4 us each whatever they carry, so what matters is how many dependent steps there are
+// between them and how few instructions each takes.
+//
+//   * No barriers between workgroups.  Every exchanged word says itself whether it is there: rows
+//     of the hidden state and of the projected predictor output start out as a bit pattern that no
+//     result has, argmax / softmax cells as zero.  A reader loads what it needs and loads it again
+//     until all of it is there, so data and "it is complete" travel together (measured for 32
+//     workgroups all exchanging 10 KB: 1.45 us against 2.08 us with flags that are polled before
+//     the data is loaded).  Words are put back by their writer once everybody has read them; see
+//     "Reuse of the exchange buffers" below.
+//   * A workgroup owns its column tiles of the predictor-side matrices for the whole call.  The four
+//     gates of a unit meet in the workgroup that updates the unit's cell, so the recurrent
+//     pre-activations and the cell state never leave its LDS; only h is exchanged.
+//   * The control state of a hypothesis (frame, label count, last labels, score ...) lives in lane g
+//     of every wavefront, the lists of active and searching hypotheses are 64-bit masks: a decision
+//     is taken by every wavefront on its own, without a workgroup barrier or LDS list.
+//   * Four wavefronts a workgroup, one per SIMD.  What a label costs beside the exchanges is the number
+//     of instructions in a row, and two wavefronts that share a SIMD take turns at them.  It also
+//     leaves 512 registers a lane: the workgroup's predictor-side weights stay in registers for the
+//     whole call where they fit one round.
+//   * In a work item every wavefront multiplies its own quarter of the reduction for all column
+//     tiles, so an activation fragment is read from LDS once; encoder rows and weight fragments of
+//     the first joint pass are requested while the hidden state is exchanged.
+//
+// Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
+// exchange (a workgroup without work item: a word of its own that everybody waits for), after it
+// has finished reading all earlier exchanges.  So a workgroup that has read joint exchange j knows
+// that all others have read joint exchange j - 1 and the h and projection rows of this label: it
+// puts its own words of those back.  The stores complete before it publishes joint exchange j + 1
+// (every wavefront waits for its stores before the workgroup barrier that precedes publishing), and
+// the next readers of those words come only behind that exchange: rows alternate between two
+// buffers by label, cells rotate through four.
+#include <math.h>
+
+#include <mutex>
+#include <type_traits>
+
+#include "tdt_internal.h"
+#include "decode_state.h"
+#include "exchange.h"
+#include "tile_gemm.h"
+
+#if TDT_TRACE
+// profiling builds only: copies the recorded time line (see TR in decode_state.h) to the host
+extern "C" int tdt_debug_trace(long long *out, int n)
+{
+    return (int)hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
+}
+#endif
+
+namespace tdt {
+namespace {
+
+constexpr unsigned kAbsent = 0xffffffffu;   // an exchanged float that is not there yet (a NaN no result is stored as)
+constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
+constexpr int kLW = kLabelThreads / 64;     // wavefronts of a workgroup
+constexpr int kRW = RT / kLW;               // rows of a tile a wavefront stages
+
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+
+// what differs between the element types: a fragment is 1 KiB = 16 columns x KS inputs
+template <typename WT> struct Frags;
+template <> struct Frags<uint16_t> {
+    static constexpr int KS = 32, PL = 3;
+    typedef bf16x8 A;
+    // element offset of lane's part of an activation row at step s
+    __device__ static int aoff(int s, int lane) { return s * 32 + (lane >> 4) * 8; }
+    __device__ static f32x4 mma(const A &a, const v4u &b, f32x4 c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8 *>(&b), c, 0, 0, 0);
+    }
+};
+template <> struct Frags<float> {
+    static constexpr int KS = 16, PL = 1;
+    typedef f32x4 A;
+    __device__ static int aoff(int s, int lane) { return s * 16 + (lane >> 4) * 4; }
+    __device__ static f32x4 mma(const A &a, const v4u &b, f32x4 c)
+    {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(b.z), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(b.w), c, 0, 0, 0);
+    }
+};
+
+__device__ inline float present(float v) { return __float_as_uint(v) == kAbsent ? __uint_as_float(0x7fc00000u) : v; }
+__device__ inline void st_co4(float *p, float4 v)   // two 8-byte stores of agent scope
+{
+    unsigned long long *q = reinterpret_cast<unsigned long long *>(p);
+    st_co64(q, (unsigned long long)__float_as_uint(v.x) | ((unsigned long long)__float_as_uint(v.y) << 32));
+    st_co64(q + 1, (unsigned long long)__float_as_uint(v.z) | ((unsigned long long)__float_as_uint(v.w) << 32));
+}
+// Buffer descriptor of `bytes` bytes of device memory from `base` on, the same in every lane.  A load
+// then takes a lane offset and a scalar offset, so that the addresses of many loads of one array
+// cost one scalar addition each; reads beyond the end give zeros.
+__device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *base, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ inline float4 as_float4(v4u v)
+{
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
+}
+__device__ inline unsigned umax4(v4u v) { return max(max(v.x, v.y), max(v.z, v.w)); }
+// agent scope: what another workgroup writes (see ld_co4)
+__device__ inline v4u ldx4(__amdgpu_buffer_rsrc_t rs, int lane_off, int off)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, off, 16 /* sc1 */);
+}
+// what no workgroup writes while the kernel runs; row is the same in every lane
+__device__ inline v4u ldg4(const float *row, unsigned lane_off)
+{
+    return *(const TDT_GLOBAL v4u *)(reinterpret_cast<const char *>(row) + lane_off);
+}
+// Gives registers a value without an instruction.  An array of which a pass fills only a part needs it:
+// what is not filled would otherwise be the value of the pass before, held in registers all the way.
+template <typename T, int N> __device__ inline void any_value(T (&x)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "=v"(x[i]));
+}
+template <typename T, int M, int N> __device__ inline void any_value(T (&x)[M][N])
+{
+#pragma unroll
+    for (int i = 0; i < M; ++i) any_value(x[i]);
+}
+// a value the compiler must not compute ahead of the loop it is used in (it would be kept, and
+// spilled, through the whole label loop for the sake of an addition)
+__device__ inline int here(int v)
+{
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+// sum / maximum over the lanes that share l % 16, in all of them
+__device__ inline float sum_over_rows(float v)
+{
+    auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(x[0]) + __uint_as_float(x[1]);
+}
+__device__ inline unsigned long long max_over_rows(unsigned long long v)
+{
+    auto lo = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
+    unsigned long long a = lo[0] | ((unsigned long long)hi[0] << 32), b = lo[1] | ((unsigned long long)hi[1] << 32);
+    v = a > b ? a : b;
+    lo = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    hi = __builtin_amdgcn_permlane32_swap((unsigned)(v >> 32), (unsigned)(v >> 32), false, false);
+    a = lo[0] | ((unsigned long long)hi[0] << 32);
+    b = lo[1] | ((unsigned long long)hi[1] << 32);
+    return a > b ? a : b;
+}
+// 1 / (1 + exp(-x)) on the hardware exponential and reciprocal, the latter with one Newton step
+// (the exponential is kept finite so that the step sees no infinity)
+__device__ inline float sigmoid(float x)
+{
+    const float d = 1.0f + fminf(__expf(-x), 1e38f), r = __builtin_amdgcn_rcpf(d);
+    return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
+
+// how a joint pass with n searching hypotheses is cut (tabulated per n when the kernel starts)
+struct LabelPlan {
+    short Kw, n_tiles, n_cg, tpg;
+    int rcp_kw;
+    short ti0, cg0;   // this workgroup's first work item
+};
+
+struct LabelShared {
+    LabelPlan plan[kLabelMaxHyps + 1];
+    unsigned long long rowb[kLabelRowsPerPass];    // best label of each row (or shares of it, see the gather)
+    unsigned long long rowd[kLabelRowsPerPass];    // frame step of the best duration class of each row
+    unsigned long long rowl[kLabelRowsPerPass];    // softmax share of each row (groups of one workgroup only)
+    int res_a[kLabelRowsPerPass], res_d[kLabelRowsPerPass];   // passes of more than 64 rows: label, frame step
+    int gid[kLabelMaxHyps];
+    int durations[TDT_MAX_DURATIONS];
+    int aborted;
+    long long tk[5], tk_last, tk_start;   // profiling builds: P, Q, J, D, waits
+};
+
+// LAYERS: 0: stateless predictor; 1: one LSTM layer, a workgroup's column tiles fit one round and the
+// group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
+template <typename WT, int LAYERS, bool CHUNKED, int NK>
+__global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
+{
+    typedef Frags<WT> F;
+    typedef typename F::A AFrag;
+    constexpr int PL = F::PL, KS = F::KS;
+    constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1;
+    constexpr int TR = label_tiles(NK);              // column tiles per round of a joint pass
+    constexpr int TQ = DEEP ? TR : 2 * TR;           // ... and of the predictor-side products
+    constexpr int PLD = TQ * CT + 4;                 // floats per row of the partial sums (padded: 16 rows, 64 banks)
+    constexpr int KI = (NK * kLW * KS + 255) / 256;  // 16-byte loads per lane for a row
+    extern __shared__ __align__(16) unsigned char dyn_lds[];
+    __shared__ LabelShared S;
+
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Called where a phase starts: what the phase derives from the thread's index is computed there.
+    // Without it the compiler computes all of it once ahead of the label loop, a hundred registers that
+    // it then spills.
+    auto fresh = [&]() __attribute__((always_inline)) {
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+    };
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int ncl = p.n_clusters;
+    const int C = gridDim.x / ncl;
+    // which group, and which place in it: as in decode.hip, every die hosts the same ranks of
+    // every group, so that its L2 keeps the columns those ranks multiply by
+    int cl, rank;
+    if (gridDim.x % kXcds == 0) {
+        const int die = blockIdx.x % kXcds, j = blockIdx.x / kXcds;
+        const int per = (int)(gridDim.x / kXcds) / ncl;
+        if (j < per * ncl) {
+            cl = j % ncl;
+            rank = die * per + j / ncl;
+        } else {
+            const int e = (j - per * ncl) * kXcds + die;
+            if (e >= ncl * (C - kXcds * per)) return;   // an empty slot: not part of any group
+            cl = e % ncl;
+            rank = kXcds * per + e / ncl;
+        }
+    } else {
+        cl = blockIdx.x % ncl;
+        rank = blockIdx.x / ncl;
+    }
+    const int B = p.B, T = p.T, H = p.H, V = p.V, D = p.D, O = p.O, VL = p.VL;
+    const bool big_blanks = p.multi_blank != 0;
+    const int hpc = p.hyps_per_cluster, b0 = cl * hpc, Bw = ncl * hpc;
+    // the group's hypotheses: dealt by length, longest first, as in decode.hip
+    const bool ranked = ncl > 1 && B <= kMaxRankedBatch;
+    int G;
+    if (ranked) {
+        const int full = B / ncl, rem = B % ncl;
+        const int pos_in_last = (full & 1) ? ncl - 1 - cl : cl;
+        G = full + (pos_in_last < rem ? 1 : 0);
+    } else {
+        G = B - b0;
+        if (G > hpc) G = hpc;
+    }
+    if (G <= 0) return;   // the whole group leaves together
+    if (ranked) {
+        int *lens = reinterpret_cast<int *>(dyn_lds);
+        for (int b = tid; b < B; b += kLabelThreads) lens[b] = min(max(p.enc_len[b], 0), T);
+        __syncthreads();
+        for (int b = tid; b < B; b += kLabelThreads) {
+            const int lb = lens[b];
+            int r = 0;
+            for (int b2 = 0; b2 < B; ++b2) {
+                const int l2 = lens[b2];
+                r += (l2 > lb || (l2 == lb && b2 < b)) ? 1 : 0;
+            }
+            const int round = r / ncl, pos = r - round * ncl;
+            if (((round & 1) ? ncl - 1 - pos : pos) == cl) S.gid[round] = b;
+        }
+        __syncthreads();   // the lengths are not needed any more
+    } else {
+        if (tid < G) S.gid[tid] = b0 + tid;
+    }
+    const int Hp = p.h_pred, L = DEEP ? p.pred_layers : 1;
+
+    // ---- LDS: the activation tile, the partial sums of a round, and what this workgroup keeps of
+    // its own units: recurrent pre-activations, cell state, (chunks) hidden state
+    const int ldb = ActTile<WT>::row_elems(p.kseg_max);
+    WT *const planes = reinterpret_cast<WT *>(dyn_lds);
+    const int plane = RT * ldb;
+    float *const part = reinterpret_cast<float *>(dyn_lds + (size_t)PL * plane * sizeof(WT));   // [kLW][16][PLD]
+    ActTile<WT> A;
+    A.planes = reinterpret_cast<decltype(A.planes)>(planes);
+    A.ldb = ldb;
+    for (int i = tid; i < p.lds_bytes / 16; i += kLabelThreads)
+        reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
+
+    // ---- this workgroup's column tiles of the predictor side: a stretch of [W_pred | W_hh] tiles,
+    // and with it a stretch of hidden units (of every layer)
+    const int nst_h = (Hp + KS - 1) / KS, nst_j = (H + KS - 1) / KS;   // fragments per tile
+    const int NT_A = (H + CT - 1) / CT, NT_B = LSTM ? (Hp + 3) / 4 : 0;
+    const int QT = LSTM ? (NT_A + NT_B + C - 1) / C : 0;
+    const int qt0 = rank * QT, nq = LSTM ? max(0, min(QT, NT_A + NT_B - qt0)) : 0;
+    const int na = max(0, min(NT_A - qt0, nq)), nr = nq - na;          // tiles of W_pred, of W_hh
+    const int r0 = max(qt0 - NT_A, 0);                                 // first W_hh tile
+    const int u0 = r0 * 4, U = nr > 0 ? min(nr * 4, Hp - u0) : 0;      // hidden units owned
+    const int Upad = QT * 4;
+    float4 *const rg_l = reinterpret_cast<float4 *>(part + kLW * RT * PLD);               // [L][hpc][Upad]
+    float *const c_l = reinterpret_cast<float *>(rg_l + (size_t)(LSTM ? L * hpc * Upad : 0));
+    float *const h_l = c_l + (LSTM ? L * hpc * Upad : 0);                                 // (chunks only)
+
+    const int rows_cap = p.rows_per_cluster;
+    float *const hx = p.hbuf;         // [2][L][Bw][Hp]
+    float *const px = p.pred_proj;    // [2][Bw][H]
+    const int cells = p.cells_per_cluster;   // joint cells of one buffer (work items x 16)
+    unsigned long long *const jb = p.row_lab + (size_t)cl * kRowBufs * cells;              // packed (logit, ~label)
+    unsigned long long *const jl = p.row_lse + (size_t)cl * kRowBufs * cells;              // (largest logit, sum of exp)
+    unsigned long long *const jd = p.row_dur + (size_t)cl * kRowBufs * 2 * rows_cap;
+    unsigned long long *const jh = p.present + (size_t)cl * (kRowBufs + 1) * C;   // (the last: state has been read)
+
+    // ---- Alg. 3 lines 3-4.  Lane g of every wavefront holds hypothesis g of the group
+    __syncthreads();
+    const bool mine = lane < G;
+    const int gid = mine ? S.gid[lane] : 0;
+    int len = mine ? p.enc_len[gid] : 0, status = 0;
+    if (len < 0) { len = 0; status = TDT_HYP_LEN_CLAMPED; }
+    if (len > T) { len = T; status = TDT_HYP_LEN_CLAMPED; }
+    int time = 0, sym = 0, last = V, last2 = V, olen = 0;
+    float score = 0.0f;   // (of the hypotheses whose scores this workgroup sums: slot % C == rank)
+    bool started = false;
+    if (CHUNKED && mine) {
+        started = p.st_started[gid] != 0;
+        time = max(p.st_time[gid], 0);
+        if (started) {
+            last = min(max(p.st_last[gid], 0), V);
+            last2 = min(max(p.st_last2[gid], 0), V);
+        }
+    }
+    bool active = mine && time < len;
+    const unsigned long long carried = CHUNKED ? __ballot(active && started) : 0ull;   // bring a state along
+    const unsigned long long took_part = __ballot(active);
+    started = started || active;
+    if (tid < TDT_MAX_DURATIONS) S.durations[tid] = p.durations[tid];
+    if (tid == 0) {
+#if TDT_TRACE
+        g_tr_n = 0;
+        g_tr_on = 0;
+#endif
+        S.aborted = 0;
+        for (int a = 0; a < 5; ++a) S.tk[a] = 0;
+        S.tk_last = S.tk_start = wall_clock64();
+    }
+    enum { kTkP = 0, kTkQ, kTkJ, kTkD, kTkBar };
+    auto lap = [&](int bucket) {   // profiling builds only: see decode.hip
+        if (TDT_PHASE_TIMERS && tid == 0) {
+            const long long now = wall_clock64();
+            S.tk[bucket] += now - S.tk_last;
+            S.tk_last = now;
+        }
+    };
+    if (CHUNKED) {   // rank 0 writes the new state when everybody has read the old one
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) st_co64(jh + (size_t)kRowBufs * C + rank, 1ull);
+    }
+    const int owner_mod = mine ? lane % C : -1;
+
+    // ---- how a joint pass is cut, per number of searching hypotheses
+    const int NT = (O + CT - 1) / CT;
+    {
+        const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles);
+        for (int n = tid + 1; n <= G; n += kLabelThreads) {
+            const int Kw = joint_window(n, p.window, rows_auto, rows_cap);
+            const int n_tiles = (n * Kw + RT - 1) / RT;
+            int n_cg, tpg;
+            split_tiles(C, n_tiles, NT, C, n_cg, tpg);
+            LabelPlan pl;
+            pl.Kw = (short)Kw;
+            pl.rcp_kw = ((1 << 20) + Kw - 1) / Kw;
+            pl.n_tiles = (short)n_tiles;
+            pl.n_cg = (short)n_cg;
+            pl.tpg = (short)tpg;
+            pl.ti0 = (short)(rank / n_cg);
+            pl.cg0 = (short)(rank % n_cg);
+            S.plan[n] = pl;
+        }
+    }
+    __syncthreads();
+
+    unsigned st_pred_passes = 0, st_joint_passes = 0;
+    long long st_pred_rows = 0, st_joint_rows = 0;
+
+    // A wavefront whose data is not there yet: every 64th time it looks whether to give up.
+    auto give_up = [&](unsigned &spins, long long &since) -> bool {
+        if (spins == 0) since = wall_clock64();
+        if ((++spins & 63u) != 0u) return false;
+        int stop = 0;
+        if (lane == 0) {
+            if (__hip_atomic_load(p.abort_flag, __ATOMIC_RELAXED, TDT_AGENT)) {
+                stop = 1;
+            } else if (wall_clock64() - since > p.timeout_ticks) {
+                __hip_atomic_store(p.abort_flag, 1, __ATOMIC_RELAXED, TDT_AGENT);
+                stop = 1;
+            }
+        }
+        stop = uni(stop);
+        if (stop && lane == 0) S.aborted = 1;
+        return stop != 0;
+    };
+    // waits until the words of every lane are there (zero: not yet) and returns them
+    auto wait_word = [&](const unsigned long long *q) __attribute__((always_inline)) {
+        unsigned spins = 0;
+        long long since = 0;
+        for (;;) {
+            const unsigned long long x = ld_co64(q);
+            if (__ballot(x == 0ull) == 0ull || give_up(spins, since)) return x;
+        }
+    };
+
+    // ---- which steps of a reduction of nst steps this wavefront takes: a contiguous stretch, the
+    // first nst % kLW wavefronts one step more
+    const int hs0 = wave * (nst_h / kLW) + min(wave, nst_h % kLW), hsn = nst_h / kLW + (wave < nst_h % kLW ? 1 : 0);
+    const int js0 = wave * (nst_j / kLW) + min(wave, nst_j % kLW), jsn = nst_j / kLW + (wave < nst_j % kLW ? 1 : 0);
+    // ---- weight fragments of a round; tile_off(t): byte offset of tile t among the fragment-major
+    // copies
+    const __amdgpu_buffer_rsrc_t wrs = buffer_of(p.packed, p.packed_bytes);
+    auto fetch = [&](auto &b, int n, int s0, int sn, auto tile_off) __attribute__((always_inline)) {
+        constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
+        any_value(b);
+#pragma unroll
+        for (int t = 0; t < TT; ++t)
+            if (t < n) {   // uniform
+                const int w = tile_off(t) + s0 * 1024;
+#pragma unroll
+                for (int s = 0; s < NK; ++s)   // (a step too many: some fragment, not used)
+                    b[t][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16, w + (s < sn ? s : 0) * 1024, 0);
+            }
+    };
+    // The round's products, into this wavefront's share of the partial sums.  A step beyond the
+    // wavefront's share reads the padding at the end of a tile row, which is zero.  The tile count is
+    // rounded up to what is compiled (what stands in the registers of the other tiles is multiplied
+    // too, and nobody looks at it): without branches between them the products of the tiles overlap.
+    // PACKED: the planes of a row are rows of one tile.
+    auto products_of = [&](auto packed_tag, auto count, const AFrag (&a)[NK][PL], const auto &b) __attribute__((always_inline)) {
+        constexpr bool PACKED = decltype(packed_tag)::value;
+        constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED ? 2 : 3;   // chains per tile
+        f32x4 c[N][NC];
+#pragma unroll
+        for (int t = 0; t < N; ++t)
+#pragma unroll
+            for (int ch = 0; ch < NC; ++ch) c[t][ch] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                if constexpr (PL == 1 || PACKED) {
+                    c[t][s % 2] = F::mma(a[s][0], b[t][s], c[t][s % 2]);
+                } else {
+#pragma unroll
+                    for (int pl = 0; pl < PL; ++pl) c[t][pl] = F::mma(a[s][pl], b[t][s], c[t][pl]);
+                }
+            }
+        float *const pw = part + (size_t)wave * RT * PLD + (lane >> 4) * 4 * PLD + (lane & 15);
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+            f32x4 sum = c[t][NC - 1];   // smallest terms first
+#pragma unroll
+            for (int ch = NC - 2; ch >= 0; --ch) sum = c[t][ch] + sum;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) pw[e * PLD + t * CT] = sum[e];
+        }
+    };
+    auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n) __attribute__((always_inline)) {
+        constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
+        const std::integral_constant<int, TT / 2> half{};
+        const std::integral_constant<int, TT> all{};
+        if (n <= TT / 2) products_of(packed_tag, half, a, b);
+        else products_of(packed_tag, all, a, b);
+    };
+    // the activation fragments of this wavefront's steps
+    auto load_a = [&](auto packed_tag, AFrag (&a)[NK][PL], int s0, int sn) __attribute__((always_inline)) {
+        constexpr bool PACKED = decltype(packed_tag)::value;
+        const WT *row = planes + (lane & 15) * ldb;
+        const int o0 = F::aoff(s0, lane), zero = ldb - 16 / (int)sizeof(WT);
+#pragma unroll
+        for (int s = 0; s < NK; ++s) {
+            const int o = s < sn ? o0 + s * KS : zero;
+#pragma unroll
+            for (int pl = 0; pl < (PACKED ? 1 : PL); ++pl) a[s][pl] = *reinterpret_cast<const AFrag *>(row + pl * plane + o);
+        }
+    };
+    const std::true_type packed_rows{};
+    const std::false_type full_rows{};
+    // four neighbouring columns of a row of the partial sums, summed over the wavefronts
+    auto gather = [&](int row, int quad) __attribute__((always_inline)) {
+        const float *q = part + (size_t)row * PLD + quad * 4;
+        float4 v = *reinterpret_cast<const float4 *>(q);
+#pragma unroll
+        for (int w = 1; w < kLW; ++w) {
+            const float4 x = *reinterpret_cast<const float4 *>(q + (size_t)w * RT * PLD);
+            v.x += x.x;
+            v.y += x.y;
+            v.z += x.z;
+            v.w += x.w;
+        }
+        return v;
+    };
+    // inputs k .. k+3 of row i of the tile (bfloat16: x == hi + lo + lo2 as in ActTile::split3, two
+    // elements packed per instruction)
+    auto put = [&](auto packed_tag, int i, int k, float4 v) __attribute__((always_inline)) {
+        if constexpr (PL == 3) {
+            const int pstride = decltype(packed_tag)::value ? kPackRows * ldb : plane;   // (packed: plane pl of row i is row pl * 4 + i)
+            WT *o = planes + i * ldb + k;
+            float x0 = v.x, x1 = v.y, x2 = v.z, x3 = v.w;
+            auto top = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
+            auto pack = [](float lo, float hi) {
+                return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+            };
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                *reinterpret_cast<uint2 *>(o + pl * pstride) = make_uint2(pack(x0, x1), pack(x2, x3));
+                if (pl < 2) {
+                    x0 -= top(x0);
+                    x1 -= top(x1);
+                    x2 -= top(x2);
+                    x3 -= top(x3);
+                }
+            }
+        } else {
+            A.store4(i, k, v);
+        }
+    };
+    // zeros between the end of rows of K inputs and the next multiple of 32 (where there is such a gap):
+    // what stood there is multiplied by zeros, but must be a number
+    auto pad_rows = [&](int K) __attribute__((always_inline)) {
+        if (K & 31) {   // uniform
+            const int k = K + (lane & 7) * 4;
+            if (k < (K + 31) / 32 * 32)
+                for (int pl = 0; pl < PL; ++pl)
+                    for (int i = tid >> 3; i < RT; i += kLabelThreads / 8) {
+                        WT *o = planes + pl * plane + i * ldb + k;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = 0;
+                    }
+        }
+    };
+    const bool qpack = PL == 3 && G <= kPackRows;
+
+    // byte offsets of this workgroup's predictor-side tiles (the fragment-major copies)
+    const int hbytes = nst_h * 1024, jbytes = nst_j * 1024;
+    auto q_tile = [&](int t) {
+        const int q = qt0 + t;
+        return q < NT_A ? p.off_w_pred + q * hbytes : p.off_w_hh[L - 1] + (q - NT_A) * hbytes;
+    };
+
+    // the LSTM cell of one unit: new cell value and new hidden value
+    auto cell = [&](float4 g4, float c_old, float &cn, float &hn) __attribute__((always_inline)) {
+        const float ig = sigmoid(g4.x), fg = sigmoid(g4.y);
+        const float gg = 2.0f * sigmoid(2.0f * g4.z) - 1.0f;
+        const float og = sigmoid(g4.w);
+        cn = fg * c_old + ig * gg;
+        hn = og * (2.0f * sigmoid(2.0f * cn) - 1.0f);
+    };
+
+    // what lane l reads of a row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
+    auto hoff = [&](int kk) { return min(lane * 4 + kk * 256, Hp - 4) * (int)sizeof(float); };
+    auto joff = [&](int kk) { return min(lane * 4 + kk * 256, H - 4) * (int)sizeof(float); };
+    const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, (size_t)2 * L * Bw * Hp * sizeof(float));
+    const __amdgpu_buffer_rsrc_t prs = buffer_of(px, (size_t)2 * Bw * H * sizeof(float));
+    const __amdgpu_buffer_rsrc_t brs = buffer_of(p.b_out, (size_t)O * sizeof(float));
+    // Rows of this label iteration's hidden state (row0: the group's first row in the exchange buffer):
+    // loads, waits, splits into the tile.  R rows a wavefront, all of them always: a slot without an
+    // active hypothesis repeats one that has (no branches, and nobody looks at the row).
+    auto stage_h = [&](auto rows_tag, auto packed_tag, int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
+        constexpr int R = decltype(rows_tag)::value;
+        v4u v[R][KI];
+        int off[R];
+        const int any = __ffsll((long long)in_tile) - 1;
+#pragma unroll
+        for (int ii = 0; ii < R; ++ii) {
+            const int g = wave + ii * kLW;
+            off[ii] = (row0 + tq * RT + ((in_tile >> g) & 1ull ? g : any)) * Hp * (int)sizeof(float);
+        }
+        unsigned spins = 0;
+        long long since = 0;
+#pragma clang loop unroll(disable)
+        for (;;) {
+            unsigned mx = 0;
+#pragma unroll
+            for (int ii = 0; ii < R; ++ii)
+#pragma unroll
+                for (int kk = 0; kk < KI; ++kk) v[ii][kk] = ldx4(hrs, hoff(kk), off[ii]);
+#pragma unroll
+            for (int ii = 0; ii < R; ++ii)
+#pragma unroll
+                for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(v[ii][kk]));
+            if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+        }
+        TR(11);
+#pragma unroll
+        for (int ii = 0; ii < R; ++ii)
+#pragma unroll
+            for (int kk = 0; kk < KI; ++kk)   // (lanes beyond the row's end write its last inputs again)
+                put(packed_tag, wave + ii * kLW, hoff(kk) / (int)sizeof(float), as_float4(v[ii][kk]));
+        pad_rows(Hp);
+    };
+    auto stage_h_any = [&](int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
+        const std::integral_constant<int, 1> one{};
+        const std::integral_constant<int, 2> two{};
+        const std::integral_constant<int, kRW> four{};
+        if (qpack) stage_h(one, packed_rows, row0, tq, in_tile);
+        else if (G <= 2 * kLW) stage_h(two, full_rows, row0, tq, in_tile);
+        else stage_h(four, full_rows, row0, tq, in_tile);
+    };
+
+    const int p_g = U > 0 ? tid / U : kLabelMaxHyps, p_u = U > 0 ? tid - p_g * U : 0;   // this thread's first cell
+    int par = 0;                     // which buffer this label's rows go through
+    unsigned jpass = 0;              // joint exchanges so far
+    int prev_items = 0, prev_tiles = 0, prev_cg = 1;   // the last pass: work items, row tiles, column groups
+    int clr_items = 0, clr_tiles = 0;                  // the one before it
+    unsigned long long act_prev = 0ull;        // who took part in the previous label's rows
+    bool first = true, ok = true;
+
+    // puts back what this workgroup wrote in the label iteration before (see the head of the file)
+    auto clear_rows = [&]() __attribute__((always_inline)) {
+        const int pb = par ^ 1;
+        if (U > 0)
+#pragma clang loop unroll(disable)
+            for (int base = 0; base < G * U; base += kLabelThreads) {
+                const int idx = base + tid;
+                int g = p_g, u = p_u;
+                if (base > 0) {
+                    g = idx / U;
+                    u = idx - g * U;
+                }
+                if (g < G && ((act_prev >> g) & 1ull))
+#pragma clang loop unroll(disable)
+                    for (int l = 0; l < L; ++l)
+                        st_co(hx + (((size_t)pb * L + l) * Bw + b0 + g) * Hp + u0 + u, __uint_as_float(kAbsent));
+            }
+        if (na > 0) {
+            const int c = (tid & 15) * 4, nc = min(na * CT, H - qt0 * CT);   // (H is a multiple of 8)
+            const float m = __uint_as_float(kAbsent);
+#pragma clang loop unroll(disable)
+            for (int c0 = 0; c0 < nc; c0 += 64)
+#pragma clang loop unroll(disable)
+                for (int g = tid >> 4; g < G; g += RT)
+                    if (((act_prev >> g) & 1ull) && c0 + c < nc)
+                        st_co4(px + ((size_t)pb * Bw + b0 + g) * H + qt0 * CT + c0 + c, make_float4(m, m, m, m));
+        }
+    };
+    // ... and its cells of the joint pass before the last
+    auto clear_cells = [&]() __attribute__((always_inline)) {
+        if (C > 1 && jpass > 1) {
+            const unsigned pb = (jpass - 2) & (kRowBufs - 1);
+#pragma clang loop unroll(disable)
+            for (int it = rank; it < clr_items; it += C)
+                if (tid < 2 * RT) st_co64((tid < RT ? jb : jl) + (size_t)pb * cells + (size_t)it * RT + (tid & 15), 0ull);
+            if (D > 0)   // (whoever wrote them: the words of a row tile are put back by rank ti)
+#pragma clang loop unroll(disable)
+                for (int ti = rank; ti < clr_tiles; ti += C)
+                    if (tid < 2 * RT) st_co64(jd + ((size_t)pb * rows_cap + (size_t)ti * RT) * 2 + tid, 0ull);
+            if (rank >= clr_items && tid == 0) st_co64(jh + (size_t)pb * C + rank, 0ull);
+        }
+    };
+
+    // ---- score terms of the labels found in the last pass, summed while the next pass's cells travel.
+    // A hypothesis' score is summed by the workgroup of rank slot % C.
+    bool pend = false;       // lane g: hypothesis g has a term to add
+    int pend_row = 0;        // the row its label was found in
+    float pend_m = 0.0f;     // that row's largest label logit
+    auto finish_scores = [&]() {
+        unsigned long long m = __ballot(pend && owner_mod == rank);
+        while (m != 0ull) {   // uniform
+            const int g = __ffsll((long long)m) - 1;
+            m &= m - 1ull;
+            const int r = __builtin_amdgcn_readlane(pend_row, g);
+            const float rowm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pend_m), g));
+            float s = 0.0f;
+#pragma clang loop unroll(disable)
+            for (int c0 = 0; c0 < prev_cg; c0 += 64) {
+                const int c = min(c0 + lane, prev_cg - 1);
+                const unsigned long long x =
+                    C == 1 ? S.rowl[r]
+                           : wait_word(jl + (size_t)((jpass - 1) & (kRowBufs - 1)) * cells +
+                                       ((size_t)(r >> 4) * prev_cg + c) * RT + (r & 15));
+                const float cm = __uint_as_float((unsigned)x), cs = __uint_as_float((unsigned)(x >> 32));
+                if (c0 + lane < prev_cg && cs > 0.0f) s += cs * __expf(cm - rowm);
+            }
+            s = wave_sum(s);
+            s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s), 63));
+            if (lane == g) score -= logf(s);   // log_softmax at the maximum = -log(sum exp(l - max))
+        }
+        pend = false;
+    };
+
+    // ---- the work item at hand.  Lane i (of every 16) holds row i of its tile: the row of enc_proj, the
+    // hypothesis, and (stateless) the labels
+    int ti = 0, cg = 0, tile0 = 0, n_ct = 0;
+    int erow_l = 0, g_l = 0, lab_l = 0, lab2_l = 0;
+    int slot_of = 0;        // lane q: the q-th searching hypothesis
+    int Kw = 1, rcp_kw = 1, n_tiles = 0, n_cg = 1, tpg = 1, items = 0, M = 0, ti0 = 0, cg0 = 0;
+    auto plan_pass = [&](unsigned long long needm) __attribute__((always_inline)) {
+        const int n_need = __popcll(needm);
+        const LabelPlan lp = S.plan[n_need];
+        // the searching hypotheses, packed to the front
+        const bool need = (needm >> lane) & 1ull;
+        const int to = need ? __popcll(needm & ((1ull << lane) - 1ull)) : 63;
+        slot_of = __builtin_amdgcn_ds_permute(to * 4, lane);
+        Kw = uni(lp.Kw);
+        n_tiles = uni(lp.n_tiles);
+        n_cg = uni(lp.n_cg);
+        tpg = uni(lp.tpg);
+        rcp_kw = uni(lp.rcp_kw);
+        ti0 = uni(lp.ti0);
+        cg0 = uni(lp.cg0);
+        items = n_tiles * n_cg;
+        M = n_need * Kw;
+    };
+    auto set_item = [&](int it) __attribute__((always_inline)) {
+        ti = ti0;
+        cg = cg0;
+        if (it != rank) {
+            ti = it / n_cg;
+            cg = it - ti * n_cg;
+        }
+        tile0 = cg * tpg;
+        n_ct = min(tpg, NT - tile0);
+        const int r = ti * RT + (lane & 15), q = min((r * rcp_kw) >> 20, 63);   // r / Kw
+        g_l = __builtin_amdgcn_ds_bpermute(q * 4, slot_of) & 63;
+        const int f = __builtin_amdgcn_ds_bpermute(g_l * 4, time) + (r - q * Kw);
+        // (every lane has to take part in every permute: what an inactive lane holds reads as zero)
+        const int len_r = __builtin_amdgcn_ds_bpermute(g_l * 4, len), gid_r = __builtin_amdgcn_ds_bpermute(g_l * 4, gid);
+        const bool v = (r < M) & (f < len_r);
+        erow_l = gid_r * T + (v ? f : 0);
+        if constexpr (!LSTM) {
+            lab_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last);
+            lab2_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last2);
+        }
+    };
+
+    // ---- LAYERS == 1: where this thread's results of phase Q go -- four columns of one row per half of
+    // a round -- and its cell.  Offsets into the exchange buffers; beyond their end where there is
+    // nothing to write (such stores are dropped), so that the stores need no branch.
+    const int nowhere = 0x7ffffff0;
+    int q_off[2] = {nowhere, nowhere}, q_unit[2] = {-1, -1}, h_off[2] = {nowhere, nowhere}, c_g[2], c_u[2];
+    float4 q_bias[2];
+    if constexpr (LAYERS == 1) {
+        const int quad = lane & 15, g = qpack ? wave : tid >> 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int t = h * 4 + (quad >> 2), col = (qt0 + t) * CT + (quad & 3) * 4, u = (t - na) * 4 + (quad & 3);
+            const bool row = g < G && (!qpack || lane < 16);
+            if (row && t < na && col < H) q_off[h] = (g * H + col) * (int)sizeof(float);
+            if (row && t >= na && t < nq && u < U) q_unit[h] = g * Upad + u;
+            q_bias[h] = *reinterpret_cast<const float4 *>(p.b_pred + (t < na && col < H ? col : 0));
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int idx = tid + h * kLabelThreads;
+            c_g[h] = U > 0 ? min(idx / max(U, 1), kLabelMaxHyps - 1) : kLabelMaxHyps - 1;
+            c_u[h] = U > 0 ? idx - idx / max(U, 1) * U : 0;
+            if (U > 0 && idx < G * U) h_off[h] = (c_g[h] * Hp + u0 + c_u[h]) * (int)sizeof(float);
+        }
+    }
+#pragma clang loop unroll(disable)
+    while (ok) {   // ---- Alg. 3 line 5: while any hypothesis is active
+        const unsigned long long act = __ballot(active);
+        if (act == 0ull) break;
+        st_pred_passes += 1;
+#if TDT_TRACE
+        if (tid == 0) g_tr_on = (st_pred_passes >= 20 && st_pred_passes < 24);
+#endif
+        TR(1);
+        st_pred_rows += __popcll(CHUNKED && first ? act & ~carried : act);
+        // who will search in the first joint pass (in a chunk a hypothesis may only be here for the
+        // predictor step of its last label)
+        bool need = active && !(CHUNKED && (time >= len || (status & TDT_HYP_TRUNCATED)));
+        unsigned long long needm = __ballot(need);
+
+        // the projected encoder frames of a work item: four rows a wavefront, always -- a row beyond the
+        // last repeats it, a frame beyond its utterance's end reads frame 0 (no branches, and nobody
+        // looks at their results)
+        v4u e4[kRW][KI];
+        any_value(e4);
+        auto request_rows = [&]() __attribute__((always_inline)) {
+            const int nrows = M - ti * RT;
+#pragma unroll
+            for (int ii = 0; ii < kRW; ++ii) {
+                const int i = max(min(wave + ii * kLW, nrows - 1), 0);
+                const float *er = p.enc_proj + (size_t)(unsigned)__builtin_amdgcn_readlane(erow_l, i) * H;
+#pragma unroll
+                for (int kk = 0; kk < KI; ++kk) e4[ii][kk] = ldg4(er, joff(kk));
+            }
+        };
+        fresh();
+        v4u bq[TQ][NK];   // LAYERS == 1: this label's predictor-side weights
+        if constexpr (LAYERS == 1) {
+            // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, W_hh * h was formed by this
+            // workgroup when h was new.  The weights of phase Q are requested behind the table row:
+            // the row takes about as long to arrive as the requests take to leave.
+            const bool two_cells = G * U > kLabelThreads;   // uniform
+            v4u t4[2];
+            any_value(t4);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (h == 0 || two_cells) {
+                    const int lab = __builtin_amdgcn_ds_bpermute(c_g[h] * 4, last);
+                    t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + c_u[h]) * 4);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(bq, nq, hs0, hsn, q_tile);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if ((h == 0 || two_cells) && h_off[h] != nowhere && ((act >> c_g[h]) & 1ull)) {
+                    const int o = c_g[h] * Upad + c_u[h];
+                    float cn, hn;
+                    if (CHUNKED && first && ((carried >> c_g[h]) & 1ull)) {
+                        const size_t src = (size_t)S.gid[c_g[h]] * Hp + u0 + c_u[h];
+                        hn = p.st_h[src];
+                        cn = p.st_c[src];
+                    } else {
+                        const float4 r4 = rg_l[o], x = as_float4(t4[h]);
+                        cell(make_float4(r4.x + x.x, r4.y + x.y, r4.z + x.z, r4.w + x.w), c_l[o], cn, hn);
+                    }
+                    c_l[o] = cn;
+                    if (CHUNKED) h_l[o] = hn;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(present(hn)), hrs, h_off[h],
+                                                          (par * Bw + b0) * Hp * (int)sizeof(float), 16 /* sc1 */);
+                }
+        }
+        if constexpr (DEEP) {
+            // ---- P: the first layer's cell update.  W_ih * emb[label] + b is a table row,
+            // W_hh * h was formed by this workgroup when h was new.
+#pragma clang loop unroll(disable)
+            for (int base = 0; base < G * U; base += kLabelThreads) {   // uniform
+                const int idx = base + tid;
+                int g = p_g, u = p_u;
+                if (base > 0) {
+                    g = idx / U;
+                    u = idx - g * U;
+                }
+                const int lab = __builtin_amdgcn_ds_bpermute((g & 63) * 4, last);
+                if (g < G && ((act >> g) & 1ull)) {
+                    const int o = g * Upad + u;
+                    float cn, hn;
+                    if (CHUNKED && first && ((carried >> g) & 1ull)) {
+                        const size_t src = (size_t)S.gid[g] * Hp + u0 + u;
+                        hn = p.st_h[src];
+                        cn = p.st_c[src];
+                    } else {
+                        const float4 t4 =
+                            *reinterpret_cast<const float4 *>(p.emb_gates + ((size_t)lab * Hp + u0 + u) * 4);
+                        const float4 r4 = rg_l[o];
+                        cell(make_float4(r4.x + t4.x, r4.y + t4.y, r4.z + t4.z, r4.w + t4.w), c_l[o], cn, hn);
+                    }
+                    c_l[o] = cn;
+                    if (CHUNKED) h_l[o] = hn;
+                    st_co(hx + ((size_t)par * L * Bw + b0 + g) * Hp + u0 + u, present(hn));
+                }
+            }
+        }
+        if constexpr (LSTM) {
+            TR(2);
+            // ---- while the hidden state travels: the first joint pass is set up, and what was exchanged
+            // for the label before is put back
+            fresh();
+            if (needm != 0ull) {
+                plan_pass(needm);
+                set_item(rank);   // (a workgroup without a work item: never used)
+                if (rank < items) request_rows();
+            }
+            TR(3);
+            if constexpr (LAYERS == 1) {
+                const v4u absent = {kAbsent, kAbsent, kAbsent, kAbsent};
+                const int pb = (par ^ 1) * Bw + b0;
+                __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[0], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
+                if (G * U > kLabelThreads)
+                    __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[1], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
+                __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[0], pb * H * (int)sizeof(float), 16 /* sc1 */);
+                if (nq > 4) __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[1], pb * H * (int)sizeof(float), 16 /* sc1 */);
+            } else {
+                clear_rows();
+            }
+            clear_cells();
+            if (wave == kLW - 1) finish_scores();
+            fresh();
+            TR(10);
+            lap(kTkP);
+            if constexpr (LAYERS == 1) {
+                // ---- Q
+                if (nq > 0) {
+                    stage_h_any(par * Bw + b0, 0, act);
+                    TR(12);
+                    lap(kTkBar);
+                    __syncthreads();
+                    TR(13);
+                    fresh();
+                    AFrag a[NK][PL];
+                    if (qpack) {
+                        load_a(packed_rows, a, hs0, hsn);
+                        TR(14);
+                        products(packed_rows, a, bq, nq);
+                    } else {
+                        load_a(full_rows, a, hs0, hsn);
+                        TR(14);
+                        products(full_rows, a, bq, nq);
+                    }
+                    TR(15);
+                    __syncthreads();
+                    TR(16);
+                    fresh();
+                    // a thread takes four columns of a row; packed: a wavefront takes a row, its lanes one
+                    // plane each, and the planes are added up
+                    const int quad = lane & 15, row = qpack ? wave + (lane >> 4) * kPackRows : tid >> 4;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        if (h == 0 || nq > 4) {   // uniform
+                            float4 v = gather(row, h * 16 + quad);
+                            if (qpack) {   // (rows 12 .. 15 of a packed tile are nobody's)
+                                v.x = sum_over_rows(lane < 48 ? v.x : 0.0f);
+                                v.y = sum_over_rows(lane < 48 ? v.y : 0.0f);
+                                v.z = sum_over_rows(lane < 48 ? v.z : 0.0f);
+                                v.w = sum_over_rows(lane < 48 ? v.w : 0.0f);
+                            }
+                            const v4u o = {__float_as_uint(present(v.x + q_bias[h].x)), __float_as_uint(present(v.y + q_bias[h].y)),
+                                           __float_as_uint(present(v.z + q_bias[h].z)), __float_as_uint(present(v.w + q_bias[h].w))};
+                            __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_off[h], (par * Bw + b0) * H * (int)sizeof(float),
+                                                                   16 /* sc1 */);
+                            if (q_unit[h] >= 0) rg_l[q_unit[h]] = v;   // the four gates of one unit
+                        }
+                }
+            }
+            const int ntq = LAYERS == 1 ? 0 : (G + RT - 1) / RT;
+            // ---- deeper layers: W_ih . [h of the layer below] + what W_hh . h left here
+#pragma clang loop unroll(disable)
+            for (int l = 0; DEEP && l < L; ++l) {
+                const int row0 = (par * L + l) * Bw + b0;
+                const bool top = !DEEP || l == L - 1;
+                // What this layer's h is multiplied by.  Below the top: first the next layer's input
+                // product (its cell follows at once), then the recurrent product for the next label;
+                // the top layer: the list of W_pred and W_hh tiles in order.
+                const int kinds = top ? 1 : 2, n_all = top ? nq : nr;
+                v4u b[TQ][NK];
+                float4 qbias;
+                auto fetch_round = [&](int kind, int t0) __attribute__((always_inline)) {
+                    const int n = min(TQ, n_all - t0);
+                    const int w = here(top ? 0 : (kind == 0 ? p.off_w_ih[l + 1] : p.off_w_hh[l]) + (r0 + t0) * hbytes);
+                    fetch(b, n, hs0, hsn, [&](int t) { return top ? q_tile(t0 + t) + w : w + t * hbytes; });
+                    const int t = t0 + ((lane & 15) >> 2), col = (qt0 + t) * CT + (lane & 3) * 4;
+                    qbias = *reinterpret_cast<const float4 *>(p.b_pred + (t < na && col < H ? col : 0));
+                };
+                bool loaded = false;   // the registers hold the fragments of the first round
+#pragma clang loop unroll(disable)
+                for (int tq = 0; tq < ntq && n_all > 0; ++tq) {
+                    const unsigned long long in_tile = act >> (tq * RT) & 0xffffull;
+                    if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
+                    if (!loaded) fetch_round(0, 0);   // while the rows are on their way
+                    loaded = top && n_all <= TQ;
+                    stage_h_any(row0, tq, in_tile);
+                    TR(12);
+                    lap(kTkBar);
+                    __syncthreads();
+                    TR(13);
+                    fresh();
+                    AFrag a[NK][PL];
+                    any_value(a);
+                    if (qpack) load_a(packed_rows, a, hs0, hsn);
+                    else load_a(full_rows, a, hs0, hsn);
+#pragma clang loop unroll(disable)
+                    for (int kind = 0; kind < (DEEP ? kinds : 1); ++kind) {
+                        const bool input = !top && kind == 0;
+#pragma clang loop unroll(disable)
+                        for (int t0 = 0; t0 < n_all; t0 += TQ) {
+                            const int n = min(TQ, n_all - t0);
+                            if (kind > 0 || t0 > 0) fetch_round(kind, t0);
+                            TR(14);
+                            if (qpack) products(packed_rows, a, b, n);
+                            else products(full_rows, a, b, n);
+                            TR(15);
+                            __syncthreads();
+                            TR(16);
+                            fresh();
+                            // a thread takes four columns of a row; packed: a wavefront takes a row, its
+                            // lanes one plane each, and the planes are added up
+                            const int quad = lane & 15, i = qpack ? wave : tid >> 4, g = tq * RT + i;
+                            float4 v = gather(qpack ? i + (lane >> 4) * kPackRows : i, quad);
+                            if (qpack) {
+                                if (lane >= 48) v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                                v.x = sum_over_rows(v.x);
+                                v.y = sum_over_rows(v.y);
+                                v.z = sum_over_rows(v.z);
+                                v.w = sum_over_rows(v.w);
+                            }
+                            if (g < G && ((act >> g) & 1ull) && quad < n * 4 && (!qpack || lane < 16)) {
+                                const int t = t0 + (quad >> 2);
+                                if (top && t < na) {   // projected predictor output
+                                    const int col = (qt0 + t) * CT + (quad & 3) * 4;
+                                    if (col < H)
+                                        st_co4(px + ((size_t)par * Bw + b0 + g) * H + col,
+                                               make_float4(present(v.x + qbias.x), present(v.y + qbias.y),
+                                                           present(v.z + qbias.z), present(v.w + qbias.w)));
+                                } else {   // the four gates of one unit
+                                    const int u = (top ? t - na : t) * 4 + (quad & 3);
+                                    if (u < U) {
+                                        if (!input) {
+                                            rg_l[((size_t)l * hpc + g) * Upad + u] = v;
+                                        } else {
+                                            const int o = ((l + 1) * hpc + g) * Upad + u;
+                                            const float *bl = p.b_lstm[l + 1] + u0 + u;
+                                            const float4 r4 = rg_l[o];
+                                            float cn, hn;
+                                            if (CHUNKED && first && ((carried >> g) & 1ull)) {
+                                                const size_t at = ((size_t)(l + 1) * B + S.gid[g]) * Hp + u0 + u;
+                                                hn = p.st_h[at];
+                                                cn = p.st_c[at];
+                                            } else {
+                                                cell(make_float4(v.x + r4.x + bl[0], v.y + r4.y + bl[Hp],
+                                                                 v.z + r4.z + bl[2 * Hp], v.w + r4.w + bl[3 * Hp]),
+                                                     c_l[o], cn, hn);
+                                            }
+                                            c_l[o] = cn;
+                                            if (CHUNKED) h_l[o] = hn;
+                                            st_co(hx + (((size_t)par * L + l + 1) * Bw + b0 + g) * Hp + u0 + u,
+                                                  present(hn));
+                                        }
+                                    }
+                                }
+                            }
+                            // (the partial sums are written again behind the next barrier only if another
+                            // round, row tile or layer follows; a joint pass has one of its own)
+                            if (t0 + TQ < n_all || kind + 1 < kinds || tq + 1 < ntq || (DEEP && l + 1 < L)) __syncthreads();
+                        }
+                    }
+                }
+            }
+            TR(17);
+            lap(kTkQ);
+        }
+        if (CHUNKED) {
+            active = need;
+            if (needm == 0ull) {   // nobody scores a frame any more: the loop ends at its test
+                act_prev = act;
+                first = false;
+                par ^= 1;
+                continue;
+            }
+        }
+        if constexpr (!LSTM) plan_pass(needm);
+        // ---- inner loop (Alg. 3 line 12): joint passes until nobody searches any more
+#pragma clang loop unroll(disable)
+        for (bool again = false; needm != 0ull; again = true) {
+            fresh();
+            if (again) plan_pass(needm);
+            const unsigned buf = jpass & (kRowBufs - 1);
+            ++jpass;
+            st_joint_passes += 1;
+            st_joint_rows += M;
+            unsigned long long *const jbb = jb + (size_t)buf * cells, *const jlb = jl + (size_t)buf * cells;
+            unsigned long long *const jdb = jd + (size_t)buf * 2 * rows_cap;
+            unsigned long long *const jhb = jh + (size_t)buf * C;
+            // the column groups that hold duration outputs (at most two: there are at most 16)
+            const int dcg0 = D > 0 ? ((VL + 1) / CT) / tpg : -1, dcg1 = D > 0 ? ((O - 1) / CT) / tpg : -1;
+
+            // ---- J
+#pragma clang loop unroll(disable)
+            for (int it = rank; it < items; it += C) {
+                if (!LSTM || again || it != rank) {
+                    set_item(it);
+                    request_rows();
+                }
+                const int nrows = M - ti * RT;
+                v4u p4[kRW][KI], b[TR][NK];
+                int po[kRW];
+                const float *pr2[kRW];
+#pragma unroll
+                for (int ii = 0; ii < kRW; ++ii) {
+                    const int i = min(wave + ii * kLW, nrows - 1);
+                    if constexpr (LSTM) {
+                        po[ii] = (par * Bw + b0 + __builtin_amdgcn_readlane(g_l, i)) * H * (int)sizeof(float);
+                    } else {
+                        // one label of context: its table row; two: the older label's table, then the newest label's
+                        const size_t row = (size_t)__builtin_amdgcn_readlane(lab_l, i);
+                        const float *pr = p.pred_tab + row * H;
+                        if (p.pred_layers == 2) {
+                            pr2[ii] = p.pred_tab + ((size_t)(V + 1) + row) * H;
+                            pr = p.pred_tab + (size_t)__builtin_amdgcn_readlane(lab2_l, i) * H;
+                        }
+#pragma unroll
+                        for (int kk = 0; kk < KI; ++kk) p4[ii][kk] = ldg4(pr, joff(kk));
+                    }
+                }
+                {
+                    const int wbase = here(p.off_w_out + tile0 * jbytes);
+                    fetch(b, min(n_ct, TR), js0, jsn, [&](int t) { return wbase + t * jbytes; });
+                }
+                // biases of this thread's four columns (zeros beyond the last)
+                v4u bias4 = __builtin_amdgcn_raw_buffer_load_b128(
+                    brs, (tile0 * CT + (lane & 15) * 4) * (int)sizeof(float), 0, 0);
+                TR(20);
+                if constexpr (LSTM) {
+                    unsigned spins = 0;
+                    long long since = 0;
+#pragma clang loop unroll(disable)
+                    for (;;) {
+                        unsigned mx = 0;
+#pragma unroll
+                        for (int ii = 0; ii < kRW; ++ii)
+#pragma unroll
+                            for (int kk = 0; kk < KI; ++kk) p4[ii][kk] = ldx4(prs, joff(kk), po[ii]);
+#pragma unroll
+                        for (int ii = 0; ii < kRW; ++ii)
+#pragma unroll
+                            for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(p4[ii][kk]));
+                        if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+                    }
+                    lap(kTkBar);
+                } else if (p.pred_layers == 2) {
+#pragma unroll
+                    for (int ii = 0; ii < kRW; ++ii)
+#pragma unroll
+                        for (int kk = 0; kk < KI; ++kk) {
+                            const float4 x = as_float4(ldg4(pr2[ii], joff(kk))), y = as_float4(p4[ii][kk]);
+                            p4[ii][kk] = v4u{__float_as_uint(y.x + x.x), __float_as_uint(y.y + x.y),
+                                             __float_as_uint(y.z + x.z), __float_as_uint(y.w + x.w)};
+                        }
+                }
+                TR(22);
+#pragma unroll
+                for (int ii = 0; ii < kRW; ++ii)
+#pragma unroll
+                    for (int kk = 0; kk < KI; ++kk) {
+                        const float4 e = as_float4(e4[ii][kk]), q = as_float4(p4[ii][kk]);
+                        put(full_rows, wave + ii * kLW, joff(kk) / (int)sizeof(float),
+                            make_float4(fmaxf(e.x + q.x, 0.0f), fmaxf(e.y + q.y, 0.0f), fmaxf(e.z + q.z, 0.0f),
+                                        fmaxf(e.w + q.w, 0.0f)));
+                    }
+                pad_rows(H);
+                TR(23);
+                __syncthreads();
+                TR(24);
+                fresh();
+                AFrag a[NK][PL];
+                load_a(full_rows, a, js0, jsn);
+                // 16 lanes share a row and take four neighbouring columns each; running statistics
+                const int i = tid >> 4, quad = lane & 15;
+                float rm = -INFINITY, rs = 0.0f, rsm = -INFINITY, rdm = -INFINITY;
+                int ra = 0x7fffffff, rda = 0;
+                // the sum of exp(logit - largest) of a round is added up when the next round is over or the
+                // largest logit has been published
+                float lg[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                auto fold_sums = [&]() __attribute__((always_inline)) {   // relative to rm, the largest so far
+                    float s = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s += lg[e] > -INFINITY ? __expf(lg[e] - rm) : 0.0f;
+                    s = row_allreduce(s, [](float x, float y) { return x + y; });
+                    rs = (rs > 0.0f ? rs * __expf(rsm - rm) : 0.0f) + s;
+                    rsm = rm;
+                };
+#pragma clang loop unroll(disable)
+                for (int t0 = 0; t0 < n_ct; t0 += TR) {
+                    const int n = min(TR, n_ct - t0);
+                    TR(25);
+                    products(full_rows, a, b, n);
+                    const float4 bb = as_float4(bias4);
+                    TR(26);
+                    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (words put back earlier have arrived)
+                    __syncthreads();
+                    TR(27);
+                    if (t0 + TR < n_ct) {   // the next round's weights, while this one's results are looked at
+                        const int wbase = here(p.off_w_out + (tile0 + t0 + TR) * jbytes);
+                        fetch(b, min(TR, n_ct - t0 - TR), js0, jsn, [&](int t) { return wbase + t * jbytes; });
+                        bias4 = __builtin_amdgcn_raw_buffer_load_b128(
+                            brs, ((tile0 + t0 + TR) * CT + quad * 4) * (int)sizeof(float), 0, 0);
+                    }
+                    if (t0 > 0) fold_sums();
+                    const float4 v = gather(i, quad);
+                    const float x4[4] = {v.x + bb.x, v.y + bb.y, v.z + bb.z, v.w + bb.w};
+                    float m = -INFINITY;
+                    int am = 0x7fffffff;
+                    const int col0 = quad < n * 4 ? (tile0 + t0) * CT + quad * 4 : O;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int col = col0 + e;
+                        lg[e] = col <= VL ? x4[e] : -INFINITY;
+                        am = lg[e] > m ? col : am;
+                        m = lg[e] > m ? lg[e] : m;
+                    }
+                    auto fmax2 = [](float x, float y) { return fmaxf(x, y); };
+                    auto imin2 = [](int x, int y) { return min(x, y); };
+                    const float mrow = row_allreduce(m, fmax2);
+                    am = row_allreduce(m == mrow ? am : 0x7fffffff, imin2);
+                    ra = mrow > rm ? am : ra;   // rounds ascend through the columns: '>' keeps the first maximum
+                    rm = fmaxf(rm, mrow);
+                    if (cg >= dcg0 && cg <= dcg1) {   // (uniform; never without a duration head)
+                        float dm = -INFINITY;
+                        int da = 0x7fffffff;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (col0 + e > VL && col0 + e < O && x4[e] > dm) { dm = x4[e]; da = col0 + e - (VL + 1); }
+                        const float drow = row_allreduce(dm, fmax2);
+                        da = row_allreduce(dm == drow ? da : 0x7fffffff, imin2);
+                        if (drow > rdm) { rdm = drow; rda = da; }
+                    }
+                    if (t0 + TR < n_ct) __syncthreads();   // before the partial sums are written again
+                }
+                TR(28);
+                // (no label column, or no logit that is a number: below every label, but present)
+                const unsigned long long best = rm > -INFINITY ? pack_best(rm, ra) : 1ull;
+                const unsigned long long bd = rdm > -INFINITY ? pack_best(rdm, rda) : 1ull;
+                const int o = it * RT + i;
+                if (C > 1 && quad == 0) {
+                    st_co64(jbb + o, best);
+                    if (cg == dcg0) st_co64(jdb + (size_t)(ti * 2) * RT + i, bd);
+                    else if (cg == dcg1) st_co64(jdb + (size_t)(ti * 2 + 1) * RT + i, bd);
+                }
+                fold_sums();
+                if (quad == 0) {
+                    if (!(rm > -INFINITY)) rs = 0.0f;
+                    const unsigned long long lse =
+                        (unsigned long long)__float_as_uint(rm) | ((unsigned long long)__float_as_uint(rs) << 32);
+                    if (C > 1) {
+                        st_co64(jlb + o, lse);
+                    } else {
+                        S.rowb[ti * RT + i] = best;
+                        S.rowl[ti * RT + i] = lse;
+                        S.rowd[ti * RT + i] = (unsigned)S.durations[unpack_index(bd) & (TDT_MAX_DURATIONS - 1)];
+                    }
+                }
+                if (it + C < items) __syncthreads();   // the next item writes the tile and the partial sums again
+            }
+            if (rank >= items) {   // no work item: say that this workgroup has come this far
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (tid == 0) st_co64(jhb + rank, 1ull);
+            }
+            TR(29);
+            lap(kTkJ);
+
+            // ---- while the cells travel: the score terms of the pass before
+            fresh();
+            if (!LSTM || again) {   // (an LSTM's first pass: summed while the hidden state travelled)
+                --jpass;   // (finish_scores looks at the last pass)
+                if (wave == kLW - 1) finish_scores();
+                ++jpass;
+            }
+            // ---- gather the cells: a wavefront takes one row tile, or a share of its column groups;
+            // lane = (column group modulo 4, row)
+            const int wsh = n_tiles == 1 && n_cg > 8 ? 2 : n_tiles <= 2 && n_cg > 4 ? 1 : 0, wpt = 1 << wsh;
+            if (C > 1) {
+                const int i = lane & 15;
+#pragma clang loop unroll(disable)
+                for (int tw = wave; tw < n_tiles << wsh; tw += kLW) {   // (more than once only for many row tiles)
+                    const int tt = tw >> wsh, wq = tw & (wpt - 1);
+                    const unsigned long long *src = jbb + (size_t)tt * n_cg * RT + i;
+                    unsigned long long best = 0ull;
+                    const int step = 4 << wsh;
+#pragma clang loop unroll(disable)
+                    for (int cb = wq * 4; cb < n_cg; cb += 4 * step) {   // uniform
+                        unsigned long long x[4];
+                        unsigned spins = 0;
+                        long long since = 0;
+                        for (;;) {
+                            bool all = true;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                x[e] = ld_co64(src + min(cb + (lane >> 4) + e * step, n_cg - 1) * RT);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) all = all & (x[e] != 0ull);
+                            if (__ballot(!all) == 0ull || give_up(spins, since)) break;
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) best = x[e] > best ? x[e] : best;
+                    }
+                    best = max_over_rows(best);
+                    if (lane < RT) S.rowb[(wq * n_tiles + tt) * RT + i] = best;
+                }
+                if (D > 0) {   // the duration head's words: one or two column groups
+                    const int two = dcg1 != dcg0 ? RT : 0;
+#pragma clang loop unroll(disable)
+                    for (int rb = (kLW - 1 - wave) * 64; rb < n_tiles * RT; rb += kLabelThreads) {   // uniform
+                        const int r = min(rb + lane, n_tiles * RT - 1);
+                        const unsigned long long *q = jdb + (size_t)(r >> 4) * 2 * RT + (r & 15);
+                        unsigned long long x = wait_word(q);
+                        if (two) {
+                            const unsigned long long y = wait_word(q + two);
+                            x = x > y ? x : y;
+                        }
+                        S.rowd[r] = (unsigned)S.durations[unpack_index(x) & (TDT_MAX_DURATIONS - 1)];   // the frame step
+                    }
+                }
+                if (items < C && wave == 1)   // the workgroups without a work item
+#pragma clang loop unroll(disable)
+                    for (int c = items; c < C; c += 64) wait_word(jhb + min(c + lane, C - 1));
+            }
+            TR(31);
+            __syncthreads();
+            TR(32);
+            lap(kTkBar);
+            // ---- D: every wavefront takes the same decisions.  Rows of passes of up to 64 rows sit in
+            // lanes; larger passes are first brought together in LDS
+            fresh();
+            const int w_rows = n_tiles * RT;
+            auto row_result = [&](int r, int &ra, int &step, unsigned long long &best) __attribute__((always_inline)) {
+                best = S.rowb[r];
+                for (int w = 1; C > 1 && w < wpt; ++w) {
+                    const unsigned long long o = S.rowb[w * w_rows + r];
+                    best = o > best ? o : best;
+                }
+                ra = unpack_index(best);
+                if ((unsigned)ra > (unsigned)VL) ra = V;   // (no logit of the row is a number)
+                // the frame step that goes with the decision: from the duration head (Sec. 3.3) or,
+                // multi-blank, from the symbol: the blank one frame, big blank i its increment
+                step = 0;
+                if (D > 0) step = (int)(unsigned)S.rowd[r];
+                else if (big_blanks) step = ra < V ? 0 : ra == V ? 1 : S.durations[(ra - V - 1) & (TDT_MAX_DURATIONS - 1)];
+            };
+            const bool plain = D == 0 && !big_blanks;
+            const int nv = need ? min(Kw, len - time) : 0;   // >= 1 where it searches
+            const int base = __popcll(needm & ((1ull << lane) - 1ull)) * Kw;   // lane g: its first row
+            int w = 0, k = V, dk = 0;
+            unsigned kb = 0;
+            bool found = false;
+            if (M <= 64) {
+                int ra, step;
+                unsigned long long best;
+                row_result(lane < M ? lane : 0, ra, step, best);
+                if (plain) {   // Alg. 3 lines 10 / 18: a blank moves one frame on
+                    const unsigned long long nb = __ballot(lane < M && ra < V);
+                    const unsigned long long sub = need ? (nb >> base) & (nv >= 64 ? ~0ull : (1ull << nv) - 1ull) : 0ull;
+                    found = sub != 0ull;
+                    w = found ? __ffsll((long long)sub) - 1 : nv;
+                } else {
+                    const int code = ra < V ? 0 : max(step, 1);   // frames a non-label moves on; 0: a label
+                    bool go = need;
+                    while (__ballot(go) != 0ull) {
+                        const int x = __builtin_amdgcn_ds_bpermute(((base + w) & 63) * 4, code);
+                        if (go) {
+                            if (x == 0) { found = true; go = false; }
+                            else { w += x; go = w < nv; }
+                        }
+                    }
+                }
+                const int at = ((base + (found ? w : 0)) & 63) * 4;
+                k = __builtin_amdgcn_ds_bpermute(at, ra);
+                kb = (unsigned)__builtin_amdgcn_ds_bpermute(at, (int)(unsigned)(best >> 32));
+                if (!plain) dk = __builtin_amdgcn_ds_bpermute(at, step);
+            } else {
+                for (int r = tid; r < M; r += kLabelThreads) {
+                    int ra, step;
+                    unsigned long long best;
+                    row_result(r, ra, step, best);
+                    S.res_a[r] = ra;
+                    S.res_d[r] = step;
+                    S.rowb[r] = best;   // (one share per row tile in passes of this size)
+                }
+                __syncthreads();
+                while (need && w < nv) {
+                    if (S.res_a[base + w] < V) { found = true; break; }
+                    const int d_ = S.res_d[base + w];
+                    w += plain ? 1 : d_ > 0 ? d_ : 1;
+                }
+                if (found) {
+                    k = S.res_a[base + w];
+                    dk = S.res_d[base + w];
+                    kb = (unsigned)(S.rowb[base + w] >> 32);
+                }
+            }
+            ok = uni(S.aborted) == 0;
+            if (!ok) break;
+            // ---- Alg. 3 line 20, Sec. 3.1 add_results (selections: a branch costs more than what it skips)
+            {
+                const bool moved = need & ((w > 0) | !found);
+                const int frame = time + w;
+                found = found & need;
+                if (rank == 0 && wave == 0 && found) {
+                    p.out_labels[(size_t)gid * p.u_cap + olen] = k;
+                    p.out_frames[(size_t)gid * p.u_cap + olen] = frame;
+                }
+                sym = (moved ? 0 : sym) + (found ? 1 : 0);
+                olen += found ? 1 : 0;
+                last2 = found ? last : last2;
+                last = found ? k : last;
+                const int dk1 = ((dk == 0) & (sym >= p.max_symbols)) ? 1 : dk;
+                const int step = found ? dk1 : 0;
+                time = need ? frame + step : time;
+                sym = step > 0 ? 0 : sym;
+                const bool full = found & (olen >= p.u_cap), more = time < len;
+                status |= full ? TDT_HYP_TRUNCATED : 0;
+                // (chunks: a hypothesis that has found a label takes one more predictor step, which its
+                // state carries on)
+                active = need ? (found & CHUNKED) | (more & !full) : active;
+                need = need & !found & more;
+            }
+            pend = found;
+            pend_row = base + w;
+            pend_m = unpack_value((unsigned long long)kb << 32);
+            needm = __ballot(need);
+            TR(33);
+            // everybody has read the pass before this one: its cells are put back (behind the label's
+            // last pass: while the next label's hidden state travels)
+            clr_items = prev_items;
+            clr_tiles = prev_tiles;
+            prev_items = items;
+            prev_tiles = n_tiles;
+            prev_cg = n_cg;
+            if (!LSTM || needm != 0ull) {
+                fresh();
+                clear_cells();
+            }
+            TR(34);
+            lap(kTkD);
+        }
+        if (!ok) break;
+        act_prev = act;
+        first = false;
+        par ^= 1;
+    }
+    if (ok && wave == kLW - 1) finish_scores();
+
+    // ---- what the next chunk takes up
+    if (CHUNKED) {
+        if (ok && rank == 0 && wave == 0)
+            for (int c = 0; c < C; c += 64) wait_word(jh + (size_t)kRowBufs * C + min(c + lane, C - 1));
+        __syncthreads();
+        ok = ok && uni(S.aborted) == 0;
+    }
+    if (CHUNKED && ok) {
+        if constexpr (LSTM) {
+            for (int idx = tid; idx < G * U; idx += kLabelThreads) {
+                const int g = idx / U, u = idx - g * U;
+                if ((took_part >> g) & 1ull)
+                    for (int l = 0; l < L; ++l) {
+                        const size_t dst = ((size_t)l * B + S.gid[g]) * Hp + u0 + u;
+                        p.st_h[dst] = h_l[(l * hpc + g) * Upad + u];
+                        p.st_c[dst] = c_l[(l * hpc + g) * Upad + u];
+                    }
+            }
+        }
+        if (rank == 0 && wave == 0 && mine) {
+            p.st_started[gid] = started;
+            // frames of the next chunk already stepped over; a hypothesis stopped at its label
+            // capacity gives up the rest of this chunk
+            p.st_time[gid] = max(time - len, 0);
+            p.st_last[gid] = last;
+            p.st_last2[gid] = last2;
+        }
+    }
+    if (wave == kLW - 1 && mine && owner_mod == rank) p.out_score[gid] = score;   // (the wavefront that summed it)
+    if (rank == 0 && wave == 0) {
+        if (mine) {
+            p.out_len[gid] = olen;
+            p.out_status[gid] = status | (ok ? 0 : TDT_HYP_ABORTED);
+        }
+        if (tid == 0 && p.out_stats) {
+            auto add = [&](int slot, long long v) {
+                atomicAdd((unsigned long long *)&p.out_stats[slot], (unsigned long long)v);
+            };
+            add(TDT_STAT_PRED_PASSES, (long long)st_pred_passes);
+            add(TDT_STAT_PRED_ROWS, st_pred_rows);
+            add(TDT_STAT_JOINT_PASSES, (long long)st_joint_passes);
+            add(TDT_STAT_JOINT_ROWS, st_joint_rows);
+            atomicMax((unsigned long long *)&p.out_stats[TDT_STAT_OUTER_MAX], (unsigned long long)st_pred_passes);
+            atomicMax((unsigned long long *)&p.out_stats[TDT_STAT_JOINT_PASSES_MAX],
+                      (unsigned long long)st_joint_passes);
+            if (!ok) add(TDT_STAT_ABORT, 1);
+            if (TDT_PHASE_TIMERS && cl == 0) {   // where the first group's time went, in wall-clock ticks
+                add(TDT_STAT_TICKS_PRED, S.tk[kTkP]);
+                add(TDT_STAT_TICKS_PROJ, S.tk[kTkQ]);
+                add(TDT_STAT_TICKS_JOINT, S.tk[kTkJ]);
+                add(TDT_STAT_TICKS_DECIDE, S.tk[kTkD]);
+                add(TDT_STAT_TICKS_BARRIER, S.tk[kTkBar]);
+                add(TDT_STAT_TICKS_TOTAL, wall_clock64() - S.tk_start);
+            }
+        }
+    }
+}
+
+constexpr size_t kLabelDynLds = kLdsBytes - sizeof(LabelShared) - 256;   // (the rest: what the compiler adds)
+
+// the compiled form for a model: steps of the reduction a wavefront takes
+int label_steps(const tdt_weights_t *w)
+{
+    const int ks = w->dtype == 1 ? 32 : 16;
+    int k = w->h_joint;
+    if (w->pred_kind == TDT_PRED_LSTM && w->h_pred > k) k = w->h_pred;
+    return ((k + ks - 1) / ks + kLW - 1) / kLW;
+}
+int label_kseg(const tdt_weights_t *w)
+{
+    return w->pred_kind == TDT_PRED_LSTM && w->h_pred > w->h_joint ? w->h_pred : w->h_joint;
+}
+
+template <typename WT, int NK> const void *label_fn(int layers, bool chunked)
+{
+    if (layers > 1)
+        return chunked ? (const void *)label_kernel<WT, 2, true, NK> : (const void *)label_kernel<WT, 2, false, NK>;
+    if (layers == 1)
+        return chunked ? (const void *)label_kernel<WT, 1, true, NK> : (const void *)label_kernel<WT, 1, false, NK>;
+    return chunked ? (const void *)label_kernel<WT, 0, true, NK> : (const void *)label_kernel<WT, 0, false, NK>;
+}
+const void *label_fn_for(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C, int &nk, int &tq)
+{
+    const int steps = label_steps(w);
+    int layers = w->pred_kind == TDT_PRED_LSTM ? 2 : 0;
+    if (layers > 0 && w->pred_layers == 1) {
+        const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
+        // one round, one row tile, one or two cells a thread
+        const int nk_ = steps <= 5 ? 5 : 8;
+        if (per_wg <= 2 * label_tiles(nk_) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads)
+            layers = 1;
+    }
+    if (w->dtype == 1) {
+        if (steps <= 5) { nk = 5; tq = (layers > 1 ? 1 : 2) * label_tiles(5); return label_fn<uint16_t, 5>(layers, chunked); }
+        if (steps <= 8) { nk = 8; tq = (layers > 1 ? 1 : 2) * label_tiles(8); return label_fn<uint16_t, 8>(layers, chunked); }
+    }
+    return nullptr;
+}
+
+}  // namespace
+
+size_t label_lds_bytes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C)
+{
+    int nk = 0, tq = 0;
+    if (!label_fn_for(w, chunked, hyps_per_cluster, C, nk, tq)) return ~(size_t)0;
+    const int k = label_kseg(w);
+    size_t n = w->dtype == 1 ? (size_t)3 * RT * ActTile<uint16_t>::row_elems(k) * sizeof(uint16_t)
+                             : (size_t)RT * ActTile<float>::row_elems(k) * sizeof(float);
+    n += (size_t)kLW * RT * (tq * CT + 4) * sizeof(float);
+    if (w->pred_kind == TDT_PRED_LSTM) {
+        const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4;
+        const size_t units = (size_t)w->pred_layers * hyps_per_cluster * ((tiles + C - 1) / C) * 4;
+        n += units * (4 + 1 + (chunked ? 1 : 0)) * sizeof(float);
+    }
+    return (n + 15) / 16 * 16;
+}
+
+bool label_kernel_takes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C)
+{
+    if (hyps_per_cluster > kLabelMaxHyps) return false;
+    const size_t dyn = label_lds_bytes(w, chunked, hyps_per_cluster, C);
+    const size_t lens = (size_t)kMaxRankedBatch * sizeof(int);   // (the batch's lengths while they are ranked)
+    if (packed_layout(w).total >= ((size_t)1 << 31)) return false;   // offsets among the copies are 32 bits
+    return dyn >= lens && dyn <= kLabelDynLds;
+}
+
+hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, int grid, hipStream_t stream)
+{
+    // the LDS limit of a compiled form is raised once per device (to all a workgroup can have)
+    static std::mutex mu;
+    static const void *ready[64][16];
+    int dev = 0, nk = 0, tq = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    const void *fn = label_fn_for(w, chunked, p.hyps_per_cluster, grid / p.n_clusters, nk, tq);
+    if (!fn) return hipErrorInvalidValue;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        int i = 0;
+        while (i < 16 && ready[dev][i] && ready[dev][i] != fn) ++i;
+        if (i == 16 || !ready[dev][i]) {
+            e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kLabelDynLds);
+            if (e != hipSuccess) return e;
+            if (i < 16) ready[dev][i] = fn;
+        }
+    }
+    DecodeParams pc = p;
+    pc.kseg_max = label_kseg(w);
+    pc.lds_bytes = (int)label_lds_bytes(w, chunked, p.hyps_per_cluster, grid / p.n_clusters);
+    void *args[] = {&pc};
+    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kLabelThreads), args, (unsigned)pc.lds_bytes, stream);
+}
+
+}  // namespace tdt

@@ -85,6 +85,46 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     off = align_up(off + 256, 256);
     L.zero_end = off;
     L.total = off;
+    // label_loop.hip lays its own arrays over the part from `partials` on; how much it needs depends
+    // on the split of the batch, which is not known here: n_clusters * hyps_per_cluster <= B + kMaxGrid
+    // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup
+    const size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
+    size_t lab = L.partials;
+    lab = align_up(lab + 2 * lstm_layers * rows * w->h_pred * sizeof(float), 256);
+    lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
+    lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 512);
+    lab = align_up(lab + kRowBufs * 2 * 64 * rows * sizeof(unsigned long long), 256);
+    lab = align_up(lab + (kRowBufs + 1) * (size_t)kMaxGrid * sizeof(unsigned long long), 256) + 256;
+    if (lab > L.total) L.total = lab;
+    return L;
+}
+
+LabelLayout label_layout(const tdt_weights_t *w, int n_clusters, int hyps_per_cluster, int C)
+{
+    LabelLayout L{};
+    const bool lstm = w->pred_kind == TDT_PRED_LSTM;
+    const size_t rows = (size_t)n_clusters * hyps_per_cluster;
+    L.rows_per_cluster = hyps_per_cluster * kMaxWindow < kLabelRowsPerPass ? hyps_per_cluster * kMaxWindow
+                                                                         : kLabelRowsPerPass;
+    const int tiles = L.rows_per_cluster / 16;   // row tiles of a joint pass
+    L.cells_per_cluster = 16 * (tiles > C ? tiles : C);
+    size_t off = 0;
+    L.ones_begin = L.hx = off;
+    if (lstm) off = align_up(off + 2 * (size_t)w->pred_layers * rows * w->h_pred * sizeof(float), 256);
+    L.px = off;
+    if (lstm) off = align_up(off + 2 * rows * w->h_joint * sizeof(float), 256);
+    L.ones_end = L.zero_begin = L.row_lab = off;
+    off = align_up(off + (size_t)n_clusters * kRowBufs * L.cells_per_cluster * sizeof(unsigned long long), 256);
+    L.row_lse = off;
+    off = align_up(off + (size_t)n_clusters * kRowBufs * L.cells_per_cluster * sizeof(unsigned long long), 256);
+    L.row_dur = off;
+    if (w->n_dur > 0 && !w->multi_blank)
+        off = align_up(off + (size_t)n_clusters * kRowBufs * 2 * L.rows_per_cluster * sizeof(unsigned long long), 256);
+    L.present = off;
+    off = align_up(off + (size_t)n_clusters * (kRowBufs + 1) * C * sizeof(unsigned long long), 256);
+    L.abort_flag = off;
+    off += 256;
+    L.zero_end = off;
     return L;
 }
 
@@ -284,8 +324,8 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         // joint passes, so more clusters pay -- until a cluster has too few workgroups to give
         // each at most four column tiles of the predictor-side products (two weight batches per
         // wavefront); `fit` is the cluster count at which that holds.  Small batches: two
-        // to four clusters.  An LSTM predictor: `fit`; from about 14 hypotheses per cluster of eight on,
-        // where the row tiles are full either way, eight.  A stateless predictor: see below.
+        // to four clusters.  An LSTM predictor: `fit`, and more for large batches.  A stateless
+        // predictor: see below.
         const bool lstm = weights->pred_kind == TDT_PRED_LSTM;
         const int nt_a = (weights->h_joint + 15) / 16, nt_b = lstm ? (weights->h_pred + 3) / 4 : 0;
         const int q4 = (nt_a + 3) / 4 + (nt_b + 3) / 4;
@@ -298,7 +338,13 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
             if (n_clusters < 2) n_clusters = 2;
         } else if (lstm) {
             n_clusters = fit;
-            if (fit < 8 && B >= 14 * 8) n_clusters = 8;
+            // from about 14 hypotheses per group of eight on: groups of one full row tile (B = 160, ten
+            // groups: 3.04 ms, eight: 3.81 ms) while a group keeps about 20 workgroups, then 16 groups
+            // (B = 256: 4.59 ms, eight: 4.91 ms)
+            if (fit < 8 && B >= 14 * 8) {
+                const int full = (B + 15) / 16;
+                n_clusters = full <= 8 ? 8 : full <= 13 ? full : 16;
+            }
         } else {
             // no predictor-side phase, no matrix but the output layer's: small groups.  Two
             // hypotheses a group up to 28 groups (nine workgroups a group: still one work item of
@@ -339,20 +385,36 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     float *pred_tab = weights->pred_kind == TDT_PRED_STATELESS && !on_the_fly
                           ? reinterpret_cast<float *>(ws + L.pred_tab) : nullptr;
     const PackedLayout PL = packed_layout(weights);
+    // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
+    // streamed output layer, groups it can hold), else the general one
+    const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
+    const bool label = algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
+                       label_kernel_takes(weights, state != nullptr, hyps_per_cluster, C);
+    LabelLayout LL{};
+    ClearRanges clear{};
+    char *const lb = ws + L.partials;
+    if (label) {
+        LL = label_layout(weights, n_clusters, hyps_per_cluster, C);
+        clear.zero = lb + LL.zero_begin;
+        clear.zero_bytes = LL.zero_end - LL.zero_begin;
+        clear.ones = lb + LL.ones_begin;
+        clear.ones_bytes = LL.ones_end - LL.ones_begin;
+    } else {
+        clear.zero = ws + L.zero_begin;
+        clear.zero_bytes = L.zero_end - L.zero_begin;
+    }
     if (!reuse_enc_proj && weights->dtype == 1) {
         // one launch: the projection, the predictor side's per-label tables, the clearing
         // (projections on the fly: no rows for the projection here)
         if (launch_prepare_bf16(enc, enc_len, on_the_fly ? 0 : B, T, weights, enc_proj, emb_gates, pred_tab, PL,
-                                on_the_fly, ws + L.packed, ws + L.zero_begin, L.zero_end - L.zero_begin,
-                                reinterpret_cast<long long *>(out_stats), s) != hipSuccess)
+                                on_the_fly, ws + L.packed, clear, reinterpret_cast<long long *>(out_stats), s) !=
+            hipSuccess)
             return TDT_ERR_LAUNCH;
     } else {
         // (a call that reuses the projections of an earlier one still gets its own copies of the
         // matrices: the caller vouches for the projections, not for what else the workspace holds)
         if (launch_pack_weights(weights, PL, on_the_fly, ws + L.packed, s) != hipSuccess) return TDT_ERR_LAUNCH;
-        if (launch_init(ws + L.zero_begin, L.zero_end - L.zero_begin, reinterpret_cast<long long *>(out_stats),
-                        s) != hipSuccess)
-            return TDT_ERR_LAUNCH;
+        if (launch_init(clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess) return TDT_ERR_LAUNCH;
     }
     if (!reuse_enc_proj && weights->dtype != 1) {
         if (!on_the_fly && launch_encoder_projection_valid(enc, enc_len, B, T, weights, enc_proj, s) != hipSuccess)
@@ -388,7 +450,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     p.n_clusters = n_clusters;
     p.frame_loop = algorithm == TDT_ALG_FRAME_LOOPING;
     p.selftest_stall = selftest_stall != 0;
-    p.hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
+    p.hyps_per_cluster = hyps_per_cluster;
     for (int j = 0; j < TDT_MAX_DURATIONS; ++j) p.durations[j] = j < weights->n_dur ? durations[j] : 0;
     p.emb = weights->emb;
     for (int l = 0; l < TDT_MAX_LSTM_LAYERS; ++l) {
@@ -449,6 +511,27 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         const int khz = wall_clock_khz();
         p.timeout_ticks = wait_timeout_us > 0 ? (long long)wait_timeout_us * khz / 1000 : 4000LL * khz;
         if (p.timeout_ticks < 1) p.timeout_ticks = 1;
+    }
+    if (label) {
+        p.hbuf = reinterpret_cast<float *>(lb + LL.hx);
+        p.pred_proj = reinterpret_cast<float *>(lb + LL.px);
+        p.packed = ws + L.packed;
+        p.packed_bytes = PL.total;
+        p.off_w_pred = (int)PL.w_pred.offset;
+        p.off_w_out = (int)PL.w_out.offset;
+        for (int l = 0; l < TDT_MAX_LSTM_LAYERS; ++l) {
+            p.off_w_ih[l] = (int)PL.w_ih[l].offset;
+            p.off_w_hh[l] = (int)PL.w_hh[l].offset;
+        }
+        p.row_lab = reinterpret_cast<unsigned long long *>(lb + LL.row_lab);
+        p.row_lse = reinterpret_cast<unsigned long long *>(lb + LL.row_lse);
+        p.row_dur = reinterpret_cast<unsigned long long *>(lb + LL.row_dur);
+        p.present = reinterpret_cast<unsigned long long *>(lb + LL.present);
+        p.abort_flag = reinterpret_cast<int *>(lb + LL.abort_flag);
+        p.rows_per_cluster = LL.rows_per_cluster;
+        p.cells_per_cluster = LL.cells_per_cluster;
+        if (launch_label(p, weights, state != nullptr, grid, s) != hipSuccess) return TDT_ERR_LAUNCH;
+        return TDT_OK;
     }
     if (launch_decode(p, weights, variant, grid, s) != hipSuccess) return TDT_ERR_LAUNCH;
     return TDT_OK;

@@ -21,6 +21,13 @@ constexpr int kBarrierStride = 32;            // uint32 slots between two workgr
 constexpr int kMaxRankedBatch = 1024;          // largest batch whose hypotheses are dealt to the clusters by length
 constexpr int kMaxDuration = 1 << 20;          // largest frame increment of a duration class
 constexpr int kRowBufs = 4;                   // rotating per-row argmax buffers
+constexpr size_t kLdsBytes = 160 * 1024;      // LDS of a compute unit
+// label_loop.hip: hypotheses a group can hold (one lane each), (hypothesis, frame) rows of a joint pass,
+// and column tiles multiplied per round (what the registers hold)
+constexpr int kLabelThreads = 256;
+constexpr int kLabelMaxHyps = 64;
+constexpr int kLabelRowsPerPass = 256;
+constexpr int label_tiles(int nk) { return nk <= 5 ? 4 : 2; }   // (nk: steps of the reduction per wavefront)
 
 // Softmax-denominator share of one slice of label columns for one joint row.
 struct __align__(8) LsePartial {
@@ -37,7 +44,7 @@ struct DecodeParams {
     int pred_kind, pred_layers, h_pred, emb_dim;
     int max_symbols, u_cap;
     int window;            // 0 = automatic
-    int joint_tiles;       // column tiles per joint work item the automatic window aims at (0 = automatic: 4 to 8)
+    int joint_tiles;       // column tiles per joint work item the automatic window aims at (0 = automatic: 4 to 12)
     int kseg_max;          // longest K segment staged at once (set by launch_decode)
     int lds_bytes;         // dynamic LDS of the launch, a multiple of 16 (set by launch_decode)
     int n_clusters, hyps_per_cluster;
@@ -77,6 +84,14 @@ struct DecodeParams {
     unsigned long long *row_lab;  // [n_clusters][kRowBufs][rows_per_cluster] packed (logit, ~label)
     unsigned long long *row_dur;  // same shape, packed (logit, ~duration class)
     int rows_per_cluster;
+    // label_loop.hip: row_lab and row_lse are [n_clusters][kRowBufs][cells_per_cluster], row_dur is
+    // [n_clusters][kRowBufs][2][rows_per_cluster], present [n_clusters][kRowBufs + 1][C] (workgroups
+    // without a work item)
+    unsigned long long *row_lse, *present;
+    int cells_per_cluster;
+    const void *packed;    // all fragment-major copies, and where each starts (bytes)
+    size_t packed_bytes;
+    int off_w_pred, off_w_out, off_w_ih[TDT_MAX_LSTM_LAYERS], off_w_hh[TDT_MAX_LSTM_LAYERS];
     unsigned *barrier;       // one flag word per workgroup, a cluster's flags side by side
     int *abort_flag;
     long long timeout_ticks; // bound on one wait, in wall-clock ticks
@@ -90,6 +105,17 @@ struct WorkspaceLayout {
 };
 
 WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T);
+
+// What label_loop.hip exchanges, laid over the part of the workspace the general kernel uses
+// from `partials` on (byte offsets from there).  [ones_begin, ones_end) is filled with ones,
+// [zero_begin, zero_end) with zeros before the kernel starts.
+struct LabelLayout {
+    size_t ones_begin, hx, px, ones_end, zero_begin, row_lab, row_lse, row_dur, present, abort_flag, zero_end;
+    int rows_per_cluster, cells_per_cluster;
+};
+LabelLayout label_layout(const tdt_weights_t *w, int n_clusters, int hyps_per_cluster, int C);
+// whether that kernel can decode groups of this many hypotheses on C workgroups each
+bool label_kernel_takes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C);
 
 // the caller-held state of tdt_greedy_decode_chunk: byte offsets of its arrays
 struct StateLayout {
@@ -138,12 +164,16 @@ PackedLayout packed_layout(const tdt_weights_t *w);
 hipError_t launch_pack_weights(const tdt_weights_t *w, const PackedLayout &pl, bool on_the_fly, void *packed,
                                hipStream_t stream);
 // (the same copies as part of the one launch that prepares a call)
+// what a call clears before its decode kernel: one range to zeros, one to ones (multiples of 16 bytes)
+struct ClearRanges {
+    void *zero, *ones;
+    size_t zero_bytes, ones_bytes;
+};
 hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
                                float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
-                               bool on_the_fly, void *packed, void *zero_begin, size_t zero_bytes,
-                               long long *out_stats, hipStream_t stream);
-hipError_t launch_init(void *zero_begin, size_t zero_bytes, long long *out_stats,
-                       hipStream_t stream);
+                               bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
+                               hipStream_t stream);
+hipError_t launch_init(const ClearRanges &clear, long long *out_stats, hipStream_t stream);
 // which compiled form of the decode kernel a call runs
 struct DecodeVariant {
     bool chunked;      // tdt_greedy_decode_chunk
@@ -153,6 +183,8 @@ struct DecodeVariant {
 };
 hipError_t launch_decode(const DecodeParams &p, const tdt_weights_t *w, DecodeVariant v, int grid,
                          hipStream_t stream);
+// the same for label_loop.hip's kernel (label_kernel_takes)
+hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, int grid, hipStream_t stream);
 // largest grid the decode kernel can run with all workgroups resident, 0 on error
 int decode_max_grid(const tdt_weights_t *w, DecodeVariant v);
 // ticks per millisecond of the device wall clock the kernels read (100000 if the query fails)

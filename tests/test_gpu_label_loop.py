@@ -1,0 +1,64 @@
+"""The label-looping kernel of csrc/label_loop.hip where its forms meet: groups that fill or just
+exceed what one staging tile packs or holds, reductions at the borders of its compiled lengths,
+output layers at the borders of a round of column tiles, groups of one workgroup, passes of more rows
+than a wavefront has lanes, and what falls back to the general kernel -- against the oracle."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2406_06220_amd import synth
+from test_gpu_parity import check, gpu  # noqa: F401  (gpu: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def config(name, **kw):
+    base = dict(dtype="bf16", pred_kind="lstm", d_enc=32, h_pred=40, emb_dim=24, h_joint=48, vocab=70, B=12, T=30,
+                len_lo=0, len_hi=30, seed=300, default_blank_bias=1.0, max_symbols=4)
+    base.update(kw)
+    return synth.small_config(name, **base)
+
+
+CASES = [
+    # hypotheses of one group: packed planes up to 4, one row per wavefront pair up to 8, one row tile up
+    # to 16, several row tiles, the most a lane holds, and beyond it
+    *[(config(f"ll_group{n}", B=n), dict(n_clusters=1)) for n in (1, 4, 5, 8, 9, 16, 17, 33, 64, 65)],
+    # more than one cell a thread; more column tiles a workgroup than a round
+    (config("ll_cells", h_pred=320, B=30), dict(n_clusters=15)),
+    (config("ll_rounds", h_pred=320, B=60), dict(n_clusters=60)),
+    # groups of one and of two workgroups
+    (config("ll_c1", B=256, T=8, len_hi=8), dict(n_clusters=256)),
+    (config("ll_c1_tdt", B=250, T=9, len_hi=9, durations=(0, 1, 2)), dict(n_clusters=250)),
+    (config("ll_c2", B=128, T=8, len_hi=8, durations=(0, 1, 3)), dict(n_clusters=128)),
+    # reductions: one step, the compiled lengths and one input group beyond, the longest
+    *[(config(f"ll_k{h}_{hp}", h_joint=h, h_pred=hp, emb_dim=24, B=5), {})
+      for h, hp in ((8, 8), (32, 648), (640, 640), (648, 32), (1024, 1000), (1032, 40))],
+    # column tiles: a multiple, one column more, duration outputs across a tile border
+    *[(config(f"ll_v{v}_{len(d)}", vocab=v, durations=d, B=7), dict(n_clusters=c))
+      for v, d, c in ((63, (), 7), (64, (), 7), (254, (0, 1, 2), 7), (1021, (0, 1, 2, 3, 4), 2))],
+    # passes of more than 64 rows, windows cut by the row limit
+    (config("ll_rows", B=30, durations=(1, 2)), dict(n_clusters=2, window=8)),
+    (config("ll_rows_cap", B=50), dict(n_clusters=1, window=64)),
+    # stateless predictors, one and two labels of context
+    (config("ll_stateless1", pred_kind="stateless", pred_layers=1, h_pred=24, B=20), {}),
+    (config("ll_stateless2", pred_kind="stateless", pred_layers=2, h_pred=48, B=70, durations=(0, 2)), {}),
+    (config("ll_mb_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, B=9, durations=(2, 4), multi_blank=True),
+     dict(n_clusters=1)),
+    # deeper LSTMs on several row tiles
+    (config("ll_deep", pred_layers=3, B=40), dict(n_clusters=2)),
+]
+
+
+@pytest.mark.parametrize("cfg,opts", CASES, ids=[c.name for c, _ in CASES])
+def test_label_loop(oracle_lib, gpu, cfg, opts):   # noqa: F811
+    check(oracle_lib, gpu, cfg, max_replayed_frac=0.1, **opts)
+
+
+@pytest.mark.parametrize("kw", [dict(B=6), dict(B=40, pred_layers=2), dict(B=9, pred_kind="stateless", h_pred=24)],
+                         ids=["one_layer", "two_layers", "stateless"])
+def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
+    from test_gpu_chunks import check_chunks
+    cfg = config("ll_chunks", durations=(0, 1, 5), **kw)
+    for ncl in (0, 1):
+        check_chunks(oracle_lib, gpu, cfg, "random", 4, n_clusters=ncl)
+    check_chunks(oracle_lib, gpu, cfg, "single", 0)
