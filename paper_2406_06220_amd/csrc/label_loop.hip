@@ -31,11 +31,12 @@
 // Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
 // exchange (a workgroup without work item: a word of its own that everybody waits for), after it
 // has finished reading all earlier exchanges.  So a workgroup that has read joint exchange j knows
-// that all others have read joint exchange j - 1 and the h and projection rows of this label: it
-// puts its own words of those back.  The stores complete before it publishes joint exchange j + 1
-// (every wavefront waits for its stores before the workgroup barrier that precedes publishing), and
-// the next readers of those words come only behind that exchange: rows alternate between two
-// buffers by label, cells rotate through four.
+// that all others have read the h and projection rows of this label, and the cells of joint exchange
+// j - 2 (those of j - 1 not for certain: the score terms found in it are summed while j's cells
+// travel): it puts its own words of those back.  The stores complete before it publishes joint
+// exchange j + 1 (every wavefront waits for its stores before the workgroup barrier that precedes
+// publishing), and the next readers of those words come only behind that exchange: rows alternate
+// between two buffers by label, cells rotate through four.
 #include <math.h>
 
 #include <mutex>
@@ -601,7 +602,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     int par = 0;                     // which buffer this label's rows go through
     unsigned jpass = 0;              // joint exchanges so far
     int prev_items = 0, prev_tiles = 0, prev_cg = 1;   // the last pass: work items, row tiles, column groups
-    int clr_items = 0, clr_tiles = 0;                  // the one before it
+    int prev2_items = 0, prev2_tiles = 0, clr_items = 0, clr_tiles = 0;   // the two before it
     unsigned long long act_prev = 0ull;        // who took part in the previous label's rows
     bool first = true, ok = true;
 
@@ -633,10 +634,10 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                         st_co4(px + ((size_t)pb * Bw + b0 + g) * H + qt0 * CT + c0 + c, make_float4(m, m, m, m));
         }
     };
-    // ... and its cells of the joint pass before the last
+    // ... and its cells of the joint pass two before the last
     auto clear_cells = [&]() __attribute__((always_inline)) {
-        if (C > 1 && jpass > 1) {
-            const unsigned pb = (jpass - 2) & (kRowBufs - 1);
+        if (C > 1 && jpass > 2) {
+            const unsigned pb = (jpass - 3) & (kRowBufs - 1);
 #pragma clang loop unroll(disable)
             for (int it = rank; it < clr_items; it += C)
                 if (tid < 2 * RT) st_co64((tid < RT ? jb : jl) + (size_t)pb * cells + (size_t)it * RT + (tid & 15), 0ull);
@@ -1036,6 +1037,8 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 #pragma clang loop unroll(disable)
         for (bool again = false; needm != 0ull; again = true) {
             fresh();
+            // (a group of one workgroup: this pass writes over what the terms of the last one are summed from)
+            if (C == 1 && (!LSTM || again) && wave == kLW - 1) finish_scores();
             if (again) plan_pass(needm);
             const unsigned buf = jpass & (kRowBufs - 1);
             ++jpass;
@@ -1224,7 +1227,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 
             // ---- while the cells travel: the score terms of the pass before
             fresh();
-            if (!LSTM || again) {   // (an LSTM's first pass: summed while the hidden state travelled)
+            if (C > 1 && (!LSTM || again)) {   // (an LSTM's first pass: summed while the hidden state travelled)
                 --jpass;   // (finish_scores looks at the last pass)
                 if (wave == kLW - 1) finish_scores();
                 ++jpass;
@@ -1382,10 +1385,12 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             pend_m = unpack_value((unsigned long long)kb << 32);
             needm = __ballot(need);
             TR(33);
-            // everybody has read the pass before this one: its cells are put back (behind the label's
+            // everybody has read the pass two before this one: its cells are put back (behind the label's
             // last pass: while the next label's hidden state travels)
-            clr_items = prev_items;
-            clr_tiles = prev_tiles;
+            clr_items = prev2_items;
+            clr_tiles = prev2_tiles;
+            prev2_items = prev_items;
+            prev2_tiles = prev_tiles;
             prev_items = items;
             prev_tiles = n_tiles;
             prev_cg = n_cg;

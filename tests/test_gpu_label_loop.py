@@ -41,6 +41,10 @@ CASES = [
     (config("ll_rows_cap", B=50), dict(n_clusters=1, window=64)),
     # stateless predictors, one and two labels of context
     (config("ll_stateless1", pred_kind="stateless", pred_layers=1, h_pred=24, B=20), {}),
+    # score terms still being summed while the next pass is exchanged: many hypotheses a workgroup, one workgroup
+    (config("ll_stateless_many", pred_kind="stateless", pred_layers=1, h_pred=24, B=2100, T=14, len_hi=14), {}),
+    (config("ll_stateless_c1", pred_kind="stateless", pred_layers=1, h_pred=24, B=256, T=20, len_hi=20),
+     dict(n_clusters=256, window=2)),
     (config("ll_stateless2", pred_kind="stateless", pred_layers=2, h_pred=48, B=70, durations=(0, 2)), {}),
     (config("ll_mb_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, B=9, durations=(2, 4), multi_blank=True),
      dict(n_clusters=1)),
