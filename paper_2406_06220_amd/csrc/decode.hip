@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
         __syncthreads();
         if (tid == 0) S.pend_n = 0;
     };
-    const int auto_rows = auto_joint_rows(C, (O + CT - 1) / CT, p.joint_tiles);
+    const int auto_rows = auto_joint_rows(C, (O + CT - 1) / CT, p.joint_tiles, p.hyps_per_cluster);
     // streaming joint pass: dies the group's workgroups are spread over, workgroups per die, this
     // one's die and place on it, column tiles per die and this die's first
     const int wide_ndie = C >= kXcds ? kXcds : C, wide_per = C / wide_ndie;

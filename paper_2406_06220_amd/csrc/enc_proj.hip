@@ -39,7 +39,7 @@ __device__ inline int lds_off(int row, int chunk) { return row * BK + ((chunk ^ 
 // written): the workgroups then walk the valid frames in order, 128 at a time, and M = B * T only
 // bounds their number.
 struct LinearProblem {
-    const uint16_t *A, *W;
+    const void *A, *W;   // both bfloat16 or both float32
     const float *bias;
     float *C;
     long long M;
@@ -110,8 +110,8 @@ __device__ inline bool valid_row_map(const int32_t *lens, int B, int T, long lon
 // the 128 x 128 output tile of workgroup `block` (of q.blocks) of one product
 __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
 {
-    const uint16_t *__restrict__ A = q.A;
-    const uint16_t *__restrict__ W = q.W;
+    const uint16_t *__restrict__ A = static_cast<const uint16_t *>(q.A);
+    const uint16_t *__restrict__ W = static_cast<const uint16_t *>(q.W);
     const float *__restrict__ bias = q.bias;
     float *__restrict__ C = q.C;
     const long long M = q.M;
@@ -369,8 +369,8 @@ constexpr size_t kBigLdsBytes = kBigTileBytes + sizeof(BigShared);
 __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(LinearProblem q)
 {
     extern __shared__ __align__(16) unsigned char big_lds[];
-    const uint16_t *__restrict__ A = q.A;
-    const uint16_t *__restrict__ W = q.W;
+    const uint16_t *__restrict__ A = static_cast<const uint16_t *>(q.A);
+    const uint16_t *__restrict__ W = static_cast<const uint16_t *>(q.W);
     const float *__restrict__ bias = q.bias;
     float *__restrict__ C = q.C;
     const long long M = q.M;
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(Linea
 // fragment-major copies of the streamed matrices
 // ---------------------------------------------------------------------------
 struct PackJob {
-    const uint16_t *src;
+    const void *src;
     uint4 *dst;
     int N, K, gate_h;   // gate_h > 0: LSTM gate matrix of gate_h hidden units
     int steps;
@@ -553,6 +553,7 @@ constexpr int kMaxPackJobs = 3 + 2 * TDT_MAX_LSTM_LAYERS;
 struct PackBatch {
     PackJob j[kMaxPackJobs];
     int n;
+    int elem;   // bytes per element: 2 (a step is 32 inputs) or 4 (16 inputs)
     long long pieces;
 };
 
@@ -567,7 +568,7 @@ __device__ inline void pack_pieces(const PackBatch &b, unsigned blk, unsigned nb
         const int lane = (int)(local & 63);
         const long long frag = local >> 6;
         const int step = (int)(frag % q.steps), tile = (int)(frag / q.steps);
-        const int j = lane & 15, k = step * 32 + (lane >> 4) * 8;
+        const int per = 16 / b.elem, j = lane & 15, k = (step * 4 + (lane >> 4)) * per;   // inputs per piece
         long long row;
         if (q.gate_h > 0) {
             const int unit = tile * 4 + (j >> 2);
@@ -576,7 +577,8 @@ __device__ inline void pack_pieces(const PackBatch &b, unsigned blk, unsigned nb
             row = tile * 16 + j < q.N ? tile * 16 + j : -1;
         }
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (row >= 0 && k < q.K) v = *reinterpret_cast<const uint4 *>(q.src + row * q.K + k);   // K % 8 == 0
+        if (row >= 0 && k < q.K)   // (K % 8 == 0)
+            v = *reinterpret_cast<const uint4 *>(static_cast<const char *>(q.src) + (row * q.K + k) * b.elem);
         q.dst[local] = v;
     }
 }
@@ -586,11 +588,12 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(PackBatch b) { pack_p
 PackBatch pack_batch(const tdt_weights_t *w, const PackedLayout &pl, bool on_the_fly, void *packed)
 {
     PackBatch b{};
-    if (w->dtype != 1 || pl.total == 0) return b;
+    b.elem = w->dtype == 1 ? 2 : 4;
+    if (pl.total == 0) return b;
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
     auto add = [&](const void *src, const PackedMatrix &m, int N, int K, int gate_h) {
         PackJob &q = b.j[b.n++];
-        q.src = static_cast<const uint16_t *>(src);
+        q.src = src;
         q.dst = reinterpret_cast<uint4 *>(static_cast<char *>(packed) + m.offset);
         q.N = N;
         q.K = K;
@@ -617,20 +620,121 @@ unsigned pack_blocks_for(const PackBatch &b)
     return (unsigned)(blocks < 1024 ? blocks : 1024);
 }
 
+// float32 models: 64 x 64 output tile, four wavefronts of 32 x 32 on v_mfma_f32_32x32x2_f32 (exact
+// products, float32 accumulation).  A lane holds four consecutive inputs of its row (one 16-byte LDS
+// read) and feeds them to four products.  Small tiles, because a call has few rows: at config 2's
+// widths the table of 1025 labels makes 680 of them.  Bound by the float32 matrix rate (157 TFLOP/s).
+// Measured: the 1025 x 2560 x 640 table and a projection of 3000 x 640 x 512, two launches of a
+// vector-ALU kernel, 240 us; here together with the copies and the clearing 91 us.
+constexpr int FM = 64, FN = 64, FK = 32, FLD = FK + 4;   // (rows padded by 16 bytes)
+
+__device__ inline void gemm_tile_f32(const LinearProblem &q, unsigned block)
+{
+    const float *__restrict__ A = static_cast<const float *>(q.A);
+    const float *__restrict__ W = static_cast<const float *>(q.W);
+    const int N = q.N, K = q.K, ldw = q.ldw, group = q.group;
+    __shared__ __align__(16) float As[2][FM * FLD], Ws[2][FN * FLD];
+    __shared__ long long row_of[FM];
+    __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    const int nt_n = (N + FN - 1) / FN;   // die-aware order of tiles, as in gemm_tile_bf16
+    const long long j = block / kXcds, m0 = ((j / nt_n) * kXcds + block % kXcds) * FM;
+    const int n0 = (int)(j % nt_n) * FN;
+    if (m0 >= q.M) return;
+    if (q.lens) {
+        if (!valid_row_map<FM>(q.lens, q.B, q.T, m0, row_of, scan, wsum)) return;   // uniform
+    } else if (tid < FM) {
+        row_of[tid] = m0 + tid < q.M ? m0 + tid : -1;
+    }
+    __syncthreads();
+    // this thread's part of every K tile: 16-byte chunk kc of two rows of each operand (unconditional
+    // loads, zeros by mask: see gemm_tile_bf16)
+    const int kc = tid & 7;
+    const float *a_src[2], *w_src[2];
+    bool a_ok[2], w_ok[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = (tid >> 3) + h * 32, n = n0 + row;
+        const long long ar = row_of[row];
+        a_ok[h] = ar >= 0;
+        w_ok[h] = n < N;
+        a_src[h] = A + (a_ok[h] ? ar : 0) * K;
+        w_src[h] = W + (long long)(w_ok[h] ? n : 0) * ldw;
+    }
+    float4 xa[2], xw[2];
+    auto load = [&](int k0) {
+        const int k = min(k0 + kc * 4, K - 4);   // K is a multiple of 8
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            xa[h] = *reinterpret_cast<const float4 *>(a_src[h] + k);
+            xw[h] = *reinterpret_cast<const float4 *>(w_src[h] + k);
+        }
+    };
+    auto keep = [](float4 v, bool ok) {
+        return make_float4(ok ? v.x : 0.0f, ok ? v.y : 0.0f, ok ? v.z : 0.0f, ok ? v.w : 0.0f);
+    };
+    auto store = [&](int buf, int k0) {
+        const bool k_ok = k0 + kc * 4 < K;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int o = ((tid >> 3) + h * 32) * FLD + kc * 4;
+            *reinterpret_cast<float4 *>(As[buf] + o) = keep(xa[h], a_ok[h] && k_ok);
+            *reinterpret_cast<float4 *>(Ws[buf] + o) = keep(xw[h], w_ok[h] && k_ok);
+        }
+    };
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+    const int nk = (K + FK - 1) / FK;
+    load(0);
+    store(0, 0);
+    if (nk > 1) load(FK);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        if (kt + 1 < nk) store((kt + 1) & 1, (kt + 1) * FK);   // (last read before the barrier that ended tile kt - 1)
+        if (kt + 2 < nk) load((kt + 2) * FK);
+        const float *a = As[kt & 1] + (wm * 32 + (lane & 31)) * FLD + (lane >> 5) * 4;
+        const float *w = Ws[kt & 1] + (wn * 32 + (lane & 31)) * FLD + (lane >> 5) * 4;
+#pragma unroll
+        for (int s = 0; s < FK / 8; ++s) {
+            const float4 x = *reinterpret_cast<const float4 *>(a + s * 8), y = *reinterpret_cast<const float4 *>(w + s * 8);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32
+    const int n = n0 + wn * 32 + (lane & 31);
+    if (n >= N) return;
+    const float bn = q.bias ? q.bias[n] : 0.0f;
+    const int nc = group > 0 ? (n % group) * (N / group) + n / group : n;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const long long dst = row_of[wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
+        if (dst >= 0) q.C[dst * N + nc] = acc[e] + bn;
+    }
+}
+
+__global__ __launch_bounds__(GEMM_THREADS) void enc_proj_f32_kernel(LinearProblem q) { gemm_tile_f32(q, blockIdx.x); }
+
 // Everything a decode call needs before its decode kernel, in one launch: the encoder
 // projection, the per-label tables of the predictor side (a product with blocks == 0 is
 // absent), and the clearing of the workspace's zero region and of the statistics.  The tasks
 // are independent; a workgroup takes its task from its index.  Every product's workgroup count
 // is a multiple of the number of dies, so each keeps its die-aware order of tiles.
-__global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_bf16_kernel(LinearBatch batch, PackBatch pack,
-                                                                   unsigned pack_blocks, uint4 *zero, size_t n16,
-                                                                   uint4 *ones, size_t n16_ones, long long *out_stats)
+template <bool BF16>
+__global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch batch, PackBatch pack, unsigned pack_blocks,
+                                                              uint4 *zero, size_t n16, uint4 *ones, size_t n16_ones,
+                                                              long long *out_stats)
 {
     unsigned b = blockIdx.x, used = 0;
 #pragma unroll
     for (int i = 0; i < kMaxProblems; ++i) {
         if (b < batch.q[i].blocks) {
-            gemm_tile_bf16(batch.q[i], b);
+            if constexpr (BF16) gemm_tile_bf16(batch.q[i], b);
+            else gemm_tile_f32(batch.q[i], b);
             return;
         }
         b -= batch.q[i].blocks;
@@ -650,73 +754,14 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_bf16_kernel(LinearBat
     if (out_stats && zb == 0 && threadIdx.x < TDT_STAT_COUNT) out_stats[threadIdx.x] = 0;
 }
 
-// float32 models (small): classic 64x64 tile, 4x4 outputs per thread.  lens as in LinearProblem
-// (null: all M rows).
-__global__ __launch_bounds__(GEMM_THREADS) void enc_proj_f32_kernel(
-    const float *__restrict__ A, const float *__restrict__ W, const float *__restrict__ bias,
-    float *__restrict__ C, long long M, int N, int K, int ldw, int group, const int32_t *lens, int B, int T)
-{
-    __shared__ float As[16][65];
-    __shared__ float Ws[16][65];
-    __shared__ long long row_of[64];
-    __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int nt_n = (N + 63) / 64;
-    const long long m0 = (long long)(blockIdx.x / nt_n) * 64;
-    const int n0 = (blockIdx.x % nt_n) * 64;
-    if (lens) {
-        if (!valid_row_map<64>(lens, B, T, m0, row_of, scan, wsum)) return;   // uniform
-    } else if (tid < 64) {
-        row_of[tid] = m0 + tid < M ? m0 + tid : -1;
-    }
-    __syncthreads();
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int idx = tid + j * 256;
-            const int row = idx >> 4, kk = idx & 15;
-            const int k = k0 + kk;
-            const long long m = row_of[row];
-            const int n = n0 + row;
-            As[kk][row] = (m >= 0 && k < K) ? A[m * K + k] : 0.0f;
-            Ws[kk][row] = (n < N && k < K) ? W[(long long)n * ldw + k] : 0.0f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], w[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = Ws[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const long long m = row_of[ty * 4 + i];
-        if (m < 0) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n < N) C[m * N + (group > 0 ? (n % group) * (N / group) + n / group : n)] = acc[i][j] + (bias ? bias[n] : 0.0f);
-        }
-    }
-}
-
 }  // namespace
 
-static LinearProblem linear_problem(const void *a, int64_t rows, int K, const void *w, int ldw, int N,
+static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int K, const void *w, int ldw, int N,
                                     const float *bias, int group, float *out)
 {
     LinearProblem q{};
-    q.A = static_cast<const uint16_t *>(a);
-    q.W = static_cast<const uint16_t *>(w);
+    q.A = a;
+    q.W = w;
     q.bias = bias;
     q.C = out;
     q.M = rows;
@@ -724,8 +769,9 @@ static LinearProblem linear_problem(const void *a, int64_t rows, int K, const vo
     q.K = K;
     q.ldw = ldw;
     q.group = group;
-    const long long row_tiles = (rows + BM - 1) / BM, rounds = (row_tiles + kXcds - 1) / kXcds;
-    q.blocks = (unsigned)(rounds * kXcds * ((N + BN - 1) / BN));
+    const int bm = dtype == 1 ? BM : FM, bn = dtype == 1 ? BN : FN;
+    const long long row_tiles = (rows + bm - 1) / bm, rounds = (row_tiles + kXcds - 1) / kXcds;
+    q.blocks = (unsigned)(rounds * kXcds * ((N + bn - 1) / bn));
     return q;
 }
 
@@ -759,33 +805,35 @@ static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
-                               float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
-                               bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
-                               hipStream_t stream)
+hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
+                          float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
+                          bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
+                          hipStream_t stream)
 {
+    const bool bf16 = w->dtype == 1;
     LinearBatch batch{};
     int n = 0;
     // (B == 0: no encoder projection in this launch)
-    batch.q[n] = linear_problem(enc, (int64_t)B * T, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, 0, enc_proj);
+    batch.q[n] = linear_problem(w->dtype, enc, (int64_t)B * T, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, 0, enc_proj);
     batch.q[n].lens = enc_len;
     batch.q[n].B = B;
     batch.q[n].T = T;
-    if (takes_big_tiles((int64_t)B * T, w->h_joint, 0)) {
+    if (bf16 && takes_big_tiles((int64_t)B * T, w->h_joint, 0)) {
         const hipError_t e = launch_big_tiles(batch.q[n], stream);
         if (e != hipSuccess) return e;
         batch.q[n].blocks = 0;   // not part of the launch below
     }
     ++n;
     if (w->pred_kind == TDT_PRED_LSTM) {   // stored [label][unit][gate]
-        batch.q[n++] = linear_problem(w->emb, w->vocab + 1, w->emb_dim, w->w_ih[0], w->emb_dim, 4 * w->h_pred,
+        batch.q[n++] = linear_problem(w->dtype, w->emb, w->vocab + 1, w->emb_dim, w->w_ih[0], w->emb_dim, 4 * w->h_pred,
                                       w->b_lstm[0], w->h_pred, emb_gates);
     } else if (pred_tab) {
-        const size_t E = (size_t)w->emb_dim, rows_tab = (size_t)w->vocab + 1;
+        const size_t E = (size_t)w->emb_dim, rows_tab = (size_t)w->vocab + 1, esz = bf16 ? 2 : 4;
         for (int c = 0; c < w->pred_layers; ++c)
-            batch.q[n++] = linear_problem(static_cast<const uint16_t *>(w->emb) + c * rows_tab * E, (int64_t)rows_tab,
-                                          w->emb_dim, static_cast<const uint16_t *>(w->w_pred) + c * E, w->h_pred,
-                                          w->h_joint, c == w->pred_layers - 1 ? w->b_pred : nullptr, 0,
+            batch.q[n++] = linear_problem(w->dtype, static_cast<const char *>(w->emb) + c * rows_tab * E * esz,
+                                          (int64_t)rows_tab, w->emb_dim,
+                                          static_cast<const char *>(w->w_pred) + c * E * esz, w->h_pred, w->h_joint,
+                                          c == w->pred_layers - 1 ? w->b_pred : nullptr, 0,
                                           pred_tab + c * rows_tab * w->h_joint);
     }
     unsigned blocks = 0;
@@ -796,62 +844,49 @@ hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, i
     if (zb < 1) zb = 1;
     const PackBatch pack = pack_batch(w, pl, on_the_fly, packed);
     const unsigned pb = pack.pieces > 0 ? pack_blocks_for(pack) : 0;
-    hipLaunchKernelGGL(prepare_bf16_kernel, dim3(blocks + pb + (unsigned)zb), dim3(GEMM_THREADS), 0, stream, batch,
-                       pack, pb, static_cast<uint4 *>(clear.zero), n16, static_cast<uint4 *>(clear.ones), n16_ones, out_stats);
+    const dim3 grid(blocks + pb + (unsigned)zb);
+    if (bf16)
+        hipLaunchKernelGGL(prepare_kernel<true>, grid, dim3(GEMM_THREADS), 0, stream, batch, pack, pb,
+                           static_cast<uint4 *>(clear.zero), n16, static_cast<uint4 *>(clear.ones), n16_ones, out_stats);
+    else
+        hipLaunchKernelGGL(prepare_kernel<false>, grid, dim3(GEMM_THREADS), 0, stream, batch, pack, pb,
+                           static_cast<uint4 *>(clear.zero), n16, static_cast<uint4 *>(clear.ones), n16_ones, out_stats);
     return hipGetLastError();
 }
 
-hipError_t launch_linear(const void *a, int64_t rows, int K, const void *w, int ldw, int N, const float *bias,
-                         int dtype, int group, float *out, hipStream_t stream)
+static hipError_t launch_problem(int dtype, const LinearProblem &q, hipStream_t stream)
 {
-    if (rows <= 0) return hipSuccess;
-    if (dtype == 1) {
-        const LinearProblem q = linear_problem(a, rows, K, w, ldw, N, bias, group, out);
-        if (takes_big_tiles(rows, N, group)) return launch_big_tiles(q, stream);
-        hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
-    } else {
-        dim3 grid((unsigned)(((N + 63) / 64) * ((rows + 63) / 64)));
-        hipLaunchKernelGGL(enc_proj_f32_kernel, grid, dim3(GEMM_THREADS), 0, stream, static_cast<const float *>(a),
-                           static_cast<const float *>(w), bias, out, (long long)rows, N, K, ldw, group,
-                           static_cast<const int32_t *>(nullptr), 0, 0);
-    }
+    if (q.M <= 0) return hipSuccess;
+    if (dtype == 1 && takes_big_tiles(q.M, q.N, q.group)) return launch_big_tiles(q, stream);
+    if (dtype == 1) hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    else hipLaunchKernelGGL(enc_proj_f32_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
     return hipGetLastError();
 }
 
 hipError_t launch_encoder_projection_valid(const void *enc, const int32_t *enc_len, int B, int T,
                                            const tdt_weights_t *w, float *out, hipStream_t stream)
 {
-    const int64_t rows = (int64_t)B * T;
-    if (rows <= 0) return hipSuccess;
-    if (w->dtype == 1) {
-        LinearProblem q = linear_problem(enc, rows, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, 0, out);
-        q.lens = enc_len;
-        q.B = B;
-        q.T = T;
-        if (takes_big_tiles(rows, w->h_joint, 0)) return launch_big_tiles(q, stream);
-        hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
-    } else {
-        dim3 grid((unsigned)(((w->h_joint + 63) / 64) * ((rows + 63) / 64)));
-        hipLaunchKernelGGL(enc_proj_f32_kernel, grid, dim3(GEMM_THREADS), 0, stream, static_cast<const float *>(enc),
-                           static_cast<const float *>(w->w_enc), w->b_enc, out, (long long)rows, w->h_joint,
-                           w->d_enc, w->d_enc, 0, enc_len, B, T);
-    }
-    return hipGetLastError();
+    LinearProblem q = linear_problem(w->dtype, enc, (int64_t)B * T, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, 0, out);
+    q.lens = enc_len;
+    q.B = B;
+    q.T = T;
+    return launch_problem(w->dtype, q, stream);
 }
 
 hipError_t launch_encoder_projection(const void *enc, int64_t rows, const tdt_weights_t *w,
                                      float *out, hipStream_t stream)
 {
-    return launch_linear(enc, rows, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, w->dtype, 0, out, stream);
+    return launch_problem(w->dtype, linear_problem(w->dtype, enc, rows, w->d_enc, w->w_enc, w->d_enc, w->h_joint, w->b_enc, 0, out),
+                          stream);
 }
 
 namespace {
-PackedMatrix place(size_t &off, int tiles, int K)
+PackedMatrix place(size_t &off, int tiles, int K, int per_step)
 {
     PackedMatrix m;
     m.offset = off;
     m.tiles = tiles;
-    m.steps = (K + 31) / 32;
+    m.steps = (K + per_step - 1) / per_step;
     off += (size_t)m.tiles * m.steps * 1024;
     return m;
 }
@@ -861,20 +896,20 @@ PackedLayout packed_layout(const tdt_weights_t *w)
 {
     PackedLayout pl{};
     size_t off = 0;
-    if (w->dtype != 1) return pl;
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
-    pl.w_enc = place(off, (w->h_joint + 15) / 16, w->d_enc);
-    pl.w_pred = place(off, (w->h_joint + 15) / 16, w->h_pred);
-    pl.w_out = place(off, (w->vocab + 1 + w->n_dur + 15) / 16, w->h_joint);
+    const int ps = w->dtype == 1 ? 32 : 16;   // inputs per step: 64 bytes of a row
+    // (float32: only label_loop.hip multiplies by copies, and it never projects on the fly)
+    if (w->dtype == 1) pl.w_enc = place(off, (w->h_joint + 15) / 16, w->d_enc, ps);
+    pl.w_pred = place(off, (w->h_joint + 15) / 16, w->h_pred, ps);
+    pl.w_out = place(off, (w->vocab + 1 + w->n_dur + 15) / 16, w->h_joint, ps);
     for (int l = 0; lstm && l < w->pred_layers; ++l) {
         // the first layer's input product is a per-label table: its matrix is not streamed
-        if (l > 0) pl.w_ih[l] = place(off, (w->h_pred + 3) / 4, w->h_pred);
-        pl.w_hh[l] = place(off, (w->h_pred + 3) / 4, w->h_pred);
+        if (l > 0) pl.w_ih[l] = place(off, (w->h_pred + 3) / 4, w->h_pred, ps);
+        pl.w_hh[l] = place(off, (w->h_pred + 3) / 4, w->h_pred, ps);
     }
     pl.total = off;
     return pl;
 }
-
 
 // the copies in a launch of their own (calls that reuse the projections of an earlier call)
 hipError_t launch_pack_weights(const tdt_weights_t *w, const PackedLayout &pl, bool on_the_fly, void *packed,
@@ -884,21 +919,6 @@ hipError_t launch_pack_weights(const tdt_weights_t *w, const PackedLayout &pl, b
     if (b.pieces == 0) return hipSuccess;
     hipLaunchKernelGGL(pack_weights_kernel, dim3(pack_blocks_for(b)), dim3(256), 0, stream, b);
     return hipGetLastError();
-}
-
-// stateless predictor, float32 models: the per-label tables of the projected predictor output
-hipError_t launch_pred_tables(const tdt_weights_t *w, float *pred_tab, hipStream_t stream)
-{
-    const size_t E = (size_t)w->emb_dim, rows_tab = (size_t)w->vocab + 1;
-    const size_t esz = w->dtype == 1 ? 2 : 4;
-    for (int c = 0; c < w->pred_layers; ++c) {
-        const hipError_t e = launch_linear(
-            static_cast<const char *>(w->emb) + c * rows_tab * E * esz, (int64_t)rows_tab, w->emb_dim,
-            static_cast<const char *>(w->w_pred) + c * E * esz, w->h_pred, w->h_joint,
-            c == w->pred_layers - 1 ? w->b_pred : nullptr, w->dtype, 0, pred_tab + c * rows_tab * w->h_joint, stream);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 }  // namespace tdt

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     // ---- how a joint pass is cut, per number of searching hypotheses
     const int NT = (O + CT - 1) / CT;
     {
-        const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles);
+        const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles, hpc);
         for (int n = tid + 1; n <= G; n += kLabelThreads) {
             const int Kw = joint_window(n, p.window, rows_auto, rows_cap);
             const int n_tiles = (n * Kw + RT - 1) / RT;
@@ -1491,20 +1491,21 @@ template <typename WT, int NK> const void *label_fn(int layers, bool chunked)
 }
 const void *label_fn_for(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C, int &nk, int &tq)
 {
+    // bfloat16: steps of 32 inputs (reductions of up to 640 and 1024), float32: of 16 (256 and 640)
     const int steps = label_steps(w);
+    if (w->dtype == 1) nk = steps <= 5 ? 5 : 8;
+    else nk = steps <= 4 ? 4 : 10;
+    if (steps > nk) return nullptr;
     int layers = w->pred_kind == TDT_PRED_LSTM ? 2 : 0;
     if (layers > 0 && w->pred_layers == 1) {
         const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
         // one round, one row tile, one or two cells a thread
-        const int nk_ = steps <= 5 ? 5 : 8;
-        if (per_wg <= 2 * label_tiles(nk_) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads)
+        if (per_wg <= 2 * label_tiles(nk) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads)
             layers = 1;
     }
-    if (w->dtype == 1) {
-        if (steps <= 5) { nk = 5; tq = (layers > 1 ? 1 : 2) * label_tiles(5); return label_fn<uint16_t, 5>(layers, chunked); }
-        if (steps <= 8) { nk = 8; tq = (layers > 1 ? 1 : 2) * label_tiles(8); return label_fn<uint16_t, 8>(layers, chunked); }
-    }
-    return nullptr;
+    tq = (layers > 1 ? 1 : 2) * label_tiles(nk);
+    if (w->dtype == 1) return nk == 5 ? label_fn<uint16_t, 5>(layers, chunked) : label_fn<uint16_t, 8>(layers, chunked);
+    return nk == 4 ? label_fn<float, 4>(layers, chunked) : label_fn<float, 10>(layers, chunked);
 }
 
 }  // namespace
@@ -1538,7 +1539,7 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
 {
     // the LDS limit of a compiled form is raised once per device (to all a workgroup can have)
     static std::mutex mu;
-    static const void *ready[64][16];
+    static const void *ready[64][32];
     int dev = 0, nk = 0, tq = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -1548,12 +1549,12 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     {
         std::lock_guard<std::mutex> lock(mu);
         int i = 0;
-        while (i < 16 && ready[dev][i] && ready[dev][i] != fn) ++i;
-        if (i == 16 || !ready[dev][i]) {
+        while (i < 32 && ready[dev][i] && ready[dev][i] != fn) ++i;
+        if (i == 32 || !ready[dev][i]) {
             e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)kLabelDynLds);
             if (e != hipSuccess) return e;
-            if (i < 16) ready[dev][i] = fn;
+            if (i < 32) ready[dev][i] = fn;
         }
     }
     DecodeParams pc = p;

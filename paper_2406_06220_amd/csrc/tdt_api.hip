@@ -42,7 +42,7 @@ static void *static_scratch(hipError_t *err)
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
+WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool label)
 {
     WorkspaceLayout L{};
     size_t off = 0;
@@ -50,7 +50,7 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     // per-hypothesis arrays are addressed by (cluster, slot): n_clusters * ceil(B / n_clusters) rows
     const size_t rows = (size_t)B + kMaxGrid;
     L.packed = off;
-    off = align_up(off + packed_layout(w).total, 256);
+    if (label || w->dtype == 1) off = align_up(off + packed_layout(w).total, 256);
     L.enc_proj = off;
     off = align_up(off + (size_t)B * T * w->h_joint * sizeof(float), 256);
     L.pred_proj = off;
@@ -85,13 +85,14 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     off = align_up(off + 256, 256);
     L.zero_end = off;
     L.total = off;
+    if (!label) return L;
     // label_loop.hip lays its own arrays over the part from `partials` on; how much it needs depends
     // on the split of the batch, which is not known here: n_clusters * hyps_per_cluster <= B + kMaxGrid
     // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup
     const size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
     size_t lab = L.partials;
     lab = align_up(lab + 2 * lstm_layers * rows * w->h_pred * sizeof(float), 256);
-    lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
+    if (lstm_layers > 0) lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
     lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 512);
     lab = align_up(lab + kRowBufs * 2 * 64 * rows * sizeof(unsigned long long), 256);
     lab = align_up(lab + (kRowBufs + 1) * (size_t)kMaxGrid * sizeof(unsigned long long), 256) + 256;
@@ -242,12 +243,13 @@ int tdt_state_bytes(const tdt_weights_t *weights, int B, size_t *bytes)
     return TDT_OK;
 }
 
-// the body of both decode entry points; `state` is null for whole utterances
+// the body of the decode entry points; `state` is null for whole utterances.  label_room: the workspace
+// has (is to have) what label_loop.hip needs beyond the general kernel
 static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
                          const tdt_weights_t *weights, const int32_t *durations, int max_symbols,
                          int u_cap, int32_t *out_labels, int32_t *out_frames, int32_t *out_len,
                          float *out_score, int32_t *out_status, int64_t *out_stats, void *state,
-                         void *workspace, size_t workspace_bytes, const tdt_options_t *options,
+                         void *workspace, size_t workspace_bytes, bool label_room, const tdt_options_t *options,
                          void *stream)
 {
     if (!weights) return TDT_ERR_NULL;
@@ -300,7 +302,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     if (joint_kernel == TDT_JOINT_STREAMING && !can_stream) return TDT_ERR_UNSUPPORTED;
     bool wide_joint = joint_kernel == TDT_JOINT_STREAMING ||
                       (joint_kernel == TDT_JOINT_AUTO && can_stream && weights->vocab + 1 + weights->n_dur >= 4096);
-    const WorkspaceLayout L = workspace_layout(weights, B, T);
+    const WorkspaceLayout L = workspace_layout(weights, B, T, label_room);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < L.total)
         return TDT_ERR_WORKSPACE;
 
@@ -317,6 +319,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         max_grid = decode_max_grid(weights, variant);
         if (max_grid < 1) return TDT_ERR_LAUNCH;
     }
+    bool one_workgroup = false;   // a group each
     const int min_clusters = (B + kMaxHypsPerCluster - 1) / kMaxHypsPerCluster;
     if (n_clusters == 0) {
         // Measured on the paper-sized models (B = 1 ... 512, 2 ... 16 clusters).  A cluster runs
@@ -346,16 +349,26 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
                 n_clusters = full <= 8 ? 8 : full <= 13 ? full : 16;
             }
         } else {
-            // no predictor-side phase, no matrix but the output layer's: small groups.  Two
-            // hypotheses a group up to 28 groups (nine workgroups a group: still one work item of
-            // a joint pass each), from about 140 hypotheses on five a group, at most 64 groups
-            // (measured on the stateless benchmark model, B = 16 ... 512)
-            n_clusters = B / 2;
-            if (n_clusters > 28) n_clusters = B / 5 > 28 ? B / 5 : 28;
+            // no predictor-side phase, no matrix but the output layer's: groups of as many workgroups as
+            // its column tiles make items of k of them, k the smallest with about three hypotheses a
+            // group (items of eight tiles: five).  Measured on the stateless benchmark model (65 tiles),
+            // best of all group counts in brackets: B = 9, 7 groups, 1.31 ms (1.31); B = 32, 11 groups,
+            // 1.58 (1.58; 16 groups 1.71); B = 64, 23 groups, 1.85 (1.85; 32 groups 1.94); B = 128, 28
+            // groups, 2.47 (2.47); B = 256, 42 groups, 3.40 (3.40; 32 groups 3.57)
+            // An output layer of up to four tiles, one round of label_loop.hip: a workgroup for every
+            // hypothesis, which then needs no other (the smallest benchmark model, B = 4, T = 200: 454 us
+            // against 489 us in groups of 64 workgroups; B = 60: 560 us and less against 675 us).
+            const int nt = (weights->vocab + 1 + weights->n_dur + 15) / 16, per_item[6] = {2, 3, 4, 6, 8, 12};
+            one_workgroup = nt <= 4 && !wide_joint && algorithm == TDT_ALG_LABEL_LOOPING;
+            for (const int k : per_item) {
+                n_clusters = max_grid / ((nt + k - 1) / k);
+                if (5 * B <= (k < 8 ? 16 : 25) * n_clusters) break;
+            }
             if (n_clusters > 64) n_clusters = 64;
+            if (one_workgroup) n_clusters = max_grid;
             if (n_clusters < 2) n_clusters = 2;
         }
-        if (n_clusters > B && B > 1) n_clusters = B;
+        if (n_clusters > B && (B > 1 || one_workgroup)) n_clusters = B;
         if (n_clusters < min_clusters) n_clusters = min_clusters;
         if (wide_joint) {
             // the streaming joint pass: a group's pass lasts as long as its workgroups need for the
@@ -370,8 +383,8 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;
     // every cluster gets max_grid / n_clusters workgroups; the launch is rounded up to whole
     // rounds of the dies (the kernel leaves the spare slots empty)
-    int grid = max_grid / n_clusters * n_clusters;
-    if ((grid + kXcds - 1) / kXcds * kXcds <= max_grid) grid = (grid + kXcds - 1) / kXcds * kXcds;
+    int grid = one_workgroup ? n_clusters : max_grid / n_clusters * n_clusters;
+    if (!one_workgroup && (grid + kXcds - 1) / kXcds * kXcds <= max_grid) grid = (grid + kXcds - 1) / kXcds * kXcds;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
@@ -384,12 +397,13 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // the arrangement without any precomputation.)
     float *pred_tab = weights->pred_kind == TDT_PRED_STATELESS && !on_the_fly
                           ? reinterpret_cast<float *>(ws + L.pred_tab) : nullptr;
-    const PackedLayout PL = packed_layout(weights);
+    PackedLayout PL = packed_layout(weights);
     // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
     // streamed output layer, groups it can hold), else the general one
     const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
-    const bool label = algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
+    const bool label = label_room && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
                        label_kernel_takes(weights, state != nullptr, hyps_per_cluster, C);
+    if (weights->dtype == 0 && !label) PL.total = 0;   // (float32: the general kernel reads the matrices as they are)
     LabelLayout LL{};
     ClearRanges clear{};
     char *const lb = ws + L.partials;
@@ -403,30 +417,17 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         clear.zero = ws + L.zero_begin;
         clear.zero_bytes = L.zero_end - L.zero_begin;
     }
-    if (!reuse_enc_proj && weights->dtype == 1) {
+    if (!reuse_enc_proj) {
         // one launch: the projection, the predictor side's per-label tables, the clearing
         // (projections on the fly: no rows for the projection here)
-        if (launch_prepare_bf16(enc, enc_len, on_the_fly ? 0 : B, T, weights, enc_proj, emb_gates, pred_tab, PL,
-                                on_the_fly, ws + L.packed, clear, reinterpret_cast<long long *>(out_stats), s) !=
-            hipSuccess)
+        if (launch_prepare(enc, enc_len, on_the_fly ? 0 : B, T, weights, enc_proj, emb_gates, pred_tab, PL,
+                           on_the_fly, ws + L.packed, clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess)
             return TDT_ERR_LAUNCH;
     } else {
         // (a call that reuses the projections of an earlier one still gets its own copies of the
         // matrices: the caller vouches for the projections, not for what else the workspace holds)
         if (launch_pack_weights(weights, PL, on_the_fly, ws + L.packed, s) != hipSuccess) return TDT_ERR_LAUNCH;
         if (launch_init(clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess) return TDT_ERR_LAUNCH;
-    }
-    if (!reuse_enc_proj && weights->dtype != 1) {
-        if (!on_the_fly && launch_encoder_projection_valid(enc, enc_len, B, T, weights, enc_proj, s) != hipSuccess)
-            return TDT_ERR_LAUNCH;
-        // first LSTM layer: its input product depends on the label only, so it is a table,
-        // stored [label][unit][gate]
-        if (weights->pred_kind == TDT_PRED_LSTM &&
-            launch_linear(weights->emb, weights->vocab + 1, weights->emb_dim, weights->w_ih[0], weights->emb_dim,
-                          4 * weights->h_pred, weights->b_lstm[0], weights->dtype, weights->h_pred, emb_gates,
-                          s) != hipSuccess)
-            return TDT_ERR_LAUNCH;
-        if (pred_tab && launch_pred_tables(weights, pred_tab, s) != hipSuccess) return TDT_ERR_LAUNCH;
     }
 
     DecodeParams p{};
@@ -545,7 +546,7 @@ int tdt_greedy_decode(const void *enc, const int32_t *enc_len, int B, int T,
 {
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, workspace,
-                         workspace_bytes, options, stream);
+                         workspace_bytes, true, options, stream);
 }
 
 int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int T,
@@ -559,7 +560,9 @@ int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int
     const int st = check_model(weights);
     if (st != TDT_OK) return st;
     // the same layout as a caller's workspace; it has to fit the array the library holds
-    const size_t need = workspace_layout(weights, B, T).total;
+    // (the largest sizes may have room for the general kernel only)
+    const bool label_room = workspace_layout(weights, B, T).total <= (size_t)TDT_STATIC_SCRATCH_BYTES;
+    const size_t need = workspace_layout(weights, B, T, label_room).total;
     if (need > (size_t)TDT_STATIC_SCRATCH_BYTES) return TDT_ERR_TOO_LARGE;
     hipError_t err = hipSuccess;
     void *ptr = static_scratch(&err);
@@ -567,7 +570,7 @@ int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int
     // decode_common clears, with a kernel, every part of the workspace that has to start at zero
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, ptr,
-                         (size_t)TDT_STATIC_SCRATCH_BYTES, options, stream);
+                         (size_t)TDT_STATIC_SCRATCH_BYTES, label_room, options, stream);
 }
 
 int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int T,
@@ -581,7 +584,7 @@ int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int 
     if ((reinterpret_cast<uintptr_t>(state) & 255) != 0) return TDT_ERR_WORKSPACE;
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, state, workspace,
-                         workspace_bytes, options, stream);
+                         workspace_bytes, true, options, stream);
 }
 
 const char *tdt_status_string(int status)

@@ -98,13 +98,15 @@ struct DecodeParams {
 };
 
 struct WorkspaceLayout {
-    size_t packed;                 // the bfloat16 matrices the decode kernel streams, fragment by fragment
+    size_t packed;                 // the matrices the decode kernel streams, fragment by fragment
     size_t enc_proj, emb_gates, pred_tab, hbuf, cbuf, rgate, pred_proj, partials, row_lab, row_dur, barrier, abort_flag, total;
     size_t row_entries;            // uint64 entries in each of row_lab / row_dur
     size_t zero_begin, zero_end;   // byte range the init kernel clears
 };
 
-WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T);
+// label: with what label_loop.hip needs beyond the general kernel (the fragment-major copies of a float32
+// model, larger exchange buffers)
+WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool label = true);
 
 // What label_loop.hip exchanges, laid over the part of the workspace the general kernel uses
 // from `partials` on (byte offsets from there).  [ones_begin, ones_end) is filled with ones,
@@ -126,27 +128,14 @@ StateLayout state_layout(const tdt_weights_t *w, int B);
 // launches (each returns a hipError_t)
 hipError_t launch_encoder_projection(const void *enc, int64_t rows, const tdt_weights_t *w,
                                      float *out, hipStream_t stream);
-// out[r][c(n)] = sum_k a[r][k] * w[n * ldw + k] + bias[n] (bias may be null); a and w in the
-// model's dtype, out float32.  c(n) = n, or with group > 0 (N a multiple of group):
-// c(n) = (n % group) * (N / group) + n / group, which puts the N / group outputs n, n + group,
-// n + 2 group, ... side by side.
-hipError_t launch_linear(const void *a, int64_t rows, int K, const void *w, int ldw, int N, const float *bias,
-                         int dtype, int group, float *out, hipStream_t stream);
-// bf16 models: encoder projection, the predictor side's per-label tables (first LSTM layer's
-// input product into emb_gates; a stateless predictor's projected output into pred_tab, which may
-// be null: then none) and the clearing of the zero region in one launch
-// (the projection covers frames t < enc_len[b] of each of the B utterances only; B == 0: none)
-
 // the encoder projection of the valid frames of B utterances (any dtype)
 hipError_t launch_encoder_projection_valid(const void *enc, const int32_t *enc_len, int B, int T,
                                            const tdt_weights_t *w, float *out, hipStream_t stream);
-// stateless predictor: pred_tab[c][label][:] = w_pred[:, c*E .. (c+1)*E) * emb_c[label] (+ b_pred
-// in the last table), one launch per table
-hipError_t launch_pred_tables(const tdt_weights_t *w, float *pred_tab, hipStream_t stream);
-// Fragment-major copies of the bfloat16 weight matrices the decode kernel multiplies by.
-// A matrix [N][K] (row-major) is cut into column tiles of 16 rows of it and steps of 32 inputs;
-// fragment (tile, step) is 1 KiB, lane l's 16 bytes at l * 16: inputs step * 32 + (l / 16) * 8 .. + 7
-// of the tile's row l % 16 -- what lane l feeds the matrix core -- zeros where the matrix ends.
+// Fragment-major copies of the weight matrices the decode kernels multiply by (float32 models:
+// label_loop.hip only).  A matrix [N][K] (row-major) is cut into column tiles of 16 rows of it and
+// steps of 32 inputs (float32: 16); fragment (tile, step) is 1 KiB, lane l's 16 bytes at l * 16: inputs
+// step * 32 + (l / 16) * 8 .. + 7 (float32: step * 16 + (l / 16) * 4 .. + 3) of the tile's row l % 16 --
+// what lane l feeds the matrix core -- zeros where the matrix ends.
 // Fragments of a tile follow each other by step.  A wavefront's fragment load is then one
 // contiguous KiB; from the row-major matrix it is 16 pieces of 64 bytes from 16 rows, which
 // the texture addresser takes four times as long over.
@@ -163,16 +152,19 @@ struct PackedLayout {
 PackedLayout packed_layout(const tdt_weights_t *w);
 hipError_t launch_pack_weights(const tdt_weights_t *w, const PackedLayout &pl, bool on_the_fly, void *packed,
                                hipStream_t stream);
-// (the same copies as part of the one launch that prepares a call)
 // what a call clears before its decode kernel: one range to zeros, one to ones (multiples of 16 bytes)
 struct ClearRanges {
     void *zero, *ones;
     size_t zero_bytes, ones_bytes;
 };
-hipError_t launch_prepare_bf16(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
-                               float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
-                               bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
-                               hipStream_t stream);
+// Everything before the decode kernel in one launch (two where the encoder projection takes the
+// 256 x 256 kernel): the encoder projection of frames t < enc_len[b] (B == 0: none), the predictor side's
+// per-label tables (first LSTM layer's input product into emb_gates; a stateless predictor's projected
+// output into pred_tab, which may be null: then none), the copies (pl.total == 0: none), the clearing
+hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T, const tdt_weights_t *w,
+                          float *enc_proj, float *emb_gates, float *pred_tab, const PackedLayout &pl,
+                          bool on_the_fly, void *packed, const ClearRanges &clear, long long *out_stats,
+                          hipStream_t stream);
 hipError_t launch_init(const ClearRanges &clear, long long *out_stats, hipStream_t stream);
 // which compiled form of the decode kernel a call runs
 struct DecodeVariant {

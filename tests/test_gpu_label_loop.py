@@ -48,6 +48,13 @@ CASES = [
     (config("ll_stateless2", pred_kind="stateless", pred_layers=2, h_pred=48, B=70, durations=(0, 2)), {}),
     (config("ll_mb_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, B=9, durations=(2, 4), multi_blank=True),
      dict(n_clusters=1)),
+    # float32: the compiled lengths and one input group beyond, several rounds of column tiles, row tiles
+    *[(config(f"ll_f32_k{h}_{hp}", dtype="fp32", h_joint=h, h_pred=hp, B=5), {})
+      for h, hp in ((8, 8), (256, 72), (264, 248), (640, 640), (648, 32))],
+    (config("ll_f32_rounds", dtype="fp32", h_pred=96, h_joint=272, vocab=260, durations=(0, 1, 2), B=40), dict(n_clusters=2)),
+    (config("ll_f32_deep", dtype="fp32", pred_layers=2, B=20), dict(n_clusters=4)),
+    # a stateless group of one workgroup by the size of the output layer, and one column beyond
+    *[(config(f"ll_one_wg{v}", dtype="fp32", pred_kind="stateless", h_pred=24, vocab=v, B=300), {}) for v in (63, 64)],
     # deeper LSTMs on several row tiles
     (config("ll_deep", pred_layers=3, B=40), dict(n_clusters=2)),
 ]
