@@ -42,7 +42,7 @@ static void *static_scratch(hipError_t *err)
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool label)
+WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
 {
     WorkspaceLayout L{};
     size_t off = 0;
@@ -50,7 +50,7 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool labe
     // per-hypothesis arrays are addressed by (cluster, slot): n_clusters * ceil(B / n_clusters) rows
     const size_t rows = (size_t)B + kMaxGrid;
     L.packed = off;
-    if (label || w->dtype == 1) off = align_up(off + packed_layout(w).total, 256);
+    if (w->dtype == 1) off = align_up(off + packed_layout(w).total, 256);
     L.enc_proj = off;
     off = align_up(off + (size_t)B * T * w->h_joint * sizeof(float), 256);
     L.pred_proj = off;
@@ -84,8 +84,7 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool labe
     L.abort_flag = off;
     off = align_up(off + 256, 256);
     L.zero_end = off;
-    L.total = off;
-    if (!label) return L;
+    L.need_general = off;
     // label_loop.hip lays its own arrays over the part from `partials` on; how much it needs depends
     // on the split of the batch, which is not known here: n_clusters * hyps_per_cluster <= B + kMaxGrid
     // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup
@@ -93,10 +92,17 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool labe
     size_t lab = L.partials;
     lab = align_up(lab + 2 * lstm_layers * rows * w->h_pred * sizeof(float), 256);
     if (lstm_layers > 0) lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
-    lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 512);
+    lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 256);
     lab = align_up(lab + kRowBufs * 2 * 64 * rows * sizeof(unsigned long long), 256);
     lab = align_up(lab + (kRowBufs + 1) * (size_t)kMaxGrid * sizeof(unsigned long long), 256) + 256;
-    if (lab > L.total) L.total = lab;
+    // float32: followed by the copies of the matrices (the general kernel does without).  A size does
+    // not depend on the type but for the copies in front: room for them is part of every workspace
+    tdt_weights_t as_f32 = *w;
+    as_f32.dtype = 0;
+    const size_t with_copies = align_up(lab + packed_layout(&as_f32).total, 256);
+    if (w->dtype == 0) L.packed = lab;
+    L.need_label = w->dtype == 0 ? with_copies : lab;
+    L.total = with_copies > off ? with_copies : off;
     return L;
 }
 
@@ -243,13 +249,13 @@ int tdt_state_bytes(const tdt_weights_t *weights, int B, size_t *bytes)
     return TDT_OK;
 }
 
-// the body of the decode entry points; `state` is null for whole utterances.  label_room: the workspace
-// has (is to have) what label_loop.hip needs beyond the general kernel
+// the body of the decode entry points; `state` is null for whole utterances.  own_scratch: the workspace
+// is the library's array, which may hold less than the size asked of a caller
 static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
                          const tdt_weights_t *weights, const int32_t *durations, int max_symbols,
                          int u_cap, int32_t *out_labels, int32_t *out_frames, int32_t *out_len,
                          float *out_score, int32_t *out_status, int64_t *out_stats, void *state,
-                         void *workspace, size_t workspace_bytes, bool label_room, const tdt_options_t *options,
+                         void *workspace, size_t workspace_bytes, bool own_scratch, const tdt_options_t *options,
                          void *stream)
 {
     if (!weights) return TDT_ERR_NULL;
@@ -302,8 +308,9 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     if (joint_kernel == TDT_JOINT_STREAMING && !can_stream) return TDT_ERR_UNSUPPORTED;
     bool wide_joint = joint_kernel == TDT_JOINT_STREAMING ||
                       (joint_kernel == TDT_JOINT_AUTO && can_stream && weights->vocab + 1 + weights->n_dur >= 4096);
-    const WorkspaceLayout L = workspace_layout(weights, B, T, label_room);
-    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < L.total)
+    const WorkspaceLayout L = workspace_layout(weights, B, T);
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
+        workspace_bytes < (own_scratch ? L.need_general : L.total))
         return TDT_ERR_WORKSPACE;
 
     DecodeVariant variant{state != nullptr, algorithm == TDT_ALG_FRAME_LOOPING, on_the_fly, wide_joint};
@@ -401,7 +408,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
     // streamed output layer, groups it can hold), else the general one
     const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
-    const bool label = label_room && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
+    const bool label = workspace_bytes >= L.need_label && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
                        label_kernel_takes(weights, state != nullptr, hyps_per_cluster, C);
     if (weights->dtype == 0 && !label) PL.total = 0;   // (float32: the general kernel reads the matrices as they are)
     LabelLayout LL{};
@@ -546,7 +553,7 @@ int tdt_greedy_decode(const void *enc, const int32_t *enc_len, int B, int T,
 {
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, workspace,
-                         workspace_bytes, true, options, stream);
+                         workspace_bytes, false, options, stream);
 }
 
 int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int T,
@@ -561,8 +568,7 @@ int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int
     if (st != TDT_OK) return st;
     // the same layout as a caller's workspace; it has to fit the array the library holds
     // (the largest sizes may have room for the general kernel only)
-    const bool label_room = workspace_layout(weights, B, T).total <= (size_t)TDT_STATIC_SCRATCH_BYTES;
-    const size_t need = workspace_layout(weights, B, T, label_room).total;
+    const size_t need = workspace_layout(weights, B, T).need_general;
     if (need > (size_t)TDT_STATIC_SCRATCH_BYTES) return TDT_ERR_TOO_LARGE;
     hipError_t err = hipSuccess;
     void *ptr = static_scratch(&err);
@@ -570,7 +576,7 @@ int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int
     // decode_common clears, with a kernel, every part of the workspace that has to start at zero
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, ptr,
-                         (size_t)TDT_STATIC_SCRATCH_BYTES, label_room, options, stream);
+                         (size_t)TDT_STATIC_SCRATCH_BYTES, true, options, stream);
 }
 
 int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int T,
@@ -584,7 +590,7 @@ int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int 
     if ((reinterpret_cast<uintptr_t>(state) & 255) != 0) return TDT_ERR_WORKSPACE;
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, state, workspace,
-                         workspace_bytes, true, options, stream);
+                         workspace_bytes, false, options, stream);
 }
 
 const char *tdt_status_string(int status)

@@ -100,13 +100,12 @@ struct DecodeParams {
 struct WorkspaceLayout {
     size_t packed;                 // the matrices the decode kernel streams, fragment by fragment
     size_t enc_proj, emb_gates, pred_tab, hbuf, cbuf, rgate, pred_proj, partials, row_lab, row_dur, barrier, abort_flag, total;
+    size_t need_general, need_label;   // what a call of decode.hip's / label_loop.hip's kernel needs (total: of a caller)
     size_t row_entries;            // uint64 entries in each of row_lab / row_dur
     size_t zero_begin, zero_end;   // byte range the init kernel clears
 };
 
-// label: with what label_loop.hip needs beyond the general kernel (the fragment-major copies of a float32
-// model, larger exchange buffers)
-WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T, bool label = true);
+WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T);
 
 // What label_loop.hip exchanges, laid over the part of the workspace the general kernel uses
 // from `partials` on (byte offsets from there).  [ones_begin, ones_end) is filled with ones,
