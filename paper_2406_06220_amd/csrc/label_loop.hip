@@ -24,9 +24,12 @@
 //     of instructions in a row, and two wavefronts that share a SIMD take turns at them.  It also
 //     leaves 512 registers a lane: the workgroup's predictor-side weights stay in registers for the
 //     whole call where they fit one round.
-//   * In a work item every wavefront multiplies its own quarter of the reduction for all column
-//     tiles, so an activation fragment is read from LDS once; encoder rows and weight fragments of
-//     the first joint pass are requested while the hidden state is exchanged.
+//   * Every wavefront multiplies its own quarter of the reduction for all column tiles.  So no two
+//     wavefronts need the same activation: each loads, waits for and splits its quarter of the rows in
+//     the registers the matrix cores read, and only the partial sums go through LDS (rows staged in LDS
+//     for all wavefronts, with the barrier that takes: config 2 at B = 1 648 us, now 610; stateless at
+//     B = 128 3.11 ms, now 2.70).  Encoder rows and weight fragments of the first joint pass are
+//     requested while the hidden state is exchanged.
 //
 // Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
 // exchange (a workgroup without work item: a word of its own that everybody waits for), after it
@@ -61,32 +64,30 @@ namespace {
 constexpr unsigned kAbsent = 0xffffffffu;   // an exchanged float that is not there yet (a NaN no result is stored as)
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kLW = kLabelThreads / 64;     // wavefronts of a workgroup
-constexpr int kRW = RT / kLW;               // rows of a tile a wavefront stages
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-// what differs between the element types: a fragment is 1 KiB = 16 columns x KS inputs
+// What differs between the element types: a fragment is 1 KiB = 16 columns x KS inputs, E of them a lane.
+// The product of 16 rows and 16 columns is formed with the weights as the left operand: lane l then
+// holds four neighbouring columns, (l / 16) * 4 .. + 3, of row l % 16.
 template <typename WT> struct Frags;
 template <> struct Frags<uint16_t> {
-    static constexpr int KS = 32, PL = 3;
+    static constexpr int KS = 32, E = 8, PL = 3;
     typedef bf16x8 A;
-    // element offset of lane's part of an activation row at step s
-    __device__ static int aoff(int s, int lane) { return s * 32 + (lane >> 4) * 8; }
     __device__ static f32x4 mma(const A &a, const v4u &b, f32x4 c)
     {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, *reinterpret_cast<const bf16x8 *>(&b), c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8 *>(&b), a, c, 0, 0, 0);
     }
 };
 template <> struct Frags<float> {
-    static constexpr int KS = 16, PL = 1;
+    static constexpr int KS = 16, E = 4, PL = 1;
     typedef f32x4 A;
-    __device__ static int aoff(int s, int lane) { return s * 16 + (lane >> 4) * 4; }
     __device__ static f32x4 mma(const A &a, const v4u &b, f32x4 c)
     {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, __uint_as_float(b.z), c, 0, 0, 0);
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, __uint_as_float(b.w), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b.x), a.x, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b.y), a.y, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b.z), a.z, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(b.w), a.w, c, 0, 0, 0);
     }
 };
 
@@ -114,10 +115,10 @@ __device__ inline v4u ldx4(__amdgpu_buffer_rsrc_t rs, int lane_off, int off)
 {
     return __builtin_amdgcn_raw_buffer_load_b128(rs, lane_off, off, 16 /* sc1 */);
 }
-// what no workgroup writes while the kernel runs; row is the same in every lane
-__device__ inline v4u ldg4(const float *row, unsigned lane_off)
+// what no workgroup writes while the kernel runs
+__device__ inline v4u ldg4(const float *row, int off)
 {
-    return *(const TDT_GLOBAL v4u *)(reinterpret_cast<const char *>(row) + lane_off);
+    return *(const TDT_GLOBAL v4u *)(reinterpret_cast<const char *>(row) + (unsigned)off);
 }
 // Gives registers a value without an instruction.  An array of which a pass fills only a part needs it:
 // what is not filled would otherwise be the value of the pass before, held in registers all the way.
@@ -193,12 +194,12 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 {
     typedef Frags<WT> F;
     typedef typename F::A AFrag;
-    constexpr int PL = F::PL, KS = F::KS;
+    constexpr int PL = F::PL, KS = F::KS, NL = F::E / 4;   // NL: 16-byte loads of float32 for a lane's part of a step
     constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1;
     constexpr int TR = label_tiles(NK);              // column tiles per round of a joint pass
     constexpr int TQ = DEEP ? TR : 2 * TR;           // ... and of the predictor-side products
-    constexpr int PLD = TQ * CT + 4;                 // floats per row of the partial sums (padded: 16 rows, 64 banks)
-    constexpr int KI = (NK * kLW * KS + 255) / 256;  // 16-byte loads per lane for a row
+    constexpr int PLQ = TQ * CT + 4, PLJ = TR * CT + 4;   // floats per row of the partial sums (padded: 16 rows, 64 banks)
+    constexpr int KI = (NK * kLW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
 
@@ -268,15 +269,13 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     }
     const int Hp = p.h_pred, L = DEEP ? p.pred_layers : 1;
 
-    // ---- LDS: the activation tile, the partial sums of a round, and what this workgroup keeps of
-    // its own units: recurrent pre-activations, cell state, (chunks) hidden state
+    // ---- LDS: the tile of packed rows (bfloat16), the partial sums of a round -- of the predictor side
+    // and of a joint pass, which may start while the former are still read -- and what this workgroup
+    // keeps of its own units: recurrent pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
-    const int plane = RT * ldb;
-    float *const part = reinterpret_cast<float *>(dyn_lds + (size_t)PL * plane * sizeof(WT));   // [kLW][16][PLD]
-    ActTile<WT> A;
-    A.planes = reinterpret_cast<decltype(A.planes)>(planes);
-    A.ldb = ldb;
+    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 ? (size_t)RT * ldb * sizeof(WT) : 0));   // [kLW][16][PLQ]
+    float *const part_j = part_q + (LSTM ? kLW * RT * PLQ : 0);                                              // [kLW][16][PLJ]
     for (int i = tid; i < p.lds_bytes / 16; i += kLabelThreads)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
 
@@ -290,7 +289,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     const int r0 = max(qt0 - NT_A, 0);                                 // first W_hh tile
     const int u0 = r0 * 4, U = nr > 0 ? min(nr * 4, Hp - u0) : 0;      // hidden units owned
     const int Upad = QT * 4;
-    float4 *const rg_l = reinterpret_cast<float4 *>(part + kLW * RT * PLD);               // [L][hpc][Upad]
+    float4 *const rg_l = reinterpret_cast<float4 *>(part_j + kLW * RT * PLJ);               // [L][hpc][Upad]
     float *const c_l = reinterpret_cast<float *>(rg_l + (size_t)(LSTM ? L * hpc * Upad : 0));
     float *const h_l = c_l + (LSTM ? L * hpc * Upad : 0);                                 // (chunks only)
 
@@ -417,17 +416,16 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             if (t < n) {   // uniform
                 const int w = tile_off(t) + s0 * 1024;
 #pragma unroll
-                for (int s = 0; s < NK; ++s)   // (a step too many: some fragment, not used)
-                    b[t][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, lane * 16, w + (s < sn ? s : 0) * 1024, 0);
+                for (int s = 0; s < NK; ++s)   // (a step beyond the wavefront's share: zeros, by an offset beyond the buffer)
+                    b[t][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, s < sn ? lane * 16 : ~0xff, w + (s < sn ? s : 0) * 1024, 0);
             }
     };
-    // The round's products, into this wavefront's share of the partial sums.  A step beyond the
-    // wavefront's share reads the padding at the end of a tile row, which is zero.  The tile count is
-    // rounded up to what is compiled (what stands in the registers of the other tiles is multiplied
+    // The round's products, into this wavefront's share of the partial sums.  The tile count is rounded up to what is compiled (what stands in the registers of the other tiles is multiplied
     // too, and nobody looks at it): without branches between them the products of the tiles overlap.
     // PACKED: the planes of a row are rows of one tile.
-    auto products_of = [&](auto packed_tag, auto count, const AFrag (&a)[NK][PL], const auto &b) __attribute__((always_inline)) {
+    auto products_of = [&](auto packed_tag, auto count, const AFrag (&a)[NK][PL], const auto &b, float *part) __attribute__((always_inline)) {
         constexpr bool PACKED = decltype(packed_tag)::value;
+        constexpr int PLD = sizeof(b) / (NK * sizeof(v4u)) * CT + 4;
         constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED ? 2 : 3;   // chains per tile
         f32x4 c[N][NC];
 #pragma unroll
@@ -445,39 +443,63 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     for (int pl = 0; pl < PL; ++pl) c[t][pl] = F::mma(a[s][pl], b[t][s], c[t][pl]);
                 }
             }
-        float *const pw = part + (size_t)wave * RT * PLD + (lane >> 4) * 4 * PLD + (lane & 15);
+        float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
 #pragma unroll
         for (int t = 0; t < N; ++t) {
             f32x4 sum = c[t][NC - 1];   // smallest terms first
 #pragma unroll
             for (int ch = NC - 2; ch >= 0; --ch) sum = c[t][ch] + sum;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pw[e * PLD + t * CT] = sum[e];
+            *reinterpret_cast<f32x4 *>(pw + t * CT) = sum;
         }
     };
-    auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n) __attribute__((always_inline)) {
+    auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n, float *part) __attribute__((always_inline)) {
         constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
         const std::integral_constant<int, TT / 2> half{};
         const std::integral_constant<int, TT> all{};
-        if (n <= TT / 2) products_of(packed_tag, half, a, b);
-        else products_of(packed_tag, all, a, b);
+        if (n <= TT / 2) products_of(packed_tag, half, a, b, part);
+        else products_of(packed_tag, all, a, b, part);
     };
-    // the activation fragments of this wavefront's steps
-    auto load_a = [&](auto packed_tag, AFrag (&a)[NK][PL], int s0, int sn) __attribute__((always_inline)) {
-        constexpr bool PACKED = decltype(packed_tag)::value;
-        const WT *row = planes + (lane & 15) * ldb;
-        const int o0 = F::aoff(s0, lane), zero = ldb - 16 / (int)sizeof(WT);
+    // ---- activation fragments.  A wavefront multiplies its own stretch of the reduction only, so it
+    // loads that stretch of all 16 rows straight into the registers the matrix cores read -- lane l part
+    // l / 16 of every step of row l % 16 -- and no row goes through LDS.
+    // Byte offset of a lane's part of step s in a row of K inputs; parts beyond the row's end read its last
+    // inputs again (they meet zeros in the weights, but must be numbers).
+    auto part_of = [&](int s, int s0, int K) __attribute__((always_inline)) {
+        return min((s0 + s) * KS + (lane >> 4) * F::E, K - F::E) * (int)sizeof(float);
+    };
+    // bfloat16: x == hi + lo + lo2 as in ActTile::split3, two elements packed per instruction
+    auto split = [&](const float (&x0)[F::E], AFrag (&a)[PL]) __attribute__((always_inline)) {
+        if constexpr (PL == 3) {
+            float x[F::E];
 #pragma unroll
-        for (int s = 0; s < NK; ++s) {
-            const int o = s < sn ? o0 + s * KS : zero;
+            for (int e = 0; e < F::E; ++e) x[e] = x0[e];
 #pragma unroll
-            for (int pl = 0; pl < (PACKED ? 1 : PL); ++pl) a[s][pl] = *reinterpret_cast<const AFrag *>(row + pl * plane + o);
+            for (int pl = 0; pl < 3; ++pl) {
+                v4u o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    o[e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302u);
+                a[pl] = *reinterpret_cast<const AFrag *>(&o);
+                if (pl < 2)
+#pragma unroll
+                    for (int e = 0; e < F::E; ++e) x[e] -= __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
+            }
+        } else {
+            a[0] = AFrag{x0[0], x0[1], x0[2], x0[3]};
         }
+    };
+    // up to kPackRows rows: through LDS, where plane pl of row i is row pl * kPackRows + i
+    auto load_packed = [&](AFrag (&a)[NK][PL], int s0, int sn) __attribute__((always_inline)) {
+        const WT *row = planes + (lane & 15) * ldb;
+#pragma unroll
+        for (int s = 0; s < NK; ++s)
+            a[s][0] = *reinterpret_cast<const AFrag *>(row + (s < sn ? (s0 + s) * KS + (lane >> 4) * F::E : ldb - F::E));
     };
     const std::true_type packed_rows{};
     const std::false_type full_rows{};
     // four neighbouring columns of a row of the partial sums, summed over the wavefronts
-    auto gather = [&](int row, int quad) __attribute__((always_inline)) {
+    auto gather = [&](auto tiles, const float *part, int row, int quad) __attribute__((always_inline)) {
+        constexpr int PLD = decltype(tiles)::value * CT + 4;
         const float *q = part + (size_t)row * PLD + quad * 4;
         float4 v = *reinterpret_cast<const float4 *>(q);
 #pragma unroll
@@ -490,43 +512,25 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         }
         return v;
     };
-    // inputs k .. k+3 of row i of the tile (bfloat16: x == hi + lo + lo2 as in ActTile::split3, two
-    // elements packed per instruction)
-    auto put = [&](auto packed_tag, int i, int k, float4 v) __attribute__((always_inline)) {
-        if constexpr (PL == 3) {
-            const int pstride = decltype(packed_tag)::value ? kPackRows * ldb : plane;   // (packed: plane pl of row i is row pl * 4 + i)
-            WT *o = planes + i * ldb + k;
-            float x0 = v.x, x1 = v.y, x2 = v.z, x3 = v.w;
-            auto top = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
-            auto pack = [](float lo, float hi) {
-                return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-            };
+    const std::integral_constant<int, TQ> q_tiles{};
+    const std::integral_constant<int, TR> j_tiles{};
+    // inputs k .. k+3 of packed row i
+    auto put = [&](int i, int k, float4 v) __attribute__((always_inline)) {
+        WT *o = planes + i * ldb + k;
+        float x0 = v.x, x1 = v.y, x2 = v.z, x3 = v.w;
+        auto top = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
+        auto pack = [](float lo, float hi) {
+            return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+        };
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                *reinterpret_cast<uint2 *>(o + pl * pstride) = make_uint2(pack(x0, x1), pack(x2, x3));
-                if (pl < 2) {
-                    x0 -= top(x0);
-                    x1 -= top(x1);
-                    x2 -= top(x2);
-                    x3 -= top(x3);
-                }
+        for (int pl = 0; pl < 3; ++pl) {
+            *reinterpret_cast<uint2 *>(o + pl * kPackRows * ldb) = make_uint2(pack(x0, x1), pack(x2, x3));
+            if (pl < 2) {
+                x0 -= top(x0);
+                x1 -= top(x1);
+                x2 -= top(x2);
+                x3 -= top(x3);
             }
-        } else {
-            A.store4(i, k, v);
-        }
-    };
-    // zeros between the end of rows of K inputs and the next multiple of 32 (where there is such a gap):
-    // what stood there is multiplied by zeros, but must be a number
-    auto pad_rows = [&](int K) __attribute__((always_inline)) {
-        if (K & 31) {   // uniform
-            const int k = K + (lane & 7) * 4;
-            if (k < (K + 31) / 32 * 32)
-                for (int pl = 0; pl < PL; ++pl)
-                    for (int i = tid >> 3; i < RT; i += kLabelThreads / 8) {
-                        WT *o = planes + pl * plane + i * ldb + k;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) o[e] = 0;
-                    }
         }
     };
     const bool qpack = PL == 3 && G <= kPackRows;
@@ -547,55 +551,69 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         hn = og * (2.0f * sigmoid(2.0f * cn) - 1.0f);
     };
 
-    // what lane l reads of a row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
+    // what lane l reads of a whole row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
     auto hoff = [&](int kk) { return min(lane * 4 + kk * 256, Hp - 4) * (int)sizeof(float); };
-    auto joff = [&](int kk) { return min(lane * 4 + kk * 256, H - 4) * (int)sizeof(float); };
     const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, (size_t)2 * L * Bw * Hp * sizeof(float));
     const __amdgpu_buffer_rsrc_t prs = buffer_of(px, (size_t)2 * Bw * H * sizeof(float));
     const __amdgpu_buffer_rsrc_t brs = buffer_of(p.b_out, (size_t)O * sizeof(float));
-    // Rows of this label iteration's hidden state (row0: the group's first row in the exchange buffer):
-    // loads, waits, splits into the tile.  R rows a wavefront, all of them always: a slot without an
-    // active hypothesis repeats one that has (no branches, and nobody looks at the row).
-    auto stage_h = [&](auto rows_tag, auto packed_tag, int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
-        constexpr int R = decltype(rows_tag)::value;
-        v4u v[R][KI];
-        int off[R];
+    // Row tile tq of this label iteration's hidden state (row0: the group's first row in the exchange
+    // buffer): loads, waits, splits.  A row without an active hypothesis repeats one that has (no
+    // branches, and nobody looks at its results).
+    auto stage_h = [&](AFrag (&a)[NK][PL], int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
         const int any = __ffsll((long long)in_tile) - 1;
-#pragma unroll
-        for (int ii = 0; ii < R; ++ii) {
-            const int g = wave + ii * kLW;
-            off[ii] = (row0 + tq * RT + ((in_tile >> g) & 1ull ? g : any)) * Hp * (int)sizeof(float);
-        }
         unsigned spins = 0;
         long long since = 0;
+        if (qpack) {   // a wavefront takes a row
+            if constexpr (PL == 3) {
+                v4u v[KI];
+                const int off = (row0 + ((in_tile >> wave) & 1ull ? wave : any)) * Hp * (int)sizeof(float);
 #pragma clang loop unroll(disable)
-        for (;;) {
-            unsigned mx = 0;
+                for (;;) {
+                    unsigned mx = 0;
 #pragma unroll
-            for (int ii = 0; ii < R; ++ii)
+                    for (int kk = 0; kk < KI; ++kk) v[kk] = ldx4(hrs, hoff(kk), off);
 #pragma unroll
-                for (int kk = 0; kk < KI; ++kk) v[ii][kk] = ldx4(hrs, hoff(kk), off[ii]);
+                    for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(v[kk]));
+                    if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+                }
+                TR(11);
 #pragma unroll
-            for (int ii = 0; ii < R; ++ii)
+                for (int kk = 0; kk < KI; ++kk)   // (lanes beyond the row's end write its last inputs again)
+                    put(wave, hoff(kk) / (int)sizeof(float), as_float4(v[kk]));
+                __syncthreads();
+                TR(13);
+                fresh();
+                load_packed(a, hs0, hsn);
+            }
+        } else {
+            v4u v[NK][NL];
+            int off[NK];
+            const int g = (in_tile >> (lane & 15)) & 1ull ? lane & 15 : any;
+            const int row = (row0 + tq * RT + g) * Hp * (int)sizeof(float);
 #pragma unroll
-                for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(v[ii][kk]));
-            if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+            for (int s = 0; s < NK; ++s) off[s] = row + part_of(s, hs0, Hp);
+#pragma clang loop unroll(disable)
+            for (;;) {
+                unsigned mx = 0;
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) v[s][l] = ldx4(hrs, off[s] + l * 16, 0);
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) mx = max(mx, umax4(v[s][l]));
+                if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+            }
+            TR(11);
+#pragma unroll
+            for (int s = 0; s < NK; ++s) {
+                float x[F::E];
+#pragma unroll
+                for (int e = 0; e < F::E; ++e) x[e] = __uint_as_float(v[s][e / 4][e % 4]);
+                split(x, a[s]);
+            }
         }
-        TR(11);
-#pragma unroll
-        for (int ii = 0; ii < R; ++ii)
-#pragma unroll
-            for (int kk = 0; kk < KI; ++kk)   // (lanes beyond the row's end write its last inputs again)
-                put(packed_tag, wave + ii * kLW, hoff(kk) / (int)sizeof(float), as_float4(v[ii][kk]));
-        pad_rows(Hp);
-    };
-    auto stage_h_any = [&](int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
-        const std::integral_constant<int, 1> one{};
-        const std::integral_constant<int, 2> two{};
-        const std::integral_constant<int, kRW> four{};
-        if (qpack) stage_h(one, packed_rows, row0, tq, in_tile);
-        else if (G <= 2 * kLW) stage_h(two, full_rows, row0, tq, in_tile);
-        else stage_h(four, full_rows, row0, tq, in_tile);
     };
 
     const int p_g = U > 0 ? tid / U : kLabelMaxHyps, p_u = U > 0 ? tid - p_g * U : 0;   // this thread's first cell
@@ -711,13 +729,13 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         }
         tile0 = cg * tpg;
         n_ct = min(tpg, NT - tile0);
-        const int r = ti * RT + (lane & 15), q = min((r * rcp_kw) >> 20, 63);   // r / Kw
+        const int r = min(ti * RT + (lane & 15), M - 1);   // (a row beyond the last repeats it)
+        const int q = (r * rcp_kw) >> 20;                  // r / Kw
         g_l = __builtin_amdgcn_ds_bpermute(q * 4, slot_of) & 63;
         const int f = __builtin_amdgcn_ds_bpermute(g_l * 4, time) + (r - q * Kw);
         // (every lane has to take part in every permute: what an inactive lane holds reads as zero)
         const int len_r = __builtin_amdgcn_ds_bpermute(g_l * 4, len), gid_r = __builtin_amdgcn_ds_bpermute(g_l * 4, gid);
-        const bool v = (r < M) & (f < len_r);
-        erow_l = gid_r * T + (v ? f : 0);
+        erow_l = gid_r * T + (f < len_r ? f : 0);   // (a frame beyond its utterance's end reads frame 0)
         if constexpr (!LSTM) {
             lab_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last);
             lab2_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last2);
@@ -763,20 +781,15 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         bool need = active && !(CHUNKED && (time >= len || (status & TDT_HYP_TRUNCATED)));
         unsigned long long needm = __ballot(need);
 
-        // the projected encoder frames of a work item: four rows a wavefront, always -- a row beyond the
-        // last repeats it, a frame beyond its utterance's end reads frame 0 (no branches, and nobody
-        // looks at their results)
-        v4u e4[kRW][KI];
+        // the projected encoder frames of a work item: this wavefront's stretch of its rows
+        v4u e4[NK][NL];
         any_value(e4);
         auto request_rows = [&]() __attribute__((always_inline)) {
-            const int nrows = M - ti * RT;
+            const float *er = p.enc_proj + (size_t)(unsigned)erow_l * H;
 #pragma unroll
-            for (int ii = 0; ii < kRW; ++ii) {
-                const int i = max(min(wave + ii * kLW, nrows - 1), 0);
-                const float *er = p.enc_proj + (size_t)(unsigned)__builtin_amdgcn_readlane(erow_l, i) * H;
+            for (int s = 0; s < NK; ++s)
 #pragma unroll
-                for (int kk = 0; kk < KI; ++kk) e4[ii][kk] = ldg4(er, joff(kk));
-            }
+                for (int l = 0; l < NL; ++l) e4[s][l] = ldg4(er, part_of(s, js0, H) + l * 16);
         };
         fresh();
         v4u bq[TQ][NK];   // LAYERS == 1: this label's predictor-side weights
@@ -876,22 +889,13 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             if constexpr (LAYERS == 1) {
                 // ---- Q
                 if (nq > 0) {
-                    stage_h_any(par * Bw + b0, 0, act);
-                    TR(12);
-                    lap(kTkBar);
-                    __syncthreads();
-                    TR(13);
-                    fresh();
                     AFrag a[NK][PL];
-                    if (qpack) {
-                        load_a(packed_rows, a, hs0, hsn);
-                        TR(14);
-                        products(packed_rows, a, bq, nq);
-                    } else {
-                        load_a(full_rows, a, hs0, hsn);
-                        TR(14);
-                        products(full_rows, a, bq, nq);
-                    }
+                    stage_h(a, par * Bw + b0, 0, act);
+                    lap(kTkBar);
+                    fresh();
+                    TR(14);
+                    if (qpack) products(packed_rows, a, bq, nq, part_q);
+                    else products(full_rows, a, bq, nq, part_q);
                     TR(15);
                     __syncthreads();
                     TR(16);
@@ -902,7 +906,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 #pragma unroll
                     for (int h = 0; h < 2; ++h)
                         if (h == 0 || nq > 4) {   // uniform
-                            float4 v = gather(row, h * 16 + quad);
+                            float4 v = gather(q_tiles, part_q, row, h * 16 + quad);
                             if (qpack) {   // (rows 12 .. 15 of a packed tile are nobody's)
                                 v.x = sum_over_rows(lane < 48 ? v.x : 0.0f);
                                 v.y = sum_over_rows(lane < 48 ? v.y : 0.0f);
@@ -943,16 +947,11 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
                     if (!loaded) fetch_round(0, 0);   // while the rows are on their way
                     loaded = top && n_all <= TQ;
-                    stage_h_any(row0, tq, in_tile);
-                    TR(12);
-                    lap(kTkBar);
-                    __syncthreads();
-                    TR(13);
-                    fresh();
                     AFrag a[NK][PL];
                     any_value(a);
-                    if (qpack) load_a(packed_rows, a, hs0, hsn);
-                    else load_a(full_rows, a, hs0, hsn);
+                    stage_h(a, row0, tq, in_tile);
+                    lap(kTkBar);
+                    fresh();
 #pragma clang loop unroll(disable)
                     for (int kind = 0; kind < (DEEP ? kinds : 1); ++kind) {
                         const bool input = !top && kind == 0;
@@ -961,8 +960,8 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                             const int n = min(TQ, n_all - t0);
                             if (kind > 0 || t0 > 0) fetch_round(kind, t0);
                             TR(14);
-                            if (qpack) products(packed_rows, a, b, n);
-                            else products(full_rows, a, b, n);
+                            if (qpack) products(packed_rows, a, b, n, part_q);
+                            else products(full_rows, a, b, n, part_q);
                             TR(15);
                             __syncthreads();
                             TR(16);
@@ -970,7 +969,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                             // a thread takes four columns of a row; packed: a wavefront takes a row, its
                             // lanes one plane each, and the planes are added up
                             const int quad = lane & 15, i = qpack ? wave : tid >> 4, g = tq * RT + i;
-                            float4 v = gather(qpack ? i + (lane >> 4) * kPackRows : i, quad);
+                            float4 v = gather(q_tiles, part_q, qpack ? i + (lane >> 4) * kPackRows : i, quad);
                             if (qpack) {
                                 if (lane >= 48) v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                                 v.x = sum_over_rows(v.x);
@@ -1014,7 +1013,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                                 }
                             }
                             // (the partial sums are written again behind the next barrier only if another
-                            // round, row tile or layer follows; a joint pass has one of its own)
+                            // round, row tile or layer follows; a joint pass has its own)
                             if (t0 + TQ < n_all || kind + 1 < kinds || tq + 1 < ntq || (DEEP && l + 1 < L)) __syncthreads();
                         }
                     }
@@ -1057,26 +1056,24 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     set_item(it);
                     request_rows();
                 }
-                const int nrows = M - ti * RT;
-                v4u p4[kRW][KI], b[TR][NK];
-                int po[kRW];
-                const float *pr2[kRW];
+                v4u p4[NK][NL], b[TR][NK];
+                int po[NK];
+                const float *pr2 = nullptr;
+                if constexpr (LSTM) {
+                    const int row = (par * Bw + b0 + g_l) * H * (int)sizeof(float);
 #pragma unroll
-                for (int ii = 0; ii < kRW; ++ii) {
-                    const int i = min(wave + ii * kLW, nrows - 1);
-                    if constexpr (LSTM) {
-                        po[ii] = (par * Bw + b0 + __builtin_amdgcn_readlane(g_l, i)) * H * (int)sizeof(float);
-                    } else {
-                        // one label of context: its table row; two: the older label's table, then the newest label's
-                        const size_t row = (size_t)__builtin_amdgcn_readlane(lab_l, i);
-                        const float *pr = p.pred_tab + row * H;
-                        if (p.pred_layers == 2) {
-                            pr2[ii] = p.pred_tab + ((size_t)(V + 1) + row) * H;
-                            pr = p.pred_tab + (size_t)__builtin_amdgcn_readlane(lab2_l, i) * H;
-                        }
-#pragma unroll
-                        for (int kk = 0; kk < KI; ++kk) p4[ii][kk] = ldg4(pr, joff(kk));
+                    for (int s = 0; s < NK; ++s) po[s] = row + part_of(s, js0, H);
+                } else {
+                    // one label of context: its table row; two: the older label's table, then the newest label's
+                    const float *pr = p.pred_tab + (size_t)lab_l * H;
+                    if (p.pred_layers == 2) {
+                        pr2 = p.pred_tab + ((size_t)(V + 1) + lab_l) * H;
+                        pr = p.pred_tab + (size_t)lab2_l * H;
                     }
+#pragma unroll
+                    for (int s = 0; s < NK; ++s)
+#pragma unroll
+                        for (int l = 0; l < NL; ++l) p4[s][l] = ldg4(pr, part_of(s, js0, H) + l * 16);
                 }
                 {
                     const int wbase = here(p.off_w_out + tile0 * jbytes);
@@ -1093,43 +1090,38 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     for (;;) {
                         unsigned mx = 0;
 #pragma unroll
-                        for (int ii = 0; ii < kRW; ++ii)
+                        for (int s = 0; s < NK; ++s)
 #pragma unroll
-                            for (int kk = 0; kk < KI; ++kk) p4[ii][kk] = ldx4(prs, joff(kk), po[ii]);
+                            for (int l = 0; l < NL; ++l) p4[s][l] = ldx4(prs, po[s] + l * 16, 0);
 #pragma unroll
-                        for (int ii = 0; ii < kRW; ++ii)
+                        for (int s = 0; s < NK; ++s)
 #pragma unroll
-                            for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(p4[ii][kk]));
+                            for (int l = 0; l < NL; ++l) mx = max(mx, umax4(p4[s][l]));
                         if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
                     }
                     lap(kTkBar);
                 } else if (p.pred_layers == 2) {
 #pragma unroll
-                    for (int ii = 0; ii < kRW; ++ii)
+                    for (int s = 0; s < NK; ++s)
 #pragma unroll
-                        for (int kk = 0; kk < KI; ++kk) {
-                            const float4 x = as_float4(ldg4(pr2[ii], joff(kk))), y = as_float4(p4[ii][kk]);
-                            p4[ii][kk] = v4u{__float_as_uint(y.x + x.x), __float_as_uint(y.y + x.y),
-                                             __float_as_uint(y.z + x.z), __float_as_uint(y.w + x.w)};
+                        for (int l = 0; l < NL; ++l) {
+                            const float4 x = as_float4(ldg4(pr2, part_of(s, js0, H) + l * 16)), y = as_float4(p4[s][l]);
+                            p4[s][l] = v4u{__float_as_uint(y.x + x.x), __float_as_uint(y.y + x.y),
+                                           __float_as_uint(y.z + x.z), __float_as_uint(y.w + x.w)};
                         }
                 }
                 TR(22);
+                AFrag a[NK][PL];
 #pragma unroll
-                for (int ii = 0; ii < kRW; ++ii)
+                for (int s = 0; s < NK; ++s) {
+                    float x[F::E];
 #pragma unroll
-                    for (int kk = 0; kk < KI; ++kk) {
-                        const float4 e = as_float4(e4[ii][kk]), q = as_float4(p4[ii][kk]);
-                        put(full_rows, wave + ii * kLW, joff(kk) / (int)sizeof(float),
-                            make_float4(fmaxf(e.x + q.x, 0.0f), fmaxf(e.y + q.y, 0.0f), fmaxf(e.z + q.z, 0.0f),
-                                        fmaxf(e.w + q.w, 0.0f)));
-                    }
-                pad_rows(H);
-                TR(23);
-                __syncthreads();
+                    for (int e = 0; e < F::E; ++e)
+                        x[e] = fmaxf(__uint_as_float(e4[s][e / 4][e % 4]) + __uint_as_float(p4[s][e / 4][e % 4]), 0.0f);
+                    split(x, a[s]);
+                }
                 TR(24);
                 fresh();
-                AFrag a[NK][PL];
-                load_a(full_rows, a, js0, jsn);
                 // 16 lanes share a row and take four neighbouring columns each; running statistics
                 const int i = tid >> 4, quad = lane & 15;
                 float rm = -INFINITY, rs = 0.0f, rsm = -INFINITY, rdm = -INFINITY;
@@ -1149,7 +1141,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                 for (int t0 = 0; t0 < n_ct; t0 += TR) {
                     const int n = min(TR, n_ct - t0);
                     TR(25);
-                    products(full_rows, a, b, n);
+                    products(full_rows, a, b, n, part_j);
                     const float4 bb = as_float4(bias4);
                     TR(26);
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (words put back earlier have arrived)
@@ -1162,7 +1154,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                             brs, ((tile0 + t0 + TR) * CT + quad * 4) * (int)sizeof(float), 0, 0);
                     }
                     if (t0 > 0) fold_sums();
-                    const float4 v = gather(i, quad);
+                    const float4 v = gather(j_tiles, part_j, i, quad);
                     const float x4[4] = {v.x + bb.x, v.y + bb.y, v.z + bb.z, v.w + bb.w};
                     float m = -INFINITY;
                     int am = 0x7fffffff;
@@ -1215,7 +1207,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                         S.rowd[ti * RT + i] = (unsigned)S.durations[unpack_index(bd) & (TDT_MAX_DURATIONS - 1)];
                     }
                 }
-                if (it + C < items) __syncthreads();   // the next item writes the tile and the partial sums again
+                if (it + C < items) __syncthreads();   // the next item writes the partial sums again
             }
             if (rank >= items) {   // no work item: say that this workgroup has come this far
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1514,10 +1506,9 @@ size_t label_lds_bytes(const tdt_weights_t *w, bool chunked, int hyps_per_cluste
 {
     int nk = 0, tq = 0;
     if (!label_fn_for(w, chunked, hyps_per_cluster, C, nk, tq)) return ~(size_t)0;
-    const int k = label_kseg(w);
-    size_t n = w->dtype == 1 ? (size_t)3 * RT * ActTile<uint16_t>::row_elems(k) * sizeof(uint16_t)
-                             : (size_t)RT * ActTile<float>::row_elems(k) * sizeof(float);
-    n += (size_t)kLW * RT * (tq * CT + 4) * sizeof(float);
+    size_t n = w->dtype == 1 ? (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t) : 0;
+    if (w->pred_kind == TDT_PRED_LSTM) n += (size_t)kLW * RT * (tq * CT + 4) * sizeof(float);
+    n += (size_t)kLW * RT * (label_tiles(nk) * CT + 4) * sizeof(float);
     if (w->pred_kind == TDT_PRED_LSTM) {
         const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4;
         const size_t units = (size_t)w->pred_layers * hyps_per_cluster * ((tiles + C - 1) / C) * 4;
