@@ -32,9 +32,12 @@ namespace {
 __shared__ int g_tr_n, g_tr_on;
 }
 }
+#ifndef TDT_TRACE_BLOCK
+#define TDT_TRACE_BLOCK 0   // the workgroup that is recorded
+#endif
 #define TR(id)                                                                                     \
     do {                                                                                           \
-        if (blockIdx.x == 0 && threadIdx.x == 0 && tdt::g_tr_on && tdt::g_tr_n < 8190) {           \
+        if (blockIdx.x == TDT_TRACE_BLOCK && threadIdx.x == 0 && tdt::g_tr_on && tdt::g_tr_n < 8190) {           \
             g_trace[1 + tdt::g_tr_n] = ((long long)(id) << 48) | (wall_clock64() & 0xffffffffffffll); \
             g_trace[0] = ++tdt::g_tr_n;                                                            \
         }                                                                                          \

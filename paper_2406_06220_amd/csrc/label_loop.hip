@@ -62,8 +62,8 @@ namespace tdt {
 namespace {
 
 constexpr unsigned kAbsent = 0xffffffffu;   // an exchanged float that is not there yet (a NaN no result is stored as)
+constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront and row of a tile in the partial sums (all uses)
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
-constexpr int kLW = kLabelThreads / 64;     // wavefronts of a workgroup
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -189,17 +189,21 @@ struct LabelShared {
 
 // LAYERS: 0: stateless predictor; 1: one LSTM layer, a workgroup's column tiles fit one round and the
 // group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
-template <typename WT, int LAYERS, bool CHUNKED, int NK>
-__global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
+// NW: wavefronts.  Four, or (WIDE) eight for output layers of many thousands of columns, see wide_rows.
+template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW>
+__global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 {
     typedef Frags<WT> F;
     typedef typename F::A AFrag;
     constexpr int PL = F::PL, KS = F::KS, NL = F::E / 4;   // NL: 16-byte loads of float32 for a lane's part of a step
-    constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1;
-    constexpr int TR = label_tiles(NK);              // column tiles per round of a joint pass
-    constexpr int TQ = DEEP ? TR : 2 * TR;           // ... and of the predictor-side products
+    constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1, WIDE = NW == 8;
+    constexpr int THREADS = NW * 64;
+    constexpr int TR = label_tiles(NK);                       // column tiles per round of a joint pass
+    constexpr int TQ = DEEP && !WIDE ? TR : 2 * TR;           // ... and of the predictor-side products
+    constexpr int QPR = THREADS / RT;                         // threads that share a row of a round, four columns each
+    static_assert(!WIDE || (LAYERS != 1 && TQ * CT == QPR * 4), "eight wavefronts: a round is one pass of the threads");
     constexpr int PLQ = TQ * CT + 4, PLJ = TR * CT + 4;   // floats per row of the partial sums (padded: 16 rows, 64 banks)
-    constexpr int KI = (NK * kLW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
+    constexpr int KI = (NK * NW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
 
@@ -251,9 +255,9 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     if (G <= 0) return;   // the whole group leaves together
     if (ranked) {
         int *lens = reinterpret_cast<int *>(dyn_lds);
-        for (int b = tid; b < B; b += kLabelThreads) lens[b] = min(max(p.enc_len[b], 0), T);
+        for (int b = tid; b < B; b += THREADS) lens[b] = min(max(p.enc_len[b], 0), T);
         __syncthreads();
-        for (int b = tid; b < B; b += kLabelThreads) {
+        for (int b = tid; b < B; b += THREADS) {
             const int lb = lens[b];
             int r = 0;
             for (int b2 = 0; b2 < B; ++b2) {
@@ -274,22 +278,26 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     // keeps of its own units: recurrent pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
-    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 ? (size_t)RT * ldb * sizeof(WT) : 0));   // [kLW][16][PLQ]
-    float *const part_j = part_q + (LSTM ? kLW * RT * PLQ : 0);                                              // [kLW][16][PLJ]
-    for (int i = tid; i < p.lds_bytes / 16; i += kLabelThreads)
+    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 && hpc <= kPackRows ? (size_t)RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
+    float *const part_j = part_q + (LSTM && !WIDE ? NW * RT * PLQ : 0);                                              // [NW][16][PLJ]
+    for (int i = tid; i < p.lds_bytes / 16; i += THREADS)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
 
-    // ---- this workgroup's column tiles of the predictor side: a stretch of [W_pred | W_hh] tiles,
-    // and with it a stretch of hidden units (of every layer)
+    // ---- this workgroup's column tiles of the predictor side, and with its W_hh tiles a stretch of hidden
+    // units (of every layer).  One round of one layer: a stretch of [W_pred | W_hh] tiles.  Else its
+    // share of each: a W_hh tile stands for three products of a deeper LSTM (its input, its recurrent
+    // product in every layer), a W_pred tile for one.
     const int nst_h = (Hp + KS - 1) / KS, nst_j = (H + KS - 1) / KS;   // fragments per tile
     const int NT_A = (H + CT - 1) / CT, NT_B = LSTM ? (Hp + 3) / 4 : 0;
     const int QT = LSTM ? (NT_A + NT_B + C - 1) / C : 0;
-    const int qt0 = rank * QT, nq = LSTM ? max(0, min(QT, NT_A + NT_B - qt0)) : 0;
-    const int na = max(0, min(NT_A - qt0, nq)), nr = nq - na;          // tiles of W_pred, of W_hh
-    const int r0 = max(qt0 - NT_A, 0);                                 // first W_hh tile
+    const int qt0 = DEEP ? rank * NT_A / C : rank * QT;                // its first W_pred tile, if it has any
+    const int na = DEEP ? (rank + 1) * NT_A / C - qt0 : LSTM ? max(0, min(NT_A - qt0, QT)) : 0;   // tiles of W_pred ...
+    const int r0 = DEEP ? rank * NT_B / C : max(qt0 - NT_A, 0);        // first W_hh tile
+    const int nr = DEEP ? (rank + 1) * NT_B / C - r0 : LSTM ? max(0, min(NT_A + NT_B - qt0, QT) - na) : 0;   // ... of W_hh
+    const int nq = na + nr;
     const int u0 = r0 * 4, U = nr > 0 ? min(nr * 4, Hp - u0) : 0;      // hidden units owned
-    const int Upad = QT * 4;
-    float4 *const rg_l = reinterpret_cast<float4 *>(part_j + kLW * RT * PLJ);               // [L][hpc][Upad]
+    const int Upad = (DEEP ? (NT_B + C - 1) / C : QT) * 4;
+    float4 *const rg_l = reinterpret_cast<float4 *>(part_j + NW * RT * (WIDE ? kWidePart : PLJ));               // [L][hpc][Upad]
     float *const c_l = reinterpret_cast<float *>(rg_l + (size_t)(LSTM ? L * hpc * Upad : 0));
     float *const h_l = c_l + (LSTM ? L * hpc * Upad : 0);                                 // (chunks only)
 
@@ -353,11 +361,11 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     const int NT = (O + CT - 1) / CT;
     {
         const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles, hpc);
-        for (int n = tid + 1; n <= G; n += kLabelThreads) {
+        for (int n = tid + 1; n <= G; n += THREADS) {
             const int Kw = joint_window(n, p.window, rows_auto, rows_cap);
             const int n_tiles = (n * Kw + RT - 1) / RT;
             int n_cg, tpg;
-            split_tiles(C, n_tiles, NT, C, n_cg, tpg);
+            split_tiles(C, WIDE ? 1 : n_tiles, NT, C, n_cg, tpg);   // (wide: a workgroup takes its columns of all rows)
             LabelPlan pl;
             pl.Kw = (short)Kw;
             pl.rcp_kw = ((1 << 20) + Kw - 1) / Kw;
@@ -402,9 +410,9 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     };
 
     // ---- which steps of a reduction of nst steps this wavefront takes: a contiguous stretch, the
-    // first nst % kLW wavefronts one step more
-    const int hs0 = wave * (nst_h / kLW) + min(wave, nst_h % kLW), hsn = nst_h / kLW + (wave < nst_h % kLW ? 1 : 0);
-    const int js0 = wave * (nst_j / kLW) + min(wave, nst_j % kLW), jsn = nst_j / kLW + (wave < nst_j % kLW ? 1 : 0);
+    // first nst % NW wavefronts one step more
+    const int hs0 = wave * (nst_h / NW) + min(wave, nst_h % NW), hsn = nst_h / NW + (wave < nst_h % NW ? 1 : 0);
+    const int js0 = wave * (nst_j / NW) + min(wave, nst_j % NW), jsn = nst_j / NW + (wave < nst_j % NW ? 1 : 0);
     // ---- weight fragments of a round; tile_off(t): byte offset of tile t among the fragment-major
     // copies
     const __amdgpu_buffer_rsrc_t wrs = buffer_of(p.packed, p.packed_bytes);
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     auto products_of = [&](auto packed_tag, auto count, const AFrag (&a)[NK][PL], const auto &b, float *part) __attribute__((always_inline)) {
         constexpr bool PACKED = decltype(packed_tag)::value;
         constexpr int PLD = sizeof(b) / (NK * sizeof(v4u)) * CT + 4;
-        constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED ? 2 : 3;   // chains per tile
+        constexpr int N = decltype(count)::value, NC = WIDE ? 1 : PL == 1 || PACKED ? 2 : 3;   // chains per tile
         f32x4 c[N][NC];
 #pragma unroll
         for (int t = 0; t < N; ++t)
@@ -437,10 +445,10 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 #pragma unroll
             for (int t = 0; t < N; ++t) {
                 if constexpr (PL == 1 || PACKED) {
-                    c[t][s % 2] = F::mma(a[s][0], b[t][s], c[t][s % 2]);
+                    c[t][s % NC] = F::mma(a[s][0], b[t][s], c[t][s % NC]);
                 } else {
 #pragma unroll
-                    for (int pl = 0; pl < PL; ++pl) c[t][pl] = F::mma(a[s][pl], b[t][s], c[t][pl]);
+                    for (int pl = PL - 1; pl >= 0; --pl) c[t][pl % NC] = F::mma(a[s][pl], b[t][s], c[t][pl % NC]);
                 }
             }
         float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
@@ -503,7 +511,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         const float *q = part + (size_t)row * PLD + quad * 4;
         float4 v = *reinterpret_cast<const float4 *>(q);
 #pragma unroll
-        for (int w = 1; w < kLW; ++w) {
+        for (int w = 1; w < NW; ++w) {
             const float4 x = *reinterpret_cast<const float4 *>(q + (size_t)w * RT * PLD);
             v.x += x.x;
             v.y += x.y;
@@ -533,14 +541,16 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             }
         }
     };
-    const bool qpack = PL == 3 && G <= kPackRows;
+    const bool qpack = PL == 3 && hpc <= kPackRows;
 
     // byte offsets of this workgroup's predictor-side tiles (the fragment-major copies)
     const int hbytes = nst_h * 1024, jbytes = nst_j * 1024;
     auto q_tile = [&](int t) {
-        const int q = qt0 + t;
-        return q < NT_A ? p.off_w_pred + q * hbytes : p.off_w_hh[L - 1] + (q - NT_A) * hbytes;
+        return t < na ? p.off_w_pred + (qt0 + t) * hbytes : p.off_w_hh[L - 1] + (r0 + t - na) * hbytes;
     };
+
+    // the four columns a thread takes of a round of phase Q (packed: a wavefront holds one row, in four places)
+    auto q_quad = [&]() { return qpack ? (wave / kPackRows) * 16 + (lane & 15) : tid % QPR; };
 
     // the LSTM cell of one unit: new cell value and new hidden value
     auto cell = [&](float4 g4, float c_old, float &cn, float &hn) __attribute__((always_inline)) {
@@ -566,7 +576,8 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         if (qpack) {   // a wavefront takes a row
             if constexpr (PL == 3) {
                 v4u v[KI];
-                const int off = (row0 + ((in_tile >> wave) & 1ull ? wave : any)) * Hp * (int)sizeof(float);
+                const bool row = wave < kPackRows;   // uniform
+                const int off = (row0 + (row && ((in_tile >> wave) & 1ull) ? wave : any)) * Hp * (int)sizeof(float);
 #pragma clang loop unroll(disable)
                 for (;;) {
                     unsigned mx = 0;
@@ -577,6 +588,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
                 }
                 TR(11);
+                if (row)
 #pragma unroll
                 for (int kk = 0; kk < KI; ++kk)   // (lanes beyond the row's end write its last inputs again)
                     put(wave, hoff(kk) / (int)sizeof(float), as_float4(v[kk]));
@@ -629,7 +641,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         const int pb = par ^ 1;
         if (U > 0)
 #pragma clang loop unroll(disable)
-            for (int base = 0; base < G * U; base += kLabelThreads) {
+            for (int base = 0; base < G * U; base += THREADS) {
                 const int idx = base + tid;
                 int g = p_g, u = p_u;
                 if (base > 0) {
@@ -647,7 +659,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 #pragma clang loop unroll(disable)
             for (int c0 = 0; c0 < nc; c0 += 64)
 #pragma clang loop unroll(disable)
-                for (int g = tid >> 4; g < G; g += RT)
+                for (int g = tid >> 4; g < G; g += THREADS / 16)
                     if (((act_prev >> g) & 1ull) && c0 + c < nc)
                         st_co4(px + ((size_t)pb * Bw + b0 + g) * H + qt0 * CT + c0 + c, make_float4(m, m, m, m));
         }
@@ -656,14 +668,16 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     auto clear_cells = [&]() __attribute__((always_inline)) {
         if (C > 1 && jpass > 2) {
             const unsigned pb = (jpass - 3) & (kRowBufs - 1);
+            const int stride = WIDE ? prev_cg : C;   // (wide: the same split in every pass)
+            if (rank < stride)
 #pragma clang loop unroll(disable)
-            for (int it = rank; it < clr_items; it += C)
+            for (int it = rank; it < clr_items; it += stride)
                 if (tid < 2 * RT) st_co64((tid < RT ? jb : jl) + (size_t)pb * cells + (size_t)it * RT + (tid & 15), 0ull);
             if (D > 0)   // (whoever wrote them: the words of a row tile are put back by rank ti)
 #pragma clang loop unroll(disable)
                 for (int ti = rank; ti < clr_tiles; ti += C)
                     if (tid < 2 * RT) st_co64(jd + ((size_t)pb * rows_cap + (size_t)ti * RT) * 2 + tid, 0ull);
-            if (rank >= clr_items && tid == 0) st_co64(jh + (size_t)pb * C + rank, 0ull);
+            if (rank >= (WIDE ? stride : clr_items) && tid == 0) st_co64(jh + (size_t)pb * C + rank, 0ull);
         }
     };
 
@@ -720,15 +734,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         items = n_tiles * n_cg;
         M = n_need * Kw;
     };
-    auto set_item = [&](int it) __attribute__((always_inline)) {
-        ti = ti0;
-        cg = cg0;
-        if (it != rank) {
-            ti = it / n_cg;
-            cg = it - ti * n_cg;
-        }
-        tile0 = cg * tpg;
-        n_ct = min(tpg, NT - tile0);
+    auto set_rows = [&]() __attribute__((always_inline)) {
         const int r = min(ti * RT + (lane & 15), M - 1);   // (a row beyond the last repeats it)
         const int q = (r * rcp_kw) >> 20;                  // r / Kw
         g_l = __builtin_amdgcn_ds_bpermute(q * 4, slot_of) & 63;
@@ -740,6 +746,17 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             lab_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last);
             lab2_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last2);
         }
+    };
+    auto set_item = [&](int it) __attribute__((always_inline)) {
+        ti = ti0;
+        cg = cg0;
+        if (it != rank) {
+            ti = it / n_cg;
+            cg = it - ti * n_cg;
+        }
+        tile0 = cg * tpg;
+        n_ct = min(tpg, NT - tile0);
+        set_rows();
     };
 
     // ---- LAYERS == 1: where this thread's results of phase Q go -- four columns of one row per half of
@@ -760,12 +777,271 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int idx = tid + h * kLabelThreads;
+            const int idx = tid + h * THREADS;
             c_g[h] = U > 0 ? min(idx / max(U, 1), kLabelMaxHyps - 1) : kLabelMaxHyps - 1;
             c_u[h] = U > 0 ? idx - idx / max(U, 1) * U : 0;
             if (U > 0 && idx < G * U) h_off[h] = (c_g[h] * Hp + u0 + c_u[h]) * (int)sizeof(float);
         }
     }
+    // ---- WIDE: R row tiles from tile tb on against this workgroup's columns.  What bounds a pass over
+    // an output layer of many thousands of columns is the stream of weights into a compute unit
+    // (64 bytes a clock) and, from two row tiles on, its matrix cores (three products per weight
+    // fragment and row tile).  So: two row tiles share one stream; a wavefront keeps the activations
+    // of its eighth of the reduction in registers and reads of the weights only that eighth; a batch
+    // of TB tiles is multiplied while the next one is on its way into the registers it leaves and the
+    // sums of the one before go through LDS into running statistics, two columns a thread, by pieces
+    // between the products.  Measured at 8198 outputs, joint width 1024, 16 workgroups a group (33 tiles
+    // each): one row tile 1.28 us per four tiles (the stream alone 1.05 us: 126 GB/s a compute unit), two
+    // 1.03 us per two tiles (matrix cores alone 0.64); 33 tiles against 48 rows 22 us + 14 us,
+    // 30 us on average in decode.hip's streaming pass, of which a call at B = 256 has 2.8 a label.
+    auto wide_rows = [&](auto rtag, int tb, unsigned long long *jbb, unsigned long long *jlb, unsigned long long *jdb, int dcg0,
+                         int dcg1) __attribute__((always_inline)) {
+        constexpr int R = decltype(rtag)::value, TB = 4 / R, PW = TB * CT + 4;
+        constexpr int CPT = 2, QR = TB * CT / CPT;   // columns a thread looks at, threads of a row
+        constexpr int PB = NW * R * RT * PW;         // floats of a buffer of partial sums (of two)
+        static_assert(2 * PB <= NW * RT * kWidePart, "two buffers");
+        fresh();
+        TR(40);
+        v4u b[TB][NK];
+        const int last_t = n_ct - 1;
+        auto fetch_tile = [&](auto &bt, int t) __attribute__((always_inline)) {   // tile t, or the last
+            const int w = p.off_w_out + (tile0 + min(t, last_t)) * jbytes + js0 * 1024;
+#pragma unroll
+            for (int s = 0; s < NK; ++s)
+                bt[s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, s < jsn ? lane * 16 : ~0xff, w + (s < jsn ? s : 0) * 1024, 0);
+        };
+        AFrag a[R][NK][PL];
+        {
+            v4u e[R][NK][NL], q[R][NK][NL];
+            int po[R];
+            const float *pr[R], *pr2[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                ti = tb + r;
+                set_rows();
+                const float *er = p.enc_proj + (size_t)(unsigned)erow_l * H;
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) e[r][s][l] = ldg4(er, part_of(s, js0, H) + l * 16);
+                po[r] = (par * Bw + b0 + g_l) * H * (int)sizeof(float);
+                if constexpr (!LSTM) {
+                    pr[r] = p.pred_tab + (size_t)lab_l * H;
+                    if (p.pred_layers == 2) {
+                        pr2[r] = p.pred_tab + ((size_t)(V + 1) + lab_l) * H;
+                        pr[r] = p.pred_tab + (size_t)lab2_l * H;
+                    }
+#pragma unroll
+                    for (int s = 0; s < NK; ++s)
+#pragma unroll
+                        for (int l = 0; l < NL; ++l) q[r][s][l] = ldg4(pr[r], part_of(s, js0, H) + l * 16);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < TB; ++t) fetch_tile(b[t], t);
+            if constexpr (LSTM) {
+                unsigned spins = 0;
+                long long since = 0;
+#pragma clang loop unroll(disable)
+                for (;;) {
+                    unsigned mx = 0;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int s = 0; s < NK; ++s)
+#pragma unroll
+                            for (int l = 0; l < NL; ++l) q[r][s][l] = ldx4(prs, po[r] + part_of(s, js0, H) + l * 16, 0);
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int s = 0; s < NK; ++s)
+#pragma unroll
+                            for (int l = 0; l < NL; ++l) mx = max(mx, umax4(q[r][s][l]));
+                    if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+                }
+                lap(kTkBar);
+                TR(41);
+            } else if (p.pred_layers == 2) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int s = 0; s < NK; ++s)
+#pragma unroll
+                        for (int l = 0; l < NL; ++l) {
+                            const float4 x = as_float4(ldg4(pr2[r], part_of(s, js0, H) + l * 16)), y = as_float4(q[r][s][l]);
+                            q[r][s][l] = v4u{__float_as_uint(y.x + x.x), __float_as_uint(y.y + x.y),
+                                             __float_as_uint(y.z + x.z), __float_as_uint(y.w + x.w)};
+                        }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int s = 0; s < NK; ++s) {
+                    float x[F::E];
+#pragma unroll
+                    for (int i = 0; i < F::E; ++i)
+                        x[i] = fmaxf(__uint_as_float(e[r][s][i / 4][i % 4]) + __uint_as_float(q[r][s][i / 4][i % 4]), 0.0f);
+                    split(x, a[r][s]);
+                }
+        }
+        fresh();
+        TR(42);
+        const int row = tid / QR, quad = tid % QR;   // this thread's row (of R * 16) and columns of a batch
+        constexpr float kNone = -3.4e38f;
+        float rm = kNone, rs = 0.0f, rdm = -INFINITY;
+        int ra = 0x7fffffff, rda = 0;
+        f32x4 acc[TB][R];
+        float bias[CPT], x4[CPT];
+        // The products of batch k; each tile's registers then take the same tile of the next batch.  Of the
+        // eight groups of products every one is followed by a piece of other work (piece(0) .. piece(7)):
+        // the other wavefront of the SIMD multiplies meanwhile.
+        auto multiply = [&](int k, auto piece) __attribute__((always_inline)) {
+            const int bo = ((tile0 + k * TB) * CT + quad * CPT) * (int)sizeof(float);
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) bias[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(brs, bo + e * 4, 0, 0));
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int r = 0; r < R; ++r) acc[t][r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {   // R == 1: two tiles, one step a group; R == 2: two tiles, half a step (three products each)
+                const int t = R == 1 ? g / NK * 2 : 0, s = R == 1 ? g % NK : g / 2;
+#pragma unroll
+                for (int pl = PL - 1; pl >= 0; --pl)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int r = R == 1 ? 0 : g % 2;
+                        acc[t + u][r] = F::mma(a[r][s][pl], b[t + u][s], acc[t + u][r]);
+                    }
+                if (R == 1 ? s == NK - 1 : g == 7)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) fetch_tile(b[t + u], (k + 1) * TB + t + u);
+                piece(g);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto store = [&](int k) __attribute__((always_inline)) {
+            float *const pw = part_q + (k & 1) * PB + (size_t)wave * R * RT * PW + (lane & 15) * PW + (lane >> 4) * 4;
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+#pragma unroll
+                for (int r = 0; r < R; ++r) *reinterpret_cast<f32x4 *>(pw + r * RT * PW + t * CT) = acc[t][r];
+        };
+        // what is done with the sums of batch k, in eight pieces
+        typedef float VC __attribute__((ext_vector_type(CPT)));
+        VC lv[NW];
+        float lg[CPT], lm, lx[CPT + 1], bb[CPT];
+        auto look = [&](int k, int step) __attribute__((always_inline)) {
+            if (step == 0) {
+                const float *q = part_q + (k & 1) * PB + (size_t)row * PW + quad * CPT;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) lv[w] = *reinterpret_cast<const VC *>(q + (size_t)w * R * RT * PW);
+            } else if (step == 2) {
+#pragma unroll
+                for (int w = 0; w < NW; w += 2) lv[w] = lv[w] + lv[w + 1];
+            } else if (step == 3) {
+                lv[0] = (lv[0] + lv[2]) + (lv[4] + lv[6]);
+            } else if (step == 4) {
+                // (no branches: columns that are not there, and logits that are no numbers, count as kNone, and what
+                // stands beside a largest logit of kNone vanishes with the first real one)
+                const int t = k * TB + quad * CPT / CT, col0 = t < n_ct ? (tile0 + t) * CT + quad * CPT % CT : O;
+                lm = rm;
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) {   // (columns ascend: '>' keeps the first maximum)
+                    x4[e] = lv[0][e] + bb[e];
+                    lg[e] = fmaxf(col0 + e <= VL ? x4[e] : kNone, kNone);
+                    ra = lg[e] > lm ? col0 + e : ra;
+                    lm = fmaxf(lm, lg[e]);
+                }
+            } else if (step == 5) {
+                lx[CPT] = __expf(rm - lm);
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) lx[e] = __expf(lg[e] - lm);
+                rm = lm;
+            } else if (step == 6) {
+                rs *= lx[CPT];
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) rs += lx[e];
+            }
+        };
+        auto durations = [&](int k) __attribute__((always_inline)) {
+            if (cg >= dcg0 && cg <= dcg1) {   // (uniform; never without a duration head)
+                const int t = k * TB + quad * CPT / CT, col0 = t < n_ct ? (tile0 + t) * CT + quad * CPT % CT : O;
+#pragma unroll
+                for (int e = 0; e < CPT; ++e)
+                    if (col0 + e > VL && col0 + e < O && x4[e] > rdm) { rdm = x4[e]; rda = col0 + e - (VL + 1); }
+            }
+        };
+        const int batches = (n_ct + TB - 1) / TB;
+        multiply(0, [](int) {});
+        TR(43);
+        __syncthreads();   // the partial sums are not read any more (phase Q, the rows before)
+        store(0);
+        __syncthreads();
+#pragma clang loop unroll(disable)
+        for (int k = 1; k < batches; ++k) {
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) bb[e] = bias[e];
+            multiply(k, [&](int step) __attribute__((always_inline)) { look(k - 1, step); });
+            durations(k - 1);
+            store(k);   // (into the buffer that was looked at before the last barrier)
+            __syncthreads();
+            TR(44);
+        }
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) bb[e] = bias[e];
+#pragma unroll
+        for (int step = 0; step < 8; ++step) look(batches - 1, step);
+        durations(batches - 1);
+        // the threads of a row
+        auto fmax2 = [](float x, float y) { return fmaxf(x, y); };
+        auto imin2 = [](int x, int y) { return min(x, y); };
+        auto fadd2 = [](float x, float y) { return x + y; };
+        auto over_row = [&](auto v, auto op) __attribute__((always_inline)) {
+            v = row_allreduce(v, op);
+            if constexpr (QR == 32) {   // (two rows of lanes)
+                unsigned u;
+                __builtin_memcpy(&u, &v, 4);
+                const auto x = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+                decltype(v) y, z;
+                const unsigned x0 = x[0], x1 = x[1];
+                __builtin_memcpy(&y, &x0, 4);
+                __builtin_memcpy(&z, &x1, 4);
+                v = op(y, z);
+            }
+            return v;
+        };
+        const float m = over_row(rm, fmax2);
+        const int am = over_row(rm == m ? ra : 0x7fffffff, imin2);
+        const float sum = over_row(rs * __expf(rm - m), fadd2);
+        float dm = -INFINITY;
+        int da = 0;
+        if (cg >= dcg0 && cg <= dcg1) {
+            dm = over_row(rdm, fmax2);
+            da = over_row(rdm == dm ? rda : 0x7fffffff, imin2);
+        }
+        TR(45);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (words put back earlier have arrived ...
+        __syncthreads();                                   // ... those of all wavefronts)
+        if (quad == 0) {
+            const int i = row & 15, tr = tb + row / RT, o = (tr * n_cg + cg) * RT + i;
+            const unsigned long long best = m > kNone ? pack_best(m, am) : 1ull;
+            const unsigned long long bd = dm > -INFINITY ? pack_best(dm, da) : 1ull;
+            const unsigned long long lse = (unsigned long long)__float_as_uint(m) |
+                                           ((unsigned long long)__float_as_uint(m > kNone ? sum : 0.0f) << 32);
+            if (C > 1) {
+                st_co64(jbb + o, best);
+                if (cg == dcg0) st_co64(jdb + (size_t)(tr * 2) * RT + i, bd);
+                else if (cg == dcg1) st_co64(jdb + (size_t)(tr * 2 + 1) * RT + i, bd);
+                st_co64(jlb + o, lse);
+            } else {
+                S.rowb[tr * RT + i] = best;
+                S.rowl[tr * RT + i] = lse;
+                S.rowd[tr * RT + i] = (unsigned)S.durations[unpack_index(bd) & (TDT_MAX_DURATIONS - 1)];
+            }
+        }
+    };
+
 #pragma clang loop unroll(disable)
     while (ok) {   // ---- Alg. 3 line 5: while any hypothesis is active
         const unsigned long long act = __ballot(active);
@@ -782,7 +1058,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         unsigned long long needm = __ballot(need);
 
         // the projected encoder frames of a work item: this wavefront's stretch of its rows
-        v4u e4[NK][NL];
+        v4u e4[NK][NL];   // (not wide)
         any_value(e4);
         auto request_rows = [&]() __attribute__((always_inline)) {
             const float *er = p.enc_proj + (size_t)(unsigned)erow_l * H;
@@ -797,7 +1073,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, W_hh * h was formed by this
             // workgroup when h was new.  The weights of phase Q are requested behind the table row:
             // the row takes about as long to arrive as the requests take to leave.
-            const bool two_cells = G * U > kLabelThreads;   // uniform
+            const bool two_cells = G * U > THREADS;   // uniform
             v4u t4[2];
             any_value(t4);
 #pragma unroll
@@ -832,7 +1108,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             // ---- P: the first layer's cell update.  W_ih * emb[label] + b is a table row,
             // W_hh * h was formed by this workgroup when h was new.
 #pragma clang loop unroll(disable)
-            for (int base = 0; base < G * U; base += kLabelThreads) {   // uniform
+            for (int base = 0; base < G * U; base += THREADS) {   // uniform
                 const int idx = base + tid;
                 int g = p_g, u = p_u;
                 if (base > 0) {
@@ -867,14 +1143,14 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             if (needm != 0ull) {
                 plan_pass(needm);
                 set_item(rank);   // (a workgroup without a work item: never used)
-                if (rank < items) request_rows();
+                if (!WIDE && rank < items) request_rows();
             }
             TR(3);
             if constexpr (LAYERS == 1) {
                 const v4u absent = {kAbsent, kAbsent, kAbsent, kAbsent};
                 const int pb = (par ^ 1) * Bw + b0;
                 __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[0], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
-                if (G * U > kLabelThreads)
+                if (G * U > THREADS)
                     __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[1], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
                 __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[0], pb * H * (int)sizeof(float), 16 /* sc1 */);
                 if (nq > 4) __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[1], pb * H * (int)sizeof(float), 16 /* sc1 */);
@@ -882,7 +1158,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                 clear_rows();
             }
             clear_cells();
-            if (wave == kLW - 1) finish_scores();
+            if (wave == NW - 1) finish_scores();
             fresh();
             TR(10);
             lap(kTkP);
@@ -937,7 +1213,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     const int n = min(TQ, n_all - t0);
                     const int w = here(top ? 0 : (kind == 0 ? p.off_w_ih[l + 1] : p.off_w_hh[l]) + (r0 + t0) * hbytes);
                     fetch(b, n, hs0, hsn, [&](int t) { return top ? q_tile(t0 + t) + w : w + t * hbytes; });
-                    const int t = t0 + ((lane & 15) >> 2), col = (qt0 + t) * CT + (lane & 3) * 4;
+                    const int t = t0 + (q_quad() >> 2), col = (qt0 + t) * CT + (lane & 3) * 4;
                     qbias = *reinterpret_cast<const float4 *>(p.b_pred + (t < na && col < H ? col : 0));
                 };
                 bool loaded = false;   // the registers hold the fragments of the first round
@@ -946,7 +1222,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                     const unsigned long long in_tile = act >> (tq * RT) & 0xffffull;
                     if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
                     if (!loaded) fetch_round(0, 0);   // while the rows are on their way
-                    loaded = top && n_all <= TQ;
+                    loaded = !WIDE && top && n_all <= TQ;
                     AFrag a[NK][PL];
                     any_value(a);
                     stage_h(a, row0, tq, in_tile);
@@ -968,7 +1244,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                             fresh();
                             // a thread takes four columns of a row; packed: a wavefront takes a row, its
                             // lanes one plane each, and the planes are added up
-                            const int quad = lane & 15, i = qpack ? wave : tid >> 4, g = tq * RT + i;
+                            const int quad = q_quad(), i = qpack ? wave % kPackRows : tid / QPR, g = tq * RT + i;
                             float4 v = gather(q_tiles, part_q, qpack ? i + (lane >> 4) * kPackRows : i, quad);
                             if (qpack) {
                                 if (lane >= 48) v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
@@ -1037,7 +1313,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         for (bool again = false; needm != 0ull; again = true) {
             fresh();
             // (a group of one workgroup: this pass writes over what the terms of the last one are summed from)
-            if (C == 1 && (!LSTM || again) && wave == kLW - 1) finish_scores();
+            if (C == 1 && (!LSTM || again) && wave == NW - 1) finish_scores();
             if (again) plan_pass(needm);
             const unsigned buf = jpass & (kRowBufs - 1);
             ++jpass;
@@ -1051,7 +1327,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 
             // ---- J
 #pragma clang loop unroll(disable)
-            for (int it = rank; it < items; it += C) {
+            for (int it = rank; !WIDE && it < items; it += C) {
                 if (!LSTM || again || it != rank) {
                     set_item(it);
                     request_rows();
@@ -1209,7 +1485,22 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                 }
                 if (it + C < items) __syncthreads();   // the next item writes the partial sums again
             }
-            if (rank >= items) {   // no work item: say that this workgroup has come this far
+            if constexpr (WIDE) {
+                if (rank < n_cg) {
+                    tile0 = rank * tpg;
+                    n_ct = min(tpg, NT - tile0);
+                    cg = rank;
+#pragma clang loop unroll(disable)
+                    for (int t = 0; t < n_tiles; t += 2) {
+                        const std::integral_constant<int, 1> one{};
+                        const std::integral_constant<int, 2> two{};
+                        if (t + 1 < n_tiles) wide_rows(two, t, jbb, jlb, jdb, dcg0, dcg1);
+                        else wide_rows(one, t, jbb, jlb, jdb, dcg0, dcg1);
+                    }
+                }
+            }
+            const int busy = WIDE ? n_cg : items;   // workgroups with a work item (or more)
+            if (rank >= busy) {   // no work item: say that this workgroup has come this far
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
                 if (tid == 0) st_co64(jhb + rank, 1ull);
@@ -1221,7 +1512,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             fresh();
             if (C > 1 && (!LSTM || again)) {   // (an LSTM's first pass: summed while the hidden state travelled)
                 --jpass;   // (finish_scores looks at the last pass)
-                if (wave == kLW - 1) finish_scores();
+                if (wave == NW - 1) finish_scores();
                 ++jpass;
             }
             // ---- gather the cells: a wavefront takes one row tile, or a share of its column groups;
@@ -1230,7 +1521,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             if (C > 1) {
                 const int i = lane & 15;
 #pragma clang loop unroll(disable)
-                for (int tw = wave; tw < n_tiles << wsh; tw += kLW) {   // (more than once only for many row tiles)
+                for (int tw = wave; tw < n_tiles << wsh; tw += NW) {   // (more than once only for many row tiles)
                     const int tt = tw >> wsh, wq = tw & (wpt - 1);
                     const unsigned long long *src = jbb + (size_t)tt * n_cg * RT + i;
                     unsigned long long best = 0ull;
@@ -1258,7 +1549,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                 if (D > 0) {   // the duration head's words: one or two column groups
                     const int two = dcg1 != dcg0 ? RT : 0;
 #pragma clang loop unroll(disable)
-                    for (int rb = (kLW - 1 - wave) * 64; rb < n_tiles * RT; rb += kLabelThreads) {   // uniform
+                    for (int rb = (NW - 1 - wave) * 64; rb < n_tiles * RT; rb += THREADS) {   // uniform
                         const int r = min(rb + lane, n_tiles * RT - 1);
                         const unsigned long long *q = jdb + (size_t)(r >> 4) * 2 * RT + (r & 15);
                         unsigned long long x = wait_word(q);
@@ -1269,9 +1560,9 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                         S.rowd[r] = (unsigned)S.durations[unpack_index(x) & (TDT_MAX_DURATIONS - 1)];   // the frame step
                     }
                 }
-                if (items < C && wave == 1)   // the workgroups without a work item
+                if (busy < C && wave == 1)   // the workgroups without a work item
 #pragma clang loop unroll(disable)
-                    for (int c = items; c < C; c += 64) wait_word(jhb + min(c + lane, C - 1));
+                    for (int c = busy; c < C; c += 64) wait_word(jhb + min(c + lane, C - 1));
             }
             TR(31);
             __syncthreads();
@@ -1326,7 +1617,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
                 kb = (unsigned)__builtin_amdgcn_ds_bpermute(at, (int)(unsigned)(best >> 32));
                 if (!plain) dk = __builtin_amdgcn_ds_bpermute(at, step);
             } else {
-                for (int r = tid; r < M; r += kLabelThreads) {
+                for (int r = tid; r < M; r += THREADS) {
                     int ra, step;
                     unsigned long long best;
                     row_result(r, ra, step, best);
@@ -1398,7 +1689,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
         first = false;
         par ^= 1;
     }
-    if (ok && wave == kLW - 1) finish_scores();
+    if (ok && wave == NW - 1) finish_scores();
 
     // ---- what the next chunk takes up
     if (CHUNKED) {
@@ -1409,7 +1700,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
     }
     if (CHUNKED && ok) {
         if constexpr (LSTM) {
-            for (int idx = tid; idx < G * U; idx += kLabelThreads) {
+            for (int idx = tid; idx < G * U; idx += THREADS) {
                 const int g = idx / U, u = idx - g * U;
                 if ((took_part >> g) & 1ull)
                     for (int l = 0; l < L; ++l) {
@@ -1428,7 +1719,7 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
             p.st_last2[gid] = last2;
         }
     }
-    if (wave == kLW - 1 && mine && owner_mod == rank) p.out_score[gid] = score;   // (the wavefront that summed it)
+    if (wave == NW - 1 && mine && owner_mod == rank) p.out_score[gid] = score;   // (the wavefront that summed it)
     if (rank == 0 && wave == 0) {
         if (mine) {
             p.out_len[gid] = olen;
@@ -1461,12 +1752,12 @@ __global__ __launch_bounds__(kLabelThreads, 1) void label_kernel(DecodeParams p)
 constexpr size_t kLabelDynLds = kLdsBytes - sizeof(LabelShared) - 256;   // (the rest: what the compiler adds)
 
 // the compiled form for a model: steps of the reduction a wavefront takes
-int label_steps(const tdt_weights_t *w)
+int label_steps(const tdt_weights_t *w, int wavefronts)
 {
     const int ks = w->dtype == 1 ? 32 : 16;
     int k = w->h_joint;
     if (w->pred_kind == TDT_PRED_LSTM && w->h_pred > k) k = w->h_pred;
-    return ((k + ks - 1) / ks + kLW - 1) / kLW;
+    return ((k + ks - 1) / ks + wavefronts - 1) / wavefronts;
 }
 int label_kseg(const tdt_weights_t *w)
 {
@@ -1476,66 +1767,91 @@ int label_kseg(const tdt_weights_t *w)
 template <typename WT, int NK> const void *label_fn(int layers, bool chunked)
 {
     if (layers > 1)
-        return chunked ? (const void *)label_kernel<WT, 2, true, NK> : (const void *)label_kernel<WT, 2, false, NK>;
+        return chunked ? (const void *)label_kernel<WT, 2, true, NK, 4> : (const void *)label_kernel<WT, 2, false, NK, 4>;
     if (layers == 1)
-        return chunked ? (const void *)label_kernel<WT, 1, true, NK> : (const void *)label_kernel<WT, 1, false, NK>;
-    return chunked ? (const void *)label_kernel<WT, 0, true, NK> : (const void *)label_kernel<WT, 0, false, NK>;
+        return chunked ? (const void *)label_kernel<WT, 1, true, NK, 4> : (const void *)label_kernel<WT, 1, false, NK, 4>;
+    return chunked ? (const void *)label_kernel<WT, 0, true, NK, 4> : (const void *)label_kernel<WT, 0, false, NK, 4>;
 }
-const void *label_fn_for(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C, int &nk, int &tq)
+const void *label_wide_fn(bool lstm, bool chunked)   // (bfloat16)
 {
+    if (lstm)
+        return chunked ? (const void *)label_kernel<uint16_t, 2, true, 4, 8> : (const void *)label_kernel<uint16_t, 2, false, 4, 8>;
+    return chunked ? (const void *)label_kernel<uint16_t, 0, true, 4, 8> : (const void *)label_kernel<uint16_t, 0, false, 4, 8>;
+}
+struct LabelForm {
+    const void *fn;   // null: none
+    int nk, nw, tq, layers;   // steps of the reduction per wavefront, wavefronts, column tiles per round of phase Q, LAYERS
+};
+LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
+{
+    const bool lstm = w->pred_kind == TDT_PRED_LSTM;
+    LabelForm f{nullptr, 0, wide ? 8 : 4, 0, lstm ? 2 : 0};
     // bfloat16: steps of 32 inputs (reductions of up to 640 and 1024), float32: of 16 (256 and 640)
-    const int steps = label_steps(w);
-    if (w->dtype == 1) nk = steps <= 5 ? 5 : 8;
-    else nk = steps <= 4 ? 4 : 10;
-    if (steps > nk) return nullptr;
-    int layers = w->pred_kind == TDT_PRED_LSTM ? 2 : 0;
-    if (layers > 0 && w->pred_layers == 1) {
+    const int steps = label_steps(w, f.nw);
+    if (wide) {
+        f.nk = 4;
+        f.tq = 2 * label_tiles(f.nk);
+        if (w->dtype == 1 && steps <= f.nk) f.fn = label_wide_fn(lstm, chunked);
+        return f;
+    }
+    if (w->dtype == 1) f.nk = steps <= 5 ? 5 : 8;
+    else f.nk = steps <= 4 ? 4 : 10;
+    if (steps > f.nk) return f;
+    if (lstm && w->pred_layers == 1) {
         const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
         // one round, one row tile, one or two cells a thread
-        if (per_wg <= 2 * label_tiles(nk) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads)
-            layers = 1;
+        if (per_wg <= 2 * label_tiles(f.nk) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads)
+            f.layers = 1;
     }
-    tq = (layers > 1 ? 1 : 2) * label_tiles(nk);
-    if (w->dtype == 1) return nk == 5 ? label_fn<uint16_t, 5>(layers, chunked) : label_fn<uint16_t, 8>(layers, chunked);
-    return nk == 4 ? label_fn<float, 4>(layers, chunked) : label_fn<float, 10>(layers, chunked);
+    f.tq = (f.layers > 1 ? 1 : 2) * label_tiles(f.nk);
+    if (w->dtype == 1) f.fn = f.nk == 5 ? label_fn<uint16_t, 5>(f.layers, chunked) : label_fn<uint16_t, 8>(f.layers, chunked);
+    else f.fn = f.nk == 4 ? label_fn<float, 4>(f.layers, chunked) : label_fn<float, 10>(f.layers, chunked);
+    return f;
 }
 
 }  // namespace
 
-size_t label_lds_bytes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C)
+static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C)
 {
-    int nk = 0, tq = 0;
-    if (!label_fn_for(w, chunked, hyps_per_cluster, C, nk, tq)) return ~(size_t)0;
-    size_t n = w->dtype == 1 ? (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t) : 0;
-    if (w->pred_kind == TDT_PRED_LSTM) n += (size_t)kLW * RT * (tq * CT + 4) * sizeof(float);
-    n += (size_t)kLW * RT * (label_tiles(nk) * CT + 4) * sizeof(float);
+    size_t n = w->dtype == 1 && hyps_per_cluster <= kPackRows
+                   ? (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t) : 0;
+    if (f.nw == 8) {
+        n += (size_t)f.nw * RT * kWidePart * sizeof(float);
+    } else {
+        if (w->pred_kind == TDT_PRED_LSTM) n += (size_t)f.nw * RT * (f.tq * CT + 4) * sizeof(float);
+        n += (size_t)f.nw * RT * (label_tiles(f.nk) * CT + 4) * sizeof(float);
+    }
     if (w->pred_kind == TDT_PRED_LSTM) {
-        const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4;
+        const int tiles = (w->h_pred + 3) / 4 + (f.layers == 1 ? (w->h_joint + CT - 1) / CT : 0);
         const size_t units = (size_t)w->pred_layers * hyps_per_cluster * ((tiles + C - 1) / C) * 4;
         n += units * (4 + 1 + (chunked ? 1 : 0)) * sizeof(float);
     }
     return (n + 15) / 16 * 16;
 }
 
-bool label_kernel_takes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C)
+bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
 {
     if (hyps_per_cluster > kLabelMaxHyps) return false;
-    const size_t dyn = label_lds_bytes(w, chunked, hyps_per_cluster, C);
+    const LabelForm f = label_form(w, chunked, wide, hyps_per_cluster, C);
+    if (!f.fn) return false;
+    const size_t dyn = label_lds_bytes(w, f, chunked, hyps_per_cluster, C);
     const size_t lens = (size_t)kMaxRankedBatch * sizeof(int);   // (the batch's lengths while they are ranked)
     if (packed_layout(w).total >= ((size_t)1 << 31)) return false;   // offsets among the copies are 32 bits
     return dyn >= lens && dyn <= kLabelDynLds;
 }
 
-hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, int grid, hipStream_t stream)
+hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, bool wide, int grid,
+                        hipStream_t stream)
 {
     // the LDS limit of a compiled form is raised once per device (to all a workgroup can have)
     static std::mutex mu;
     static const void *ready[64][32];
-    int dev = 0, nk = 0, tq = 0;
+    int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    const void *fn = label_fn_for(w, chunked, p.hyps_per_cluster, grid / p.n_clusters, nk, tq);
+    const LabelForm f = label_form(w, chunked, wide, p.hyps_per_cluster, grid / p.n_clusters);
+    const void *fn = f.fn;
     if (!fn) return hipErrorInvalidValue;
     {
         std::lock_guard<std::mutex> lock(mu);
@@ -1550,9 +1866,9 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     }
     DecodeParams pc = p;
     pc.kseg_max = label_kseg(w);
-    pc.lds_bytes = (int)label_lds_bytes(w, chunked, p.hyps_per_cluster, grid / p.n_clusters);
+    pc.lds_bytes = (int)label_lds_bytes(w, f, chunked, p.hyps_per_cluster, grid / p.n_clusters);
     void *args[] = {&pc};
-    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(kLabelThreads), args, (unsigned)pc.lds_bytes, stream);
+    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(f.nw * 64), args, (unsigned)pc.lds_bytes, stream);
 }
 
 }  // namespace tdt

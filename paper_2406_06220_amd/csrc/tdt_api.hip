@@ -87,8 +87,10 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     L.need_general = off;
     // label_loop.hip lays its own arrays over the part from `partials` on; how much it needs depends
     // on the split of the batch, which is not known here: n_clusters * hyps_per_cluster <= B + kMaxGrid
-    // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup
-    const size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
+    // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup -- or one for
+    // each of at most 16 row tiles a workgroup
+    size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
+    if (cells < 16 * 16 * (size_t)kMaxGrid) cells = 16 * 16 * (size_t)kMaxGrid;
     size_t lab = L.partials;
     lab = align_up(lab + 2 * lstm_layers * rows * w->h_pred * sizeof(float), 256);
     if (lstm_layers > 0) lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
@@ -106,7 +108,7 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     return L;
 }
 
-LabelLayout label_layout(const tdt_weights_t *w, int n_clusters, int hyps_per_cluster, int C)
+LabelLayout label_layout(const tdt_weights_t *w, bool wide, int n_clusters, int hyps_per_cluster, int C)
 {
     LabelLayout L{};
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
@@ -114,7 +116,9 @@ LabelLayout label_layout(const tdt_weights_t *w, int n_clusters, int hyps_per_cl
     L.rows_per_cluster = hyps_per_cluster * kMaxWindow < kLabelRowsPerPass ? hyps_per_cluster * kMaxWindow
                                                                          : kLabelRowsPerPass;
     const int tiles = L.rows_per_cluster / 16;   // row tiles of a joint pass
-    L.cells_per_cluster = 16 * (tiles > C ? tiles : C);
+    // one cell a row for every work item: a workgroup has one, or more where there are more row tiles than
+    // workgroups; wide: one for every row tile
+    L.cells_per_cluster = 16 * (wide ? tiles * C : tiles > C ? tiles : C);
     size_t off = 0;
     L.ones_begin = L.hx = off;
     if (lstm) off = align_up(off + 2 * (size_t)w->pred_layers * rows * w->h_pred * sizeof(float), 256);
@@ -408,14 +412,14 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
     // streamed output layer, groups it can hold), else the general one
     const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
-    const bool label = workspace_bytes >= L.need_label && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly && !wide_joint &&
-                       label_kernel_takes(weights, state != nullptr, hyps_per_cluster, C);
+    const bool label = workspace_bytes >= L.need_label && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly &&
+                       label_kernel_takes(weights, state != nullptr, wide_joint, hyps_per_cluster, C);
     if (weights->dtype == 0 && !label) PL.total = 0;   // (float32: the general kernel reads the matrices as they are)
     LabelLayout LL{};
     ClearRanges clear{};
     char *const lb = ws + L.partials;
     if (label) {
-        LL = label_layout(weights, n_clusters, hyps_per_cluster, C);
+        LL = label_layout(weights, wide_joint, n_clusters, hyps_per_cluster, C);
         clear.zero = lb + LL.zero_begin;
         clear.zero_bytes = LL.zero_end - LL.zero_begin;
         clear.ones = lb + LL.ones_begin;
@@ -538,7 +542,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         p.abort_flag = reinterpret_cast<int *>(lb + LL.abort_flag);
         p.rows_per_cluster = LL.rows_per_cluster;
         p.cells_per_cluster = LL.cells_per_cluster;
-        if (launch_label(p, weights, state != nullptr, grid, s) != hipSuccess) return TDT_ERR_LAUNCH;
+        if (launch_label(p, weights, state != nullptr, wide_joint, grid, s) != hipSuccess) return TDT_ERR_LAUNCH;
         return TDT_OK;
     }
     if (launch_decode(p, weights, variant, grid, s) != hipSuccess) return TDT_ERR_LAUNCH;

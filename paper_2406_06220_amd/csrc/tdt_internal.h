@@ -114,9 +114,9 @@ struct LabelLayout {
     size_t ones_begin, hx, px, ones_end, zero_begin, row_lab, row_lse, row_dur, present, abort_flag, zero_end;
     int rows_per_cluster, cells_per_cluster;
 };
-LabelLayout label_layout(const tdt_weights_t *w, int n_clusters, int hyps_per_cluster, int C);
+LabelLayout label_layout(const tdt_weights_t *w, bool wide, int n_clusters, int hyps_per_cluster, int C);
 // whether that kernel can decode groups of this many hypotheses on C workgroups each
-bool label_kernel_takes(const tdt_weights_t *w, bool chunked, int hyps_per_cluster, int C);
+bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C);
 
 // the caller-held state of tdt_greedy_decode_chunk: byte offsets of its arrays
 struct StateLayout {
@@ -175,7 +175,7 @@ struct DecodeVariant {
 hipError_t launch_decode(const DecodeParams &p, const tdt_weights_t *w, DecodeVariant v, int grid,
                          hipStream_t stream);
 // the same for label_loop.hip's kernel (label_kernel_takes)
-hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, int grid, hipStream_t stream);
+hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, bool wide, int grid, hipStream_t stream);
 // largest grid the decode kernel can run with all workgroups resident, 0 on error
 int decode_max_grid(const tdt_weights_t *w, DecodeVariant v);
 // ticks per millisecond of the device wall clock the kernels read (100000 if the query fails)

@@ -55,6 +55,12 @@ CASES = [
     (config("ll_f32_deep", dtype="fp32", pred_layers=2, B=20), dict(n_clusters=4)),
     # a stateless group of one workgroup by the size of the output layer, and one column beyond
     *[(config(f"ll_one_wg{v}", dtype="fp32", pred_kind="stateless", h_pred=24, vocab=v, B=300), {}) for v in (63, 64)],
+    # the form of eight wavefronts: row tiles in pairs and one left over, columns that are no multiple of a
+    # batch, workgroups without columns, packed rows, the longest reduction, durations in the last columns
+    *[(config(f"ll_wide{w}_{B}_{v}", vocab=v, durations=d, B=B, pred_layers=n, h_joint=h), dict(n_clusters=4, window=w, joint_kernel=2))
+      for w, B, v, d, n, h in ((4, 16, 1100, (0, 1, 2), 1, 48), (8, 16, 1023, (), 2, 264), (5, 36, 3000, (1, 2), 2, 1024),
+                               (64, 8, 40, (0, 1), 1, 8), (3, 44, 500, (), 1, 1000))],
+    (config("ll_wide_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, vocab=700, B=40), dict(n_clusters=4, joint_kernel=2)),
     # deeper LSTMs on several row tiles
     (config("ll_deep", pred_layers=3, B=40), dict(n_clusters=2)),
 ]
