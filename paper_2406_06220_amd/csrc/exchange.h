@@ -296,12 +296,16 @@ __device__ inline int auto_joint_rows(int C, int NT, int joint_tiles, int hpc)
     return max(1, C / ((NT + tiles_per_item - 1) / tiles_per_item)) * RT;
 }
 // frames per hypothesis when n of them search (window: the caller's, 0 = automatic)
-__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap)
+// (C, NT: see auto_joint_rows)
+__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap, int C, int NT)
 {
     int Kw = window;
     if (Kw <= 0) {
         Kw = auto_rows / n;
-        if (Kw < 3) Kw = 3;   // (2, 4 and 5 measured no better on any benchmark model)
+        // (2, 4 and 5 measured no better on the benchmark models but where a workgroup has so many column tiles
+        // that streaming them is what a pass costs: 8198 outputs, B = 256, four frames 7.60 ms, three 7.80)
+        const int least = C * 12 < NT ? 4 : 3;
+        if (Kw < least) Kw = least;
         // the row tiles this window needs are paid for whole: as many frames as fill them
         const int fill = (n * Kw + RT - 1) / RT * RT / n;
         if (fill > Kw) Kw = fill;

@@ -199,9 +199,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1, WIDE = NW == 8;
     constexpr int THREADS = NW * 64;
     constexpr int TR = label_tiles(NK);                       // column tiles per round of a joint pass
-    constexpr int TQ = DEEP && !WIDE ? TR : 2 * TR;           // ... and of the predictor-side products
+    constexpr int TQ = WIDE ? 6 : DEEP ? TR : 2 * TR;         // ... and of the predictor-side products
     constexpr int QPR = THREADS / RT;                         // threads that share a row of a round, four columns each
-    static_assert(!WIDE || (LAYERS != 1 && TQ * CT == QPR * 4), "eight wavefronts: a round is one pass of the threads");
+    static_assert(!WIDE || (LAYERS != 1 && TQ * CT <= QPR * 4), "eight wavefronts: a round is one pass of the threads");
     constexpr int PLQ = TQ * CT + 4, PLJ = TR * CT + 4;   // floats per row of the partial sums (padded: 16 rows, 64 banks)
     constexpr int KI = (NK * NW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
     extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // ---- Alg. 3 lines 3-4.  Lane g of every wavefront holds hypothesis g of the group
     __syncthreads();
     const bool mine = lane < G;
-    const int gid = mine ? S.gid[lane] : 0;
+    int gid = mine ? S.gid[lane] : 0;   // (read again where it is needed)
     int len = mine ? p.enc_len[gid] : 0, status = 0;
     if (len < 0) { len = 0; status = TDT_HYP_LEN_CLAMPED; }
     if (len > T) { len = T; status = TDT_HYP_LEN_CLAMPED; }
@@ -355,14 +355,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         __syncthreads();
         if (tid == 0) st_co64(jh + (size_t)kRowBufs * C + rank, 1ull);
     }
-    const int owner_mod = mine ? lane % C : -1;
+    const unsigned long long owned = __ballot(mine && lane % C == rank);   // whose scores this workgroup sums
 
     // ---- how a joint pass is cut, per number of searching hypotheses
     const int NT = (O + CT - 1) / CT;
     {
         const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles, hpc);
         for (int n = tid + 1; n <= G; n += THREADS) {
-            const int Kw = joint_window(n, p.window, rows_auto, rows_cap);
+            const int Kw = joint_window(n, p.window, rows_auto, rows_cap, C, NT);
             const int n_tiles = (n * Kw + RT - 1) / RT;
             int n_cg, tpg;
             split_tiles(C, WIDE ? 1 : n_tiles, NT, C, n_cg, tpg);   // (wide: a workgroup takes its columns of all rows)
@@ -434,7 +434,24 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     auto products_of = [&](auto packed_tag, auto count, const AFrag (&a)[NK][PL], const auto &b, float *part) __attribute__((always_inline)) {
         constexpr bool PACKED = decltype(packed_tag)::value;
         constexpr int PLD = sizeof(b) / (NK * sizeof(v4u)) * CT + 4;
-        constexpr int N = decltype(count)::value, NC = WIDE ? 1 : PL == 1 || PACKED ? 2 : 3;   // chains per tile
+        constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED ? 2 : 3;   // chains per tile
+        float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
+        if constexpr (WIDE) {   // (half the registers a lane: two tiles at a time; the other wavefront of the SIMD fills the gaps)
+#pragma unroll
+            for (int t = 0; t < N; t += 2) {
+                f32x4 c[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int pl = PACKED ? 0 : PL - 1; pl >= 0; --pl)
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) c[u] = F::mma(a[s][pl], b[t + u][s], c[u]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) *reinterpret_cast<f32x4 *>(pw + (t + u) * CT) = c[u];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
         f32x4 c[N][NC];
 #pragma unroll
         for (int t = 0; t < N; ++t)
@@ -451,7 +468,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     for (int pl = PL - 1; pl >= 0; --pl) c[t][pl % NC] = F::mma(a[s][pl], b[t][s], c[t][pl % NC]);
                 }
             }
-        float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
 #pragma unroll
         for (int t = 0; t < N; ++t) {
             f32x4 sum = c[t][NC - 1];   // smallest terms first
@@ -462,9 +478,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     };
     auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n, float *part) __attribute__((always_inline)) {
         constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
-        const std::integral_constant<int, TT / 2> half{};
+        constexpr int H2 = WIDE ? (TT + 2) / 4 * 2 : TT / 2;   // (wide: pairs)
+        const std::integral_constant<int, H2> half{};
         const std::integral_constant<int, TT> all{};
-        if (n <= TT / 2) products_of(packed_tag, half, a, b, part);
+        if (n <= H2) products_of(packed_tag, half, a, b, part);
         else products_of(packed_tag, all, a, b, part);
     };
     // ---- activation fragments.  A wavefront multiplies its own stretch of the reduction only, so it
@@ -628,7 +645,15 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         }
     };
 
-    const int p_g = U > 0 ? tid / U : kLabelMaxHyps, p_u = U > 0 ? tid - p_g * U : 0;   // this thread's first cell
+    // this thread's first two cells (hypothesis, unit), and the h-th from base on
+    auto cell_at = [&](int idx) { return U > 0 ? (idx / U) << 16 | (idx - idx / U * U) : kLabelMaxHyps << 16; };
+    const int place0 = cell_at(tid), place1 = cell_at(tid + THREADS);
+    auto place = [&](int base, int h, int &g, int &u) __attribute__((always_inline)) {
+        const int at = base > 0 ? cell_at(base + h * THREADS + tid) : h == 0 ? place0 : place1;
+        g = at >> 16;
+        u = at & 0xffff;
+    };
+    const int nowhere = 0x7ffffff0;   // an offset beyond every exchange buffer: such a store is dropped
     int par = 0;                     // which buffer this label's rows go through
     unsigned jpass = 0;              // joint exchanges so far
     int prev_items = 0, prev_tiles = 0, prev_cg = 1;   // the last pass: work items, row tiles, column groups
@@ -639,29 +664,30 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // puts back what this workgroup wrote in the label iteration before (see the head of the file)
     auto clear_rows = [&]() __attribute__((always_inline)) {
         const int pb = par ^ 1;
+        const int hrow = Hp * (int)sizeof(float), jrow = H * (int)sizeof(float);
         if (U > 0)
 #pragma clang loop unroll(disable)
-            for (int base = 0; base < G * U; base += THREADS) {
-                const int idx = base + tid;
-                int g = p_g, u = p_u;
-                if (base > 0) {
-                    g = idx / U;
-                    u = idx - g * U;
-                }
-                if (g < G && ((act_prev >> g) & 1ull))
+            for (int base = 0; base < G * U; base += 2 * THREADS)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    int g, u;
+                    place(base, h, g, u);
+                    const int off = g < G && ((act_prev >> g) & 1ull) ? (b0 + g) * hrow + (u0 + u) * (int)sizeof(float) : nowhere;
+                    if (base + h * THREADS < G * U)   // uniform
 #pragma clang loop unroll(disable)
-                    for (int l = 0; l < L; ++l)
-                        st_co(hx + (((size_t)pb * L + l) * Bw + b0 + g) * Hp + u0 + u, __uint_as_float(kAbsent));
-            }
+                        for (int l = 0; l < L; ++l)
+                            __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, off, (pb * L + l) * Bw * hrow, 16 /* sc1 */);
+                }
         if (na > 0) {
             const int c = (tid & 15) * 4, nc = min(na * CT, H - qt0 * CT);   // (H is a multiple of 8)
-            const float m = __uint_as_float(kAbsent);
+            const v4u absent = {kAbsent, kAbsent, kAbsent, kAbsent};
 #pragma clang loop unroll(disable)
             for (int c0 = 0; c0 < nc; c0 += 64)
 #pragma clang loop unroll(disable)
                 for (int g = tid >> 4; g < G; g += THREADS / 16)
                     if (((act_prev >> g) & 1ull) && c0 + c < nc)
-                        st_co4(px + ((size_t)pb * Bw + b0 + g) * H + qt0 * CT + c0 + c, make_float4(m, m, m, m));
+                        __builtin_amdgcn_raw_buffer_store_b128(absent, prs, (b0 + g) * jrow + (qt0 * CT + c0 + c) * (int)sizeof(float),
+                                                               pb * Bw * jrow, 16 /* sc1 */);
         }
     };
     // ... and its cells of the joint pass two before the last
@@ -687,7 +713,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     int pend_row = 0;        // the row its label was found in
     float pend_m = 0.0f;     // that row's largest label logit
     auto finish_scores = [&]() {
-        unsigned long long m = __ballot(pend && owner_mod == rank);
+        unsigned long long m = __ballot(pend) & owned;
         while (m != 0ull) {   // uniform
             const int g = __ffsll((long long)m) - 1;
             m &= m - 1ull;
@@ -740,7 +766,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         g_l = __builtin_amdgcn_ds_bpermute(q * 4, slot_of) & 63;
         const int f = __builtin_amdgcn_ds_bpermute(g_l * 4, time) + (r - q * Kw);
         // (every lane has to take part in every permute: what an inactive lane holds reads as zero)
-        const int len_r = __builtin_amdgcn_ds_bpermute(g_l * 4, len), gid_r = __builtin_amdgcn_ds_bpermute(g_l * 4, gid);
+        const int len_r = __builtin_amdgcn_ds_bpermute(g_l * 4, len), gid_r = S.gid[g_l];
         erow_l = gid_r * T + (f < len_r ? f : 0);   // (a frame beyond its utterance's end reads frame 0)
         if constexpr (!LSTM) {
             lab_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last);
@@ -761,8 +787,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 
     // ---- LAYERS == 1: where this thread's results of phase Q go -- four columns of one row per half of
     // a round -- and its cell.  Offsets into the exchange buffers; beyond their end where there is
-    // nothing to write (such stores are dropped), so that the stores need no branch.
-    const int nowhere = 0x7ffffff0;
+    // nothing to write, so that the stores need no branch.
     int q_off[2] = {nowhere, nowhere}, q_unit[2] = {-1, -1}, h_off[2] = {nowhere, nowhere}, c_g[2], c_u[2];
     float4 q_bias[2];
     if constexpr (LAYERS == 1) {
@@ -1108,31 +1133,32 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // ---- P: the first layer's cell update.  W_ih * emb[label] + b is a table row,
             // W_hh * h was formed by this workgroup when h was new.
 #pragma clang loop unroll(disable)
-            for (int base = 0; base < G * U; base += THREADS) {   // uniform
-                const int idx = base + tid;
-                int g = p_g, u = p_u;
-                if (base > 0) {
-                    g = idx / U;
-                    u = idx - g * U;
+            for (int base = 0; base < G * U; base += 2 * THREADS) {   // uniform
+                int g[2], u[2];
+                v4u t4[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {   // (both table rows are requested before either is used)
+                    place(base, h, g[h], u[h]);
+                    const int lab = __builtin_amdgcn_ds_bpermute(min(g[h], kLabelMaxHyps - 1) * 4, last);
+                    t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + u[h]) * 4);
                 }
-                const int lab = __builtin_amdgcn_ds_bpermute((g & 63) * 4, last);
-                if (g < G && ((act >> g) & 1ull)) {
-                    const int o = g * Upad + u;
-                    float cn, hn;
-                    if (CHUNKED && first && ((carried >> g) & 1ull)) {
-                        const size_t src = (size_t)S.gid[g] * Hp + u0 + u;
-                        hn = p.st_h[src];
-                        cn = p.st_c[src];
-                    } else {
-                        const float4 t4 =
-                            *reinterpret_cast<const float4 *>(p.emb_gates + ((size_t)lab * Hp + u0 + u) * 4);
-                        const float4 r4 = rg_l[o];
-                        cell(make_float4(r4.x + t4.x, r4.y + t4.y, r4.z + t4.z, r4.w + t4.w), c_l[o], cn, hn);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (g[h] < G && ((act >> g[h]) & 1ull)) {
+                        const int o = g[h] * Upad + u[h];
+                        float cn, hn;
+                        if (CHUNKED && first && ((carried >> g[h]) & 1ull)) {
+                            const size_t src = (size_t)S.gid[g[h]] * Hp + u0 + u[h];
+                            hn = p.st_h[src];
+                            cn = p.st_c[src];
+                        } else {
+                            const float4 r4 = rg_l[o], x = as_float4(t4[h]);
+                            cell(make_float4(r4.x + x.x, r4.y + x.y, r4.z + x.z, r4.w + x.w), c_l[o], cn, hn);
+                        }
+                        c_l[o] = cn;
+                        if (CHUNKED) h_l[o] = hn;
+                        st_co(hx + ((size_t)par * L * Bw + b0 + g[h]) * Hp + u0 + u[h], present(hn));
                     }
-                    c_l[o] = cn;
-                    if (CHUNKED) h_l[o] = hn;
-                    st_co(hx + ((size_t)par * L * Bw + b0 + g) * Hp + u0 + u, present(hn));
-                }
             }
         }
         if constexpr (LSTM) {
@@ -1234,11 +1260,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 #pragma clang loop unroll(disable)
                         for (int t0 = 0; t0 < n_all; t0 += TQ) {
                             const int n = min(TQ, n_all - t0);
-                            if (kind > 0 || t0 > 0) fetch_round(kind, t0);
                             TR(14);
                             if (qpack) products(packed_rows, a, b, n, part_q);
                             else products(full_rows, a, b, n, part_q);
                             TR(15);
+                            const float4 bias = qbias;
+                            if (t0 + TQ < n_all) fetch_round(kind, t0 + TQ);   // while the results are looked at
+                            else if (kind + 1 < kinds) fetch_round(kind + 1, 0);
                             __syncthreads();
                             TR(16);
                             fresh();
@@ -1259,8 +1287,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                                     const int col = (qt0 + t) * CT + (quad & 3) * 4;
                                     if (col < H)
                                         st_co4(px + ((size_t)par * Bw + b0 + g) * H + col,
-                                               make_float4(present(v.x + qbias.x), present(v.y + qbias.y),
-                                                           present(v.z + qbias.z), present(v.w + qbias.w)));
+                                               make_float4(present(v.x + bias.x), present(v.y + bias.y),
+                                                           present(v.z + bias.z), present(v.w + bias.w)));
                                 } else {   // the four gates of one unit
                                     const int u = (top ? t - na : t) * 4 + (quad & 3);
                                     if (u < U) {
@@ -1645,6 +1673,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 const int frame = time + w;
                 found = found & need;
                 if (rank == 0 && wave == 0 && found) {
+                    const int gid = S.gid[lane];
                     p.out_labels[(size_t)gid * p.u_cap + olen] = k;
                     p.out_frames[(size_t)gid * p.u_cap + olen] = frame;
                 }
@@ -1711,6 +1740,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
         }
         if (rank == 0 && wave == 0 && mine) {
+            gid = S.gid[lane];
             p.st_started[gid] = started;
             // frames of the next chunk already stepped over; a hypothesis stopped at its label
             // capacity gives up the rest of this chunk
@@ -1719,7 +1749,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             p.st_last2[gid] = last2;
         }
     }
-    if (wave == NW - 1 && mine && owner_mod == rank) p.out_score[gid] = score;   // (the wavefront that summed it)
+    gid = mine ? S.gid[lane] : 0;
+    if (wave == NW - 1 && ((owned >> lane) & 1ull)) p.out_score[gid] = score;   // (the wavefront that summed it)
     if (rank == 0 && wave == 0) {
         if (mine) {
             p.out_len[gid] = olen;
@@ -1790,7 +1821,6 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     const int steps = label_steps(w, f.nw);
     if (wide) {
         f.nk = 4;
-        f.tq = 2 * label_tiles(f.nk);
         if (w->dtype == 1 && steps <= f.nk) f.fn = label_wide_fn(lstm, chunked);
         return f;
     }

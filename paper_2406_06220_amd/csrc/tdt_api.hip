@@ -382,13 +382,13 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         if (n_clusters > B && (B > 1 || one_workgroup)) n_clusters = B;
         if (n_clusters < min_clusters) n_clusters = min_clusters;
         if (wide_joint) {
-            // the streaming joint pass: a group's pass lasts as long as its workgroups need for the
-            // output matrix, whatever the number of rows up to a full row tile -- groups of one
-            // row tile (measured at B = 256: 16 groups 45 ms, 8 groups 51 ms, 4 groups 59 ms)
-            const int full = (B + 15) / 16;   // row tiles of 16
-            if (n_clusters < full) n_clusters = full < 16 ? full : 16;
+            // the streaming joint pass: every group streams the whole output matrix in every pass, and a
+            // pass lasts as long as its workgroups need for that, so groups are few while the batch is
+            // small (8198 outputs, T = 300: B = 4, four groups 1.47 ms, eight 1.71; B = 32, eight 2.69,
+            // four 2.93, sixteen 2.99; B = 130, sixteen 5.24, eight 5.67; B = 256, sixteen 7.8, eight 9.1,
+            // thirty-two 8.8)
+            n_clusters = min_stream_clusters * (B < 12 ? 1 : B <= 96 ? 2 : 4);   // (some may stay empty)
             if (n_clusters < min_clusters) n_clusters = min_clusters;
-            if (n_clusters < min_stream_clusters) n_clusters = min_stream_clusters;   // some may stay empty
         }
     }
     if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;
