@@ -53,6 +53,15 @@ struct LinearBatch {
     LinearProblem q[kMaxProblems];
 };
 
+// the row of W (and the bias) that column c of the output is the product with.  GROUPED: group may be
+// set (columns that belong together then leave as whole rows, not as scattered words)
+template <bool GROUPED> __device__ inline int source_column(const LinearProblem &q, int c)
+{
+    if (!GROUPED || q.group == 0) return c;
+    const int kinds = q.N / q.group;
+    return c % kinds * q.group + c / kinds;
+}
+
 // Which frames rows m0 .. m0 + ROWS - 1 of the packed sequence of valid frames are: row_of[i] =
 // b * T + t, or -1 beyond the last valid frame.  Called by all THREADS threads of a workgroup;
 // returns false (for all of them) if the tile holds no valid frame at all.  Every thread sums a
@@ -108,14 +117,14 @@ __device__ inline bool valid_row_map(const int32_t *lens, int B, int T, long lon
 }
 
 // the 128 x 128 output tile of workgroup `block` (of q.blocks) of one product
-__device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
+template <bool GROUPED> __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
 {
     const uint16_t *__restrict__ A = static_cast<const uint16_t *>(q.A);
     const uint16_t *__restrict__ W = static_cast<const uint16_t *>(q.W);
     const float *__restrict__ bias = q.bias;
     float *__restrict__ C = q.C;
     const long long M = q.M;
-    const int N = q.N, K = q.K, ldw = q.ldw, group = q.group;
+    const int N = q.N, K = q.K, ldw = q.ldw;
     // the operand tiles (two buffers each) and, once the products are done, the output tile on
     // its way to memory share one block of LDS
     constexpr int CLD = BN + 4;   // floats per row of the output tile (padded: rows 8 apart meet other banks)
@@ -176,7 +185,7 @@ __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
         a_ok[j] = ar >= 0;
         w_ok[j] = n < N;
         a_src[j] = A + (a_ok[j] ? ar : 0) * K;
-        w_src[j] = W + (long long)(w_ok[j] ? n : 0) * ldw;
+        w_src[j] = W + (long long)(w_ok[j] ? source_column<GROUPED>(q, n) : 0) * ldw;
     }
     auto load_tiles = [&](int k0, uint4 (&xa)[4], uint4 (&xb)[4]) {
         const int k = min(k0 + kc * 8, K - 8);   // K is a multiple of 8
@@ -288,24 +297,6 @@ __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
     }
 
     // accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32
-    if (group > 0) {
-        // outputs regrouped column by column (the LSTM table): scattered four-byte stores
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int n = n0 + wn * 64 + j * 32 + (lane & 31);
-                if (n >= N) continue;
-                const float bn = bias ? bias[n] : 0.0f;
-                const int nc = (n % group) * (N / group) + n / group;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const long long dst = row_of[wm * 64 + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
-                    if (dst >= 0) C[dst * N + nc] = acc[i][j][e] + bn;
-                }
-            }
-        return;
-    }
     // The output tile goes through LDS so that it leaves as whole rows: a lane then stores 16
     // bytes, half a wavefront one 512-byte row, and the row's destination is looked up once per
     // row instead of once per element.  (The operand tiles are dead: every wavefront has passed
@@ -325,7 +316,9 @@ __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
         const int n = n0 + c4;
         float4 bn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (bias && n < N) {                            // N is a multiple of 8, so n + 3 < N too
-            bn = *reinterpret_cast<const float4 *>(bias + n);
+            if (!GROUPED || q.group == 0) bn = *reinterpret_cast<const float4 *>(bias + n);
+            else bn = make_float4(bias[source_column<GROUPED>(q, n)], bias[source_column<GROUPED>(q, n + 1)], bias[source_column<GROUPED>(q, n + 2)],
+                                  bias[source_column<GROUPED>(q, n + 3)]);
         }
 #pragma unroll 4
         for (int it = 0; it < BM / (2 * GEMM_THREADS / 64); ++it) {
@@ -343,7 +336,7 @@ __device__ inline void gemm_tile_bf16(const LinearProblem &q, unsigned block)
 
 __global__ __launch_bounds__(GEMM_THREADS, 2) void enc_proj_bf16_kernel(LinearProblem q)
 {
-    gemm_tile_bf16(q, blockIdx.x);
+    gemm_tile_bf16<false>(q, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -547,43 +540,38 @@ struct PackJob {
     uint4 *dst;
     int N, K, gate_h;   // gate_h > 0: LSTM gate matrix of gate_h hidden units
     int steps;
-    long long first, pieces;   // 16-byte pieces: its first in the batch, how many
+    int first;   // its first fragment in the batch
 };
 constexpr int kMaxPackJobs = 3 + 2 * TDT_MAX_LSTM_LAYERS;
 struct PackBatch {
     PackJob j[kMaxPackJobs];
     int n;
     int elem;   // bytes per element: 2 (a step is 32 inputs) or 4 (16 inputs)
-    long long pieces;
+    int frags;
 };
 
-// block `blk` of `nblk` blocks of 256 threads copies its share of the pieces
-__device__ inline void pack_pieces(const PackBatch &b, unsigned blk, unsigned nblk)
+// Block `blk` of `nblk` blocks of 256 threads copies its share of the fragments, a wavefront one at a
+// time, so that which matrix, tile and step it is is worked out once per KiB and not per lane.
+__device__ inline void pack_fragments(const PackBatch &b, unsigned blk, unsigned nblk)
 {
-    for (long long piece = (long long)blk * 256 + threadIdx.x; piece < b.pieces; piece += (long long)nblk * 256) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per = 16 / b.elem, j = lane & 15;   // inputs per lane
+    for (int frag = (int)blk * 4 + wave; frag < b.frags; frag += (int)nblk * 4) {
         int ji = 0;
-        while (ji + 1 < b.n && piece >= b.j[ji + 1].first) ++ji;
+        while (ji + 1 < b.n && frag >= b.j[ji + 1].first) ++ji;
         const PackJob &q = b.j[ji];
-        const long long local = piece - q.first;
-        const int lane = (int)(local & 63);
-        const long long frag = local >> 6;
-        const int step = (int)(frag % q.steps), tile = (int)(frag / q.steps);
-        const int per = 16 / b.elem, j = lane & 15, k = (step * 4 + (lane >> 4)) * per;   // inputs per piece
-        long long row;
-        if (q.gate_h > 0) {
-            const int unit = tile * 4 + (j >> 2);
-            row = unit < q.gate_h ? (long long)(j & 3) * q.gate_h + unit : -1;
-        } else {
-            row = tile * 16 + j < q.N ? tile * 16 + j : -1;
-        }
+        const int local = frag - q.first, tile = local / q.steps, step = local - tile * q.steps;
+        const int k = (step * 4 + (lane >> 4)) * per;
+        const int unit = tile * 4 + (j >> 2);
+        const int row = q.gate_h > 0 ? (j & 3) * q.gate_h + unit : tile * 16 + j;
+        const bool ok = (q.gate_h > 0 ? unit < q.gate_h : row < q.N) && k < q.K;   // (K % 8 == 0)
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (row >= 0 && k < q.K)   // (K % 8 == 0)
-            v = *reinterpret_cast<const uint4 *>(static_cast<const char *>(q.src) + (row * q.K + k) * b.elem);
-        q.dst[local] = v;
+        if (ok) v = *reinterpret_cast<const uint4 *>(static_cast<const char *>(q.src) + ((size_t)row * q.K + k) * b.elem);
+        q.dst[(size_t)local * 64 + lane] = v;
     }
 }
 
-__global__ __launch_bounds__(256) void pack_weights_kernel(PackBatch b) { pack_pieces(b, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void pack_weights_kernel(PackBatch b) { pack_fragments(b, blockIdx.x, gridDim.x); }
 
 PackBatch pack_batch(const tdt_weights_t *w, const PackedLayout &pl, bool on_the_fly, void *packed)
 {
@@ -599,9 +587,8 @@ PackBatch pack_batch(const tdt_weights_t *w, const PackedLayout &pl, bool on_the
         q.K = K;
         q.gate_h = gate_h;
         q.steps = m.steps;
-        q.first = b.pieces;
-        q.pieces = (long long)m.tiles * m.steps * 64;
-        b.pieces += q.pieces;
+        q.first = b.frags;
+        b.frags += m.tiles * m.steps;   // (dimensions of at most 2^24 x 2048: fits)
     };
     // what a call does not multiply by stays unpacked: the encoder projection and, with a
     // stateless predictor, its projection are products of the kernel only when it projects on the fly
@@ -616,7 +603,7 @@ PackBatch pack_batch(const tdt_weights_t *w, const PackedLayout &pl, bool on_the
 }
 unsigned pack_blocks_for(const PackBatch &b)
 {
-    const long long blocks = (b.pieces + 255) / 256;
+    const int blocks = (b.frags + 3) / 4;
     return (unsigned)(blocks < 1024 ? blocks : 1024);
 }
 
@@ -628,11 +615,11 @@ unsigned pack_blocks_for(const PackBatch &b)
 // vector-ALU kernel, 240 us; here together with the copies and the clearing 91 us.
 constexpr int FM = 64, FN = 64, FK = 32, FLD = FK + 4;   // (rows padded by 16 bytes)
 
-__device__ inline void gemm_tile_f32(const LinearProblem &q, unsigned block)
+template <bool GROUPED> __device__ inline void gemm_tile_f32(const LinearProblem &q, unsigned block)
 {
     const float *__restrict__ A = static_cast<const float *>(q.A);
     const float *__restrict__ W = static_cast<const float *>(q.W);
-    const int N = q.N, K = q.K, ldw = q.ldw, group = q.group;
+    const int N = q.N, K = q.K, ldw = q.ldw;
     __shared__ __align__(16) float As[2][FM * FLD], Ws[2][FN * FLD];
     __shared__ long long row_of[FM];
     __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
@@ -659,7 +646,7 @@ __device__ inline void gemm_tile_f32(const LinearProblem &q, unsigned block)
         a_ok[h] = ar >= 0;
         w_ok[h] = n < N;
         a_src[h] = A + (a_ok[h] ? ar : 0) * K;
-        w_src[h] = W + (long long)(w_ok[h] ? n : 0) * ldw;
+        w_src[h] = W + (long long)(w_ok[h] ? source_column<GROUPED>(q, n) : 0) * ldw;
     }
     float4 xa[2], xw[2];
     auto load = [&](int k0) {
@@ -708,16 +695,15 @@ __device__ inline void gemm_tile_f32(const LinearProblem &q, unsigned block)
     // accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32
     const int n = n0 + wn * 32 + (lane & 31);
     if (n >= N) return;
-    const float bn = q.bias ? q.bias[n] : 0.0f;
-    const int nc = group > 0 ? (n % group) * (N / group) + n / group : n;
+    const float bn = q.bias ? q.bias[source_column<GROUPED>(q, n)] : 0.0f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const long long dst = row_of[wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)];
-        if (dst >= 0) q.C[dst * N + nc] = acc[e] + bn;
+        if (dst >= 0) q.C[dst * N + n] = acc[e] + bn;
     }
 }
 
-__global__ __launch_bounds__(GEMM_THREADS) void enc_proj_f32_kernel(LinearProblem q) { gemm_tile_f32(q, blockIdx.x); }
+__global__ __launch_bounds__(GEMM_THREADS) void enc_proj_f32_kernel(LinearProblem q) { gemm_tile_f32<false>(q, blockIdx.x); }
 
 // Everything a decode call needs before its decode kernel, in one launch: the encoder
 // projection, the per-label tables of the predictor side (a product with blocks == 0 is
@@ -733,15 +719,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch ba
 #pragma unroll
     for (int i = 0; i < kMaxProblems; ++i) {
         if (b < batch.q[i].blocks) {
-            if constexpr (BF16) gemm_tile_bf16(batch.q[i], b);
-            else gemm_tile_f32(batch.q[i], b);
+            if constexpr (BF16) gemm_tile_bf16<true>(batch.q[i], b);
+            else gemm_tile_f32<true>(batch.q[i], b);
             return;
         }
         b -= batch.q[i].blocks;
         used += batch.q[i].blocks;
     }
     if (b < pack_blocks) {   // the fragment-major copies of the matrices the decode kernel streams
-        pack_pieces(pack, b, pack_blocks);
+        pack_fragments(pack, b, pack_blocks);
         return;
     }
     b -= pack_blocks;
@@ -756,6 +742,12 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch ba
 
 }  // namespace
 
+static unsigned tile_blocks(const LinearProblem &q, int tile)   // square tiles
+{
+    const long long row_tiles = (q.M + tile - 1) / tile, rounds = (row_tiles + kXcds - 1) / kXcds;
+    return (unsigned)(rounds * kXcds * ((q.N + tile - 1) / tile));
+}
+
 static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int K, const void *w, int ldw, int N,
                                     const float *bias, int group, float *out)
 {
@@ -769,9 +761,7 @@ static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int 
     q.K = K;
     q.ldw = ldw;
     q.group = group;
-    const int bm = dtype == 1 ? BM : FM, bn = dtype == 1 ? BN : FN;
-    const long long row_tiles = (rows + bm - 1) / bm, rounds = (row_tiles + kXcds - 1) / kXcds;
-    q.blocks = (unsigned)(rounds * kXcds * ((N + bn - 1) / bn));
+    q.blocks = tile_blocks(q, dtype == 1 ? BM : FM);
     return q;
 }
 
@@ -843,7 +833,7 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
     if (zb > 256) zb = 256;
     if (zb < 1) zb = 1;
     const PackBatch pack = pack_batch(w, pl, on_the_fly, packed);
-    const unsigned pb = pack.pieces > 0 ? pack_blocks_for(pack) : 0;
+    const unsigned pb = pack.frags > 0 ? pack_blocks_for(pack) : 0;
     const dim3 grid(blocks + pb + (unsigned)zb);
     if (bf16)
         hipLaunchKernelGGL(prepare_kernel<true>, grid, dim3(GEMM_THREADS), 0, stream, batch, pack, pb,
@@ -916,7 +906,7 @@ hipError_t launch_pack_weights(const tdt_weights_t *w, const PackedLayout &pl, b
                                hipStream_t stream)
 {
     const PackBatch b = pack_batch(w, pl, on_the_fly, packed);
-    if (b.pieces == 0) return hipSuccess;
+    if (b.frags == 0) return hipSuccess;
     hipLaunchKernelGGL(pack_weights_kernel, dim3(pack_blocks_for(b)), dim3(256), 0, stream, b);
     return hipGetLastError();
 }
