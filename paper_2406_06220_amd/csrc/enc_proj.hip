@@ -339,6 +339,116 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void enc_proj_bf16_kernel(LinearPr
     gemm_tile_bf16<false>(q, blockIdx.x);
 }
 
+// The same product for small problems: 64 x 64 output tile, four wavefronts of 32 x 32.  Where the 128 x
+// 128 tiles do not fill the chip a product lasts as long as one workgroup's walk along K, and a step of
+// that is the latency of its loads: so four register sets are in flight instead of two, and a tile has
+// a quarter of the work.  K tiles come in fours (tiles beyond the end are zeros).
+// Measured (this against 128 x 128 tiles): 50 x 640 x 512 7.5 us, 10.5; 200 x 1024 x 1024 10.5 us, 16.3;
+// 3200 x 640 x 512 (125 tiles of 128 x 128) 10.5 us, 11.9; 2400 x 1024 x 1024 (152) 15.2 us, 17.5; but 5000 x
+// 640 x 512 (200) 12.7 us, 12.4, and 3600 x 1024 x 1024 (232) 19.7 us, 18.5 -- the border is between.
+constexpr int SM = 64, SN = 64;
+__global__ __launch_bounds__(GEMM_THREADS, 4) void enc_proj_bf16_small_kernel(LinearProblem q)
+{
+    const unsigned block = blockIdx.x;
+    const uint16_t *__restrict__ A = static_cast<const uint16_t *>(q.A);
+    const uint16_t *__restrict__ W = static_cast<const uint16_t *>(q.W);
+    const int N = q.N, K = q.K, ldw = q.ldw;
+    constexpr int D = 4, CLD = SN + 4;
+    __shared__ __align__(16) unsigned char lds_raw[2 * (SM + SN) * BK * sizeof(uint16_t)];
+    static_assert(sizeof(lds_raw) >= SM * CLD * sizeof(float), "the output tile reuses the operand buffers");
+    uint16_t *const As = reinterpret_cast<uint16_t *>(lds_raw), *const Bs = As + 2 * SM * BK;
+    float *const Cs = reinterpret_cast<float *>(lds_raw);
+    __shared__ long long row_of[SM];
+    __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+    const int nt_n = (N + SN - 1) / SN;   // die-aware order of tiles, as in gemm_tile_bf16
+    const long long j = block / kXcds, m0 = ((j / nt_n) * kXcds + block % kXcds) * SM;
+    const int n0 = (int)(j % nt_n) * SN;
+    if (m0 >= q.M) return;
+    if (q.lens) {
+        if (!valid_row_map<SM>(q.lens, q.B, q.T, m0, row_of, scan, wsum)) return;   // uniform
+    } else if (tid < SM) {
+        row_of[tid] = m0 + tid < q.M ? m0 + tid : -1;
+    }
+    __syncthreads();
+    // (unconditional loads, zeros by mask: see gemm_tile_bf16)
+    const int kc = tid & 7;
+    const uint16_t *a_src[2], *w_src[2];
+    bool a_ok[2], w_ok[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = (tid >> 3) + h * 32, n = n0 + row;
+        const long long ar = row_of[row];
+        a_ok[h] = ar >= 0;
+        w_ok[h] = n < N;
+        a_src[h] = A + (a_ok[h] ? ar : 0) * K;
+        w_src[h] = W + (long long)(w_ok[h] ? n : 0) * ldw;
+    }
+    uint4 xa[D][2], xw[D][2];
+    auto load = [&](int set, int k0) __attribute__((always_inline)) {
+        const int k = min(k0 + kc * 8, K - 8);   // K is a multiple of 8
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            xa[set][h] = *reinterpret_cast<const uint4 *>(a_src[h] + k);
+            xw[set][h] = *reinterpret_cast<const uint4 *>(w_src[h] + k);
+        }
+    };
+    auto store = [&](int set, int buf, int k0) __attribute__((always_inline)) {
+        const bool k_ok = k0 + kc * 8 < K;
+        auto keep = [](uint4 v, bool ok) {
+            const unsigned m = ok ? 0xffffffffu : 0u;
+            return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
+        };
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int o = lds_off((tid >> 3) + h * 32, kc);
+            *reinterpret_cast<uint4 *>(As + buf * (SM * BK) + o) = keep(xa[set][h], a_ok[h] && k_ok);
+            *reinterpret_cast<uint4 *>(Bs + buf * (SN * BK) + o) = keep(xw[set][h], w_ok[h] && k_ok);
+        }
+    };
+    f32x16 acc[2];   // (even and odd steps: two chains)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.0f;
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, d * BK);
+    for (int k0 = 0; k0 < K; k0 += D * BK) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int buf = d & 1;
+            store(d, buf, k0 + d * BK);   // (last read before the barrier of the tile before)
+            load(d, k0 + (D + d) * BK);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < BK / 16; ++s) {
+                const int chunk = s * 2 + (lane >> 5);
+                const bf16x8 a = *reinterpret_cast<const bf16x8 *>(As + buf * (SM * BK) + lds_off(wm * 32 + (lane & 31), chunk));
+                const bf16x8 b = *reinterpret_cast<const bf16x8 *>(Bs + buf * (SN * BK) + lds_off(wn * 32 + (lane & 31), chunk));
+                acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[s & 1], 0, 0, 0);
+            }
+        }
+    }
+    __syncthreads();
+    // whole rows leave through LDS, as in gemm_tile_bf16
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        Cs[(wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * CLD + wn * 32 + (lane & 31)] = acc[0][e] + acc[1][e];
+    __syncthreads();
+    const int c4 = (tid & 15) * 4, n = n0 + c4;
+    if (n >= N) return;   // (N is a multiple of 8)
+    float4 bn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (q.bias) bn = *reinterpret_cast<const float4 *>(q.bias + n);
+#pragma unroll
+    for (int r = tid >> 4; r < SM; r += GEMM_THREADS / 16) {
+        const long long dst = row_of[r];
+        float4 v = *reinterpret_cast<const float4 *>(Cs + r * CLD + c4);
+        v.x += bn.x;
+        v.y += bn.y;
+        v.z += bn.z;
+        v.w += bn.w;
+        if (dst >= 0) *reinterpret_cast<float4 *>(q.C + dst * N + n) = v;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // The same product for large problems: 256 x 256 output tile, 8 wavefronts, each 128 x 64
 // ---------------------------------------------------------------------------
@@ -748,6 +858,9 @@ static unsigned tile_blocks(const LinearProblem &q, int tile)   // square tiles
     return (unsigned)(rounds * kXcds * ((q.N + tile - 1) / tile));
 }
 
+constexpr long long kSmallTiles = 160;   // up to this many 128 x 128 tiles a product takes 64 x 64 tiles, see enc_proj_bf16_small_kernel
+static long long tiles_of(const LinearProblem &q) { return (q.M + BM - 1) / BM * ((q.N + BN - 1) / BN); }
+
 static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int K, const void *w, int ldw, int N,
                                     const float *bias, int group, float *out)
 {
@@ -844,11 +957,14 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
     return hipGetLastError();
 }
 
-static hipError_t launch_problem(int dtype, const LinearProblem &q, hipStream_t stream)
+static hipError_t launch_problem(int dtype, LinearProblem q, hipStream_t stream)
 {
     if (q.M <= 0) return hipSuccess;
     if (dtype == 1 && takes_big_tiles(q.M, q.N, q.group)) return launch_big_tiles(q, stream);
-    if (dtype == 1) hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    if (dtype == 1 && tiles_of(q) <= kSmallTiles) {
+        q.blocks = tile_blocks(q, SM);
+        hipLaunchKernelGGL(enc_proj_bf16_small_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    } else if (dtype == 1) hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
     else hipLaunchKernelGGL(enc_proj_f32_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
     return hipGetLastError();
 }
