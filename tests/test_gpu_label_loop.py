@@ -4,10 +4,11 @@ output layers at the borders of a round of column tiles, groups of one workgroup
 than a wavefront has lanes, and what falls back to the general kernel -- against the oracle."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 
 from paper_2406_06220_amd import synth
-from test_gpu_parity import check, gpu  # noqa: F401  (gpu: the fixture)
+from test_gpu_parity import check, gpu, run_gpu  # noqa: F401  (gpu: the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +80,62 @@ def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
     for ncl in (0, 1):
         check_chunks(oracle_lib, gpu, cfg, "random", 4, n_clusters=ncl)
     check_chunks(oracle_lib, gpu, cfg, "single", 0)
+
+
+# ------------------------------------------------------------------ values that are no numbers
+KINDS = {
+    "lstm": (dict(B=9), {}),
+    "lstm_groups": (dict(B=33, h_pred=96), dict(n_clusters=1)),
+    "lstm_packed": (dict(B=3), dict(n_clusters=1)),
+    "deep": (dict(B=9, pred_layers=3), {}),
+    "fp32": (dict(B=9, dtype="fp32"), {}),
+    "wide": (dict(B=20, vocab=600, durations=(0, 1, 2)), dict(n_clusters=4, joint_kernel=2)),
+    "stateless": (dict(B=9, pred_kind="stateless", pred_layers=2, h_pred=48), {}),
+    "stateless_fp32": (dict(B=9, dtype="fp32", pred_kind="stateless", h_pred=24), {}),
+}
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_values_that_are_no_numbers(oracle_lib, gpu, kind):   # noqa: F811
+    """NaN in valid frames and in what one label puts into the predictor (a NaN gate stays in the state:
+    from that label on the joint network sees the encoder alone), masks of minus infinity and of the
+    type's lowest value in the output bias: the oracle's hypotheses.  Infinite frames, whose logits are
+    not all numbers: what the general kernel gives."""
+    kw, opts = KINDS[kind]
+    cfg = config(f"ll_nan_{kind}", **kw)
+    w = synth.generate_model(cfg)
+    enc, ln = synth.generate_inputs(cfg)
+    ln[0] = cfg.T
+    rng = np.random.default_rng(5)
+    # the labels that are emitted most, in a clean run: poisoned, the decode has to meet them
+    u_cap = cfg.T * cfg.max_symbols
+    clean = run_gpu(gpu, cfg, w, enc, ln, u_cap, **opts)
+    seen = np.concatenate([clean["labels"][b, :clean["len"][b]] for b in range(cfg.B)])
+    labels = np.argsort(np.bincount(seen, minlength=cfg.vocab))[::-1][:3]
+    wn = {k: v.copy() for k, v in w.items()}
+    emb = wn["emb"].reshape(-1, cfg.vocab + 1, cfg.emb_dim)   # (stateless: one table a context position)
+    for k in labels:
+        emb[:, k, int(rng.integers(cfg.emb_dim))] = np.nan
+    en = enc.copy()
+    for b in range(0, cfg.B, 2):
+        if ln[b] > 0:
+            en[b, int(rng.integers(ln[b])), int(rng.integers(cfg.d_enc))] = np.nan
+            en[b, int(rng.integers(ln[b]))] = np.nan
+    check(oracle_lib, gpu, cfg, wn, en, ln, **opts)
+    wm = {k: v.copy() for k, v in w.items()}
+    masked = rng.permutation(cfg.vocab)[:cfg.vocab // 2]
+    wm["b_out"][masked[::2]] = -np.inf
+    wm["b_out"][masked[1::2]] = np.finfo(np.float32).min
+    out, _ = check(oracle_lib, gpu, cfg, wm, enc, ln, **opts)
+    for b in range(cfg.B):
+        assert not np.isin(out["labels"][b, :out["len"][b]], masked).any()
+    ei = enc.copy()
+    for b in range(1, cfg.B, 2):
+        if ln[b] > 0:
+            ei[b, int(rng.integers(ln[b])), :2] = np.inf, -np.inf
+    a = run_gpu(gpu, cfg, w, ei, ln, u_cap, **opts)
+    g = run_gpu(gpu, cfg, w, ei, ln, u_cap, algorithm=1)   # (frame-looping: the general kernel)
+    assert (a["len"] == g["len"]).all()
+    for b in range(cfg.B):
+        n = a["len"][b]
+        assert (a["labels"][b, :n] == g["labels"][b, :n]).all() and (a["frames"][b, :n] == g["frames"][b, :n]).all()
