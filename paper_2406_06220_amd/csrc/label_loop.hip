@@ -48,6 +48,7 @@
 #include "tdt_internal.h"
 #include "decode_state.h"
 #include "exchange.h"
+#include "split.h"
 #include "tile_gemm.h"
 
 #if TDT_TRACE
@@ -286,18 +287,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
 
     // ---- this workgroup's column tiles of the predictor side, and with its W_hh tiles a stretch of hidden
-    // units (of every layer).  One round of one layer: a stretch of [W_pred | W_hh] tiles.  Else its
-    // share of each: a W_hh tile stands for three products of a deeper LSTM (its input, its recurrent
-    // product in every layer), a W_pred tile for one.
+    // units (see pred_share)
     const int nst_h = (Hp + KS - 1) / KS, nst_j = (H + KS - 1) / KS;   // fragments per tile
     const int NT_A = (H + CT - 1) / CT, NT_B = LSTM ? (Hp + 3) / 4 : 0;
-    const int QT = LSTM ? (NT_A + NT_B + C - 1) / C : 0;
-    const int qt0 = DEEP ? rank * NT_A / C : rank * QT;                // its first W_pred tile, if it has any
-    const int na = DEEP ? (rank + 1) * NT_A / C - qt0 : LSTM ? max(0, min(NT_A - qt0, QT)) : 0;   // tiles of W_pred ...
-    const int r0 = DEEP ? rank * NT_B / C : max(qt0 - NT_A, 0);        // first W_hh tile
-    const int nr = DEEP ? (rank + 1) * NT_B / C - r0 : LSTM ? max(0, min(NT_A + NT_B - qt0, QT) - na) : 0;   // ... of W_hh
-    const int nq = na + nr;
-    const int u0 = r0 * 4, U = nr > 0 ? min(nr * 4, Hp - u0) : 0;      // hidden units owned
+    const PredShare share = pred_share(DEEP, NT_A, NT_B, Hp, C, rank);
+    const int qt0 = share.qt0, na = share.na, r0 = share.r0, nr = share.nr, nq = na + nr;
+    const int u0 = share.u0, U = share.U, QT = (NT_A + NT_B + C - 1) / C;
     const int Upad = (DEEP ? (NT_B + C - 1) / C : QT) * 4;
     float4 *const rg_l = reinterpret_cast<float4 *>(part_j + NW * RT * (WIDE ? kWidePart : PLJ));               // [L][hpc][Upad]
     float *const c_l = reinterpret_cast<float *>(rg_l + (size_t)(LSTM ? L * hpc * Upad : 0));
