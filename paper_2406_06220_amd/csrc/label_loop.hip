@@ -396,6 +396,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         if (stop && lane == 0) S.aborted = 1;
         return stop != 0;
     };
+    // Reads rows until no word of them is absent: read() requests them, leaves them where its caller wants
+    // them and returns the largest word.  The intrinsic behind ldx4 does not say that what it reads changes;
+    // the statement in front of it does, so that every turn issues the loads again.
+    auto until_there = [&](auto read) __attribute__((always_inline)) {
+        unsigned spins = 0;
+        long long since = 0;
+#pragma clang loop unroll(disable)
+        for (;;) {
+            asm volatile("" ::: "memory");
+            const unsigned mx = read();
+            if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
+        }
+    };
     // waits until the words of every lane are there (zero: not yet) and returns them
     auto wait_word = [&](const unsigned long long *q) __attribute__((always_inline)) {
         unsigned spins = 0;
@@ -585,22 +598,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // branches, and nobody looks at its results).
     auto stage_h = [&](AFrag (&a)[NK][PL], int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
         const int any = __ffsll((long long)in_tile) - 1;
-        unsigned spins = 0;
-        long long since = 0;
         if (qpack) {   // a wavefront takes a row
             if constexpr (PL == 3) {
                 v4u v[KI];
                 const bool row = wave < kPackRows;   // uniform
                 const int off = (row0 + (row && ((in_tile >> wave) & 1ull) ? wave : any)) * Hp * (int)sizeof(float);
-#pragma clang loop unroll(disable)
-                for (;;) {
+                until_there([&]() __attribute__((always_inline)) {
                     unsigned mx = 0;
 #pragma unroll
                     for (int kk = 0; kk < KI; ++kk) v[kk] = ldx4(hrs, hoff(kk), off);
 #pragma unroll
                     for (int kk = 0; kk < KI; ++kk) mx = max(mx, umax4(v[kk]));
-                    if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
-                }
+                    return mx;
+                });
                 TR(11);
                 if (row)
 #pragma unroll
@@ -618,8 +628,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             const int row = (row0 + tq * RT + g) * Hp * (int)sizeof(float);
 #pragma unroll
             for (int s = 0; s < NK; ++s) off[s] = row + part_of(s, hs0, Hp);
-#pragma clang loop unroll(disable)
-            for (;;) {
+            until_there([&]() __attribute__((always_inline)) {
                 unsigned mx = 0;
 #pragma unroll
                 for (int s = 0; s < NK; ++s)
@@ -629,8 +638,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int s = 0; s < NK; ++s)
 #pragma unroll
                     for (int l = 0; l < NL; ++l) mx = max(mx, umax4(v[s][l]));
-                if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
-            }
+                return mx;
+            });
             TR(11);
 #pragma unroll
             for (int s = 0; s < NK; ++s) {
@@ -862,10 +871,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 #pragma unroll
             for (int t = 0; t < TB; ++t) fetch_tile(b[t], t);
             if constexpr (LSTM) {
-                unsigned spins = 0;
-                long long since = 0;
-#pragma clang loop unroll(disable)
-                for (;;) {
+                until_there([&]() __attribute__((always_inline)) {
                     unsigned mx = 0;
 #pragma unroll
                     for (int r = 0; r < R; ++r)
@@ -879,8 +885,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         for (int s = 0; s < NK; ++s)
 #pragma unroll
                             for (int l = 0; l < NL; ++l) mx = max(mx, umax4(q[r][s][l]));
-                    if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
-                }
+                    return mx;
+                });
                 lap(kTkBar);
                 TR(41);
             } else if (p.pred_layers == 2) {
@@ -1385,10 +1391,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     brs, (tile0 * CT + (lane & 15) * 4) * (int)sizeof(float), 0, 0);
                 TR(20);
                 if constexpr (LSTM) {
-                    unsigned spins = 0;
-                    long long since = 0;
-#pragma clang loop unroll(disable)
-                    for (;;) {
+                    until_there([&]() __attribute__((always_inline)) {
                         unsigned mx = 0;
 #pragma unroll
                         for (int s = 0; s < NK; ++s)
@@ -1398,8 +1401,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         for (int s = 0; s < NK; ++s)
 #pragma unroll
                             for (int l = 0; l < NL; ++l) mx = max(mx, umax4(p4[s][l]));
-                        if (__ballot(mx == kAbsent) == 0ull || give_up(spins, since)) break;
-                    }
+                        return mx;
+                    });
                     lap(kTkBar);
                 } else if (p.pred_layers == 2) {
 #pragma unroll

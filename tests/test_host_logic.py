@@ -86,3 +86,18 @@ def test_chunk_helpers_cut_and_stitch():
     s = chunks.stitch(parts, b, 4)
     assert s["len"][0] == 3 and s["labels"][0, :3].tolist() == [4, 9, 7]
     assert s["frames"][0, :3].tolist() == [0, 2, 4] and s["score"][0] == -1.5 and s["status"][0] == 1
+
+
+def test_rows_written_by_others_are_only_read_in_the_loop_that_rereads():
+    """csrc/label_loop.hip reads what other workgroups write through ldx4, an intrinsic the compiler may
+    take to read the same value every time: only where until_there(), whose turns begin with a compiler
+    barrier, asks for it again."""
+    import re
+    src = open(os.path.join(ROOT, "paper_2406_06220_amd", "csrc", "label_loop.hip")).read()
+    helper = re.search(r"auto until_there = .*?\n    };", src, re.S).group(0)
+    loop = helper[helper.index("for (;;)"):]
+    assert loop.index('asm volatile("" ::: "memory")') < loop.index("read()")
+    body = src[src.index("__global__"):]
+    calls = [m.start() for m in re.finditer(r"\bldx4\(", body)]
+    inside = [m.span() for m in re.finditer(r"until_there\(\[&\]\(\).*?\n\s*}\);", body, re.S)]
+    assert calls and all(any(a < c < b for a, b in inside) for c in calls)
