@@ -93,6 +93,7 @@ template <> struct Frags<float> {
 };
 
 __device__ inline float present(float v) { return __float_as_uint(v) == kAbsent ? __uint_as_float(0x7fc00000u) : v; }
+__device__ inline void st_co32(int *p, int v) { __hip_atomic_store((TDT_GLOBAL int *)p, v, __ATOMIC_RELAXED, TDT_AGENT); }
 __device__ inline void st_co4(float *p, float4 v)   // two 8-byte stores of agent scope
 {
     unsigned long long *q = reinterpret_cast<unsigned long long *>(p);
@@ -1751,10 +1752,23 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     }
     gid = mine ? S.gid[lane] : 0;
     if (wave == NW - 1 && ((owned >> lane) & 1ull)) p.out_score[gid] = score;   // (the wavefront that summed it)
+    // Rank 0 writes labels, lengths and status, but a score is summed elsewhere, and that workgroup may have
+    // given up where rank 0 went on to the end.  It adds its mark behind the call's abort flag; rank 0 looks
+    // at the flag once more behind its own stores: either it sees the flag or the mark comes later.
+    if (rank != 0 && wave == NW - 1 && uni(S.aborted) != 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if ((owned >> lane) & 1ull) atomicOr(&p.out_status[gid], TDT_HYP_ABORTED);
+        if (lane == 0 && p.out_stats) atomicAdd((unsigned long long *)&p.out_stats[TDT_STAT_ABORT], 1ull);
+    }
     if (rank == 0 && wave == 0) {
         if (mine) {
             p.out_len[gid] = olen;
-            p.out_status[gid] = status | (ok ? 0 : TDT_HYP_ABORTED);
+            st_co32(&p.out_status[gid], status | (ok ? 0 : TDT_HYP_ABORTED));
+        }
+        if (C > 1) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (__hip_atomic_load(p.abort_flag, __ATOMIC_RELAXED, TDT_AGENT) && mine)
+                atomicOr(&p.out_status[gid], TDT_HYP_ABORTED);
         }
         if (tid == 0 && p.out_stats) {
             auto add = [&](int slot, long long v) {

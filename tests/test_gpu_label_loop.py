@@ -139,3 +139,35 @@ def test_values_that_are_no_numbers(oracle_lib, gpu, kind):   # noqa: F811
     for b in range(cfg.B):
         n = a["len"][b]
         assert (a["labels"][b, :n] == g["labels"][b, :n]).all() and (a["frames"][b, :n] == g["frames"][b, :n]).all()
+
+
+# ------------------------------------------------------------------ waits that run out
+@pytest.mark.parametrize("kind,blank_bias,T", [("stateless", 1e4, 15), ("stateless", 1.0, 40), ("lstm", 1.0, 20)])
+def test_a_wait_of_the_label_loop_that_runs_out(oracle_lib, gpu, kind, blank_bias, T):   # noqa: F811
+    """15 groups of 17 workgroups and 17 hypotheses, 16 row tiles a pass and an output layer of 1024 column
+    tiles: the last workgroup has no work item and waits for the others far longer than the microsecond
+    it is given.  Every workgroup leaves the kernel, every hypothesis says so -- also where nothing is
+    left to do for the others, who never wait in vain (the first case: one pass, no labels) -- and
+    the next call on the same workspace is sound."""
+    import parity
+    import torch
+    kw = dict(pred_kind="stateless", pred_layers=1, h_pred=24) if kind == "stateless" else {}
+    cfg = config(f"ll_wait_{kind}_{T}", vocab=16383, B=255, T=T, len_lo=T, len_hi=T, max_symbols=2, **kw)
+    w = synth.generate_model(cfg, blank_bias)
+    enc, ln = synth.generate_inputs(cfg)
+    u_cap = cfg.T * cfg.max_symbols
+    model = gpu.DeviceModel(cfg, w)
+    dec = gpu.Decoder(model, cfg.B, cfg.T, u_cap, window=15, n_clusters=15, joint_kernel=1)
+    enc_d, len_d = model.upload_enc(enc), torch.from_numpy(ln).to(model.device)
+    dec.options.wait_timeout_us = 1
+    parity.announce(f"waits bounded to 1 us, cfg={cfg.name} blank_bias={blank_bias}")
+    dec(enc_d, len_d)
+    out = dec.results()
+    assert out["stats"]["abort"] >= 1 and (out["status"] & gpu.TDT_HYP_ABORTED).all()
+    dec.options.wait_timeout_us = 0
+    parity.announce("  the next call on the same workspace")
+    dec(enc_d, len_d)
+    out = dec.results()
+    assert out["stats"]["abort"] == 0 and not (out["status"] & gpu.TDT_HYP_ABORTED).any()
+    res = parity.compare(oracle_lib, oracle_lib.OracleModel(cfg, w), cfg, enc, ln, out, u_cap, rows=range(0, cfg.B, 17))
+    assert res["replayed"] <= 1, res
