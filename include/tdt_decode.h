@@ -47,7 +47,7 @@ enum tdt_status {
     TDT_ERR_SHAPE = -2,       /* B, T, u_cap or max_symbols < 1, or a model dim out of range */
     TDT_ERR_UNSUPPORTED = -3, /* dtype, predictor kind, layer count or option not supported */
     TDT_ERR_DURATIONS = -4,   /* n_dur / durations mismatch, entry outside [0, 2^20], or no positive entry */
-    TDT_ERR_WORKSPACE = -5,   /* workspace NULL, misaligned or smaller than tdt_workspace_bytes */
+    TDT_ERR_WORKSPACE = -5,   /* workspace NULL, misaligned or too small for the call */
     TDT_ERR_LAUNCH = -6,      /* the HIP runtime refused a launch or a query */
     TDT_ERR_TOO_LARGE = -7,   /* tdt_greedy_decode_static: the sizes need more than TDT_STATIC_SCRATCH_BYTES */
     TDT_ERR_ALIGN = -8        /* enc, a matrix, an embedding table, a bias or a projection output is not 16-byte aligned */
@@ -217,9 +217,12 @@ enum tdt_stat {
 
 /*
  * Bytes of DEVICE workspace tdt_greedy_decode needs for this model and these
- * sizes (projected encoder frames [B][T][h_joint] in float32 dominate; a bfloat16
- * model also gets copies of its matrices there, re-ordered for the matrix cores,
- * which every call writes anew: the caller's weights are only read).
+ * sizes (projected encoder frames [B][T][h_joint] in float32 dominate; the model
+ * also gets copies of its matrices there, re-ordered for the matrix cores, which
+ * every call writes anew: the caller's weights are only read).  The size is that of
+ * a float32 model plus, for bfloat16, the bfloat16 copies.  A call takes less where
+ * it is enough: a bfloat16 call needs no room for float32 copies, and a float32 call
+ * without it runs a slower kernel.
  * Host-only computation.  Returns TDT_OK or TDT_ERR_NULL / _SHAPE / _UNSUPPORTED.
  */
 int tdt_workspace_bytes(const tdt_weights_t *weights, int B, int T, int u_cap, size_t *bytes);
@@ -248,7 +251,7 @@ int tdt_workspace_bytes(const tdt_weights_t *weights, int B, int T, int u_cap, s
  *               log_softmax(label logits)[label]
  *   out_status  DEVICE [B] int32 TDT_HYP_* bits
  *   out_stats   DEVICE [TDT_STAT_COUNT] int64, or NULL
- *   workspace   DEVICE, 256-byte aligned, >= tdt_workspace_bytes(); contents are
+ *   workspace   DEVICE, 256-byte aligned; tdt_workspace_bytes() is enough; contents are
  *               scratch and may be reused by the caller after the stream drains
  *   stream      hipStream_t (NULL = default stream)
  *

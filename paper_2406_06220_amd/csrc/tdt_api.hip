@@ -85,10 +85,10 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     off = align_up(off + 256, 256);
     L.zero_end = off;
     L.need_general = off;
-    // label_loop.hip lays its own arrays over the part from `partials` on; how much it needs depends
-    // on the split of the batch, which is not known here: n_clusters * hyps_per_cluster <= B + kMaxGrid
-    // rows, and at most four row tiles (64 frames) of cells per row or one per workgroup -- or one for
-    // each of at most 16 row tiles a workgroup
+    // label_loop.hip lays its own arrays over the part from `partials` on.  How much they take depends on
+    // the split of the batch, which is known when a call is made (label_layout); here its bound:
+    // n_clusters * hyps_per_cluster <= B + kMaxGrid rows, and at most four row tiles (64 frames) of cells
+    // per row or one per workgroup -- or one for each of at most 16 row tiles a workgroup
     size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
     if (cells < 16 * 16 * (size_t)kMaxGrid) cells = 16 * 16 * (size_t)kMaxGrid;
     size_t lab = L.partials;
@@ -97,13 +97,12 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 256);
     lab = align_up(lab + kRowBufs * 2 * 64 * rows * sizeof(unsigned long long), 256);
     lab = align_up(lab + (kRowBufs + 1) * (size_t)kMaxGrid * sizeof(unsigned long long), 256) + 256;
-    // float32: followed by the copies of the matrices (the general kernel does without).  A size does
-    // not depend on the type but for the copies in front: room for them is part of every workspace
+    // A float32 model's copies of the matrices follow these arrays.  The size asked of a caller counts them
+    // for both types: a bfloat16 model's is a float32 model's plus its own copies in front.  (A call takes
+    // less where it is enough, see decode_common.)
     tdt_weights_t as_f32 = *w;
     as_f32.dtype = 0;
     const size_t with_copies = align_up(lab + packed_layout(&as_f32).total, 256);
-    if (w->dtype == 0) L.packed = lab;
-    L.need_label = w->dtype == 0 ? with_copies : lab;
     L.total = with_copies > off ? with_copies : off;
     return L;
 }
@@ -253,13 +252,13 @@ int tdt_state_bytes(const tdt_weights_t *weights, int B, size_t *bytes)
     return TDT_OK;
 }
 
-// the body of the decode entry points; `state` is null for whole utterances.  own_scratch: the workspace
-// is the library's array, which may hold less than the size asked of a caller
+// The body of the decode entry points; `state` is null for whole utterances.  A workspace that holds what the
+// general kernel needs is taken, and label_loop.hip's kernel runs where its arrays fit as well.
 static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
                          const tdt_weights_t *weights, const int32_t *durations, int max_symbols,
                          int u_cap, int32_t *out_labels, int32_t *out_frames, int32_t *out_len,
                          float *out_score, int32_t *out_status, int64_t *out_stats, void *state,
-                         void *workspace, size_t workspace_bytes, bool own_scratch, const tdt_options_t *options,
+                         void *workspace, size_t workspace_bytes, const tdt_options_t *options,
                          void *stream)
 {
     if (!weights) return TDT_ERR_NULL;
@@ -314,7 +313,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
                       (joint_kernel == TDT_JOINT_AUTO && can_stream && weights->vocab + 1 + weights->n_dur >= 4096);
     const WorkspaceLayout L = workspace_layout(weights, B, T);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
-        workspace_bytes < (own_scratch ? L.need_general : L.total))
+        workspace_bytes < L.need_general)
         return TDT_ERR_WORKSPACE;
 
     DecodeVariant variant{state != nullptr, algorithm == TDT_ALG_FRAME_LOOPING, on_the_fly, wide_joint};
@@ -412,14 +411,19 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
     // streamed output layer, groups it can hold), else the general one
     const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
-    const bool label = workspace_bytes >= L.need_label && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly &&
+    const LabelLayout LL = label_layout(weights, wide_joint, n_clusters, hyps_per_cluster, C);
+    size_t packed_at = L.packed, label_end = L.partials + LL.zero_end;
+    if (weights->dtype == 0) {   // (float32: the copies follow the label kernel's arrays)
+        packed_at = align_up(label_end, 256);
+        label_end = packed_at + PL.total;
+    }
+    const bool label = workspace_bytes >= label_end && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly &&
                        label_kernel_takes(weights, state != nullptr, wide_joint, hyps_per_cluster, C);
-    if (weights->dtype == 0 && !label) PL.total = 0;   // (float32: the general kernel reads the matrices as they are)
-    LabelLayout LL{};
+    if (weights->dtype == 0 && !label) PL.total = 0;   // (... and the general kernel reads the matrices as they are)
+    char *const packed = ws + packed_at;
     ClearRanges clear{};
     char *const lb = ws + L.partials;
     if (label) {
-        LL = label_layout(weights, wide_joint, n_clusters, hyps_per_cluster, C);
         clear.zero = lb + LL.zero_begin;
         clear.zero_bytes = LL.zero_end - LL.zero_begin;
         clear.ones = lb + LL.ones_begin;
@@ -432,12 +436,12 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         // one launch: the projection, the predictor side's per-label tables, the clearing
         // (projections on the fly: no rows for the projection here)
         if (launch_prepare(enc, enc_len, on_the_fly ? 0 : B, T, weights, enc_proj, emb_gates, pred_tab, PL,
-                           on_the_fly, ws + L.packed, clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess)
+                           on_the_fly, packed, clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess)
             return TDT_ERR_LAUNCH;
     } else {
         // (a call that reuses the projections of an earlier one still gets its own copies of the
         // matrices: the caller vouches for the projections, not for what else the workspace holds)
-        if (launch_pack_weights(weights, PL, on_the_fly, ws + L.packed, s) != hipSuccess) return TDT_ERR_LAUNCH;
+        if (launch_pack_weights(weights, PL, on_the_fly, packed, s) != hipSuccess) return TDT_ERR_LAUNCH;
         if (launch_init(clear, reinterpret_cast<long long *>(out_stats), s) != hipSuccess) return TDT_ERR_LAUNCH;
     }
 
@@ -478,7 +482,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     p.w_out = weights->w_out;
     p.b_out = weights->b_out;
     if (weights->dtype == 1) {   // the kernel multiplies by the fragment-major copies
-        const char *pk = ws + L.packed;
+        const char *pk = packed;
         p.w_enc = pk + PL.w_enc.offset;
         p.w_pred = pk + PL.w_pred.offset;
         p.w_out = pk + PL.w_out.offset;
@@ -527,7 +531,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     if (label) {
         p.hbuf = reinterpret_cast<float *>(lb + LL.hx);
         p.pred_proj = reinterpret_cast<float *>(lb + LL.px);
-        p.packed = ws + L.packed;
+        p.packed = packed;
         p.packed_bytes = PL.total;
         p.off_w_pred = (int)PL.w_pred.offset;
         p.off_w_out = (int)PL.w_out.offset;
@@ -557,7 +561,7 @@ int tdt_greedy_decode(const void *enc, const int32_t *enc_len, int B, int T,
 {
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, workspace,
-                         workspace_bytes, false, options, stream);
+                         workspace_bytes, options, stream);
 }
 
 int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int T,
@@ -580,7 +584,7 @@ int tdt_greedy_decode_static(const void *enc, const int32_t *enc_len, int B, int
     // decode_common clears, with a kernel, every part of the workspace that has to start at zero
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, nullptr, ptr,
-                         (size_t)TDT_STATIC_SCRATCH_BYTES, true, options, stream);
+                         (size_t)TDT_STATIC_SCRATCH_BYTES, options, stream);
 }
 
 int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int T,
@@ -594,7 +598,7 @@ int tdt_greedy_decode_chunk(const void *enc, const int32_t *enc_len, int B, int 
     if ((reinterpret_cast<uintptr_t>(state) & 255) != 0) return TDT_ERR_WORKSPACE;
     return decode_common(enc, enc_len, B, T, weights, durations, max_symbols, u_cap, out_labels,
                          out_frames, out_len, out_score, out_status, out_stats, state, workspace,
-                         workspace_bytes, false, options, stream);
+                         workspace_bytes, options, stream);
 }
 
 const char *tdt_status_string(int status)

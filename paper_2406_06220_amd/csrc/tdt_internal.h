@@ -98,9 +98,9 @@ struct DecodeParams {
 };
 
 struct WorkspaceLayout {
-    size_t packed;                 // the matrices the decode kernel streams, fragment by fragment
+    size_t packed;                 // bfloat16: the matrices the decode kernel streams, fragment by fragment
     size_t enc_proj, emb_gates, pred_tab, hbuf, cbuf, rgate, pred_proj, partials, row_lab, row_dur, barrier, abort_flag, total;
-    size_t need_general, need_label;   // what a call of decode.hip's / label_loop.hip's kernel needs (total: of a caller)
+    size_t need_general;           // what a call of decode.hip's kernel needs (total: what a caller is asked for)
     size_t row_entries;            // uint64 entries in each of row_lab / row_dur
     size_t zero_begin, zero_end;   // byte range the init kernel clears
 };

@@ -171,3 +171,61 @@ def test_a_wait_of_the_label_loop_that_runs_out(oracle_lib, gpu, kind, blank_bia
     assert out["stats"]["abort"] == 0 and not (out["status"] & gpu.TDT_HYP_ABORTED).any()
     res = parity.compare(oracle_lib, oracle_lib.OracleModel(cfg, w), cfg, enc, ln, out, u_cap, rows=range(0, cfg.B, 17))
     assert res["replayed"] <= 1, res
+
+
+# ------------------------------------------------------------------ workspaces
+def least_workspace(cfg, B, T):
+    """Bytes of the general kernel's arrays, each at a multiple of 256: what every call has to have."""
+    up = lambda n: -(-n // 256) * 256
+    H, Hp, V, rows = cfg.h_joint, cfg.h_pred, cfg.vocab, B + 256
+    L = cfg.pred_layers if cfg.pred_kind == "lstm" else 0
+    n = 0
+    if cfg.dtype == "bf16":   # the fragment-major copies
+        frags = lambda tiles, k: tiles * -(-k // 32) * 1024
+        n += up(frags(-(-H // 16), cfg.d_enc) + frags(-(-H // 16), Hp) + frags(-(-cfg.n_out // 16), H) +
+                max(2 * L - 1, 0) * frags(-(-Hp // 4), Hp))
+    n += up(B * T * H * 4) + up(rows * H * 4)
+    n += up((V + 1) * 4 * Hp * 4) if L else up(cfg.pred_layers * (V + 1) * H * 4)
+    n += up(2 * 1024 * 256 * 8) + 2 * up(4 * rows * 64 * 8)
+    n += up(2 * L * rows * Hp * 4) + up(L * rows * Hp * 4) + (up(rows * 4 * Hp * 4) if L else 0)
+    return n + up(257 * 32 * 4) + 256
+
+
+@pytest.mark.parametrize("kw,opts,label_kernel", [
+    (dict(B=5, h_pred=320, h_joint=320), {}, True), (dict(B=30, pred_layers=3), {}, True),
+    (dict(B=9, vocab=4200, h_joint=200), dict(joint_kernel=2), True),
+    (dict(B=40, pred_kind="stateless", h_pred=24), {}, True),
+    (dict(B=5, dtype="fp32", h_pred=320, h_joint=320, vocab=3000), {}, False)])
+def test_least_workspace(oracle_lib, gpu, kw, opts, label_kernel):   # noqa: F811
+    """A workspace without room for float32 copies of the matrices is enough: nothing beyond it is written,
+    and a bfloat16 call gives bit for bit what it gives with the size it is asked for.  With less a
+    call is refused."""
+    import parity
+    import torch
+    cfg = config("ll_least_ws", **kw)
+    w = synth.generate_model(cfg)
+    enc, ln = synth.generate_inputs(cfg)
+    u_cap = cfg.T * cfg.max_symbols
+    model = gpu.DeviceModel(cfg, w)
+    dec = gpu.Decoder(model, cfg.B, cfg.T, u_cap, **opts)
+    enc_d, len_d = model.upload_enc(enc), torch.from_numpy(ln).to(model.device)
+    least = least_workspace(cfg, cfg.B, cfg.T)
+    assert least <= dec.ws_bytes
+    parity.announce(f"workspace of {least} of {dec.ws_bytes} bytes, cfg={cfg.name} {kw}")
+    dec(enc_d, len_d)
+    full = dec.results()
+    dec.workspace.fill_(0xA5)
+    dec.ws_bytes = least
+    dec(enc_d, len_d)
+    out = dec.results()
+    assert out["stats"]["abort"] == 0
+    at = dec.ws_ptr - dec.workspace.data_ptr()
+    assert (dec.workspace[at + least:] == 0xA5).all() and (dec.workspace[:at] == 0xA5).all()
+    if label_kernel:
+        for key in ("labels", "frames", "len", "score", "status", "stats"):
+            assert np.all(full[key] == out[key]), key
+    parity.compare(oracle_lib, oracle_lib.OracleModel(cfg, w), cfg, enc, ln, out, u_cap)
+    dec.ws_bytes = least - 256
+    with pytest.raises(gpu.TdtError) as e:
+        dec(enc_d, len_d)
+    assert e.value.code == -5
