@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
     // thread per count, so that a pass looks it up instead of dividing.
     for (int n = tid + 1; n <= G; n += kThreads) {
         const int NT = (O + CT - 1) / CT;
-        const int Kw = joint_window(n, FRAMELOOP ? 1 : p.window, auto_rows, rows_cap, C, (O + CT - 1) / CT);   // (Alg. 2 looks at one frame per step)
+        const int Kw = joint_window(n, FRAMELOOP ? 1 : p.window, auto_rows, rows_cap, C, NT, p.window_most);   // (Alg. 2 looks at one frame per step)
         const int n_tiles = (n * Kw + RT - 1) / RT;
         int n_cg, tpg;
         split_tiles(C, n_tiles, NT, max_cg, n_cg, tpg);

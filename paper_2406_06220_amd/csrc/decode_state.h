@@ -52,7 +52,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int RT = 16;       // activation rows per tile
+constexpr int RT = kRowTile; // activation rows per tile
 constexpr int CT = 16;       // weight columns per tile
 constexpr int KSEG = 1024;   // longest stretch of the reduction dimension staged at once
 constexpr int CP_LD = CT + 1;

@@ -296,8 +296,8 @@ __device__ inline int auto_joint_rows(int C, int NT, int joint_tiles, int hpc)
     return max(1, C / ((NT + tiles_per_item - 1) / tiles_per_item)) * RT;
 }
 // frames per hypothesis when n of them search (window: the caller's, 0 = automatic)
-// (C, NT: see auto_joint_rows)
-__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap, int C, int NT)
+// (C, NT: see auto_joint_rows; most: the longest automatic window)
+__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap, int C, int NT, int most = kMaxWindow)
 {
     int Kw = window;
     if (Kw <= 0) {
@@ -309,6 +309,7 @@ __device__ inline int joint_window(int n, int window, int auto_rows, int rows_ca
         // the row tiles this window needs are paid for whole: as many frames as fill them
         const int fill = (n * Kw + RT - 1) / RT * RT / n;
         if (fill > Kw) Kw = fill;
+        if (Kw > most) Kw = most;
     }
     if (Kw > kMaxWindow) Kw = kMaxWindow;
     if (Kw * n > rows_cap) Kw = rows_cap / n;

@@ -329,72 +329,40 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         max_grid = decode_max_grid(weights, variant);
         if (max_grid < 1) return TDT_ERR_LAUNCH;
     }
-    bool one_workgroup = false;   // a group each
-    const int min_clusters = (B + kMaxHypsPerCluster - 1) / kMaxHypsPerCluster;
-    if (n_clusters == 0) {
-        // Measured on the paper-sized models (B = 1 ... 512, 2 ... 16 clusters).  A cluster runs
-        // as long as its longest hypothesis and the fewer hypotheses it holds the shorter its
-        // joint passes, so more clusters pay -- until a cluster has too few workgroups to give
-        // each at most four column tiles of the predictor-side products (two weight batches per
-        // wavefront); `fit` is the cluster count at which that holds.  Small batches: two
-        // to four clusters.  An LSTM predictor: `fit`, and more for large batches.  A stateless
-        // predictor: see below.
-        const bool lstm = weights->pred_kind == TDT_PRED_LSTM;
-        const int nt_a = (weights->h_joint + 15) / 16, nt_b = lstm ? (weights->h_pred + 3) / 4 : 0;
-        const int q4 = (nt_a + 3) / 4 + (nt_b + 3) / 4;
-        int fit = (2 * max_grid + q4) / (2 * q4);   // max_grid / q4, rounded
-        if (fit < 1) fit = 1;
-        if (B < 16 && lstm) {
-            // two groups also for a single hypothesis (half the workgroups synchronise faster),
-            // four from four hypotheses on (3 to 8 % faster than two at B = 4 ... 12)
-            n_clusters = B < 4 ? 2 : (fit < 4 ? fit : 4);
-            if (n_clusters < 2) n_clusters = 2;
-        } else if (lstm) {
-            n_clusters = fit;
-            // from about 14 hypotheses per group of eight on: groups of one full row tile (B = 160, ten
-            // groups: 3.04 ms, eight: 3.81 ms) while a group keeps about 20 workgroups, then 16 groups
-            // (B = 256: 4.59 ms, eight: 4.91 ms)
-            if (fit < 8 && B >= 14 * 8) {
-                const int full = (B + 15) / 16;
-                n_clusters = full <= 8 ? 8 : full <= 13 ? full : 16;
-            }
-        } else {
-            // no predictor-side phase, no matrix but the output layer's: groups of as many workgroups as
-            // its column tiles make items of k of them, k the smallest with about three hypotheses a
-            // group (items of eight tiles: five).  Measured on the stateless benchmark model (65 tiles),
-            // best of all group counts in brackets: B = 9, 7 groups, 1.31 ms (1.31); B = 32, 11 groups,
-            // 1.58 (1.58; 16 groups 1.71); B = 64, 23 groups, 1.85 (1.85; 32 groups 1.94); B = 128, 28
-            // groups, 2.47 (2.47); B = 256, 42 groups, 3.40 (3.40; 32 groups 3.57)
-            // An output layer of up to four tiles, one round of label_loop.hip: a workgroup for every
-            // hypothesis, which then needs no other (the smallest benchmark model, B = 4, T = 200: 454 us
-            // against 489 us in groups of 64 workgroups; B = 60: 560 us and less against 675 us).
-            const int nt = (weights->vocab + 1 + weights->n_dur + 15) / 16, per_item[6] = {2, 3, 4, 6, 8, 12};
-            one_workgroup = nt <= 4 && !wide_joint && algorithm == TDT_ALG_LABEL_LOOPING;
-            for (const int k : per_item) {
-                n_clusters = max_grid / ((nt + k - 1) / k);
-                if (5 * B <= (k < 8 ? 16 : 25) * n_clusters) break;
-            }
-            if (n_clusters > 64) n_clusters = 64;
-            if (one_workgroup) n_clusters = max_grid;
-            if (n_clusters < 2) n_clusters = 2;
+    // Which kernel, and how the batch is split: label_loop.hip's kernel with the groups its rules give (or
+    // the caller asks for) wherever it can -- the default loops, projections ahead of them, groups and
+    // reductions it can hold, a workspace with room for its arrays -- else the general one with its own.
+    const SplitModel sm{weights->pred_kind == TDT_PRED_LSTM, (weights->h_joint + 15) / 16, (weights->h_pred + 3) / 4,
+                        (weights->vocab + 1 + weights->n_dur + 15) / 16};
+    const int min_clusters = enough_groups(1, B), asked = n_clusters, streaming_least = wide_joint ? min_stream_clusters : 0;
+    PackedLayout PL = packed_layout(weights);
+    LabelLayout LL{};
+    GroupSplit split{asked, false, kMaxWindow};
+    size_t packed_at = L.packed;
+    int grid = 0, C = 0, hyps_per_cluster = 0;
+    bool label = algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly;
+    for (;;) {
+        if (asked == 0)
+            split = label ? label_split(sm, B, max_grid, streaming_least)
+                          : general_split(sm, B, max_grid, streaming_least, on_the_fly);
+        n_clusters = split.n_clusters;
+        if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;
+        // every cluster gets max_grid / n_clusters workgroups; the launch is rounded up to whole
+        // rounds of the dies (the kernel leaves the spare slots empty)
+        grid = split.one_workgroup ? n_clusters : max_grid / n_clusters * n_clusters;
+        if (!split.one_workgroup && (grid + kXcds - 1) / kXcds * kXcds <= max_grid) grid = (grid + kXcds - 1) / kXcds * kXcds;
+        C = grid / n_clusters;
+        hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
+        if (!label) break;
+        LL = label_layout(weights, wide_joint, n_clusters, hyps_per_cluster, C);
+        size_t label_end = L.partials + LL.zero_end;
+        if (weights->dtype == 0) {   // (float32: the copies follow the label kernel's arrays)
+            packed_at = align_up(label_end, 256);
+            label_end = packed_at + PL.total;
         }
-        if (n_clusters > B && (B > 1 || one_workgroup)) n_clusters = B;
-        if (n_clusters < min_clusters) n_clusters = min_clusters;
-        if (wide_joint) {
-            // the streaming joint pass: every group streams the whole output matrix in every pass, and a
-            // pass lasts as long as its workgroups need for that, so groups are few while the batch is
-            // small (8198 outputs, T = 300: B = 4, four groups 1.47 ms, eight 1.71; B = 32, eight 2.69,
-            // four 2.93, sixteen 2.99; B = 130, sixteen 5.24, eight 5.67; B = 256, sixteen 7.8, eight 9.1,
-            // thirty-two 8.8)
-            n_clusters = min_stream_clusters * (B < 12 ? 1 : B <= 96 ? 2 : 4);   // (some may stay empty)
-            if (n_clusters < min_clusters) n_clusters = min_clusters;
-        }
+        if (workspace_bytes >= label_end && label_kernel_takes(weights, state != nullptr, wide_joint, hyps_per_cluster, C)) break;
+        label = false;
     }
-    if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;
-    // every cluster gets max_grid / n_clusters workgroups; the launch is rounded up to whole
-    // rounds of the dies (the kernel leaves the spare slots empty)
-    int grid = one_workgroup ? n_clusters : max_grid / n_clusters * n_clusters;
-    if (!one_workgroup && (grid + kXcds - 1) / kXcds * kXcds <= max_grid) grid = (grid + kXcds - 1) / kXcds * kXcds;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
@@ -407,19 +375,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // the arrangement without any precomputation.)
     float *pred_tab = weights->pred_kind == TDT_PRED_STATELESS && !on_the_fly
                           ? reinterpret_cast<float *>(ws + L.pred_tab) : nullptr;
-    PackedLayout PL = packed_layout(weights);
-    // which kernel: label_loop.hip's wherever it can (the default loops, projections ahead of them, no
-    // streamed output layer, groups it can hold), else the general one
-    const int C = grid / n_clusters, hyps_per_cluster = (B + n_clusters - 1) / n_clusters;
-    const LabelLayout LL = label_layout(weights, wide_joint, n_clusters, hyps_per_cluster, C);
-    size_t packed_at = L.packed, label_end = L.partials + LL.zero_end;
-    if (weights->dtype == 0) {   // (float32: the copies follow the label kernel's arrays)
-        packed_at = align_up(label_end, 256);
-        label_end = packed_at + PL.total;
-    }
-    const bool label = workspace_bytes >= label_end && algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly &&
-                       label_kernel_takes(weights, state != nullptr, wide_joint, hyps_per_cluster, C);
-    if (weights->dtype == 0 && !label) PL.total = 0;   // (... and the general kernel reads the matrices as they are)
+    if (weights->dtype == 0 && !label) PL.total = 0;   // (float32: the general kernel reads the matrices as they are)
     char *const packed = ws + packed_at;
     ClearRanges clear{};
     char *const lb = ws + L.partials;
@@ -462,6 +418,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     p.max_symbols = max_symbols;
     p.u_cap = u_cap;
     p.window = window;
+    p.window_most = split.window_most;
     p.joint_tiles = joint_tiles;
     p.n_clusters = n_clusters;
     p.frame_loop = algorithm == TDT_ALG_FRAME_LOOPING;

@@ -4,6 +4,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "split.h"
 #include "tdt_decode.h"
 
 namespace tdt {
@@ -11,12 +12,9 @@ namespace tdt {
 constexpr int kThreads = 512;                 // threads per workgroup of the decode kernel
 constexpr int kWaves = kThreads / 64;         // 64-wide wavefronts per workgroup
 constexpr int kMaxGrid = 256;                 // one workgroup per compute unit
-constexpr int kMaxHypsPerCluster = 256;       // hypotheses one group of workgroups decodes
 constexpr int kMaxRowsPerPass = 1024;         // (hypothesis, frame) rows of one joint pass
 constexpr int kMaxColGroups = 64;             // output-column slices of one joint pass
-constexpr int kMaxWindow = 64;                // frames of one hypothesis per joint pass
 constexpr int kPartialEntries = kMaxRowsPerPass * kMaxGrid;  // per partial buffer
-constexpr int kXcds = 8;                      // accelerator dies of an MI355X; workgroups are dealt to them in turn
 constexpr int kBarrierStride = 32;            // uint32 slots between two workgroups' barrier flags
 constexpr int kMaxRankedBatch = 1024;          // largest batch whose hypotheses are dealt to the clusters by length
 constexpr int kMaxDuration = 1 << 20;          // largest frame increment of a duration class
@@ -44,6 +42,7 @@ struct DecodeParams {
     int pred_kind, pred_layers, h_pred, emb_dim;
     int max_symbols, u_cap;
     int window;            // 0 = automatic
+    int window_most;       // longest automatic window (decode.hip)
     int joint_tiles;       // column tiles per joint work item the automatic window aims at (0 = automatic: 4 to 12)
     int kseg_max;          // longest K segment staged at once (set by launch_decode)
     int lds_bytes;         // dynamic LDS of the launch, a multiple of 16 (set by launch_decode)

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from paper_2406_06220_amd import synth
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
@@ -17,6 +19,13 @@ extern "C" void pred_share_c(int deep, int nt_a, int nt_b, int h_pred, int C, in
     const PredShare s = pred_share(deep != 0, nt_a, nt_b, h_pred, C, rank);
     const int v[6] = {s.qt0, s.na, s.r0, s.nr, s.u0, s.U};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+extern "C" void group_split_c(int general, int lstm, int nt_a, int nt_b, int nt_out, int B, int streaming_least, int on_the_fly, int *out)
+{
+    const SplitModel m{lstm != 0, nt_a, nt_b, nt_out};
+    const GroupSplit s = general ? general_split(m, B, 256, streaming_least, on_the_fly != 0) : label_split(m, B, 256, streaming_least);
+    const int v[3] = {s.n_clusters, s.one_workgroup, s.window_most};
+    for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
 """
 
@@ -56,3 +65,43 @@ def test_stateless_predictor_has_no_share(split):
     out = (C.c_int * 6)()
     split.pred_share_c(0, 40, 0, 640, 9, 4, out)
     assert list(out) == [0] * 6
+
+
+def group_split(split, cfg, general=0, on_the_fly=0, streaming=0):
+    out = (C.c_int * 3)()
+    lstm = int(cfg.pred_kind == "lstm")
+    split.group_split_c(general, lstm, -(-cfg.h_joint // 16), -(-cfg.h_pred // 4), -(-cfg.n_out // 16), cfg.B,
+                        4 * streaming, on_the_fly, out)
+    return list(out)
+
+
+def test_group_counts_of_the_benchmark_models(split):
+    got = [group_split(split, c) for c in (synth.CFG1, synth.CFG2, synth.CFG3, synth.CFG4, synth.CFG2_B128,
+                                           synth.CFG2.with_batch(1), synth.CFG2.with_batch(7), synth.CFG2.with_batch(256))]
+    assert got == [[4, 1, 64], [5, 0, 64], [5, 0, 64], [28, 0, 64], [8, 0, 64], [2, 0, 64], [4, 0, 64], [16, 0, 64]]
+    assert group_split(split, synth.CFG5, streaming=1) == [16, 0, 64]
+
+
+@pytest.mark.parametrize("general", [0, 1])
+@pytest.mark.parametrize("kind", ["lstm", "stateless"])
+def test_group_counts_over_all_sizes(split, kind, general):
+    """Groups exist, hold what they may hold, and the general kernel's are never single workgroups: with
+    all of the chip's workgroups dealt out, a group of it has more than one while it can."""
+    for vocab in (1, 40, 63, 64, 1024, 9000):
+        for H, Hp in ((8, 8), (640, 640), (2048, 1024)):
+            for B in (1, 2, 3, 15, 16, 64, 111, 112, 300, 1500, 16640, 65536):
+                for streaming in (0, 1):
+                    cfg = synth.small_config("split", pred_kind=kind, vocab=vocab, h_joint=H, h_pred=Hp, emb_dim=Hp, B=B)
+                    n, one, most = group_split(split, cfg, general, 0, streaming)
+                    assert 1 <= n <= 256 and -(-B // n) <= 256 and most == 64
+                    assert not (general and one) and (not one or n == min(B, 256))
+                    if general and B <= 64 * 64:
+                        assert 256 // n >= 2
+
+
+def test_projections_on_the_fly_of_small_output_layers(split):
+    """One hypothesis a group and one row tile a pass, as its group of one workgroup has by default."""
+    for B in (4, 60):
+        cfg = synth.CFG1.with_batch(B)
+        assert group_split(split, cfg) == [B, 1, 64]
+        assert group_split(split, cfg, general=1, on_the_fly=1) == [B, 0, 16]
