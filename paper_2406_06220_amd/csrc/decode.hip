@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
         __syncthreads();
         if (tid == 0) S.pend_n = 0;
     };
-    const int auto_rows = auto_joint_rows(C, (O + CT - 1) / CT, p.joint_tiles, p.hyps_per_cluster);
+    const int auto_rows = general_joint_rows(sizeof(WT) == 2, C, (O + CT - 1) / CT, p.joint_tiles, G);
     // streaming joint pass: dies the group's workgroups are spread over, workgroups per die, this
     // one's die and place on it, column tiles per die and this die's first
     const int wide_ndie = C >= kXcds ? kXcds : C, wide_per = C / wide_ndie;
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_kernel(DecodeParams p)
     // thread per count, so that a pass looks it up instead of dividing.
     for (int n = tid + 1; n <= G; n += kThreads) {
         const int NT = (O + CT - 1) / CT;
-        const int Kw = joint_window(n, FRAMELOOP ? 1 : p.window, auto_rows, rows_cap, C, NT, p.window_most);   // (Alg. 2 looks at one frame per step)
+        const int Kw = general_window(n, FRAMELOOP ? 1 : p.window, auto_rows, rows_cap, p.window_most);   // (Alg. 2 looks at one frame per step)
         const int n_tiles = (n * Kw + RT - 1) / RT;
         int n_cg, tpg;
         split_tiles(C, n_tiles, NT, max_cg, n_cg, tpg);

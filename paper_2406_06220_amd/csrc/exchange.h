@@ -275,47 +275,6 @@ __device__ inline void split_tiles(int C, int n_row_tiles, int n_units, int max_
     n_groups = (n_units + per_group - 1) / per_group;
 }
 
-// Automatic window of a joint pass: as many rows as give every workgroup at most one joint work item of
-// so many column tiles.  Fewer tiles make a shorter pass, more a longer window and fewer passes.  Four
-// -- one round of label_loop.hip -- where that leaves the group three row tiles (config 2 at B = 32,
-// five groups of 51: 1.40 ms against 1.57 ms with eight) or every hypothesis of the group five frames
-// (stateless, 16 hypotheses in groups of two: 1.35 ms against 1.45 ms; in groups of five, where it
-// leaves three frames: 2.01 ms against 1.83 ms); else eight by the like rule (two row tiles or five
-// frames; config 2 at B = 128, eight groups of 32: 2.71 ms against 3.21 ms with four); else twelve
-// (B = 256, 16 groups of 16: 4.59 ms against 4.99 ms with eight).  By the hypotheses a group has, not
-// those that search: the last few that search are in a stretch of blanks and want a long window (by the
-// latter, B = 128: 3.23 ms).
-// C workgroups, NT column tiles of the output layer, hpc hypotheses a group.
-__device__ inline int auto_joint_rows(int C, int NT, int joint_tiles, int hpc)
-{
-    const int four = C / ((NT + 3) / 4), eight = C / ((NT + 7) / 8);
-    const int tiles_per_item = joint_tiles > 0                          ? joint_tiles
-                               : four >= 3 || four * RT >= 5 * hpc      ? 4
-                               : eight >= 2 || eight * RT >= 5 * hpc    ? 8
-                                                                        : 12;
-    return max(1, C / ((NT + tiles_per_item - 1) / tiles_per_item)) * RT;
-}
-// frames per hypothesis when n of them search (window: the caller's, 0 = automatic)
-// (C, NT: see auto_joint_rows; most: the longest automatic window)
-__device__ inline int joint_window(int n, int window, int auto_rows, int rows_cap, int C, int NT, int most = kMaxWindow)
-{
-    int Kw = window;
-    if (Kw <= 0) {
-        Kw = auto_rows / n;
-        // (2, 4 and 5 measured no better on the benchmark models but where a workgroup has so many column tiles
-        // that streaming them is what a pass costs: 8198 outputs, B = 256, four frames 7.60 ms, three 7.80)
-        const int least = C * 12 < NT ? 4 : 3;
-        if (Kw < least) Kw = least;
-        // the row tiles this window needs are paid for whole: as many frames as fill them
-        const int fill = (n * Kw + RT - 1) / RT * RT / n;
-        if (fill > Kw) Kw = fill;
-        if (Kw > most) Kw = most;
-    }
-    if (Kw > kMaxWindow) Kw = kMaxWindow;
-    if (Kw * n > rows_cap) Kw = rows_cap / n;
-    return Kw;
-}
-
 }  // namespace
 }  // namespace tdt
 

@@ -358,9 +358,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // ---- how a joint pass is cut, per number of searching hypotheses
     const int NT = (O + CT - 1) / CT;
     {
-        const int rows_auto = auto_joint_rows(C, NT, p.joint_tiles, hpc);
+        const int rows_auto = label_joint_rows(C, NT, p.joint_tiles, hpc);
         for (int n = tid + 1; n <= G; n += THREADS) {
-            const int Kw = joint_window(n, p.window, rows_auto, rows_cap, C, NT);
+            const int Kw = label_window(n, p.window, rows_auto, rows_cap, C, NT);
             const int n_tiles = (n * Kw + RT - 1) / RT;
             int n_cg, tpg;
             split_tiles(C, WIDE ? 1 : n_tiles, NT, C, n_cg, tpg);   // (wide: a workgroup takes its columns of all rows)

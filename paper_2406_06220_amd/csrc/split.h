@@ -44,22 +44,27 @@ inline int lstm_groups(const SplitModel &m, int B, int max_grid, bool *may_grow)
     const int n = B < 4 ? 2 : (fit < 4 ? fit : 4);
     return n < 2 ? 2 : n;
 }
+// A large LSTM batch: groups of one full row tile (label_loop.hip, B = 160, ten groups: 3.04 ms, eight: 3.81
+// ms) while a group keeps about 20 workgroups, then 16 groups (B = 256: 4.59 ms, eight: 4.91 ms)
+inline int full_tile_groups(int B)
+{
+    const int full = (B + kRowTile - 1) / kRowTile;
+    return full <= 8 ? 8 : full <= 13 ? full : 16;
+}
 // A stateless predictor: no predictor-side phase, no matrix but the output layer's.  Groups of as many
-// workgroups as its column tiles make items of k of them, k the smallest with about three hypotheses a
-// group (items of eight tiles: five).  Measured with label_loop.hip on the stateless benchmark model
-// (65 tiles), best of all group counts in brackets: B = 9, 7 groups, 1.31 ms (1.31); B = 32, 11 groups,
-// 1.58 (1.58; 16 groups 1.71); B = 64, 23 groups, 1.85 (1.85; 32 groups 1.94); B = 128, 28 groups, 2.47
-// (2.47); B = 256, 42 groups, 3.40 (3.40; 32 groups 3.57)
-inline int stateless_groups(const SplitModel &m, int B, int max_grid)
+// workgroups as its column tiles make items of k of them, k the smallest with about `fifths` / 5 hypotheses
+// a group (items of eight tiles: five): three, see the figures of each kernel below.
+inline int stateless_groups(const SplitModel &m, int B, int max_grid, int fifths)
 {
     const int per_item[6] = {2, 3, 4, 6, 8, 12};
     int n = 2;
     for (const int k : per_item) {
         n = max_grid / ((m.nt_out + k - 1) / k);
-        if (5 * B <= (k < 8 ? 16 : 25) * n) break;
+        if (5 * B <= (k < 8 ? fifths : 25) * n) break;
     }
     return n > 64 ? 64 : n < 2 ? 2 : n;
 }
+constexpr int kThreeHyps = 16, kTwoHyps = 10;
 // A streamed output layer (`least`: the fewest groups that form takes): every group streams the whole
 // output matrix in every pass, and a pass lasts as long as its workgroups need for that, so groups are few
 // while the batch is small (8198 outputs, T = 300: B = 4, four groups 1.47 ms, eight 1.71; B = 32, eight
@@ -72,13 +77,13 @@ inline int enough_groups(int n, int B)
     const int least = (B + kMaxHypsPerCluster - 1) / kMaxHypsPerCluster;
     return n < least ? least : n;
 }
-// Groups of a call of label_loop.hip's kernel.  Large LSTM batches, from about 14 hypotheses per group of
-// eight on: groups of one full row tile (B = 160, ten groups: 3.04 ms, eight: 3.81 ms) while a group keeps
-// about 20 workgroups, then 16 groups (B = 256: 4.59 ms, eight: 4.91 ms).  A stateless predictor with an
-// output layer of up to four tiles, one round of the kernel: a workgroup for every hypothesis, which then
-// needs no other (the smallest benchmark model, B = 4, T = 200: 454 us against 489 us in groups of 64
-// workgroups; B = 60: 560 us and less against 675 us).
-// (streaming_least: 0, or see streaming_groups)
+// Groups of a call of label_loop.hip's kernel (streaming_least: 0, or see streaming_groups).
+// Stateless benchmark model (65 tiles), best of all group counts in brackets: B = 9, 7 groups, 1.31 ms
+// (1.31); B = 32, 11 groups, 1.58 (1.58; 16 groups 1.71); B = 64, 23 groups, 1.85 (1.85; 32 groups 1.94);
+// B = 128, 28 groups, 2.47 (2.47); B = 256, 42 groups, 3.40 (3.40; 32 groups 3.57).
+// With an output layer of up to four tiles, one round of the kernel: a workgroup for every hypothesis,
+// which then needs no other (the smallest benchmark model, B = 4, T = 200: 454 us against 489 us in
+// groups of 64 workgroups; B = 60: 560 us and less against 675 us).
 inline GroupSplit label_split(const SplitModel &m, int B, int max_grid, int streaming_least)
 {
     GroupSplit s{1, false, kMaxWindow};
@@ -88,36 +93,119 @@ inline GroupSplit label_split(const SplitModel &m, int B, int max_grid, int stre
     }
     s.one_workgroup = !m.lstm && m.nt_out <= 4;
     bool may_grow = false;
-    int n = s.one_workgroup ? max_grid : m.lstm ? lstm_groups(m, B, max_grid, &may_grow) : stateless_groups(m, B, max_grid);
-    if (may_grow && B >= 14 * 8) {
-        const int full = (B + 15) / 16;
-        n = full <= 8 ? 8 : full <= 13 ? full : 16;
-    }
+    int n = s.one_workgroup ? max_grid
+            : m.lstm        ? lstm_groups(m, B, max_grid, &may_grow)
+                            : stateless_groups(m, B, max_grid, kThreeHyps);
+    if (may_grow && B >= 14 * 8) n = full_tile_groups(B);
     if (n > B && (B > 1 || s.one_workgroup)) n = B;
     s.n_clusters = enough_groups(n, B);
     return s;
 }
-// Groups of a call of the general kernel (decode.hip), which never does without its group: one workgroup a
-// hypothesis took 12.3 ms against 3.6 ms in groups of 64 (projections on the fly, 51 outputs, joint width
-// 640, B = 4), 0.44 ms against 0.37 ms (the smallest benchmark model, the same) and 22.9 ms against
-// 19.4 ms (float32, joint width 1024, 51 outputs, B = 32).
-// Projections on the fly, an output layer of up to four tiles, a hypothesis or a few a group: of a pass's
-// rows every one is projected, so a hypothesis gets at most one row tile of frames -- as many as it
-// has with projections ahead of the loops, where its group is one workgroup (one hypothesis a group:
-// B = 60, 1.26 ms against 1.58 ms with 64 frames; 51 outputs, joint width 640, B = 32, 5.3 ms against 9.4 ms).
-inline GroupSplit general_split(const SplitModel &m, int B, int max_grid, int streaming_least, bool on_the_fly)
+// Groups of a call of the general kernel (decode.hip), measured on it.
+//   A large LSTM batch: eight groups, whose row tiles are full either way (B = 256, projections on the fly:
+// 6.37 ms, 16 groups 6.69; reductions of 1280: 1.83 ms, 2.32) -- frame-looping, which looks at one frame a
+// step, groups of one row tile (21.9 ms, eight groups 29.7).
+//   Stateless: as above (on the fly, B = 32, 11 groups, 1.99 ms, 16 groups 2.04; B = 64, 23 groups, 2.12,
+// 28 groups 2.33; B = 256, 42 groups, 4.92, 51 groups 5.75), frame-looping with two hypotheses a group
+// instead of three (B = 32, 23 groups, 2.72 ms, 11 groups 3.35; B = 64, 28 groups, 3.32, 23 groups 3.50).
+//   Never a workgroup alone, which a whole reduction or projection is too much for: one a hypothesis took
+// 12.3 ms against 3.6 ms in groups of 64 (projections on the fly, 51 outputs, joint width 640, B = 4),
+// 0.44 ms against 0.37 ms (the smallest benchmark model, the same) and 22.9 ms against 17.3 ms in 16
+// groups (float32, joint width 1024, 51 outputs, B = 32).  An output layer of up to four tiles: two
+// hypotheses a group, at most 28 groups (that model, 32 groups: 19.5 ms; B = 64, 28 groups, 20.2 ms, 64
+// groups 21.3; in bfloat16 all of these are within 4 %).
+//   Projections on the fly and an output layer of up to four tiles: of a pass's rows every one is projected, so a
+// hypothesis gets at most one row tile of frames, and a group of its own -- what it has with projections ahead
+// of the loops (B = 60, 1.26 ms against 1.58 ms with 64 frames; 51 outputs, joint width 640, B = 32, 5.3 ms
+// against 9.4 ms).
+inline GroupSplit general_split(const SplitModel &m, int B, int max_grid, int streaming_least, bool frame_loop, bool on_the_fly)
 {
-    GroupSplit s = label_split(m, B, max_grid, streaming_least);
-    if (s.one_workgroup) {
-        s.one_workgroup = false;
-        s.n_clusters = stateless_groups(m, B, max_grid);
-        if (s.n_clusters > B && B > 1) s.n_clusters = B;
-        s.n_clusters = enough_groups(s.n_clusters, B);
+    GroupSplit s{1, false, kMaxWindow};
+    if (streaming_least > 0) return label_split(m, B, max_grid, streaming_least);
+    bool may_grow = false;
+    int n = m.lstm ? lstm_groups(m, B, max_grid, &may_grow)
+                   : stateless_groups(m, B, max_grid, frame_loop ? kTwoHyps : kThreeHyps);
+    if (may_grow && B >= 14 * 8) n = frame_loop ? full_tile_groups(B) : 8;
+    if (!m.lstm && m.nt_out <= 4 && !frame_loop) {
         if (on_the_fly) s.window_most = kRowTile;
+        else n = B / 2 > 28 ? 28 : B / 2 < 4 ? 4 : B / 2;
     }
+    if (n > B && B > 1) n = B;
+    s.n_clusters = enough_groups(n, B);
     return s;
 }
 
+// ---- automatic window of a joint pass: as many rows as give every workgroup at most one joint work item of
+// so many column tiles.  Fewer tiles make a shorter pass, more a longer window and fewer passes.
+// C workgroups a group, nt column tiles of the output layer, joint_tiles: the caller's choice or 0.
+TDT_HD inline int rows_of_items(int C, int nt, int tiles_per_item)
+{
+    const int tiles = C / ((nt + tiles_per_item - 1) / tiles_per_item);
+    return (tiles > 1 ? tiles : 1) * kRowTile;
+}
+// frames per hypothesis when n of them search, auto_rows rows are aimed at, and a window has at least
+// `least` and at most `most` frames: the row tiles it needs are paid for whole, so as many frames as fill them
+TDT_HD inline int window_of_rows(int n, int auto_rows, int least, int most)
+{
+    int w = auto_rows / n;
+    if (w < least) w = least;
+    const int fill = (n * w + kRowTile - 1) / kRowTile * kRowTile / n;
+    if (fill > w) w = fill;
+    return w > most ? most : w;
+}
+// label_loop.hip.  Four tiles an item -- one round of its kernel -- where that leaves the group three row
+// tiles (config 2 at B = 32, five groups of 51: 1.40 ms against 1.57 ms with eight) or every hypothesis of
+// the group five frames (stateless, 16 hypotheses in groups of two: 1.35 ms against 1.45 ms; in groups
+// of five, where it leaves three frames: 2.01 ms against 1.83 ms); else eight by the like rule (two row
+// tiles or five frames; config 2 at B = 128, eight groups of 32: 2.71 ms against 3.21 ms with four); else
+// twelve (B = 256, 16 groups of 16: 4.59 ms against 4.99 ms with eight).  By the hypotheses a group has
+// (hpc), not those that search: the last few that search are in a stretch of blanks and want a long
+// window (by the latter, B = 128: 3.23 ms).
+TDT_HD inline int label_joint_rows(int C, int nt, int joint_tiles, int hpc)
+{
+    const int four = C / ((nt + 3) / 4), eight = C / ((nt + 7) / 8);
+    return rows_of_items(C, nt, joint_tiles > 0                                     ? joint_tiles
+                                : four >= 3 || four * kRowTile >= 5 * hpc   ? 4
+                                : eight >= 2 || eight * kRowTile >= 5 * hpc ? 8
+                                                                            : 12);
+}
+// (window: the caller's, or 0.  Least windows of 2, 4 and 5 frames measured no better than 3 on the benchmark
+// models but where a workgroup has so many column tiles that streaming them is what a pass costs: 8198
+// outputs, B = 256, four frames 7.60 ms, three 7.80)
+TDT_HD inline int label_window(int n, int window, int auto_rows, int rows_cap, int C, int nt)
+{
+    int w = window > 0 ? window : window_of_rows(n, auto_rows, C * 12 < nt ? 4 : 3, kMaxWindow);
+    if (w > kMaxWindow) w = kMaxWindow;
+    return w * n > rows_cap ? rows_cap / n : w;
+}
+// The general kernel, whose rounds take eight tiles, one a wavefront.  bfloat16: eight in groups of five
+// hypotheses or more (the longer windows save more passes than the longer items cost: 2 to 5 % at 6 to 13
+// hypotheses a group), four in smaller groups (1 to 2 % the other way), up to eight where the
+// hypotheses' least windows of four frames would otherwise make more items than there are workgroups.  With
+// the label loop's rule instead, projections on the fly: config 2 at B = 32 2.87 ms against 2.79 ms, B = 128
+// in five groups 5.35 ms against 4.99 ms, config 3 1.36 ms against 1.29 ms.  float32, whose tiles are
+// twice the bytes: four (LSTM and joint width of 1024, B = 16, a label on every fourth frame: 2.02 ms
+// against 2.19 ms with eight; three labels a frame: 14.6 ms against 16.5 ms).
+// (hyps: those of this group)
+TDT_HD inline int general_joint_rows(bool bf16, int C, int nt, int joint_tiles, int hyps)
+{
+    int t = joint_tiles;
+    if (t <= 0) {
+        const int row_tiles = (hyps * 4 + kRowTile - 1) / kRowTile, fit = C / row_tiles > 1 ? C / row_tiles : 1;
+        t = (nt + fit - 1) / fit;
+        t = hyps >= 5 || t > 8 ? 8 : t < 4 ? 4 : t;
+        if (!bf16) t = 4;
+    }
+    return rows_of_items(C, nt, t);
+}
+TDT_HD inline int general_window(int n, int window, int auto_rows, int rows_cap, int most)
+{
+    int w = window > 0 ? window : window_of_rows(n, auto_rows, 3, most);
+    if (w > kMaxWindow) w = kMaxWindow;
+    return w * n > rows_cap ? rows_cap / n : w;
+}
+
+// ---- the predictor side of a group
 // What a workgroup of label_loop.hip owns of the predictor side: `na` column tiles of W_pred from `qt0` on,
 // `nr` of W_hh from `r0` on, and with those the hidden units u0 .. u0 + U - 1 (of every layer).
 struct PredShare {

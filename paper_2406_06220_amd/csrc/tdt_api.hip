@@ -344,7 +344,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     for (;;) {
         if (asked == 0)
             split = label ? label_split(sm, B, max_grid, streaming_least)
-                          : general_split(sm, B, max_grid, streaming_least, on_the_fly);
+                          : general_split(sm, B, max_grid, streaming_least, algorithm == TDT_ALG_FRAME_LOOPING, on_the_fly);
         n_clusters = split.n_clusters;
         if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;
         // every cluster gets max_grid / n_clusters workgroups; the launch is rounded up to whole

@@ -27,3 +27,12 @@ def test_small_output_layer_keeps_its_group(oracle_lib, gpu, dtype, H):   # noqa
     check(oracle_lib, gpu, cfg)
     out = run_gpu(gpu, cfg, *only_blanks(cfg), 10)
     assert (out["len"] == 0).all() and out["stats"]["joint_passes_max"] == 1
+
+
+def test_windows_of_the_general_kernel(oracle_lib, gpu):   # noqa: F811
+    """Projections on the fly at config 2's sizes: eight column tiles an item, so seven hypotheses look 11
+    frames ahead and six 13 (the label loop's rule gives six and eight), 250 frames in 23 passes."""
+    import dataclasses
+    cfg = dataclasses.replace(synth.CFG2, name="gen_windows", d_enc=64, emb_dim=64, vocab=1024)
+    out = run_gpu(gpu, cfg, *only_blanks(cfg), 10, projections=1)
+    assert out["stats"]["joint_passes_max"] == 23

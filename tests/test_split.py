@@ -20,12 +20,19 @@ extern "C" void pred_share_c(int deep, int nt_a, int nt_b, int h_pred, int C, in
     const int v[6] = {s.qt0, s.na, s.r0, s.nr, s.u0, s.U};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
-extern "C" void group_split_c(int general, int lstm, int nt_a, int nt_b, int nt_out, int B, int streaming_least, int on_the_fly, int *out)
+extern "C" void group_split_c(int general, int lstm, int nt_a, int nt_b, int nt_out, int B, int streaming_least,
+                              int frame_loop, int on_the_fly, int *out)
 {
     const SplitModel m{lstm != 0, nt_a, nt_b, nt_out};
-    const GroupSplit s = general ? general_split(m, B, 256, streaming_least, on_the_fly != 0) : label_split(m, B, 256, streaming_least);
+    const GroupSplit s = general ? general_split(m, B, 256, streaming_least, frame_loop != 0, on_the_fly != 0)
+                                 : label_split(m, B, 256, streaming_least);
     const int v[3] = {s.n_clusters, s.one_workgroup, s.window_most};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
+}
+extern "C" int window_c(int general, int C, int nt, int hyps, int hpc, int n, int window, int rows_cap, int most)
+{
+    return general ? general_window(n, window, general_joint_rows(general == 1, C, nt, 0, hyps), rows_cap, most)
+                   : label_window(n, window, label_joint_rows(C, nt, 0, hpc), rows_cap, C, nt);
 }
 """
 
@@ -67,11 +74,11 @@ def test_stateless_predictor_has_no_share(split):
     assert list(out) == [0] * 6
 
 
-def group_split(split, cfg, general=0, on_the_fly=0, streaming=0):
+def group_split(split, cfg, general=0, on_the_fly=0, streaming=0, frame_loop=0):
     out = (C.c_int * 3)()
     lstm = int(cfg.pred_kind == "lstm")
     split.group_split_c(general, lstm, -(-cfg.h_joint // 16), -(-cfg.h_pred // 4), -(-cfg.n_out // 16), cfg.B,
-                        4 * streaming, on_the_fly, out)
+                        4 * streaming, frame_loop, on_the_fly, out)
     return list(out)
 
 
@@ -90,9 +97,9 @@ def test_group_counts_over_all_sizes(split, kind, general):
     for vocab in (1, 40, 63, 64, 1024, 9000):
         for H, Hp in ((8, 8), (640, 640), (2048, 1024)):
             for B in (1, 2, 3, 15, 16, 64, 111, 112, 300, 1500, 16640, 65536):
-                for streaming in (0, 1):
+                for streaming, frame_loop in ((0, 0), (1, 0), (0, general)):
                     cfg = synth.small_config("split", pred_kind=kind, vocab=vocab, h_joint=H, h_pred=Hp, emb_dim=Hp, B=B)
-                    n, one, most = group_split(split, cfg, general, 0, streaming)
+                    n, one, most = group_split(split, cfg, general, 0, streaming, frame_loop)
                     assert 1 <= n <= 256 and -(-B // n) <= 256 and most == 64
                     assert not (general and one) and (not one or n == min(B, 256))
                     if general and B <= 64 * 64:
@@ -105,3 +112,35 @@ def test_projections_on_the_fly_of_small_output_layers(split):
         cfg = synth.CFG1.with_batch(B)
         assert group_split(split, cfg) == [B, 1, 64]
         assert group_split(split, cfg, general=1, on_the_fly=1) == [B, 0, 16]
+
+
+def test_group_counts_of_the_general_kernel(split):
+    """Where its rules leave the label loop's."""
+    b256 = synth.CFG2.with_batch(256)
+    assert group_split(split, b256)[0] == 16 and group_split(split, b256, general=1)[0] == 8
+    assert group_split(split, b256, general=1, frame_loop=1)[0] == 16
+    assert [group_split(split, synth.CFG4.with_batch(32), general=1, frame_loop=f)[0] for f in (0, 1)] == [11, 23]
+    assert group_split(split, synth.CFG1.with_batch(32), general=1)[0] == 16
+
+
+def test_windows(split):
+    """A window has at least a frame, at most 64 or the longest asked for, keeps its pass within the row limit and
+    fills the row tiles it needs; the general kernel's items take eight column tiles (config 2: 11 frames
+    of seven hypotheses), the label loop's four there (six frames)."""
+    assert split.window_c(1, 51, 65, 7, 7, 7, 0, 448, 64) == 11 and split.window_c(0, 51, 65, 7, 7, 7, 0, 256, 64) == 6
+    assert split.window_c(2, 51, 65, 7, 7, 7, 0, 448, 64) == 6   # (float32: four tiles)
+    for general, cap in ((1, 1024), (2, 1024), (0, 256)):
+        for C_ in (1, 2, 9, 17, 51, 128, 256):
+            for nt in (1, 4, 5, 65, 513):
+                for hyps in (1, 4, 5, 16, 64):
+                    rows_cap = min(hyps * 64, cap)
+                    for n in range(1, hyps + 1):
+                        for window, most in ((0, 64), (0, 16), (1, 64), (64, 64)):
+                            w = split.window_c(general, C_, nt, hyps, hyps, n, window, rows_cap, most)
+                            assert 1 <= w <= 64 and w * n <= rows_cap
+                            if window:
+                                assert w == min(window, rows_cap // n)
+                            elif general:
+                                assert w <= most
+                            if not window and w < (most if general else 64) and w * n <= rows_cap - n:
+                                assert -(-n * (w + 1) // 16) > -(-n * w // 16)   # (a frame more takes a row tile more)
