@@ -59,10 +59,6 @@
 #include "exchange.h"
 #include "tile_gemm.h"
 
-#ifndef TDT_TIMER_GROUP
-#define TDT_TIMER_GROUP 0   // the hypothesis group whose phase timers a build with TDT_PHASE_TIMERS reports
-#endif
-
 namespace tdt {
 namespace {
 
@@ -1266,6 +1262,13 @@ size_t lds_bytes_for(const tdt_weights_t *w, bool on_the_fly)
 }
 
 }  // namespace
+
+#if TDT_TRACE
+hipError_t copy_trace_general(long long *out, int n)
+{
+    return hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
+}
+#endif
 
 hipError_t launch_init(const ClearRanges &clear, long long *out_stats, hipStream_t stream)
 {

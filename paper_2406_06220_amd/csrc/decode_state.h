@@ -18,14 +18,12 @@
 #define TDT_PHASE_TIMERS TDT_FINE_TIMERS
 #endif
 
-// 1: profiling build.  Thread 0 of workgroup 0 records (event id, device wall clock) pairs of a
-// few label-loop iterations into a device array that tdt_debug_trace() copies out -- a time line
-// of one workgroup through the phases, their barriers and the steps of a work item.
-#ifndef TDT_TRACE
-#define TDT_TRACE 0
+#ifndef TDT_TIMER_GROUP
+#define TDT_TIMER_GROUP 0   // the hypothesis group whose phase timers are reported
 #endif
 
 #if TDT_TRACE
+// (an array in each kernel's file; tdt_debug_trace reads that of the last call's kernel)
 static __device__ long long g_trace[8192];   // [0]: events recorded; then (id << 48) | ticks
 namespace tdt {
 namespace {

@@ -51,14 +51,6 @@
 #include "split.h"
 #include "tile_gemm.h"
 
-#if TDT_TRACE
-// profiling builds only: copies the recorded time line (see TR in decode_state.h) to the host
-extern "C" int tdt_debug_trace(long long *out, int n)
-{
-    return (int)hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
-}
-#endif
-
 namespace tdt {
 namespace {
 
@@ -1782,7 +1774,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             atomicMax((unsigned long long *)&p.out_stats[TDT_STAT_JOINT_PASSES_MAX],
                       (unsigned long long)st_joint_passes);
             if (!ok) add(TDT_STAT_ABORT, 1);
-            if (TDT_PHASE_TIMERS && cl == 0) {   // where the first group's time went, in wall-clock ticks
+            if (TDT_PHASE_TIMERS && cl == TDT_TIMER_GROUP) {   // where one group's time went, in wall-clock ticks
                 add(TDT_STAT_TICKS_PRED, S.tk[kTkP]);
                 add(TDT_STAT_TICKS_PROJ, S.tk[kTkQ]);
                 add(TDT_STAT_TICKS_JOINT, S.tk[kTkJ]);
@@ -1872,6 +1864,13 @@ static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool c
     }
     return (n + 15) / 16 * 16;
 }
+
+#if TDT_TRACE
+hipError_t copy_trace_label(long long *out, int n)
+{
+    return hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
+}
+#endif
 
 bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
 {

@@ -199,7 +199,19 @@ static int check_model_pointers(const tdt_weights_t *w, bool need_decoder)
 
 using namespace tdt;
 
+#if TDT_TRACE
+static bool g_traced_label;   // (profiling builds: one thread, one stream)
+#endif
+
 extern "C" {
+
+#if TDT_TRACE
+// copies the time line that the last call's kernel recorded (see TR in decode_state.h) to the host
+int tdt_debug_trace(long long *out, int n)
+{
+    return (int)(g_traced_label ? copy_trace_label(out, n) : copy_trace_general(out, n));
+}
+#endif
 
 int tdt_workspace_bytes(const tdt_weights_t *weights, int B, int T, int u_cap, size_t *bytes)
 {
@@ -485,6 +497,9 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
         p.timeout_ticks = wait_timeout_us > 0 ? (long long)wait_timeout_us * khz / 1000 : 4000LL * khz;
         if (p.timeout_ticks < 1) p.timeout_ticks = 1;
     }
+#if TDT_TRACE
+    g_traced_label = label;
+#endif
     if (label) {
         p.hbuf = reinterpret_cast<float *>(lb + LL.hx);
         p.pred_proj = reinterpret_cast<float *>(lb + LL.px);

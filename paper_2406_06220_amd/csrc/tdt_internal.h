@@ -7,6 +7,13 @@
 #include "split.h"
 #include "tdt_decode.h"
 
+// 1: profiling build.  Thread 0 of workgroup 0 records (event id, device wall clock) pairs of a
+// few label-loop iterations into a device array that tdt_debug_trace() copies out -- a time line
+// of one workgroup through the phases, their exchanges and the steps of a work item.
+#ifndef TDT_TRACE
+#define TDT_TRACE 0
+#endif
+
 namespace tdt {
 
 constexpr int kThreads = 512;                 // threads per workgroup of the decode kernel
@@ -177,6 +184,10 @@ hipError_t launch_decode(const DecodeParams &p, const tdt_weights_t *w, DecodeVa
 hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chunked, bool wide, int grid, hipStream_t stream);
 // largest grid the decode kernel can run with all workgroups resident, 0 on error
 int decode_max_grid(const tdt_weights_t *w, DecodeVariant v);
+#if TDT_TRACE
+hipError_t copy_trace_general(long long *out, int n);
+hipError_t copy_trace_label(long long *out, int n);
+#endif
 // ticks per millisecond of the device wall clock the kernels read (100000 if the query fails)
 int wall_clock_khz();
 

@@ -101,3 +101,19 @@ def test_rows_written_by_others_are_only_read_in_the_loop_that_rereads():
     calls = [m.start() for m in re.finditer(r"\bldx4\(", body)]
     inside = [m.span() for m in re.finditer(r"until_there\(\[&\]\(\).*?\n\s*}\);", body, re.S)]
     assert calls and all(any(a < c < b for a, b in inside) for c in calls)
+
+
+def test_every_traced_kernel_is_read():
+    """A profiling build's time line sits in an array of each kernel's own file: every file that records
+    one hands it out, and tdt_debug_trace reads them all."""
+    import glob
+    import re
+    csrc = os.path.join(ROOT, "paper_2406_06220_amd", "csrc")
+    text = {f: open(f).read() for f in glob.glob(os.path.join(csrc, "*.hip"))}
+    api = text[os.path.join(csrc, "tdt_api.hip")]
+    reader = re.search(r"int tdt_debug_trace\(.*?\n}", api, re.S).group(0)
+    recording = [f for f, s in text.items() if re.search(r"\bTR\(\d", s)]
+    assert len(recording) == 2
+    for f in recording:
+        copy = re.search(r"hipError_t (copy_trace_\w+)\(.*?g_trace", text[f], re.S)
+        assert copy and copy.group(1) + "(" in reader, f
