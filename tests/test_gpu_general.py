@@ -36,3 +36,29 @@ def test_windows_of_the_general_kernel(oracle_lib, gpu):   # noqa: F811
     cfg = dataclasses.replace(synth.CFG2, name="gen_windows", d_enc=64, emb_dim=64, vocab=1024)
     out = run_gpu(gpu, cfg, *only_blanks(cfg), 10, projections=1)
     assert out["stats"]["joint_passes_max"] == 23
+
+
+# ------------------------------------------------------------------ the streaming joint pass of this kernel
+def streamed(**kw):
+    base = dict(dtype="bf16", pred_kind="lstm", d_enc=48, h_pred=56, emb_dim=24, h_joint=72, vocab=700, B=13, T=30, len_lo=0,
+                len_hi=30, seed=402, default_blank_bias=1.5, max_symbols=3)
+    base.update(kw)
+    return synth.small_config("gen_streaming", **base)
+
+
+@pytest.mark.parametrize("kw,opts", [
+    # an LSTM wider than label_loop.hip's reductions: labels and durations in one tile, a last tile that is
+    # mostly padding; several row tiles of a pass; a joint width that is no multiple of a chunk, the widest
+    (dict(h_pred=1096, vocab=4501, durations=(0, 1, 2, 4)), {}), (dict(h_pred=1032, B=40), dict(window=9, n_clusters=4)),
+    (dict(h_pred=1032, h_joint=1000, B=5, T=12, len_hi=12), dict(window=1)), (dict(h_pred=1032, h_joint=1024, B=5, T=12, len_hi=12), {}),
+    # more hypotheses a group than it has lanes for
+    (dict(B=300, T=14, len_hi=14), dict(n_clusters=4)), (dict(B=270, T=14, len_hi=14, durations=(0, 2)), dict(n_clusters=4, window=64)),
+    (dict(B=300, T=14, len_hi=14, pred_kind="stateless", pred_layers=2, h_pred=48), dict(n_clusters=4)),
+    (dict(B=270, T=14, len_hi=14, durations=(2, 3), multi_blank=True), dict(n_clusters=4))])
+def test_streaming_joint_pass_of_the_general_kernel(oracle_lib, gpu, kw, opts):   # noqa: F811
+    check(oracle_lib, gpu, streamed(**kw), joint_kernel=2, **opts)
+
+
+def test_streaming_joint_pass_of_the_general_kernel_in_chunks(oracle_lib, gpu):   # noqa: F811
+    from test_gpu_chunks import check_chunks
+    check_chunks(oracle_lib, gpu, streamed(h_pred=1032, durations=(0, 1, 5)), "random", 3, joint_kernel=2)
