@@ -1219,12 +1219,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         }
                 }
             }
-            const int ntq = LAYERS == 1 ? 0 : (G + RT - 1) / RT;
+            const int ntq = (G + RT - 1) / RT;
             // ---- deeper layers: W_ih . [h of the layer below] + what W_hh . h left here
+            if constexpr (DEEP)
 #pragma clang loop unroll(disable)
-            for (int l = 0; DEEP && l < L; ++l) {
+            for (int l = 0; l < L; ++l) {
                 const int row0 = (par * L + l) * Bw + b0;
-                const bool top = !DEEP || l == L - 1;
+                const bool top = l == L - 1;
                 // What this layer's h is multiplied by.  Below the top: first the next layer's input
                 // product (its cell follows at once), then the recurrent product for the next label;
                 // the top layer: the list of W_pred and W_hh tiles in order.
@@ -1251,7 +1252,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     lap(kTkBar);
                     fresh();
 #pragma clang loop unroll(disable)
-                    for (int kind = 0; kind < (DEEP ? kinds : 1); ++kind) {
+                    for (int kind = 0; kind < kinds; ++kind) {
                         const bool input = !top && kind == 0;
 #pragma clang loop unroll(disable)
                         for (int t0 = 0; t0 < n_all; t0 += TQ) {
@@ -1314,7 +1315,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             }
                             // (the partial sums are written again behind the next barrier only if another
                             // round, row tile or layer follows; a joint pass has its own)
-                            if (t0 + TQ < n_all || kind + 1 < kinds || tq + 1 < ntq || (DEEP && l + 1 < L)) __syncthreads();
+                            if (t0 + TQ < n_all || kind + 1 < kinds || tq + 1 < ntq || l + 1 < L) __syncthreads();
                         }
                     }
                 }
