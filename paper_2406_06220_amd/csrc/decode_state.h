@@ -1,7 +1,7 @@
 // Shapes of the tile GEMMs and what a workgroup of the decode kernel keeps in LDS: its replica
 // of the per-hypothesis control state (paper Sec. 3.1: the batched hypothesis arrays), the
 // scratch of the current work item, and the descriptors a phase hands to the tile code.
-// Included by decode.hip only.
+// (label_loop.hip keeps its own state; it uses the tile shapes, the vector types and the profiling macros.)
 #ifndef TDT_DECODE_STATE_H
 #define TDT_DECODE_STATE_H
 

@@ -1,7 +1,6 @@
 // How the workgroups of a cluster exchange data and wait for each other: agent-scope relaxed
-// atomics that are served at the device's coherence point, packed (value, index) cells for
-// atomic maxima, the split barrier, and the small list / split helpers of the label loop.
-// Included by decode.hip only.
+// atomics that are served at the device's coherence point, packed (value, index) cells, reductions across
+// lanes (both kernels); the split barrier and the small list / split helpers of decode.hip's label loop.
 #ifndef TDT_EXCHANGE_H
 #define TDT_EXCHANGE_H
 

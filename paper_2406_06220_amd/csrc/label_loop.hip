@@ -1,11 +1,14 @@
-// The label-looping decoder (paper Algorithm 3, Sec. 3.2; TDT Sec. 3.3) as a chain of three
-// exchanges per label.  decode.hip holds the general kernel and explains the phases P (predictor
-// step), Q (products with the new predictor state), J (joint pass) and D (decision); this one runs
-// the same phases for the default loops (label-looping, precomputed projections) of groups of at
-// most kLabelMaxHyps hypotheses whose rows fit one staging tile, and is built for the length of
-// the chain: at the benchmark sizes a label costs two exchanges between workgroups that are
-// about 1.4 us each whatever they carry, so what matters is how many dependent steps there are
-// between them and how few instructions each takes.
+// The label-looping decoder (paper Algorithm 3, Sec. 3.2; TDT Sec. 3.3) as a chain of
+// exchanges: two for the predictor side of a label, one for every joint pass.  decode.hip holds the
+// general kernel and explains the phases P (predictor step), Q (products with the new predictor state),
+// J (joint pass) and D (decision); this one runs the same phases for the default loops (label-looping,
+// precomputed projections) of groups of at most kLabelMaxHyps hypotheses with reductions of the compiled
+// lengths (label_form), and is built for the length of the chain: an exchange between workgroups is about
+// 1.4 us whatever it carries, so what matters is how many dependent steps there are between them and how
+// few instructions each takes.  Config 2 at B = 32, a label with one joint pass, microseconds by a time line
+// of one workgroup: P 1.4; the pass set up while the hidden state travels 1.2, and 0.8 until it is there; Q
+// 2.0; rows and weights of the pass requested 1.0, and 0.5 until the projected output is there; J 2.9;
+// cells gathered 1.3; D 1.0 (13 with the time stamps; 12 a label without).
 //
 //   * No barriers between workgroups.  Every exchanged word says itself whether it is there: rows
 //     of the hidden state and of the projected predictor output start out as a bit pattern that no
@@ -22,8 +25,10 @@
 //     is taken by every wavefront on its own, without a workgroup barrier or LDS list.
 //   * Four wavefronts a workgroup, one per SIMD.  What a label costs beside the exchanges is the number
 //     of instructions in a row, and two wavefronts that share a SIMD take turns at them.  It also
-//     leaves 512 registers a lane: the workgroup's predictor-side weights stay in registers for the
-//     whole call where they fit one round.
+//     leaves 512 registers a lane, for the rows and the weights of a whole round at once; the weights of
+//     phase Q are requested anew for every label, behind its table row and ahead of the exchange that hides
+//     them.  Scalar registers are short: 100 to 400 scalar values of a form are kept in lanes of vector
+//     registers and moved back where they are used (243 in the one-layer form for reductions to 640).
 //   * Every wavefront multiplies its own quarter of the reduction for all column tiles.  So no two
 //     wavefronts need the same activation: each loads, waits for and splits its quarter of the rows in
 //     the registers the matrix cores read, and only the partial sums go through LDS (rows staged in LDS
@@ -814,7 +819,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // of its eighth of the reduction in registers and reads of the weights only that eighth; a batch
     // of TB tiles is multiplied while the next one is on its way into the registers it leaves and the
     // sums of the one before go through LDS into running statistics, two columns a thread, by pieces
-    // between the products.  Measured at 8198 outputs, joint width 1024, 16 workgroups a group (33 tiles
+    // between the products.  The three planes of a product share one accumulator, smallest first within a
+    // step (registers); score error against 64 bits at 8198 outputs, joint width 1024: 2.2e-6 rms per root of
+    // a label count, 2.8e-6 in decode.hip's streaming pass, which keeps three and adds the smallest first.
+    // Measured at 8198 outputs, joint width 1024, 16 workgroups a group (33 tiles
     // each): one row tile 1.28 us per four tiles (the stream alone 1.05 us: 126 GB/s a compute unit), two
     // 1.03 us per two tiles (matrix cores alone 0.64); 33 tiles against 48 rows 22 us + 14 us,
     // 30 us on average in decode.hip's streaming pass, of which a call at B = 256 has 2.8 a label.
@@ -1824,7 +1832,9 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
 {
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
     LabelForm f{nullptr, 0, wide ? 8 : 4, 0, lstm ? 2 : 0};
-    // bfloat16: steps of 32 inputs (reductions of up to 640 and 1024), float32: of 16 (256 and 640)
+    // bfloat16: steps of 32 inputs (reductions of up to 640 and 1024), float32: of 16 (256 and 640; for 1024,
+    // 16 steps a wavefront, the rows of two operands and the weights of a round would take more than the 512
+    // registers of a lane: 128 and 128 in a joint pass, 256 more for the round of phase Q held meanwhile)
     const int steps = label_steps(w, f.nw);
     if (wide) {
         f.nk = 4;

@@ -31,8 +31,9 @@ struct GroupSplit {
 // holds the shorter its joint passes, so more groups pay -- until a group has too few workgroups
 // to give each at most four column tiles of the predictor-side products (two weight batches per
 // wavefront); that many groups are the rule from 16 hypotheses on.  Small batches: two groups
-// also for a single hypothesis (half the workgroups synchronise faster), four from four hypotheses on
-// (3 to 8 % faster than two at B = 4 ... 12; measured on the general kernel).
+// also for a single hypothesis, whose group then has half the workgroups, four from four hypotheses on.
+// label_loop.hip, config 2, microseconds in 1 / 2 / 4 groups: B = 1, 372 / 365 / 379; B = 4, 954 / 809 / 757;
+// B = 12, 1445 / 1126 / 978 (five groups: 374, 739, 950); general kernel: 3 to 8 % from two to four at B = 4 ... 12.
 // Returned beside it: whether a larger batch takes yet more groups.
 inline int lstm_groups(const SplitModel &m, int B, int max_grid, bool *may_grow)
 {

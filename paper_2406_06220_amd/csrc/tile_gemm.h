@@ -1,7 +1,7 @@
 // The small-M GEMM every heavy phase of the decode kernel is made of: 16 activation rows staged
 // in LDS (split exactly into three bfloat16 planes for the matrix cores) against 16-column
 // tiles of a weight matrix; run_item drives one work item through staging, products and
-// epilogue.  Included by decode.hip only.
+// epilogue.  The work items are decode.hip's; label_loop.hip uses the row layout and the reductions.
 #ifndef TDT_TILE_GEMM_H
 #define TDT_TILE_GEMM_H
 
