@@ -69,13 +69,15 @@ def algorithmic_bytes(cfg, stats):
 def roofline_block(cfg, stats, kernel_ms, kernel_ms_min=None):
     per_group, one_stream = algorithmic_bytes(cfg, stats)
     k_s = kernel_ms * 1e-3
-    blk = {"bound": "hbm", "kernel": "decode_kernel",
+    blk = {"bound": "hbm", "kernel": "label_kernel",
            "achieved": per_group / k_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": per_group / k_s / 1e9 / HBM_PEAK_GBS,
            "algorithmic_bytes_per_launch": per_group,
            "achieved_one_stream_per_step": one_stream / k_s / 1e9,
            "frac_one_stream_per_step": one_stream / k_s / 1e9 / HBM_PEAK_GBS,
            "algorithmic_bytes_one_stream_per_step": one_stream,
+           "note": "achieved and frac count the matrices once per pass of every group; nearly all of that comes from L2 "
+                   "(traffic: the HBM side), so frac says how busy the load path is and can exceed 1",
            "kernel_ms": kernel_ms,
            "traffic": traffic_from_profiles(cfg.name),
            "traffic_source": "profiles/hbm_traffic.json (rocprofv3 FETCH_SIZE / WRITE_SIZE of an earlier "

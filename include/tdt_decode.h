@@ -278,10 +278,10 @@ int tdt_greedy_decode(const void *enc, const int32_t *enc_len, int B, int T,
  * nothing; everything else -- arguments, outputs, options, error codes, asynchrony -- is
  * tdt_greedy_decode's.
  *
- * Limit: tdt_workspace_bytes(weights, B, T, u_cap) must not exceed
- * TDT_STATIC_SCRATCH_BYTES (64 MiB: e.g. B = 32 utterances of T = 250 frames with a joint
- * width of 640 and a 1024-label LSTM predictor need 37 MB); otherwise TDT_ERR_TOO_LARGE, and
- * nothing is enqueued.  All calls on one GPU share that GPU's array, which still holds what
+ * Limit: the least workspace of the call, which is below tdt_workspace_bytes(weights, B, T,
+ * u_cap), must not exceed TDT_STATIC_SCRATCH_BYTES (64 MiB: e.g. B = 32 utterances of T = 250
+ * frames with a joint width of 640 and a 1024-label LSTM predictor of width 640 in bfloat16 need
+ * 48.4 MB); otherwise TDT_ERR_TOO_LARGE, and nothing is enqueued.  All calls on one GPU share that GPU's array, which still holds what
  * the previous call left there; the call clears, with a kernel on `stream`, every part that
  * has to start at zero.  Calls that overlap on one GPU (different streams, or host threads
  * without ordering between them) race on the array and give undefined results; calls on
