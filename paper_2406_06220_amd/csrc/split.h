@@ -144,16 +144,6 @@ TDT_HD inline int rows_of_items(int C, int nt, int tiles_per_item)
     const int tiles = C / ((nt + tiles_per_item - 1) / tiles_per_item);
     return (tiles > 1 ? tiles : 1) * kRowTile;
 }
-// frames per hypothesis when n of them search, auto_rows rows are aimed at, and a window has at least
-// `least` and at most `most` frames: the row tiles it needs are paid for whole, so as many frames as fill them
-TDT_HD inline int window_of_rows(int n, int auto_rows, int least, int most)
-{
-    int w = auto_rows / n;
-    if (w < least) w = least;
-    const int fill = (n * w + kRowTile - 1) / kRowTile * kRowTile / n;
-    if (fill > w) w = fill;
-    return w > most ? most : w;
-}
 // label_loop.hip.  Four tiles an item -- one round of its kernel -- where that leaves the group three row
 // tiles (config 2 at B = 32, five groups of 51: 1.40 ms against 1.57 ms with eight) or every hypothesis of
 // the group five frames (stateless, 16 hypotheses in groups of two: 1.35 ms against 1.45 ms; in groups
@@ -170,14 +160,24 @@ TDT_HD inline int label_joint_rows(int C, int nt, int joint_tiles, int hpc)
                                 : eight >= 2 || eight * kRowTile >= 5 * hpc ? 8
                                                                             : 12);
 }
-// (window: the caller's, or 0.  Least windows of 2, 4 and 5 frames measured no better than 3 on the benchmark
+// Frames per hypothesis when n of them search and auto_rows rows are aimed at (window: the caller's, or 0;
+// rows_cap: rows of a pass).  Least windows of 2, 4 and 5 frames measured no better than 3 on the benchmark
 // models but where a workgroup has so many column tiles that streaming them is what a pass costs: 8198
-// outputs, B = 256, four frames 7.60 ms, three 7.80)
+// outputs, B = 256, four frames 7.60 ms, three 7.80.
 TDT_HD inline int label_window(int n, int window, int auto_rows, int rows_cap, int C, int nt)
 {
-    int w = window > 0 ? window : window_of_rows(n, auto_rows, C * 12 < nt ? 4 : 3, kMaxWindow);
+    int w = window;
+    if (w <= 0) {
+        w = auto_rows / n;
+        const int least = C * 12 < nt ? 4 : 3;
+        if (w < least) w = least;
+        // the row tiles this window needs are paid for whole: as many frames as fill them
+        const int fill = (n * w + kRowTile - 1) / kRowTile * kRowTile / n;
+        if (fill > w) w = fill;
+    }
     if (w > kMaxWindow) w = kMaxWindow;
-    return w * n > rows_cap ? rows_cap / n : w;
+    if (w * n > rows_cap) w = rows_cap / n;
+    return w;
 }
 // The general kernel, whose rounds take eight tiles, one a wavefront.  bfloat16: eight in groups of five
 // hypotheses or more (the longer windows save more passes than the longer items cost: 2 to 5 % at 6 to 13
@@ -199,11 +199,20 @@ TDT_HD inline int general_joint_rows(bool bf16, int C, int nt, int joint_tiles, 
     }
     return rows_of_items(C, nt, t);
 }
+// (most: the longest automatic window)
 TDT_HD inline int general_window(int n, int window, int auto_rows, int rows_cap, int most)
 {
-    int w = window > 0 ? window : window_of_rows(n, auto_rows, 3, most);
+    int w = window;
+    if (w <= 0) {
+        w = auto_rows / n;
+        if (w < 3) w = 3;   // (2, 4 and 5 measured no better on any benchmark model)
+        const int fill = (n * w + kRowTile - 1) / kRowTile * kRowTile / n;
+        if (fill > w) w = fill;
+        if (w > most) w = most;
+    }
     if (w > kMaxWindow) w = kMaxWindow;
-    return w * n > rows_cap ? rows_cap / n : w;
+    if (w * n > rows_cap) w = rows_cap / n;
+    return w;
 }
 
 // ---- the predictor side of a group

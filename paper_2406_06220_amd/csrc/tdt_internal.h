@@ -49,7 +49,6 @@ struct DecodeParams {
     int pred_kind, pred_layers, h_pred, emb_dim;
     int max_symbols, u_cap;
     int window;            // 0 = automatic
-    int window_most;       // longest automatic window (decode.hip)
     int joint_tiles;       // column tiles per joint work item the automatic window aims at (0 = automatic: 4 to 12)
     int kseg_max;          // longest K segment staged at once (set by launch_decode)
     int lds_bytes;         // dynamic LDS of the launch, a multiple of 16 (set by launch_decode)
@@ -101,6 +100,7 @@ struct DecodeParams {
     unsigned *barrier;       // one flag word per workgroup, a cluster's flags side by side
     int *abort_flag;
     long long timeout_ticks; // bound on one wait, in wall-clock ticks
+    int window_most;         // longest automatic window (decode.hip)
 };
 
 struct WorkspaceLayout {
