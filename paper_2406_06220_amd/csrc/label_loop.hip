@@ -219,10 +219,6 @@ __device__ inline float sigmoid(float x)
 // So rows are loaded that way and change lanes through LDS, in an area of the wavefront's own: no barrier.
 // With the split between the products below, one case timed alone on both sides: stateless at B = 128 2.74 -> 2.42
 // ms, config 2 at B = 32 1.53 -> 1.47 ms, at B = 128 2.51 -> 2.39 ms, config 3 at B = 32 0.62 -> 0.59 ms.
-// Column tiles of a joint pass's first round.  A stateless group of few workgroups has items of eight tiles: in one round
-// there are as many products as the split between them leaves room for, and one look at the sums instead of two
-// (65 tiles, B = 128: 2.20 ms in rounds of four, 2.12).
-constexpr int first_tiles(int layers, int nk, int nw, int planes) { return layers == 0 && nk <= 5 && nw == 4 && planes == 3 ? 8 : label_tiles(nk); }
 constexpr bool stages_rows(int layers, int nw) { return layers < 2 && nw == 4; }
 constexpr int staged_row(int nk, int ks) { return nk * ks + 4; }   // floats (padded: 16 rows start in 16 different banks)
 // a second area for the predictor's rows, which then stay from pass to pass of a label
@@ -2247,14 +2243,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 
 constexpr size_t kLabelDynLds = kLdsBytes - sizeof(LabelShared) - 256;   // (the rest: what the compiler adds)
 
-// the compiled form for a model: steps of the reduction a wavefront takes
-int label_steps(const tdt_weights_t *w, int wavefronts)
-{
-    const int ks = w->dtype == 1 ? 32 : 16;
-    int k = w->h_joint;
-    if (w->pred_kind == TDT_PRED_LSTM && w->h_pred > k) k = w->h_pred;
-    return ((k + ks - 1) / ks + wavefronts - 1) / wavefronts;
-}
 int label_kseg(const tdt_weights_t *w)
 {
     return w->pred_kind == TDT_PRED_LSTM && w->h_pred > w->h_joint ? w->h_pred : w->h_joint;
@@ -2286,15 +2274,14 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     // bfloat16: steps of 32 inputs (reductions of up to 640 and 1024), float32: of 16 (256 and 640; for 1024,
     // 16 steps a wavefront, the rows of two operands and the weights of a round would take more than the 512
     // registers of a lane: 128 and 128 in a joint pass, 256 more for the round of phase Q held meanwhile)
-    const int steps = label_steps(w, f.nw);
+    const int kseg = label_kseg(w);
     if (wide) {
         f.nk = 4;
-        if (w->dtype == 1 && steps <= f.nk) f.fn = label_wide_fn(lstm, chunked);
+        if (w->dtype == 1 && label_steps(true, kseg, f.nw) <= f.nk) f.fn = label_wide_fn(lstm, chunked);
         return f;
     }
-    if (w->dtype == 1) f.nk = steps <= 5 ? 5 : 8;
-    else f.nk = steps <= 4 ? 4 : 10;
-    if (steps > f.nk) return f;
+    f.nk = label_nk(w->dtype == 1, kseg);
+    if (f.nk == 0) return f;
     f.tq = label_tiles(f.nk);
     if (lstm && w->pred_layers == 1) {
         const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
@@ -2342,11 +2329,6 @@ hipError_t copy_trace_label(long long *out, int n)
     return hipMemcpyFromSymbol(out, HIP_SYMBOL(g_trace), (size_t)n * sizeof(long long));
 }
 #endif
-
-bool label_eight_a_round(const tdt_weights_t *w)
-{
-    return w->pred_kind != TDT_PRED_LSTM && w->dtype == 1 && first_tiles(0, (label_steps(w, 4) <= 5 ? 5 : 8), 4, 3) == 8;
-}
 
 bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
 {

@@ -344,9 +344,8 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     // Which kernel, and how the batch is split: label_loop.hip's kernel with the groups its rules give (or
     // the caller asks for) wherever it can -- the default loops, projections ahead of them, groups and
     // reductions it can hold, a workspace with room for its arrays -- else the general one with its own.
-    const SplitModel sm{weights->pred_kind == TDT_PRED_LSTM, (weights->h_joint + 15) / 16, (weights->h_pred + 3) / 4,
-                        (weights->vocab + 1 + weights->n_dur + 15) / 16,
-                        weights->pred_kind == TDT_PRED_LSTM && weights->pred_layers == 1, label_eight_a_round(weights)};
+    const SplitModel sm = split_model(weights->dtype == 1, weights->pred_kind == TDT_PRED_LSTM, weights->pred_layers, weights->h_joint,
+                                      weights->h_pred, weights->vocab + 1 + weights->n_dur);
     const int min_clusters = enough_groups(1, B), asked = n_clusters, streaming_least = wide_joint ? min_stream_clusters : 0;
     PackedLayout PL = packed_layout(weights);
     LabelLayout LL{};

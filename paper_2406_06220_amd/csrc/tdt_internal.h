@@ -27,12 +27,10 @@ constexpr int kMaxRankedBatch = 1024;          // largest batch whose hypotheses
 constexpr int kMaxDuration = 1 << 20;          // largest frame increment of a duration class
 constexpr int kRowBufs = 4;                   // rotating per-row argmax buffers
 constexpr size_t kLdsBytes = 160 * 1024;      // LDS of a compute unit
-// label_loop.hip: hypotheses a group can hold (one lane each), (hypothesis, frame) rows of a joint pass,
-// and column tiles multiplied per round (what the registers hold)
+// label_loop.hip: hypotheses a group can hold (one lane each), (hypothesis, frame) rows of a joint pass
 constexpr int kLabelThreads = 256;
 constexpr int kLabelMaxHyps = 64;
 constexpr int kLabelRowsPerPass = 256;
-constexpr int label_tiles(int nk) { return nk <= 5 ? 4 : 2; }   // (nk: steps of the reduction per wavefront)
 
 // Softmax-denominator share of one slice of label columns for one joint row.
 struct __align__(8) LsePartial {
@@ -123,8 +121,6 @@ struct LabelLayout {
 LabelLayout label_layout(const tdt_weights_t *w, bool wide, int n_clusters, int hyps_per_cluster, int C);
 // whether that kernel can decode groups of this many hypotheses on C workgroups each
 bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C);
-// whether it multiplies eight column tiles in the first round of a joint pass of this model (SplitModel)
-bool label_eight_a_round(const tdt_weights_t *w);
 
 // the caller-held state of tdt_greedy_decode_chunk: byte offsets of its arrays
 struct StateLayout {

@@ -20,20 +20,14 @@ extern "C" void pred_share_c(int deep, int nt_a, int nt_b, int h_pred, int C, in
     const int v[6] = {s.qt0, s.na, s.r0, s.nr, s.u0, s.U};
     for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
-extern "C" void group_split_c(int general, int lstm, int nt_a, int nt_b, int nt_out, int B, int streaming_least,
-                              int frame_loop, int on_the_fly, int *out)
+extern "C" void group_split_c(int general, int bf16, int lstm, int layers, int h_joint, int h_pred, int outputs, int B,
+                              int streaming_least, int frame_loop, int on_the_fly, int *out)
 {
-    const SplitModel m{lstm != 0, nt_a, nt_b, nt_out};
+    const SplitModel m = split_model(bf16 != 0, lstm != 0, layers, h_joint, h_pred, outputs);
     const GroupSplit s = general ? general_split(m, B, 256, streaming_least, frame_loop != 0, on_the_fly != 0)
                                  : label_split(m, B, 256, streaming_least);
     const int v[3] = {s.n_clusters, s.one_workgroup, s.window_most};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
-}
-extern "C" void label_split_c(int lstm, int nt_a, int nt_b, int nt_out, int one_layer, int eight, int B, int *out)
-{
-    const GroupSplit s = label_split(SplitModel{lstm != 0, nt_a, nt_b, nt_out, one_layer != 0, eight != 0}, B, 256, 0);
-    out[0] = s.n_clusters;
-    out[1] = s.one_workgroup;
 }
 extern "C" int window_c(int general, int C, int nt, int hyps, int hpc, int n, int window, int rows_cap, int most)
 {
@@ -82,29 +76,29 @@ def test_stateless_predictor_has_no_share(split):
 
 def group_split(split, cfg, general=0, on_the_fly=0, streaming=0, frame_loop=0):
     out = (C.c_int * 3)()
-    lstm = int(cfg.pred_kind == "lstm")
-    split.group_split_c(general, lstm, -(-cfg.h_joint // 16), -(-cfg.h_pred // 4), -(-cfg.n_out // 16), cfg.B,
-                        4 * streaming, frame_loop, on_the_fly, out)
+    split.group_split_c(general, int(cfg.dtype == "bf16"), int(cfg.pred_kind == "lstm"), cfg.pred_layers, cfg.h_joint, cfg.h_pred,
+                        cfg.n_out, cfg.B, 4 * streaming, frame_loop, on_the_fly, out)
     return list(out)
 
 
 def test_group_counts_of_the_benchmark_models(split):
     got = [group_split(split, c) for c in (synth.CFG1, synth.CFG2, synth.CFG3, synth.CFG4, synth.CFG2_B128,
                                            synth.CFG2.with_batch(1), synth.CFG2.with_batch(7), synth.CFG2.with_batch(256))]
-    assert got == [[4, 1, 64], [5, 0, 64], [5, 0, 64], [28, 0, 64], [8, 0, 64], [2, 0, 64], [4, 0, 64], [16, 0, 64]]
+    assert got == [[4, 1, 64], [5, 0, 64], [5, 0, 64], [28, 0, 64], [8, 0, 64], [2, 0, 64], [5, 0, 64], [16, 0, 64]]
     assert group_split(split, synth.CFG5, streaming=1) == [16, 0, 64]
 
 
 @pytest.mark.parametrize("general", [0, 1])
 @pytest.mark.parametrize("kind", ["lstm", "stateless"])
-def test_group_counts_over_all_sizes(split, kind, general):
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_group_counts_over_all_sizes(split, kind, general, dtype):
     """Groups exist, hold what they may hold, and the general kernel's are never single workgroups: with
     all of the chip's workgroups dealt out, a group of it has more than one while it can."""
     for vocab in (1, 40, 63, 64, 1024, 9000):
         for H, Hp in ((8, 8), (640, 640), (2048, 1024)):
             for B in (1, 2, 3, 15, 16, 64, 111, 112, 300, 1500, 16640, 65536):
                 for streaming, frame_loop in ((0, 0), (1, 0), (0, general)):
-                    cfg = synth.small_config("split", pred_kind=kind, vocab=vocab, h_joint=H, h_pred=Hp, emb_dim=Hp, B=B)
+                    cfg = synth.small_config("split", dtype=dtype, pred_kind=kind, vocab=vocab, h_joint=H, h_pred=Hp, emb_dim=Hp, B=B)
                     n, one, most = group_split(split, cfg, general, 0, streaming, frame_loop)
                     assert 1 <= n <= 256 and -(-B // n) <= 256 and most == 64
                     assert not (general and one) and (not one or n == min(B, 256))
@@ -153,19 +147,33 @@ def test_windows(split):
 
 
 def test_group_counts_of_forms_that_keep_their_weights(split):
-    """One LSTM layer: five groups already in small batches, never more than hypotheses but for one alone;
-    eight column tiles a round: groups by the items they make.  Every count is one a call can run with."""
-    def groups(lstm, one_layer, eight, B, nt_out=65, nt_a=40, nt_b=160):
-        out = (C.c_int * 2)()
-        split.label_split_c(lstm, nt_a, nt_b, nt_out, one_layer, eight, B, out)
-        assert not out[1]
-        return out[0]
-    assert [groups(1, 1, 0, B) for B in (1, 2, 3, 4, 5, 7, 15, 16, 32, 128)] == [2, 2, 3, 4, 5, 5, 5, 5, 5, 8]
-    assert [groups(1, 0, 0, B) for B in (1, 2, 3, 4, 5, 7, 15, 16, 32, 128)] == [2, 2, 2, 4, 4, 4, 4, 5, 5, 8]
-    assert [groups(1, 1, 0, B, nt_a=3, nt_b=8) for B in (1, 3, 5, 15)] == [2, 2, 4, 4]   # (many would fit)
-    assert [groups(0, 0, 1, B) for B in (1, 4, 25, 26, 32, 140, 141, 256)] == [5, 4, 5, 26, 28, 28, 42, 42]
-    for nt_out in (5, 8, 16, 64, 65, 200, 1025):
+    """One LSTM layer where five groups fit: five already in small batches while a group's workgroups have at most two
+    rounds of column tiles; three hypotheses in three groups where that makes no second round of one; never
+    more groups than hypotheses but for one alone.  Two layers, widths that leave a workgroup more tiles (and
+    with them not the one-layer form), models that more groups fit: four at most.  Eight column tiles a
+    round: groups by the items they make."""
+    def groups(B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025):
+        cfg = synth.small_config("split", dtype=dtype, pred_kind=kind, pred_layers=layers, h_joint=H, h_pred=Hp, emb_dim=Hp,
+                                 vocab=n_out - 1, B=B)
+        n, one, _ = group_split(split, cfg)
+        assert not one
+        return n
+    batches = (1, 2, 3, 4, 5, 7, 15, 16, 32, 128)
+    one_round, two_rounds, four = [2, 2, 3, 4, 5, 5, 5, 5, 5, 8], [2, 2, 2, 4, 5, 5, 5, 5, 5, 8], [2, 2, 2, 4, 4, 4, 4, 5, 5, 8]
+    for H, Hp in ((640, 640), (448, 640), (640, 592)):
+        assert [groups(B, H=H, Hp=Hp) for B in batches] == one_round, (H, Hp)
+        assert [groups(B, H=H, Hp=Hp, dtype="fp32") for B in batches] == two_rounds, (H, Hp)
+    for H, Hp in ((648, 648), (1024, 512), (128, 768)):
+        assert [groups(B, H=H, Hp=Hp) for B in batches] == two_rounds, (H, Hp)
+    for H, Hp in ((704, 704), (1024, 640), (512, 768)):
+        assert [groups(B, H=H, Hp=Hp) for B in batches] == four, (H, Hp)
+    assert [groups(B, layers=2) for B in batches] == four
+    assert [groups(B, H=48, Hp=40) for B in (1, 3, 5, 15)] == [2, 2, 4, 4]   # (many would fit)
+    assert [groups(B, H=768, Hp=768) for B in (2, 3, 4, 5, 15, 16)] == [2, 2, 4, 4, 4, 4]
+    assert [groups(B, H=1024, Hp=1024) for B in (2, 3, 4, 5, 15, 16)] == [2, 3, 3, 3, 3, 3]
+    assert [groups(B, kind="stateless") for B in (1, 4, 25, 26, 32, 140, 141, 256)] == [5, 4, 5, 26, 28, 28, 42, 42]
+    for n_out in (80, 128, 256, 1024, 1025, 3200, 16400):
         for B in (*range(1, 70), 128, 500, 20000):
-            for args in ((1, 1, 0), (0, 0, 1)):
-                n = groups(*args, B, nt_out)
-                assert max(1, -(-B // 256)) <= n <= max(64, -(-B // 256)) and (n <= B or B == 1), (args, nt_out, B)
+            for kind in ("lstm", "stateless"):
+                n = groups(B, kind=kind, n_out=n_out)
+                assert max(1, -(-B // 256)) <= n <= max(64, -(-B // 256)) and (n <= B or B == 1), (kind, n_out, B)
