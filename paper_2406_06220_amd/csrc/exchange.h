@@ -262,18 +262,6 @@ __device__ inline void build_two_lists(HypShared &S, int G, const unsigned char 
     __syncthreads();
 }
 
-// deal `n_units` column tiles to the workgroups left after `n_row_tiles` took theirs
-__device__ inline void split_tiles(int C, int n_row_tiles, int n_units, int max_groups, int &n_groups,
-                                   int &per_group)
-{
-    int g = C / (n_row_tiles > 0 ? n_row_tiles : 1);
-    if (g < 1) g = 1;
-    if (g > max_groups) g = max_groups;
-    if (g > n_units) g = n_units;
-    per_group = (n_units + g - 1) / g;
-    n_groups = (n_units + per_group - 1) / per_group;
-}
-
 }  // namespace
 }  // namespace tdt
 

@@ -247,7 +247,7 @@ struct LabelShared {
 // LAYERS: 0: stateless predictor; 1: one LSTM layer, a workgroup's column tiles fit one round and the
 // group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
 // NW: wavefronts.  Four, or (WIDE) eight for output layers of many thousands of columns, see wide_rows.
-// TQ: column tiles of a round of the predictor-side products.
+// TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round.
 template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW, int TQ>
 __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 {
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1, WIDE = NW == 8;
     constexpr int THREADS = NW * 64;
     constexpr int TR = label_tiles(NK);                       // column tiles per round of a joint pass
-    constexpr int TJ = first_tiles(LAYERS, NK, NW, PL);       // ... per its first round
+    constexpr int TJ = LAYERS == 0 && !WIDE ? TQ : TR;        // ... per its first round
     constexpr int JH = TJ > 4 ? 2 : 1;                        // which is looked at four tiles, four columns a thread, at a time
     constexpr int QPR = THREADS / RT;                         // threads that share a row of a round, four columns each
     static_assert(!WIDE || (LAYERS != 1 && TQ * CT <= QPR * 4), "eight wavefronts: a round is one pass of the threads");
@@ -1835,8 +1835,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 };
                 if (KEEP1 && !KEEP2 && n_ct > TJ) fetch_round(b2, bias1, TJ);
                 if constexpr (STREAMED) {
-                    // (all tiles: they are paid for by the split)
+                    // (all tiles: they are paid for by the split -- but half of them in the stateless form for small items, whose
+                    // passes of one or two tiles an item would else be slower than with the split ahead of the products: one
+                    // frame a pass, 128 hypotheses in two groups, 46.7 ms that way, 47.6 with all four, 46.1; the form
+                    // with eight has no registers left for a third copy of the products)
+                    const std::integral_constant<int, (TR + 1) / 2> half{};
                     if (JH > 1 && n_ct <= TR) split_and_multiply(r_tiles, j_source, a, b, j_tiles, part_j);
+                    else if (LAYERS == 0 && JH == 1 && TR > 2 && n_ct <= TR / 2) split_and_multiply(half, j_source, a, b, j_tiles, part_j);
                     else split_and_multiply(j_tiles, j_source, a, b, j_tiles, part_j);
                 } else {
 #pragma unroll
@@ -2257,6 +2262,8 @@ template <typename WT, int NK> const void *label_fn(int layers, int tq, bool chu
     constexpr int TR = label_tiles(NK);
     if (layers > 1) return label_form_of<WT, 2, NK, 4, TR>(chunked);
     if (layers == 1) return tq > TR ? label_form_of<WT, 1, NK, 4, 2 * TR>(chunked) : label_form_of<WT, 1, NK, 4, TR>(chunked);
+    if constexpr (first_tiles(Frags<WT>::PL == 3, NK) > TR)
+        if (tq > TR) return label_form_of<WT, 0, NK, 4, first_tiles(true, NK)>(chunked);
     return label_form_of<WT, 0, NK, 4, TR>(chunked);
 }
 const void *label_wide_fn(bool lstm, bool chunked)   // (bfloat16)
@@ -2265,9 +2272,12 @@ const void *label_wide_fn(bool lstm, bool chunked)   // (bfloat16)
 }
 struct LabelForm {
     const void *fn;   // null: none
-    int nk, nw, tq, layers;   // steps of the reduction per wavefront, wavefronts, column tiles per round of phase Q, LAYERS
+    int nk, nw, tq, layers;   // steps of the reduction per wavefront, wavefronts, TQ, LAYERS
 };
-LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
+// item: column tiles of a usual work item of a joint pass.  A stateless group where that is at most a round's four takes four
+// in the first round too, or two where an item has no more (one frame a pass, 128 hypotheses in three groups,
+// 37.7 ms with eight, 35.8; before there were eight 36.4).
+LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C, int item)
 {
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
     LabelForm f{nullptr, 0, wide ? 8 : 4, 0, lstm ? 2 : 0};
@@ -2283,6 +2293,7 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     f.nk = label_nk(w->dtype == 1, kseg);
     if (f.nk == 0) return f;
     f.tq = label_tiles(f.nk);
+    if (!lstm && item > f.tq) f.tq = first_tiles(w->dtype == 1, f.nk);
     if (lstm && w->pred_layers == 1) {
         const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
         // one round, one row tile, one or two cells a thread
@@ -2309,7 +2320,7 @@ static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool c
         n += (size_t)f.nw * RT * kWidePart * sizeof(float);
     } else {
         if (w->pred_kind == TDT_PRED_LSTM) n += (size_t)f.nw * RT * (f.tq * CT + 4) * sizeof(float);
-        n += (size_t)f.nw * RT * (first_tiles(f.layers, f.nk, f.nw, w->dtype == 1 ? 3 : 1) * CT + 4) * sizeof(float);
+        n += (size_t)f.nw * RT * ((f.layers == 0 ? f.tq : label_tiles(f.nk)) * CT + 4) * sizeof(float);
     }
     if (stages_rows(f.layers, f.nw)) {
         const int ks = w->dtype == 1 ? 32 : 16, rows = RT + (two_areas(f.nk, ks) ? pred_area_rows(f.layers, hyps_per_cluster) : 0);
@@ -2333,7 +2344,7 @@ hipError_t copy_trace_label(long long *out, int n)
 bool label_kernel_takes(const tdt_weights_t *w, bool chunked, bool wide, int hyps_per_cluster, int C)
 {
     if (hyps_per_cluster > kLabelMaxHyps) return false;
-    const LabelForm f = label_form(w, chunked, wide, hyps_per_cluster, C);
+    const LabelForm f = label_form(w, chunked, wide, hyps_per_cluster, C, 64);   // (the larger of two for a stateless model)
     if (!f.fn) return false;
     const size_t dyn = label_lds_bytes(w, f, chunked, hyps_per_cluster, C);
     const size_t lens = (size_t)kMaxRankedBatch * sizeof(int);   // (the batch's lengths while they are ranked)
@@ -2351,7 +2362,10 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    const LabelForm f = label_form(w, chunked, wide, p.hyps_per_cluster, grid / p.n_clusters);
+    const int C = grid / p.n_clusters;
+    const int item = w->pred_kind == TDT_PRED_LSTM || wide
+                         ? 0 : usual_item(C, (p.O + CT - 1) / CT, p.hyps_per_cluster, p.window, p.joint_tiles, p.rows_per_cluster);
+    const LabelForm f = label_form(w, chunked, wide, p.hyps_per_cluster, C, item);
     const void *fn = f.fn;
     if (!fn) return hipErrorInvalidValue;
     {
@@ -2367,7 +2381,7 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     }
     DecodeParams pc = p;
     pc.kseg_max = label_kseg(w);
-    pc.lds_bytes = (int)label_lds_bytes(w, f, chunked, p.hyps_per_cluster, grid / p.n_clusters);
+    pc.lds_bytes = (int)label_lds_bytes(w, f, chunked, p.hyps_per_cluster, C);
     void *args[] = {&pc};
     // A group of one workgroup waits for nobody, so its workgroups need not all be resident.  A cooperative launch, which
     // sees to that, goes through another queue: 11 us from the kernel before to this one and 11 to the next (the

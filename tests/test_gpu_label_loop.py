@@ -73,6 +73,13 @@ CASES = [
                                 ("fp32", 320, 500, 40, 5, 4), ("fp32", 96, 900, 48, 16, 8))],
     *[(config(f"ll_kept_stateless_v{v}_{c}", pred_kind="stateless", h_pred=24, vocab=v, B=60, T=40, len_lo=1, len_hi=40),
        dict(n_clusters=c, joint_tiles=j)) for v, c, j in ((1000, 20, 8), (1000, 30, 12), (300, 60, 4))],
+    # stateless work items of one to four column tiles, of six and seven in passes of all hypotheses only, and at the border to
+    # the form that takes eight at once; duration outputs in an item of their own
+    *[(config(f"ll_items_stateless{n}_v{v}_{B}_{c}_w{w}", pred_kind="stateless", pred_layers=n, emb_dim=24, h_pred=24 * n, h_joint=h,
+              vocab=v, durations=d, B=B, T=16, len_hi=16), dict(n_clusters=c, window=w))
+      for n, h, v, d, B, c, w in ((1, 48, 1000, (), 10, 1, 1), (2, 640, 1021, (0, 1, 2, 3, 4), 40, 1, 2), (1, 72, 1000, (), 60, 1, 3),
+                                  (2, 48, 1000, (1, 2), 60, 1, 4), (1, 616, 1000, (), 150, 3, 2), (2, 48, 1021, (0, 2), 160, 3, 2),
+                                  (1, 48, 1000, (), 30, 1, 0), (2, 104, 300, (), 12, 4, 0))],
     # column groups at the borders of what a lane of the gather takes at a time: 16, 17, 24, 25, 49
     *[(config(f"ll_column_groups{n}", vocab=n * 16 - 2, B=6, T=20, len_hi=20), dict(n_clusters=1, joint_tiles=1, window=w))
       for n, w in ((16, 8), (17, 8), (24, 8), (25, 8), (49, 8), (40, 1))],
@@ -104,8 +111,9 @@ def test_label_loop(oracle_lib, gpu, cfg, opts):   # noqa: F811
     check(oracle_lib, gpu, cfg, max_replayed_frac=0.1, **opts)
 
 
-@pytest.mark.parametrize("kw", [dict(B=6), dict(B=40, pred_layers=2), dict(B=9, pred_kind="stateless", h_pred=24)],
-                         ids=["one_layer", "two_layers", "stateless"])
+@pytest.mark.parametrize("kw", [dict(B=6), dict(B=40, pred_layers=2), dict(B=9, pred_kind="stateless", h_pred=24),
+                                dict(B=20, pred_kind="stateless", h_pred=24, vocab=1000)],
+                         ids=["one_layer", "two_layers", "stateless", "stateless_items"])
 def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
     from test_gpu_chunks import check_chunks
     cfg = config("ll_chunks", durations=(0, 1, 5), **kw)

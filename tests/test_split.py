@@ -34,6 +34,10 @@ extern "C" int window_c(int general, int C, int nt, int hyps, int hpc, int n, in
     return general ? general_window(n, window, general_joint_rows(general == 1, C, nt, 0, hyps), rows_cap, most)
                    : label_window(n, window, label_joint_rows(C, nt, 0, hpc), rows_cap, C, nt);
 }
+extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
+{
+    return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
+}
 """
 
 
@@ -144,6 +148,18 @@ def test_windows(split):
                                 assert w <= most
                             if not window and w < (most if general else 64) and w * n <= rows_cap - n:
                                 assert -(-n * (w + 1) // 16) > -(-n * w // 16)   # (a frame more takes a row tile more)
+
+
+def test_usual_items(split):
+    """65 column tiles.  One frame a pass: 32 of 64 hypotheses are two row tiles, a workgroup each of 128 for a column
+    tile and one over; by default items of the tiles the window aims at, and never more than there are."""
+    assert [split.item_c(C_, 65, hpc, 1, 0) for C_, hpc in ((256, 32), (128, 64), (85, 43), (51, 26), (32, 16), (16, 8))] == [1, 2, 2, 2, 3, 5]
+    assert [split.item_c(C_, 65, hpc, 0, 0) for C_, hpc in ((51, 5), (9, 5), (9, 2), (256, 1))] == [4, 8, 8, 2]
+    for C_ in (1, 2, 9, 51, 256):
+        for nt in (5, 65, 255):
+            for hpc in (1, 2, 16, 63, 64):
+                for window in (0, 1, 8, 64):
+                    assert -(-nt // C_) <= split.item_c(C_, nt, hpc, window, 0) <= nt
 
 
 def test_group_counts_of_forms_that_keep_their_weights(split):
