@@ -61,6 +61,7 @@ namespace {
 
 constexpr unsigned kAbsent = 0xffffffffu;   // an exchanged float that is not there yet (a NaN no result is stored as)
 constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront and row of a tile in the partial sums (all uses)
+static_assert(kNowhere >= 2ll * TDT_MAX_LSTM_LAYERS * kMaxGrid * kLabelMaxHyps * kLabelLongest * 4, "the largest exchange buffer");
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kPairRows = 8;                // up to this many rows two planes do (one LSTM layer)
 
@@ -786,7 +787,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         hn = og * (2.0f * sigmoid(2.0f * cn) - 1.0f);
     };
 
-    const int nowhere = 0x7ffffff0;   // an offset beyond every exchange buffer: such a store is dropped, such a load gives zeros
     // what lane l reads of a whole row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
     auto hoff = [&](int kk) { return min(lane * 4 + kk * 256, Hp - 4) * (int)sizeof(float); };
     const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, (size_t)2 * L * Bw * Hp * sizeof(float));
@@ -837,7 +837,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {   // (nothing is loaded for a row without an active hypothesis)
                     const int g = h * 8 + (lane >> 3);
-                    off[h] = (in_tile >> g) & 1ull ? (row0 + g) * Hp * (int)sizeof(float) : nowhere;
+                    off[h] = (in_tile >> g) & 1ull ? (row0 + g) * Hp * (int)sizeof(float) : kNowhere;
                 }
                 const bool upper = (in_tile >> 8) != 0ull;
                 until_there([&]() __attribute__((always_inline)) {
@@ -925,7 +925,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int h = 0; h < 2; ++h) {
                     int g, u;
                     place(base, h, g, u);
-                    const int off = g < G && ((act_prev >> g) & 1ull) ? (b0 + g) * hrow + (u0 + u) * (int)sizeof(float) : nowhere;
+                    const int off = g < G && ((act_prev >> g) & 1ull) ? (b0 + g) * hrow + (u0 + u) * (int)sizeof(float) : kNowhere;
                     if (base + h * THREADS < G * U)   // uniform
 #pragma clang loop unroll(disable)
                         for (int l = 0; l < L; ++l)
@@ -1045,7 +1045,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // a round -- and its cell.  Offsets into the exchange buffers; beyond their end where there is
     // nothing to write, so that the stores need no branch.
     constexpr int QH = TQ > 4 ? 2 : 1;   // halves of a round: four tiles, four columns a thread
-    int q_off[2] = {nowhere, nowhere}, q_unit[2] = {-1, -1}, h_off[2] = {nowhere, nowhere}, c_g[2], c_u[2];
+    int q_off[2] = {kNowhere, kNowhere}, q_unit[2] = {-1, -1}, h_off[2] = {kNowhere, kNowhere}, c_g[2], c_u[2];
     float4 q_bias[2];
     if constexpr (LAYERS == 1) {
         const int quad = lane & 15, g = qpack ? wave : qpair ? wave * 2 + ((lane >> 4) & 1) : tid >> 4;
@@ -1429,7 +1429,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                if ((h == 0 || two_cells) && h_off[h] != nowhere && ((act >> c_g[h]) & 1ull)) {
+                if ((h == 0 || two_cells) && h_off[h] != kNowhere && ((act >> c_g[h]) & 1ull)) {
                     const int o = c_g[h] * Upad + c_u[h];
                     float cn, hn;
                     if (CHUNKED && first && ((carried >> c_g[h]) & 1ull)) {
@@ -1714,7 +1714,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int g = h * 8 + (lane >> 3);
-                        po[h] = (act >> g) & 1ull ? (par * Bw + b0 + g) * H * (int)sizeof(float) : nowhere;
+                        po[h] = (act >> g) & 1ull ? (par * Bw + b0 + g) * H * (int)sizeof(float) : kNowhere;
                     }
                 } else if constexpr (STAGED) {
                     const int q0 = uni(q_l), q1 = __builtin_amdgcn_readlane(q_l, 15);

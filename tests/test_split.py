@@ -34,6 +34,11 @@ extern "C" int window_c(int general, int C, int nt, int hyps, int hpc, int n, in
     return general ? general_window(n, window, general_joint_rows(general == 1, C, nt, 0, hyps), rows_cap, most)
                    : label_window(n, window, label_joint_rows(C, nt, 0, hpc), rows_cap, C, nt);
 }
+extern "C" void nowhere_c(int *out)
+{
+    const int v[3] = {kNowhere, kLabelLongest, label_nk(true, kLabelLongest) > 0 && label_nk(true, kLabelLongest + 1) == 0};
+    for (int i = 0; i < 3; ++i) out[i] = v[i];
+}
 extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
 {
     return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
@@ -148,6 +153,16 @@ def test_windows(split):
                                 assert w <= most
                             if not window and w < (most if general else 64) and w * n <= rows_cap - n:
                                 assert -(-n * (w + 1) // 16) > -(-n * w // 16)   # (a frame more takes a row tile more)
+
+
+def test_an_offset_that_is_nowhere(split):
+    """It lies beyond the largest exchange buffer and stays a positive number with any offset inside a row added."""
+    out = (C.c_int * 3)()
+    split.nowhere_c(out)
+    nowhere, longest, longest_taken = out
+    assert longest_taken
+    assert nowhere + 4 * longest < 2 ** 31
+    assert nowhere >= 2 * 4 * 256 * 64 * longest * 4
 
 
 def test_usual_items(split):
