@@ -40,6 +40,19 @@ def build_timers_library(verbose: bool = False) -> str:
     return build_library(verbose, defines=("TDT_PHASE_TIMERS=1",), out=TIMERS_LIB)
 
 
+TERMS_TEST_LIB = os.path.join(ROOT, "tests", "native", "libterms.so")
+
+
+def build_terms_test_library() -> str:
+    """The kernel behind tests/test_gpu_terms.py."""
+    cmd = ["hipcc"] + HIPCC_FLAGS + ["-I", os.path.join(PKG, "csrc"), os.path.join(ROOT, "tests", "native", "terms.hip"),
+                                     "-o", TERMS_TEST_LIB]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("hipcc failed:\n" + res.stdout)
+    return TERMS_TEST_LIB
+
+
 if __name__ == "__main__":
     import sys
     if "--phase-timers" in sys.argv:

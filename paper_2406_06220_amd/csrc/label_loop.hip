@@ -55,6 +55,7 @@
 #include "exchange.h"
 #include "split.h"
 #include "tile_gemm.h"
+#include "terms.h"
 
 namespace tdt {
 namespace {
@@ -109,18 +110,6 @@ __device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void *base, size_t byte
 __device__ inline float4 as_float4(v4u v)
 {
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-}
-// x + a . b of two bfloat16 pairs.  With (-1, 0) or (0, -1) for b, and x a float whose top 16 bits are that half of
-// a, the result is exact: compared with the subtraction bit for bit over 6 million pairs of every
-// magnitude, subnormal ones among them (an infinity or a NaN in one half makes the other's result a NaN too:
-// the row it stands in has no finite sum either way).  One instruction instead of two.
-__device__ inline float less_term(unsigned a, unsigned b, float x)
-{
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16x2 u, v;
-    __builtin_memcpy(&u, &a, 4);
-    __builtin_memcpy(&v, &b, 4);
-    return __builtin_amdgcn_fdot2_f32_bf16(u, v, x, false);
 }
 __device__ inline unsigned umax4(v4u v) { return max(max(v.x, v.y), max(v.z, v.w)); }
 // agent scope: what another workgroup writes (see ld_co4)
@@ -568,13 +557,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         return min((s0 + s) * KS + (lane >> 4) * F::E, K - F::E) * (int)sizeof(float);
     };
     // bfloat16: x == hi + lo + lo2 as in ActTile::split3, two elements packed per instruction.  A term is taken off its
-    // element by a product with (-1, 0) or (0, -1) of the packed pair (the factors in registers: as a
-    // literal the compiler hands the instruction (1, 0) as (0, 1)).
+    // element by a product with (-1, 0) or (0, -1) of the packed pair (terms.h).
     // That instruction runs where products do and waits for them, so a split beside products uses two.
     const std::true_type beside_products{};
     const std::false_type alone{};
-    unsigned minus_low = 0x0000bf80u, minus_high = 0xbf800000u;
-    asm volatile("" : "+s"(minus_low), "+s"(minus_high));
+    const MinusOne minus;
     auto split = [&](const float (&x0)[F::E], AFrag (&a)[PL], auto beside) __attribute__((always_inline)) {
         if constexpr (PL == 3) {
             float x[F::E];
@@ -585,13 +572,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 v4u o;
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    o[e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302u);
+                    o[e] = top_halves(x[2 * e], x[2 * e + 1]);
                 a[pl] = *reinterpret_cast<const AFrag *>(&o);
                 if (pl < 2)
 #pragma unroll
                     for (int e = 0; e < F::E; ++e) {
                         if constexpr (decltype(beside)::value) x[e] -= __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
-                        else x[e] = less_term(o[e / 2], e % 2 ? minus_high : minus_low, x[e]);
+                        else x[e] = less_term(o[e / 2], e % 2 ? minus.high : minus.low, x[e]);
                     }
             }
         } else {
@@ -730,14 +717,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(v[i][e]);
 #pragma unroll
                 for (int pl = 0; pl < 3; ++pl) {
-                    const unsigned lo = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
-                    const unsigned hi = __builtin_amdgcn_perm(__float_as_uint(x[3]), __float_as_uint(x[2]), 0x07060302u);
+                    const unsigned lo = top_halves(x[0], x[1]), hi = top_halves(x[2], x[3]);
                     *reinterpret_cast<uint2 *>(at + pl * plane + i * 32) = make_uint2(lo, hi);
                     if (pl < 2) {
-                        x[0] = less_term(lo, minus_low, x[0]);
-                        x[1] = less_term(lo, minus_high, x[1]);
-                        x[2] = less_term(hi, minus_low, x[2]);
-                        x[3] = less_term(hi, minus_high, x[3]);
+                        x[0] = less_term(lo, minus.low, x[0]);
+                        x[1] = less_term(lo, minus.high, x[1]);
+                        x[2] = less_term(hi, minus.low, x[2]);
+                        x[3] = less_term(hi, minus.high, x[3]);
                     }
                 }
             }
