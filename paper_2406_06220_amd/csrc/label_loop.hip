@@ -977,10 +977,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     };
 
     // ---- the work item at hand.  Lane i (of every 16) holds row i of its tile: the row of enc_proj, the
-    // hypothesis, and (stateless) the labels
+    // hypothesis, and which of the searching ones that is
     int ti = 0, cg = 0, tile0 = 0, n_ct = 0;
-    int erow_l = 0, g_l = 0, lab_l = 0, lab2_l = 0;
-    int q_l = 0;            // ... and which of the searching hypotheses it is
+    int erow_l = 0, g_l = 0, q_l = 0;
     bool have_p = false;    // (TWO) this label's projected predictor output is staged
     int slot_of = 0;        // lane q: the q-th searching hypothesis
     int Kw = 1, rcp_kw = 1, n_tiles = 0, n_cg = 1, tpg = 1, items = 0, M = 0, ti0 = 0, cg0 = 0;
@@ -1010,10 +1009,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         // (every lane has to take part in every permute: what an inactive lane holds reads as zero)
         const int len_r = __builtin_amdgcn_ds_bpermute(g_l * 4, len), gid_r = S.gid[g_l];
         erow_l = gid_r * T + (f < len_r ? f : 0);   // (a frame beyond its utterance's end reads frame 0)
-        if constexpr (!LSTM) {
-            lab_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last);
-            lab2_l = __builtin_amdgcn_ds_bpermute(g_l * 4, last2);
-        }
     };
     auto set_item = [&](int it) __attribute__((always_inline)) {
         ti = ti0;
@@ -1501,12 +1496,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     TR(14);
                     const std::integral_constant<int, (TR + 1) / 2> half{};
                     if (PLANES && qpack) {
-                        if (TQ > TR || nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
+                        if (nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
                         else plane_products(full_rows, half, bq, q_tiles, part_q);
-                        if (TQ > TR && nq > TR) plane_products(full_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
                     } else if (PLANES && qpair) {
                         plane_products(packed_rows, r_tiles, bq, q_tiles, part_q);
-                        if (TQ > TR && nq > TR) plane_products(packed_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
                     } else if constexpr (PL == 3) {
                         if (TQ > TR || nq > TR / 2) split_and_multiply(r_tiles, h_source, a, bq, q_tiles, part_q);
                         else split_and_multiply(half, h_source, a, bq, q_tiles, part_q);
@@ -1692,7 +1685,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 v4u p4[NK][NL], pv[2 * C32];
                 any_value(pv);
                 int po[NK];
-                const float *pr2 = nullptr;
                 bool upper = G > 8;   // more than eight rows of the predictor's
                 const bool load_p = !(LSTM && TWO) || !have_p;
                 // the predictor's rows: of the group's hypotheses (LSTM), of those in this row tile (stateless)
