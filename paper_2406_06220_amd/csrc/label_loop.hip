@@ -1337,6 +1337,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 S.rowd[tr * RT + i] = (unsigned)S.durations[unpack_index(bd) & (TDT_MAX_DURATIONS - 1)];
             }
         }
+        lap(kTkJ);
     };
 
     // Weights that stay (see the head of the file): those of a work item's first round; of its second where items have
@@ -1643,6 +1644,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             if (t0 + TQ < n_all || kind + 1 < kinds || tq + 1 < ntq || l + 1 < L) __syncthreads();
                         }
                     }
+                    lap(kTkQ);   // (behind every wait what followed it: the next one starts here)
                 }
             }
             TR(17);
@@ -1927,6 +1929,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     }
                 }
                 if (it + C < items) __syncthreads();   // the next item writes the partial sums again
+                lap(kTkJ);
             }
             if constexpr (WIDE) {
                 if (rank < n_cg) {
