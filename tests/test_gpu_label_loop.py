@@ -122,15 +122,36 @@ def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
     check_chunks(oracle_lib, gpu, cfg, "single", 0)
 
 
+@pytest.mark.parametrize("kw,ncl", [
+    # more than one round of phase Q's tiles a workgroup: six and five of four, four of two
+    (dict(B=32, h_pred=320), 16), (dict(B=30, h_pred=248, dtype="fp32"), 16), (dict(B=30, h_pred=320, dtype="fp32"), 10),
+    # the longer reductions: one round and two
+    (dict(B=15, h_pred=648, h_joint=648), 2), (dict(B=9, h_pred=648, h_joint=648), 3),
+    # a row tile of five to eight hypotheses, staged as planes, and a full one
+    (dict(B=8, h_pred=96), 1), (dict(B=13, h_pred=96), 1), (dict(B=16, h_pred=640, h_joint=640), 2)],
+    ids=["two_rounds", "fp32_two_rounds", "fp32_two_rounds_long", "long", "long_two_rounds", "planes", "full_tile", "planes_640"])
+def test_label_loop_chunks_of_one_layer(oracle_lib, gpu, kw, ncl):   # noqa: F811
+    """The state that a chunk takes up and leaves, in the forms of one LSTM layer."""
+    from test_gpu_chunks import check_chunks
+    cfg = config("ll_chunks1", durations=(0, 1, 5), T=20, len_hi=20, **kw)
+    check_chunks(oracle_lib, gpu, cfg, "random", 3, n_clusters=ncl)
+
+
 # ------------------------------------------------------------------ values that are no numbers
 KINDS = {
     "lstm": (dict(B=9), {}),
+    "lstm_planes": (dict(B=7), dict(n_clusters=1)),
+    "lstm_full_tile": (dict(B=13), dict(n_clusters=1)),
+    "lstm_two_rounds": (dict(B=32, h_pred=320), dict(n_clusters=16)),
+    "lstm_long": (dict(B=7, h_joint=648, h_pred=648), dict(n_clusters=2)),
     "lstm_groups": (dict(B=33, h_pred=96), dict(n_clusters=1)),
     "lstm_packed": (dict(B=3), dict(n_clusters=1)),
     "deep": (dict(B=9, pred_layers=3), {}),
     "fp32": (dict(B=9, dtype="fp32"), {}),
     "wide": (dict(B=20, vocab=600, durations=(0, 1, 2)), dict(n_clusters=4, joint_kernel=2)),
     "stateless": (dict(B=9, pred_kind="stateless", pred_layers=2, h_pred=48), {}),
+    "stateless_items": (dict(B=12, pred_kind="stateless", pred_layers=2, h_pred=48, vocab=300), dict(n_clusters=1)),
+    "stateless_eight": (dict(B=12, pred_kind="stateless", pred_layers=2, h_pred=48, vocab=1000), dict(n_clusters=12, joint_tiles=8)),
     "stateless_fp32": (dict(B=9, dtype="fp32", pred_kind="stateless", h_pred=24), {}),
 }
 
