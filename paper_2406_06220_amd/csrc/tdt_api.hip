@@ -355,7 +355,7 @@ static int decode_common(const void *enc, const int32_t *enc_len, int B, int T,
     bool label = algorithm == TDT_ALG_LABEL_LOOPING && !on_the_fly;
     for (;;) {
         if (asked == 0)
-            split = label ? label_split(sm, B, max_grid, streaming_least)
+            split = label ? label_split(sm, B, max_grid, streaming_least, JointAsked{window, joint_tiles})
                           : general_split(sm, B, max_grid, streaming_least, algorithm == TDT_ALG_FRAME_LOOPING, on_the_fly);
         n_clusters = split.n_clusters;
         if (n_clusters < min_clusters || n_clusters > max_grid) return TDT_ERR_UNSUPPORTED;

@@ -21,11 +21,11 @@ extern "C" void pred_share_c(int deep, int nt_a, int nt_b, int h_pred, int C, in
     for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
 extern "C" void group_split_c(int general, int bf16, int lstm, int layers, int h_joint, int h_pred, int outputs, int B,
-                              int streaming_least, int frame_loop, int on_the_fly, int *out)
+                              int streaming_least, int frame_loop, int on_the_fly, int window, int joint_tiles, int *out)
 {
     const SplitModel m = split_model(bf16 != 0, lstm != 0, layers, h_joint, h_pred, outputs);
     const GroupSplit s = general ? general_split(m, B, 256, streaming_least, frame_loop != 0, on_the_fly != 0)
-                                 : label_split(m, B, 256, streaming_least);
+                                 : label_split(m, B, 256, streaming_least, JointAsked{window, joint_tiles});
     const int v[3] = {s.n_clusters, s.one_workgroup, s.window_most};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
@@ -83,10 +83,10 @@ def test_stateless_predictor_has_no_share(split):
     assert list(out) == [0] * 6
 
 
-def group_split(split, cfg, general=0, on_the_fly=0, streaming=0, frame_loop=0):
+def group_split(split, cfg, general=0, on_the_fly=0, streaming=0, frame_loop=0, window=0, joint_tiles=0):
     out = (C.c_int * 3)()
     split.group_split_c(general, int(cfg.dtype == "bf16"), int(cfg.pred_kind == "lstm"), cfg.pred_layers, cfg.h_joint, cfg.h_pred,
-                        cfg.n_out, cfg.B, 4 * streaming, frame_loop, on_the_fly, out)
+                        cfg.n_out, cfg.B, 4 * streaming, frame_loop, on_the_fly, window, joint_tiles, out)
     return list(out)
 
 
@@ -177,18 +177,19 @@ def test_usual_items(split):
                     assert -(-nt // C_) <= split.item_c(C_, nt, hpc, window, 0) <= nt
 
 
-def test_group_counts_of_forms_that_keep_their_weights(split):
-    """One LSTM layer where five groups fit: five already in small batches while a group's workgroups have at most two
-    rounds of column tiles; three hypotheses in three groups where that makes no second round of one; never
-    more groups than hypotheses but for one alone.  Two layers, widths that leave a workgroup more tiles (and
-    with them not the one-layer form), models that more groups fit: four at most.  Eight column tiles a
-    round: groups by the items they make."""
-    def groups(B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025):
-        cfg = synth.small_config("split", dtype=dtype, pred_kind=kind, pred_layers=layers, h_joint=H, h_pred=Hp, emb_dim=Hp,
-                                 vocab=n_out - 1, B=B)
-        n, one, _ = group_split(split, cfg)
-        assert not one
-        return n
+def label_groups(split, B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025, **asked):
+    cfg = synth.small_config("split", dtype=dtype, pred_kind=kind, pred_layers=layers, h_joint=H, h_pred=Hp, emb_dim=Hp, vocab=n_out - 1, B=B)
+    n, one, _ = group_split(split, cfg, **asked)
+    assert not one
+    return n
+
+
+def test_group_counts_of_one_lstm_layer(split):
+    """Where five groups fit: five already in small batches while a group's workgroups have at most two rounds of column
+    tiles; three hypotheses in three groups where that makes no second round of one; never more groups than
+    hypotheses but for one alone.  Two layers, widths that leave a workgroup more tiles (and with them not the
+    one-layer form), models that more groups fit: four at most."""
+    groups = lambda B, **kw: label_groups(split, B, **kw)
     batches = (1, 2, 3, 4, 5, 7, 15, 16, 32, 128)
     one_round, two_rounds, four = [2, 2, 3, 4, 5, 5, 5, 5, 5, 8], [2, 2, 2, 4, 5, 5, 5, 5, 5, 8], [2, 2, 2, 4, 4, 4, 4, 5, 5, 8]
     for H, Hp in ((640, 640), (448, 640), (640, 592)):
@@ -202,9 +203,37 @@ def test_group_counts_of_forms_that_keep_their_weights(split):
     assert [groups(B, H=48, Hp=40) for B in (1, 3, 5, 15)] == [2, 2, 4, 4]   # (many would fit)
     assert [groups(B, H=768, Hp=768) for B in (2, 3, 4, 5, 15, 16)] == [2, 2, 4, 4, 4, 4]
     assert [groups(B, H=1024, Hp=1024) for B in (2, 3, 4, 5, 15, 16)] == [2, 3, 3, 3, 3, 3]
-    assert [groups(B, kind="stateless") for B in (1, 4, 25, 26, 32, 140, 141, 256)] == [5, 4, 5, 26, 28, 28, 42, 42]
+
+
+def test_group_counts_by_the_joint_passes(split):
+    """One LSTM layer of 640: four groups where the windows of five would hold fewer row tiles, or a caller's window
+    would make their items take more rounds; windows of more than eight frames by the general rule."""
+    groups = lambda B, n_out, window=0, joint_tiles=0, **kw: label_groups(split, B, n_out=n_out, window=window, joint_tiles=joint_tiles, **kw)
+    for dtype in ("bf16", "fp32"):
+        assert [groups(9, n_out, dtype=dtype) for n_out in (128, 501, 1025, 1088, 2001, 3300, 4091)] == [5, 4, 5, 5, 4, 4, 4]
+        assert [groups(15, n_out, dtype=dtype) for n_out in (128, 501, 1025, 2001, 4091)] == [5, 4, 5, 4, 5]
+    assert [groups(9, 1025, window=w) for w in (1, 4, 8, 9, 64)] == [5, 5, 5, 4, 4]
+    assert [groups(9, 4091, window=w) for w in (1, 4, 8, 9, 64)] == [4, 4, 4, 4, 4]
+    assert [groups(3, 1025, window=w) for w in (0, 1, 8, 9, 64)] == [3, 3, 3, 2, 2]
+    assert [groups(9, 501, joint_tiles=j) for j in (1, 4, 8)] == [4, 4, 5]
+
+
+def test_group_counts_of_stateless_models(split):
+    """Eight column tiles a round: few groups with items of four tiles on three row tiles while that leaves five
+    hypotheses a group and gives five to twenty of them, then groups by items of eight and twelve tiles.  A caller's
+    window of up to eight frames: the groups of the other stateless forms instead of the few."""
+    groups = lambda B, n_out=1025, **kw: label_groups(split, B, kind="stateless", n_out=n_out, **kw)
+    assert [groups(B) for B in (1, 4, 25, 26, 32, 140, 141, 256)] == [5, 4, 5, 26, 28, 28, 42, 42]
+    assert [groups(B, n_out=501) for B in (16, 48, 50, 51, 128)] == [10, 10, 10, 51, 64]
+    assert [groups(B, n_out=128) for B in (16, 48, 128)] == [16, 48, 64]
+    assert [groups(B, n_out=2049) for B in (4, 8, 10, 11, 24)] == [3, 3, 5, 11, 15]
+    assert [groups(24, window=w) for w in (0, 1, 8, 9, 64)] == [5, 11, 11, 5, 5]
+    assert [groups(24, joint_tiles=j) for j in (0, 1, 8)] == [5, 5, 5]
+    assert [groups(64, window=w) for w in (0, 1, 64)] == [28, 28, 28]
+    assert [groups(24, dtype="fp32", window=w) for w in (0, 1, 64)] == [11, 11, 11]
     for n_out in (80, 128, 256, 1024, 1025, 3200, 16400):
         for B in (*range(1, 70), 128, 500, 20000):
             for kind in ("lstm", "stateless"):
-                n = groups(B, kind=kind, n_out=n_out)
-                assert max(1, -(-B // 256)) <= n <= max(64, -(-B // 256)) and (n <= B or B == 1), (kind, n_out, B)
+                for asked in ({}, dict(window=1), dict(window=64), dict(joint_tiles=1)):
+                    n = label_groups(split, B, kind=kind, n_out=n_out, **asked)
+                    assert max(1, -(-B // 256)) <= n <= max(64, -(-B // 256)) and (n <= B or B == 1), (kind, n_out, B, asked)
