@@ -256,6 +256,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr bool STAGED = stages_rows(LAYERS, NW);          // rows go through LDS, see stage_rows
     constexpr int C32 = NK * KS / 32, LDX = staged_row(NK, KS);   // 128-byte pieces of a wavefront's stretch of a row, floats of a staged row
     constexpr bool TWO = two_areas(NK, KS);
+    // Weights of a joint pass's later rounds have registers of their own, and a thread asks for all its partial sums at
+    // once.  Not in deeper LSTMs, which keep no weights and where both cost (two layers, bfloat16, B = 32, 1760 us,
+    // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890).
+    constexpr bool OWN2 = !DEEP || (PL == 1 && NK > 4);
     constexpr bool PLANES = PL == 3 && LAYERS == 1 && TQ == TR;   // few rows of the hidden state: staged as planes, see stage_planes
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
@@ -665,7 +669,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         float4 x[NW];   // (all on their way before the first is looked at)
 #pragma unroll
         for (int w = 0; w < NW; ++w) x[w] = *reinterpret_cast<const float4 *>(q + (size_t)w * RT * PLD);
-        if (!WIDE) __builtin_amdgcn_sched_barrier(0);
+        if (!WIDE && OWN2) __builtin_amdgcn_sched_barrier(0);
         float4 v = x[0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) {
@@ -1854,18 +1858,22 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int t0 = 0, next = TJ; t0 < n_ct; t0 = next, next += TR) {
                     const int n = min(next - t0, n_ct - t0);
                     TR(25);
-                    if (t0 > 0) products(full_rows, a, b2, n, j_tiles, jsn, part_j);
+                    if (OWN2 && t0 > 0) products(full_rows, a, b2, n, j_tiles, jsn, part_j);
                     else if (!STREAMED) products(full_rows, a, b, n, j_tiles, jsn, part_j);
                     float4 bb[JH];
 #pragma unroll
-                    for (int h = 0; h < JH; ++h) bb[h] = as_float4(h == 0 && t0 > 0 ? bias1[0] : bias0[h]);
+                    for (int h = 0; h < JH; ++h) bb[h] = as_float4(OWN2 && h == 0 && t0 > 0 ? bias1[0] : bias0[h]);
                     TR(26);
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (words put back earlier have arrived)
                     __syncthreads();
                     TR(27);
                     if ((!KEEP1 || t0 > 0) && next < n_ct) {   // the next round's weights, while this one's results are looked at
-                        fetch_round(b2, bias1, next);
-                        in_b2 = key(next, TR);
+                        if constexpr (OWN2) {
+                            fetch_round(b2, bias1, next);
+                            in_b2 = key(next, TR);
+                        } else {
+                            fetch_round(b, bias0, next);
+                        }
                     }
                     if (t0 > 0) fold_sums();
                     float x4[4 * JH], m = -INFINITY;
