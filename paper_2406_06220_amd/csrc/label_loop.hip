@@ -27,7 +27,7 @@
 //     of instructions in a row, and two wavefronts that share a SIMD take turns at them.  It also
 //     leaves 512 registers a lane, and the weights stay in them: those of phase Q for the whole call (one
 //     layer), those of a joint pass while its work items cover the same column tiles, which a group's
-//     plans seldom change.  Scalar registers are short: 100 to 400 scalar values of a form are kept in lanes of
+//     plans seldom change (stateless, and one layer unless phase Q has two rounds in bfloat16).  Scalar registers are short: 100 to 400 scalar values of a form are kept in lanes of
 //     vector registers and moved back where they are used.
 //   * Every wavefront multiplies its own quarter of the reduction for all column tiles.  So no two
 //     wavefronts need the same activation: each loads, waits for and splits its quarter of the rows, and
@@ -256,10 +256,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr bool STAGED = stages_rows(LAYERS, NW);          // rows go through LDS, see stage_rows
     constexpr int C32 = NK * KS / 32, LDX = staged_row(NK, KS);   // 128-byte pieces of a wavefront's stretch of a row, floats of a staged row
     constexpr bool TWO = two_areas(NK, KS);
+    constexpr bool TWO_ROUNDS = LAYERS == 1 && TQ > TR;       // phase Q has two rounds
     // Weights of a joint pass's later rounds have registers of their own, and a thread asks for all its partial sums at
     // once.  Not in deeper LSTMs, which keep no weights and where both cost (two layers, bfloat16, B = 32, 1760 us,
-    // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890).
-    constexpr bool OWN2 = !DEEP || (PL == 1 && NK > 4);
+    // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890) --
+    // nor, the registers, where phase Q's second round has them (see "Weights that stay").
+    constexpr bool OWN2 = DEEP ? PL == 1 && NK > 4 : !(TWO_ROUNDS && PL == 3);
     constexpr bool PLANES = PL == 3 && LAYERS == 1 && TQ == TR;   // few rows of the hidden state: staged as planes, see stage_planes
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
@@ -669,7 +671,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         float4 x[NW];   // (all on their way before the first is looked at)
 #pragma unroll
         for (int w = 0; w < NW; ++w) x[w] = *reinterpret_cast<const float4 *>(q + (size_t)w * RT * PLD);
-        if (!WIDE && OWN2) __builtin_amdgcn_sched_barrier(0);
+        if (!WIDE && (!DEEP || OWN2)) __builtin_amdgcn_sched_barrier(0);
         float4 v = x[0];
 #pragma unroll
         for (int w = 1; w < NW; ++w) {
@@ -1344,16 +1346,20 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         lap(kTkJ);
     };
 
-    // Weights that stay (see the head of the file): those of a work item's first round; of its second where items have
-    // two, that is in stateless groups and in groups of so few workgroups that phase Q has more tiles than a joint
-    // round; those of phase Q's first round, but not in bfloat16 where it has two (registers: they are then
-    // requested for every label, behind its table row; config 2 at B = 128, all three kept 2.57 ms, the
-    // second joint round fetched in every pass 2.45, neither joint round kept 2.40, phase Q's not kept 2.33; float32
-    // at B = 16 1.53, 1.57, 1.70 and 1.58).  Fetched anew for every label and pass, the code before: stateless at
-    // B = 128 2.42 ms, now 2.19; config 2 at B = 32 1.47 ms, now 1.32, at B = 1 375 us, now 351.
-    constexpr bool KEEP1 = STAGED, KEEP2 = STAGED && (LAYERS == 0 || TQ > TR), KEEPQ = TQ == TR || PL == 1;
-    v4u bq[TR][NK];   // LAYERS == 1: the predictor-side weights, of the first TR tiles
-    if constexpr (LAYERS == 1 && KEEPQ) fetch(bq, min(nq, TR), hs0, hsn, q_tile);
+    // Weights that stay (see the head of the file).  Phase Q's, of both rounds where it has two; those of a joint pass's
+    // first round; and of its second where items have two, in stateless groups and in groups of so few workgroups
+    // that phase Q has two rounds as well.  Registers hold two of the four kinds in bfloat16 and three in float32's
+    // longest form.  bfloat16: phase Q's (config 2 at B = 128, the joint rounds' and none of phase Q's 1555 us, 18 registers
+    // in scratch, phase Q's first round only 1507, both 1502; 1024 units and joint width, B = 24, 7388, 7314, 7067; all
+    // kept 1700 and more).  Float32: not phase Q's second, requested for every label behind its table row (config 2's
+    // model, B = 16, 1207; with it, 53 registers in scratch, 1249).  Nothing kept, the code before, against
+    // what one round of phase Q keeps: stateless at B = 128 2.42 ms, 2.19; config 2 at B = 32 1.47 ms, 1.32, at B = 1 375 us,
+    // 351.
+    constexpr bool KEEP1 = STAGED && !(TWO_ROUNDS && PL == 3), KEEP2 = KEEP1 && (LAYERS == 0 || TWO_ROUNDS), KEEPQ2 = PL == 3 || NK <= 4;
+    v4u bq[TR][NK], bq2_kept[TR][NK];   // LAYERS == 1: the predictor-side weights, of the first TR tiles and of the others
+    auto fetch_second = [&](auto &w) __attribute__((always_inline)) { fetch(w, nq - TR, hs0, hsn, [&](int t) { return q_tile(TR + t); }); };
+    if constexpr (LAYERS == 1) fetch(bq, min(nq, TR), hs0, hsn, q_tile);
+    if constexpr (TWO_ROUNDS && KEEPQ2) fetch_second(bq2_kept);
     v4u b[TJ][NK];    // the first column tiles of the work item at hand, and which
     v4u b2[TR][NK];   // ... and those of later rounds
     v4u bias0[JH], bias1[1];
@@ -1396,7 +1402,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int l = 0; l < NL; ++l) e4[s][l] = ldg4(er, part_of(s, js0, H) + l * 16);
         };
         fresh();
-        v4u bq2[TR][NK];
+        v4u bq2_now[TR][NK];
+        auto &bq2 = KEEPQ2 ? bq2_kept : bq2_now;
         if constexpr (LAYERS == 1) {
             // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, W_hh * h was formed by this
             // workgroup when h was new.
@@ -1410,8 +1417,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + c_u[h]) * 4);
                 }
             __builtin_amdgcn_sched_barrier(0);
-            if (!KEEPQ) fetch(bq, min(nq, TR), hs0, hsn, q_tile);
-            if (TQ > TR) fetch(bq2, nq - TR, hs0, hsn, [&](int t) { return q_tile(TR + t); });   // (they take about as long to leave as the row to arrive)
+            if (TWO_ROUNDS && !KEEPQ2) fetch_second(bq2);   // (they take about as long to leave as the row to arrive)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -1859,7 +1865,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const int n = min(next - t0, n_ct - t0);
                     TR(25);
                     if (OWN2 && t0 > 0) products(full_rows, a, b2, n, j_tiles, jsn, part_j);
-                    else if (!STREAMED) products(full_rows, a, b, n, j_tiles, jsn, part_j);
+                    else if (!STREAMED || t0 > 0) products(full_rows, a, b, n, j_tiles, jsn, part_j);
                     float4 bb[JH];
 #pragma unroll
                     for (int h = 0; h < JH; ++h) bb[h] = as_float4(OWN2 && h == 0 && t0 > 0 ? bias1[0] : bias0[h]);

@@ -71,6 +71,11 @@ CASES = [
     *[(config(f"ll_kept_{t}_v{v}_{B}_{c}", dtype=t, h_pred=hp, vocab=v, B=B, T=40, len_lo=1, len_hi=40), dict(n_clusters=c, joint_tiles=j))
       for t, hp, v, B, c, j in (("bf16", 320, 1000, 40, 5, 4), ("bf16", 320, 1000, 60, 10, 8), ("bf16", 320, 700, 32, 16, 12),
                                 ("fp32", 320, 500, 40, 5, 4), ("fp32", 96, 900, 48, 16, 8))],
+    # the same, one layer with two rounds of phase Q: joint items of one round to four, reductions of both lengths
+    *[(config(f"ll_two_rounds_{t}_{h}_{hp}_v{v}_{B}_{c}", dtype=t, h_joint=h, h_pred=hp, vocab=v, B=B, T=20, len_lo=1, len_hi=20), dict(n_clusters=c, joint_tiles=j))
+      for t, h, hp, v, B, c, j in (("bf16", 48, 320, 60, 40, 16, 1), ("bf16", 48, 320, 900, 208, 16, 15), ("bf16", 640, 640, 1000, 100, 8, 8),
+                                   ("bf16", 648, 648, 500, 60, 4, 2), ("bf16", 648, 648, 1000, 60, 4, 8), ("bf16", 1000, 128, 300, 39, 4, 8),
+                                   ("fp32", 48, 248, 900, 40, 16, 15), ("fp32", 272, 320, 500, 60, 10, 8), ("fp32", 640, 640, 300, 30, 5, 4))],
     *[(config(f"ll_kept_stateless_v{v}_{c}", pred_kind="stateless", h_pred=24, vocab=v, B=60, T=40, len_lo=1, len_hi=40),
        dict(n_clusters=c, joint_tiles=j)) for v, c, j in ((1000, 20, 8), (1000, 30, 12), (300, 60, 4))],
     # stateless work items of one to four column tiles, of six and seven in passes of all hypotheses only, and at the border to
