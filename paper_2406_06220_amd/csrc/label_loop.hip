@@ -1698,15 +1698,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 any_value(pv);
                 int po[NK];
                 bool upper = G > 8;   // more than eight rows of the predictor's
-                const bool load_p = !(LSTM && TWO) || !have_p;
-                // the predictor's rows: of the group's hypotheses (LSTM), of those in this row tile (stateless)
-                if constexpr (STAGED && LSTM) {
+                const bool load_p = !LSTM || !have_p;
+                // the predictor's rows: of the group's hypotheses (LSTM), of those in this row tile (stateless); one area and an
+                // LSTM: each lane its own row's part, as it is fed (few of the 16 rows are different ones, so they take few of the
+                // requests that made rows go through LDS, and the way through the encoder's area twice is saved: 1024
+                // units and joint width, B = 24, 7067 us, 6996; joint width 648, 576 units, two frames a pass, 4779, 4670)
+                constexpr bool DIRECT = STAGED && LSTM && !TWO;
+                if constexpr (STAGED && LSTM && TWO) {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int g = h * 8 + (lane >> 3);
                         po[h] = (act >> g) & 1ull ? (par * Bw + b0 + g) * H * (int)sizeof(float) : kNowhere;
                     }
-                } else if constexpr (STAGED) {
+                } else if constexpr (STAGED && !LSTM) {
                     const int q0 = uni(q_l), q1 = __builtin_amdgcn_readlane(q_l, 15);
                     upper = q1 - q0 >= 8;
                     const float *t0[2], *t1[2];
@@ -1759,7 +1763,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     in_b2 = key(TJ, TR);
                 }
                 TR(20);
-                if constexpr (STAGED) {
+                if constexpr (STAGED && !DIRECT) {
                     if (TWO) stage_rows(xe, ev, true);
                     if (load_p) {
                         if constexpr (LSTM) {
@@ -1783,7 +1787,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         have_p = true;
                     }
                     if (!TWO) {   // one area: the predictor's rows make way for the encoder's
-                        const int prow = LSTM ? g_l : q_l - uni(q_l);
+                        const int prow = q_l - uni(q_l);
 #pragma unroll
                         for (int s = 0; s < NK; ++s)
 #pragma unroll
@@ -1794,6 +1798,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         stage_rows(xe, ev, true);
                     }
                 } else {
+                    if (DIRECT) stage_rows(xe, ev, true);
                     until_there([&]() __attribute__((always_inline)) {
                         unsigned mx = 0;
 #pragma unroll

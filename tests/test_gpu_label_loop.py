@@ -78,6 +78,11 @@ CASES = [
                                    ("fp32", 48, 248, 900, 40, 16, 15), ("fp32", 272, 320, 500, 60, 10, 8), ("fp32", 640, 640, 300, 30, 5, 4))],
     *[(config(f"ll_kept_stateless_v{v}_{c}", pred_kind="stateless", h_pred=24, vocab=v, B=60, T=40, len_lo=1, len_hi=40),
        dict(n_clusters=c, joint_tiles=j)) for v, c, j in ((1000, 20, 8), (1000, 30, 12), (300, 60, 4))],
+    # one staging area and the predictor's rows as they are fed: one to sixteen different ones in a row tile, reductions
+    # that end inside a step, one round of phase Q and two
+    *[(config(f"ll_fed_k{h}_{hp}_{B}_{c}_w{w}", h_joint=h, h_pred=hp, B=B, T=24, len_lo=1, len_hi=24), dict(n_clusters=c, window=w))
+      for h, hp, B, c, w in ((648, 40, 1, 1, 64), (648, 40, 16, 1, 1), (1000, 1024, 15, 1, 3), (1024, 648, 8, 1, 0), (1016, 64, 9, 1, 2),
+                             (648, 648, 44, 4, 1), (1024, 320, 20, 3, 5))],
     # stateless work items of one to four column tiles, of six and seven in passes of all hypotheses only, and at the border to
     # the form that takes eight at once; duration outputs in an item of their own
     *[(config(f"ll_items_stateless{n}_v{v}_{B}_{c}_w{w}", pred_kind="stateless", pred_layers=n, emb_dim=24, h_pred=24 * n, h_joint=h,
