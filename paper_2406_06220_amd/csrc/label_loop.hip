@@ -262,7 +262,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890) --
     // nor, the registers, where phase Q's second round has them (see "Weights that stay").
     constexpr bool OWN2 = DEEP ? PL == 1 && NK > 4 : !(TWO_ROUNDS && PL == 3);
-    constexpr bool PLANES = PL == 3 && LAYERS == 1 && TQ == TR;   // few rows of the hidden state: staged as planes, see stage_planes
+    constexpr bool PLANES = PL == 3 && LAYERS == 1;   // few rows of the hidden state: staged as planes, see stage_planes
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
 
@@ -709,7 +709,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // none for rows that are not there, and stages the planes.  Up to four rows they are the rows of one tile (plane
     // pl of row i is row pl * 4 + i), up to eight those of a tile and a half (rows 0 .. 7 the first terms, 8 .. 15 the
     // first remainders; a second tile's rows 0 .. 7 the second ones, its others zeros): one or two products a step
-    // instead of three.  One label's phase Q up to its partial sums, microseconds: 7 rows 1.45 -> 1.20, 1 row 1.35 -> 0.87.
+    // instead of three.  One label's phase Q up to its partial sums, microseconds: 7 rows 1.45 -> 1.20, 1 row 1.35 -> 0.87; a
+    // call with two rounds, 648 units and joint width, B = 12, 2185 -> 2110.
     constexpr int LDP = NK * 32 + 8;   // elements of a plane's row (padded: 16 rows start in 16 different banks)
     auto stage_planes = [&](const v4u (&v)[2 * C32]) __attribute__((always_inline)) {
         uint16_t *const at = reinterpret_cast<uint16_t *>(xe) + (lane >> 3) * LDP + (lane & 7) * 4;
@@ -1507,10 +1508,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     TR(14);
                     const std::integral_constant<int, (TR + 1) / 2> half{};
                     if (PLANES && qpack) {
-                        if (nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
+                        if (TWO_ROUNDS || nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
                         else plane_products(full_rows, half, bq, q_tiles, part_q);
+                        if (TWO_ROUNDS && nq > TR) plane_products(full_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
                     } else if (PLANES && qpair) {
                         plane_products(packed_rows, r_tiles, bq, q_tiles, part_q);
+                        if (TWO_ROUNDS && nq > TR) plane_products(packed_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
                     } else if constexpr (PL == 3) {
                         if (TQ > TR || nq > TR / 2) split_and_multiply(r_tiles, h_source, a, bq, q_tiles, part_q);
                         else split_and_multiply(half, h_source, a, bq, q_tiles, part_q);
@@ -2313,7 +2316,7 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
 static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C)
 {
     size_t n = 0;
-    if (w->dtype == 1 && f.layers == 1 && f.tq == label_tiles(f.nk) && hyps_per_cluster <= kPairRows) n = (size_t)f.nk * 64;
+    if (w->dtype == 1 && f.layers == 1 && hyps_per_cluster <= kPairRows) n = (size_t)f.nk * 64;
     else if (w->dtype == 1 && f.layers > 1 && hyps_per_cluster <= kPackRows)
         n = (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t);
     if (f.nw == 8) {

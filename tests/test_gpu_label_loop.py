@@ -83,6 +83,10 @@ CASES = [
     *[(config(f"ll_fed_k{h}_{hp}_{B}_{c}_w{w}", h_joint=h, h_pred=hp, B=B, T=24, len_lo=1, len_hi=24), dict(n_clusters=c, window=w))
       for h, hp, B, c, w in ((648, 40, 1, 1, 64), (648, 40, 16, 1, 1), (1000, 1024, 15, 1, 3), (1024, 648, 8, 1, 0), (1016, 64, 9, 1, 2),
                              (648, 648, 44, 4, 1), (1024, 320, 20, 3, 5))],
+    # planes with two rounds of phase Q: one to eight rows, a second round of one tile and of all
+    *[(config(f"ll_planes2_k{h}_{hp}_{B}_{c}", h_joint=h, h_pred=hp, B=B, T=24, len_lo=1, len_hi=24), dict(n_clusters=c))
+      for h, hp, B, c in ((48, 320, 16, 16), (48, 320, 48, 16), (48, 320, 64, 16), (48, 248, 80, 16), (16, 256, 112, 16), (48, 496, 128, 16),
+                          (648, 648, 4, 4), (648, 648, 16, 4), (1024, 1000, 10, 2), (616, 704, 28, 4), (648, 696, 32, 4))],
     # stateless work items of one to four column tiles, of six and seven in passes of all hypotheses only, and at the border to
     # the form that takes eight at once; duration outputs in an item of their own
     *[(config(f"ll_items_stateless{n}_v{v}_{B}_{c}_w{w}", pred_kind="stateless", pred_layers=n, emb_dim=24, h_pred=24 * n, h_joint=h,
