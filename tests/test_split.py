@@ -221,14 +221,14 @@ def test_group_counts_by_the_joint_passes(split):
 def test_group_counts_of_stateless_models(split):
     """Eight column tiles a round: few groups with items of four tiles on three row tiles while that leaves five
     hypotheses a group and gives five to twenty of them, then groups by items of eight and twelve tiles.  A caller's
-    window of up to eight frames: the groups of the other stateless forms instead of the few."""
+    window of up to eight frames or size of the items: the groups of the other stateless forms instead of the few."""
     groups = lambda B, n_out=1025, **kw: label_groups(split, B, kind="stateless", n_out=n_out, **kw)
     assert [groups(B) for B in (1, 4, 25, 26, 32, 140, 141, 256)] == [5, 4, 5, 26, 28, 28, 42, 42]
     assert [groups(B, n_out=501) for B in (16, 48, 50, 51, 128)] == [10, 10, 10, 51, 64]
     assert [groups(B, n_out=128) for B in (16, 48, 128)] == [16, 48, 64]
     assert [groups(B, n_out=2049) for B in (4, 8, 10, 11, 24)] == [3, 3, 5, 11, 15]
     assert [groups(24, window=w) for w in (0, 1, 8, 9, 64)] == [5, 11, 11, 5, 5]
-    assert [groups(24, joint_tiles=j) for j in (0, 1, 8)] == [5, 5, 5]
+    assert [groups(24, joint_tiles=j) for j in (0, 1, 8)] == [5, 11, 11]
     assert [groups(64, window=w) for w in (0, 1, 64)] == [28, 28, 28]
     assert [groups(24, dtype="fp32", window=w) for w in (0, 1, 64)] == [11, 11, 11]
     for n_out in (80, 128, 256, 1024, 1025, 3200, 16400):
