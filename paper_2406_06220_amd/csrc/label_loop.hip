@@ -26,15 +26,16 @@
 //   * Four wavefronts a workgroup, one per SIMD.  What a label costs beside the exchanges is the number
 //     of instructions in a row, and two wavefronts that share a SIMD take turns at them.  It also
 //     leaves 512 registers a lane, and the weights stay in them: those of phase Q for the whole call (one
-//     layer), those of a joint pass while its work items cover the same column tiles, which a group's
-//     plans seldom change (stateless, and one layer unless phase Q has two rounds in bfloat16).  Scalar registers are short: 100 to 400 scalar values of a form are kept in lanes of
-//     vector registers and moved back where they are used.
+//     layer; float32's longest form with two rounds: the first), those of a joint pass while its work
+//     items cover the same column tiles, which a group's plans seldom change (stateless, and one layer but
+//     for two rounds in bfloat16).  Scalar registers are short: 100 to 400 scalar values of a form are
+//     kept in lanes of vector registers and moved back where they are used.
 //   * Every wavefront multiplies its own quarter of the reduction for all column tiles.  So no two
 //     wavefronts need the same activation: each loads, waits for and splits its quarter of the rows, and
 //     only the partial sums are shared (rows staged in LDS for all wavefronts, with the barrier that
-//     takes: config 2 at B = 1 648 us against 610; stateless at B = 128 3.11 ms against 2.70).  A wavefront's
-//     rows change lanes through LDS of its own (stages_rows) and are split between the products of the
-//     step before (split_and_multiply).
+//     takes: config 2 at B = 1 648 us against 610; stateless at B = 128 3.11 ms against 2.70).  Where there is
+//     one LSTM layer or none, a wavefront's rows change lanes through LDS of its own (stages_rows) and are
+//     split between the products of the step before (split_and_multiply).
 //
 // Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
 // exchange (a workgroup without work item: a word of its own that everybody waits for), after it
@@ -332,9 +333,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     }
     const int Hp = p.h_pred, L = DEEP ? p.pred_layers : 1;
 
-    // ---- LDS: the tile of packed rows (bfloat16), the partial sums of a round -- of the predictor side
-    // and of a joint pass, which may start while the former are still read -- and what this workgroup
-    // keeps of its own units: recurrent pre-activations, cell state, (chunks) hidden state
+    // ---- LDS: in deeper LSTMs of few hypotheses the tile of packed rows, with planes the zeros that stand for the rows
+    // of their second tile (bfloat16); the partial sums of a round -- of the predictor side and of a joint
+    // pass, which may start while the former are still read; every wavefront's staged rows (STAGED; eight
+    // wavefronts: over the partial sums); and what this workgroup keeps of its own units: recurrent
+    // pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
     float *const part_q = reinterpret_cast<float *>(dyn_lds + (PLANES && hpc <= kPairRows ? NK * 64 : PL == 3 && DEEP && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
@@ -554,9 +557,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         if (n <= H2) products_of(packed_tag, half, a, b, tiles, sn, part);
         else products_of(packed_tag, all, a, b, tiles, sn, part);
     };
-    // ---- activation fragments.  A wavefront multiplies its own stretch of the reduction only, so it
-    // loads that stretch of all 16 rows straight into the registers the matrix cores read -- lane l part
-    // l / 16 of every step of row l % 16 -- and no row goes through LDS.
+    // ---- activation fragments.  A wavefront multiplies its own stretch of the reduction only.  In the deep
+    // form of four wavefronts it loads that stretch of all 16 rows straight into the registers the matrix
+    // cores read, lane l part l / 16 of every step of row l % 16 (up to kPackRows rows of the hidden state: see
+    // load_packed); in the others rows are staged (stage_rows).
     // Byte offset of a lane's part of step s in a row of K inputs; parts beyond the row's end read its last
     // inputs again (they meet zeros in the weights, but must be numbers).
     auto part_of = [&](int s, int s0, int K) __attribute__((always_inline)) {
@@ -591,7 +595,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             a[0] = AFrag{x0[0], x0[1], x0[2], x0[3]};
         }
     };
-    // staged rows: eight lanes take 128 bytes of a row; this lane's are inputs fcol() .. + 3 of piece i of rows
+    // staged rows: eight lanes take 128 bytes of a row; this lane's are inputs i * 32 + lane % 8 * 4 .. + 3 of the wavefront's stretch of rows
     // lane / 8 and lane / 8 + 8 (inputs beyond the row's end: its last ones again)
     auto flat_off = [&](int i, int s0, int K) __attribute__((always_inline)) {
         return min(s0 * KS + i * 32 + (lane & 7) * 4, K - 4) * (int)sizeof(float);
@@ -796,8 +800,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         }
     };
     // Row tile tq of this label iteration's hidden state (row0: the group's first row in the exchange
-    // buffer): loads, waits, splits.  A row without an active hypothesis repeats one that has (no
-    // branches, and nobody looks at its results).
+    // buffer): loads, waits, splits.  For a row without an active hypothesis nothing is loaded where rows are
+    // staged, elsewhere it repeats one that has (nobody looks at its results).
     auto stage_h = [&](AFrag (&a)[NK][PL], int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
         const int any = __ffsll((long long)in_tile) - 1;
         if (DEEP && qpack) {   // a wavefront takes a row
