@@ -3,6 +3,7 @@ bit the subtraction of the number with its lower 16 bits masked away."""
 from __future__ import annotations
 
 import ctypes as C
+import os
 
 import numpy as np
 import pytest
@@ -31,6 +32,8 @@ def patterns():
 @pytest.mark.parametrize("partner", ["itself", "zero", "edge", "drawn"])
 def test_what_a_term_leaves(partner):
     import torch
+    if not os.path.exists(build.TERMS_TEST_LIB):
+        build.build_terms_test_library()
     lib = C.CDLL(build.TERMS_TEST_LIB)
     x = patterns()
     rng = np.random.default_rng(3)
