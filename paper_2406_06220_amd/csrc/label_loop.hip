@@ -135,6 +135,11 @@ template <typename T, int M, int N> __device__ inline void any_value(T (&x)[M][N
 #pragma unroll
     for (int i = 0; i < M; ++i) any_value(x[i]);
 }
+template <typename T, int M, int N> __device__ inline void any_acc(T (&x)[M][N])
+{
+#pragma unroll
+    for (int i = 0; i < M * N; ++i) asm volatile("" : "=a"(x[i / N][i % N]));
+}
 // a value the compiler must not compute ahead of the loop it is used in (it would be kept, and
 // spilled, through the whole label loop for the sake of an addition)
 __device__ inline int here(int v)
@@ -491,7 +496,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     const __amdgpu_buffer_rsrc_t wrs = buffer_of(p.packed, p.packed_bytes);
     auto fetch = [&](auto &b, int n, int s0, int sn, auto tile_off) __attribute__((always_inline)) {
         constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
-        any_value(b);
+        if constexpr (PL == 3 && !WIDE) any_acc(b);
+        else any_value(b);
 #pragma unroll
         for (int t = 0; t < TT; ++t)
             if (t < n) {   // uniform
@@ -910,6 +916,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     int prev2_items = 0, prev2_tiles = 0, clr_items = 0, clr_tiles = 0;   // the two before it
     unsigned long long act_prev = 0ull;        // who took part in the previous label's rows
     bool first = true, ok = true;
+    int dcg0 = -1, dcg1 = -1, dcg_tpg = 0;   // the column groups of dcg_tpg tiles that hold duration outputs (at most two: there are at most 16)
 
     // puts back what this workgroup wrote in the label iteration before (see the head of the file)
     auto clear_rows = [&]() __attribute__((always_inline)) {
@@ -1025,7 +1032,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         ti = ti0;
         cg = cg0;
         if (it != rank) {
-            ti = it / n_cg;
+            ti = it / here(n_cg);   // (the division's preparation stays in here)
             cg = it - ti * n_cg;
         }
         tile0 = cg * tpg;
@@ -1386,8 +1393,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 
         // the projected encoder frames of a work item: this wavefront's stretch of its rows
         v4u e4[NK][NL], ev[2 * C32];   // (not wide; staged: ev)
-        any_value(e4);
-        any_value(ev);
         have_p = false;
         auto request_rows = [&]() __attribute__((always_inline)) {
             if constexpr (STAGED) {
@@ -1424,6 +1429,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             __builtin_amdgcn_sched_barrier(0);
             if (TWO_ROUNDS && !KEEPQ2) fetch_second(bq2);   // (they take about as long to leave as the row to arrive)
             __builtin_amdgcn_sched_barrier(0);
+            // (waited for here, in all lanes: behind a branch that some lanes or workgroups skip the compiler takes the
+            // loads for pending still and waits for what was sent after them, the published hidden state)
+            asm volatile("" ::"v"(t4[0]), "v"(t4[1]));
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 if ((h == 0 || two_cells) && h_off[h] != kNowhere && ((act >> c_g[h]) & 1ull)) {
@@ -1691,8 +1699,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             unsigned long long *const jbb = jb + (size_t)buf * cells, *const jlb = jl + (size_t)buf * cells;
             unsigned long long *const jdb = jd + (size_t)buf * 2 * rows_cap;
             unsigned long long *const jhb = jh + (size_t)buf * C;
-            // the column groups that hold duration outputs (at most two: there are at most 16)
-            const int dcg0 = D > 0 ? ((VL + 1) / CT) / tpg : -1, dcg1 = D > 0 ? ((O - 1) / CT) / tpg : -1;
+            if (D > 0 && tpg != dcg_tpg) {   // uniform
+                dcg_tpg = tpg;
+                dcg0 = ((VL + 1) / CT) / tpg;
+                dcg1 = ((O - 1) / CT) / tpg;
+            }
 
             // ---- J
 #pragma clang loop unroll(disable)
