@@ -252,6 +252,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr int PL = F::PL, KS = F::KS, NL = F::E / 4;   // NL: 16-byte loads of float32 for a lane's part of a step
     constexpr bool LSTM = LAYERS > 0, DEEP = LAYERS > 1, WIDE = NW == 8;
     constexpr int THREADS = NW * 64;
+    constexpr int kClearer = NW - 2;                          // the wavefront that puts cells back (the last one sums scores meanwhile)
     constexpr int TR = label_tiles(NK);                       // column tiles per round of a joint pass
     constexpr int TJ = LAYERS == 0 && !WIDE ? TQ : TR;        // ... per its first round
     constexpr int JH = TJ > 4 ? 2 : 1;                        // which is looked at four tiles, four columns a thread, at a time
@@ -370,10 +371,24 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     float *const hx = p.hbuf;         // [2][L][Bw][Hp]
     float *const px = p.pred_proj;    // [2][Bw][H]
     const int cells = p.cells_per_cluster;   // joint cells of one buffer (work items x 16)
-    unsigned long long *const jb = p.row_lab + (size_t)cl * kRowBufs * cells;              // packed (logit, ~label)
-    unsigned long long *const jl = p.row_lse + (size_t)cl * kRowBufs * cells;              // (largest logit, sum of exp)
-    unsigned long long *const jd = p.row_dur + (size_t)cl * kRowBufs * 2 * rows_cap;
-    unsigned long long *const jh = p.present + (size_t)cl * (kRowBufs + 1) * C;   // (the last: state has been read)
+    // The words of the joint exchanges lie behind one another (label_layout, two megabytes at most) and are reached through
+    // one descriptor: a lane offset and a scalar offset instead of 64-bit sums of pointers, of which a pass needed some
+    // twenty.  Byte offsets of this group's, and the bytes of one of their kRowBufs buffers:
+    auto behind = [&](const unsigned long long *q) { return (int)((q - p.row_lab) * sizeof(unsigned long long)); };
+    const int jb_n = cells * 8, jd_n = 2 * rows_cap * 8, jh_n = C * 8;
+    const int jb = cl * kRowBufs * jb_n;                          // packed (logit, ~label)
+    const int jl = behind(p.row_lse) + jb;                        // (largest logit, sum of exp)
+    const int jd = behind(p.row_dur) + cl * kRowBufs * jd_n;      // packed (logit, ~duration class)
+    const int jh = behind(p.present) + cl * (kRowBufs + 1) * jh_n;   // workgroups without a work item (the last: state has been read)
+    const __amdgpu_buffer_rsrc_t crs = buffer_of(p.row_lab, (size_t)behind(p.present) + (size_t)ncl * (kRowBufs + 1) * jh_n);
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    auto ld_word = [&](int lane_off, int off) __attribute__((always_inline)) {
+        const v2u x = __builtin_amdgcn_raw_buffer_load_b64(crs, lane_off, off, 16 /* sc1 */);
+        return (unsigned long long)x.x | ((unsigned long long)x.y << 32);
+    };
+    auto st_word = [&](int lane_off, int off, unsigned long long v) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_buffer_store_b64(v2u{(unsigned)v, (unsigned)(v >> 32)}, crs, lane_off, off, 16 /* sc1 */);
+    };
 
     // ---- Alg. 3 lines 3-4.  Lane g of every wavefront holds hypothesis g of the group
     __syncthreads();
@@ -418,7 +433,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     if (CHUNKED) {   // rank 0 writes the new state when everybody has read the old one
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) st_co64(jh + (size_t)kRowBufs * C + rank, 1ull);
+        if (tid == 0) st_word(rank * 8, jh + kRowBufs * jh_n, 1ull);
     }
     const unsigned long long owned = __ballot(mine && lane % C == rank);   // whose scores this workgroup sums
 
@@ -478,11 +493,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         }
     };
     // waits until the words of every lane are there (zero: not yet) and returns them
-    auto wait_word = [&](const unsigned long long *q) __attribute__((always_inline)) {
+    auto wait_word = [&](int lane_off, int off) __attribute__((always_inline)) {
         unsigned spins = 0;
         long long since = 0;
         for (;;) {
-            const unsigned long long x = ld_co64(q);
+            asm volatile("" ::: "memory");   // (see until_there)
+            const unsigned long long x = ld_word(lane_off, off);
             if (__ballot(x == 0ull) == 0ull || give_up(spins, since)) return x;
         }
     };
@@ -949,18 +965,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     };
     // ... and its cells of the joint pass two before the last
     auto clear_cells = [&]() __attribute__((always_inline)) {
-        if (C > 1 && jpass > 2) {
-            const unsigned pb = (jpass - 3) & (kRowBufs - 1);
+        if (C > 1 && jpass > 2 && wave == kClearer) {   // uniform
+            const int pb = (int)((jpass - 3) & (kRowBufs - 1));
             const int stride = WIDE ? prev_cg : C;   // (wide: the same split in every pass)
+            const int cell = (lane & 16 ? jl : jb) + (lane & 15) * 8;
             if (rank < stride)
 #pragma clang loop unroll(disable)
             for (int it = rank; it < clr_items; it += stride)
-                if (tid < 2 * RT) st_co64((tid < RT ? jb : jl) + (size_t)pb * cells + (size_t)it * RT + (tid & 15), 0ull);
+                if (lane < 2 * RT) st_word(cell, pb * jb_n + it * RT * 8, 0ull);
             if (D > 0)   // (whoever wrote them: the words of a row tile are put back by rank ti)
 #pragma clang loop unroll(disable)
                 for (int ti = rank; ti < clr_tiles; ti += C)
-                    if (tid < 2 * RT) st_co64(jd + ((size_t)pb * rows_cap + (size_t)ti * RT) * 2 + tid, 0ull);
-            if (rank >= (WIDE ? stride : clr_items) && tid == 0) st_co64(jh + (size_t)pb * C + rank, 0ull);
+                    if (lane < 2 * RT) st_word(lane * 8, jd + pb * jd_n + ti * RT * 16, 0ull);
+            if (rank >= (WIDE ? stride : clr_items) && lane == 0) st_word(rank * 8, jh + pb * jh_n, 0ull);
         }
     };
 
@@ -982,8 +999,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 const int c = min(c0 + lane, prev_cg - 1);
                 const unsigned long long x =
                     C == 1 ? S.rowl[r]
-                           : wait_word(jl + (size_t)((jpass - 1) & (kRowBufs - 1)) * cells +
-                                       ((size_t)(r >> 4) * prev_cg + c) * RT + (r & 15));
+                           : wait_word(c * RT * 8, jl + (int)((jpass - 1) & (kRowBufs - 1)) * jb_n + ((r >> 4) * prev_cg * RT + (r & 15)) * 8);
                 const float cm = __uint_as_float((unsigned)x), cs = __uint_as_float((unsigned)(x >> 32));
                 if (c0 + lane < prev_cg && cs > 0.0f) s += cs * __expf(cm - rowm);
             }
@@ -1080,8 +1096,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // all at the end of a batch) 31.9; the barrier in the middle as well 30.3.  Two row tiles take 0.95 us a
     // batch of two tiles, of which the matrix cores need 0.8 (96 products a SIMD, 18 cycles each at 2.1 GHz);
     // one takes 1.2 us a batch of four (the stream of weights alone 1.05 us: 126 GB/s a compute unit).
-    auto wide_rows = [&](auto rtag, int tb, unsigned long long *jbb, unsigned long long *jlb, unsigned long long *jdb, int dcg0,
-                         int dcg1) __attribute__((always_inline)) {
+    auto wide_rows = [&](auto rtag, int tb, int jbb, int jlb, int jdb) __attribute__((always_inline)) {
         constexpr int R = decltype(rtag)::value, TB = 4 / R, PW = TB * CT + 4;
         constexpr int CPT = 2, QR = TB * CT / CPT;   // columns a thread looks at, threads of a row
         constexpr int PB = NW * R * RT * PW;         // floats of a buffer of partial sums (of two)
@@ -1345,10 +1360,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             const unsigned long long lse = (unsigned long long)__float_as_uint(m) |
                                            ((unsigned long long)__float_as_uint(m > kNone ? sum : 0.0f) << 32);
             if (C > 1) {
-                st_co64(jbb + o, best);
-                if (cg == dcg0) st_co64(jdb + (size_t)(tr * 2) * RT + i, bd);
-                else if (cg == dcg1) st_co64(jdb + (size_t)(tr * 2 + 1) * RT + i, bd);
-                st_co64(jlb + o, lse);
+                st_word(o * 8, jbb, best);
+                if (cg == dcg0) st_word((tr * 2 * RT + i) * 8, jdb, bd);
+                else if (cg == dcg1) st_word(((tr * 2 + 1) * RT + i) * 8, jdb, bd);
+                st_word(o * 8, jlb, lse);
             } else {
                 S.rowb[tr * RT + i] = best;
                 S.rowl[tr * RT + i] = lse;
@@ -1692,13 +1707,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // (a group of one workgroup: this pass writes over what the terms of the last one are summed from)
             if (C == 1 && (!LSTM || again) && wave == NW - 1) finish_scores();
             if (again) plan_pass(needm);
-            const unsigned buf = jpass & (kRowBufs - 1);
+            const int buf = (int)(jpass & (kRowBufs - 1));
             ++jpass;
             st_joint_passes += 1;
             st_joint_rows += M;
-            unsigned long long *const jbb = jb + (size_t)buf * cells, *const jlb = jl + (size_t)buf * cells;
-            unsigned long long *const jdb = jd + (size_t)buf * 2 * rows_cap;
-            unsigned long long *const jhb = jh + (size_t)buf * C;
+            const int jbb = jb + buf * jb_n, jlb = jl + buf * jb_n, jdb = jd + buf * jd_n, jhb = jh + buf * jh_n;
             if (D > 0 && tpg != dcg_tpg) {   // uniform
                 dcg_tpg = tpg;
                 dcg0 = ((VL + 1) / CT) / tpg;
@@ -1946,11 +1959,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 // (no label column, or no logit that is a number: below every label, but present)
                 const unsigned long long best = rm > -INFINITY ? pack_best(rm, ra) : 1ull;
                 const unsigned long long bd = rdm > -INFINITY ? pack_best(rdm, rda) : 1ull;
-                const int o = it * RT + i;
                 if (C > 1 && quad == 0) {
-                    st_co64(jbb + o, best);
-                    if (cg == dcg0) st_co64(jdb + (size_t)(ti * 2) * RT + i, bd);
-                    else if (cg == dcg1) st_co64(jdb + (size_t)(ti * 2 + 1) * RT + i, bd);
+                    st_word(i * 8, jbb + it * RT * 8, best);
+                    if (cg == dcg0) st_word(i * 8, jdb + ti * 2 * RT * 8, bd);
+                    else if (cg == dcg1) st_word(i * 8, jdb + (ti * 2 + 1) * RT * 8, bd);
                 }
                 fold_sums();
                 if (quad == 0) {
@@ -1958,7 +1970,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const unsigned long long lse =
                         (unsigned long long)__float_as_uint(rm) | ((unsigned long long)__float_as_uint(rs) << 32);
                     if (C > 1) {
-                        st_co64(jlb + o, lse);
+                        st_word(i * 8, jlb + it * RT * 8, lse);
                     } else {
                         S.rowb[ti * RT + i] = best;
                         S.rowl[ti * RT + i] = lse;
@@ -1978,8 +1990,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     for (int t = 0; t < n_tiles; t += 2) {
                         const std::integral_constant<int, 1> one{};
                         const std::integral_constant<int, 2> two{};
-                        if (t + 1 < n_tiles) wide_rows(two, t, jbb, jlb, jdb, dcg0, dcg1);
-                        else wide_rows(one, t, jbb, jlb, jdb, dcg0, dcg1);
+                        if (t + 1 < n_tiles) wide_rows(two, t, jbb, jlb, jdb);
+                        else wide_rows(one, t, jbb, jlb, jdb);
                     }
                 }
             }
@@ -1987,7 +1999,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             if (rank >= busy) {   // no work item: say that this workgroup has come this far
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
-                if (tid == 0) st_co64(jhb + rank, 1ull);
+                if (tid == 0) st_word(rank * 8, jhb, 1ull);
             }
             TR(29);
             lap(kTkJ);
@@ -2003,11 +2015,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // lane = (column group modulo 4, row)
             const int wsh = n_tiles == 1 && n_cg > 8 ? 2 : n_tiles <= 2 && n_cg > 4 ? 1 : 0, wpt = 1 << wsh;
             if (C > 1) {
-                const int i = lane & 15;
+                const int i = (lane & 15) * 8;
 #pragma clang loop unroll(disable)
                 for (int tw = wave; tw < n_tiles << wsh; tw += NW) {   // (more than once only for many row tiles)
                     const int tt = tw >> wsh, wq = tw & (wpt - 1);
-                    const unsigned long long *src = jbb + (size_t)tt * n_cg * RT + i;
+                    const int src = jbb + tt * n_cg * RT * 8;
                     unsigned long long best = 0ull;
                     const int step = 4 << wsh;
                     // Words a lane takes at a time: four, or six where four would leave out some of 17 to 24 column groups and
@@ -2025,10 +2037,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             long long since = 0;
                             for (;;) {
                                 bool all = true;
+                                asm volatile("" ::: "memory");   // (see until_there)
 #pragma unroll
                                 for (int e = 0; e < N; ++e) {
                                     const int c = cb + (lane >> 4) + e * step;
-                                    x[e] = ld_co64(src + (e > 3 && c >= n_cg ? cb + (lane >> 4) : min(c, n_cg - 1)) * RT);
+                                    x[e] = ld_word(i + (e > 3 && c >= n_cg ? cb + (lane >> 4) : min(c, n_cg - 1)) * (RT * 8), src);
                                 }
 #pragma unroll
                                 for (int e = 0; e < N; ++e) all = all & (x[e] != 0ull);
@@ -2043,17 +2056,17 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     if (n_cg <= 4 * step || n_cg > 24) gather_cells(four);
                     else gather_cells(six);
                     best = max_over_rows(best);
-                    if (lane < RT) S.rowb[(wq * n_tiles + tt) * RT + i] = best;
+                    if (lane < RT) S.rowb[(wq * n_tiles + tt) * RT + lane] = best;
                 }
                 if (D > 0) {   // the duration head's words: one or two column groups
                     const int two = dcg1 != dcg0 ? RT : 0;
 #pragma clang loop unroll(disable)
                     for (int rb = (NW - 1 - wave) * 64; rb < n_tiles * RT; rb += THREADS) {   // uniform
                         const int r = min(rb + lane, n_tiles * RT - 1);
-                        const unsigned long long *q = jdb + (size_t)(r >> 4) * 2 * RT + (r & 15);
-                        unsigned long long x = wait_word(q);
+                        const int q = ((r >> 4) * 2 * RT + (r & 15)) * 8;
+                        unsigned long long x = wait_word(q, jdb);
                         if (two) {
-                            const unsigned long long y = wait_word(q + two);
+                            const unsigned long long y = wait_word(q + two * 8, jdb);
                             x = x > y ? x : y;
                         }
                         S.rowd[r] = (unsigned)S.durations[unpack_index(x) & (TDT_MAX_DURATIONS - 1)];   // the frame step
@@ -2061,7 +2074,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 }
                 if (busy < C && wave == 1)   // the workgroups without a work item
 #pragma clang loop unroll(disable)
-                    for (int c = busy; c < C; c += 64) wait_word(jhb + min(c + lane, C - 1));
+                    for (int c = busy; c < C; c += 64) wait_word(min(c + lane, C - 1) * 8, jhb);
             }
             TR(31);
             __syncthreads();
@@ -2070,12 +2083,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // ---- D: every wavefront takes the same decisions.  Rows of passes of up to 64 rows sit in
             // lanes; larger passes are first brought together in LDS
             fresh();
-            const int w_rows = n_tiles * RT;
+            const int w_rows = n_tiles * RT, stop = S.aborted;
             auto row_result = [&](int r, int &ra, int &step, unsigned long long &best) __attribute__((always_inline)) {
                 best = S.rowb[r];
-                for (int w = 1; C > 1 && w < wpt; ++w) {
-                    const unsigned long long o = S.rowb[w * w_rows + r];
-                    best = o > best ? o : best;
+                if (wpt > 1) {   // uniform; two shares or four, all on their way before the first is looked at
+                    const unsigned long long x = S.rowb[w_rows + r], y = S.rowb[(wpt - 2) * w_rows + r], z = S.rowb[(wpt - 1) * w_rows + r];
+                    best = x > best ? x : best;
+                    best = y > best ? y : best;
+                    best = z > best ? z : best;
                 }
                 ra = unpack_index(best);
                 if ((unsigned)ra > (unsigned)VL) ra = V;   // (no logit of the row is a number)
@@ -2103,12 +2118,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 } else {
                     const int code = ra < V ? 0 : max(step, 1);   // frames a non-label moves on; 0: a label
                     bool go = need;
-                    while (__ballot(go) != 0ull) {
+                    while (__ballot(go) != 0ull) {   // (selections: branches on lanes are three times the instructions)
                         const int x = __builtin_amdgcn_ds_bpermute(((base + w) & 63) * 4, code);
-                        if (go) {
-                            if (x == 0) { found = true; go = false; }
-                            else { w += x; go = w < nv; }
-                        }
+                        found = found | (go & (x == 0));
+                        w += go ? x : 0;
+                        go = go & (x != 0) & (w < nv);
                     }
                 }
                 const int at = ((base + (found ? w : 0)) & 63) * 4;
@@ -2136,7 +2150,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     kb = (unsigned)(S.rowb[base + w] >> 32);
                 }
             }
-            ok = uni(S.aborted) == 0;
+            ok = uni(stop) == 0;
             if (!ok) break;
             // ---- Alg. 3 line 20, Sec. 3.1 add_results (selections: a branch costs more than what it skips)
             {
@@ -2194,7 +2208,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // ---- what the next chunk takes up
     if (CHUNKED) {
         if (ok && rank == 0 && wave == 0)
-            for (int c = 0; c < C; c += 64) wait_word(jh + (size_t)kRowBufs * C + min(c + lane, C - 1));
+            for (int c = 0; c < C; c += 64) wait_word(min(c + lane, C - 1) * 8, jh + kRowBufs * jh_n);
         __syncthreads();
         ok = ok && uni(S.aborted) == 0;
     }
