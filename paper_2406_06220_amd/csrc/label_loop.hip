@@ -1500,15 +1500,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         }
         if constexpr (LSTM) {
             TR(2);
-            // ---- while the hidden state travels: the first joint pass is set up, and what was exchanged
-            // for the label before is put back
+            // ---- while the hidden state travels: what was exchanged for the label before is put back, and the first joint
+            // pass is set up
             fresh();
-            if (needm != 0ull) {
-                plan_pass(needm);
-                set_item(rank);   // (a workgroup without a work item: never used)
-                if (!WIDE && rank < items) request_rows();
-            }
-            TR(3);
             if constexpr (LAYERS == 1) {
                 const v4u absent = {kAbsent, kAbsent, kAbsent, kAbsent};
                 const int pb = (par ^ 1) * Bw + b0;
@@ -1521,6 +1515,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 clear_rows();
             }
             clear_cells();
+            if (needm != 0ull) {
+                plan_pass(needm);
+                set_item(rank);   // (a workgroup without a work item: never used)
+                if (!WIDE && rank < items) request_rows();
+            }
+            TR(3);
             if (wave == NW - 1) finish_scores();
             fresh();
             TR(10);
