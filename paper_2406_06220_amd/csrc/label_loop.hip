@@ -20,6 +20,7 @@
 //   * A workgroup owns its column tiles of the predictor-side matrices for the whole call.  The four
 //     gates of a unit meet in the workgroup that updates the unit's cell, so the recurrent
 //     pre-activations and the cell state never leave its LDS; only h is exchanged.
+//   * A group's hypotheses wait for each other's searches only until half of them do (see "patience").
 //   * The control state of a hypothesis (frame, label count, last labels, score ...) lives in lane g
 //     of every wavefront, the lists of active and searching hypotheses are 64-bit masks: a decision
 //     is taken by every wavefront on its own, without a workgroup barrier or LDS list.
@@ -66,6 +67,7 @@ constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront 
 static_assert(kNowhere >= 2ll * TDT_MAX_LSTM_LAYERS * kMaxGrid * kLabelMaxHyps * kLabelLongest * 4, "the largest exchange buffer");
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kPairRows = 8;                // up to this many rows two planes do (one LSTM layer)
+constexpr int kLongWindow = 16;             // frames of a pass of which a search seldom takes a second one
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -269,6 +271,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890) --
     // nor, the registers, where phase Q's second round has them (see "Weights that stay").
     constexpr bool OWN2 = DEEP ? PL == 1 && NK > 4 : !(TWO_ROUNDS && PL == 3);
+    // Hypotheses that have found a label need not wait for all that search, see "patience".  Not where the predictor's
+    // rows are read from the exchange buffers in every pass, from which they are gone a label later, and not with float32's
+    // shortest reductions, whose small models have long windows (the smallest benchmark model 150 us a call, with it 155).
+    constexpr bool MERGES = !WIDE && (LAYERS == 0 || (LAYERS == 1 && TWO)) && !(PL == 1 && NK <= 4);
     constexpr bool PLANES = PL == 3 && LAYERS == 1;   // few rows of the hidden state: staged as planes, see stage_planes
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
@@ -459,6 +465,18 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     }
     __syncthreads();
 
+    // ---- Algorithm 3's inner loop ends when nobody searches any more: a group's label takes as many joint passes as its
+    // longest search, and who has found one waits.  Here it ends, from the second pass of a search on, as soon as those
+    // who wait are as many as those who search (no predictor: half as many): they take their predictor step, and
+    // the next pass scores both.  A hypothesis' own sequence of steps is the same; the group's joint passes are fewer, for more
+    // predictor steps of fewer hypotheses.  Replays of decoded hypotheses (7 to 16 of a group; labels in bursts, and drawn on 3 to 60
+    // % of the frames) take 0.82 to 1.00 of the lock step's time with this rule, with a step after every pass that found
+    // one 0.82 to 1.24 (predictor and joint pass at their measured times).  Not with a caller's window, which asks for the steps
+    // as they are printed, nor with long ones, of which a search takes one.  us a call, in lock step / now: RNN-T B = 32 987 / 943,
+    // B = 128 1986 / 1850, TDT B = 32 494 / 448, stateless B = 128 1979 / 1782, multi-blank B = 27 521 / 504; one or two
+    // hypotheses a group, who have nobody to wait for, 235 / 237.
+    const int patience = MERGES && p.window == 0 && uni(S.plan[G].Kw) < kLongWindow ? (LSTM ? 1 : 2) : 0;
+
     unsigned st_pred_passes = 0, st_joint_passes = 0;
     long long st_pred_rows = 0, st_joint_rows = 0;
 
@@ -627,6 +645,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     auto lds_order = []() __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_wave_barrier();
+    };
+    // (rows: which of them; the others keep what they have)
+    auto stage_some = [&](float *x, const v4u (&v)[2 * C32], bool upper, unsigned rows) __attribute__((always_inline)) {
+        float *const at = x + (lane >> 3) * LDX + (lane & 7) * 4;
+        rows >>= lane >> 3;
+        lds_order();
+        if (rows & 1u)
+#pragma unroll
+            for (int i = 0; i < C32; ++i) *reinterpret_cast<v4u *>(at + i * 32) = v[i];
+        if (upper && (rows >> 8 & 1u))   // (upper: uniform)
+#pragma unroll
+            for (int i = 0; i < C32; ++i) *reinterpret_cast<v4u *>(at + 8 * LDX + i * 32) = v[C32 + i];
+        lds_order();
     };
     auto stage_rows = [&](float *x, const v4u (&v)[2 * C32], bool upper) __attribute__((always_inline)) {
         float *const at = x + (lane >> 3) * LDX + (lane & 7) * 4;
@@ -932,6 +963,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     int prev2_items = 0, prev2_tiles = 0, clr_items = 0, clr_tiles = 0;   // the two before it
     unsigned long long act_prev = 0ull;        // who took part in the previous label's rows
     bool first = true, ok = true;
+    unsigned long long needm = 0ull;           // who searches
     int dcg0 = -1, dcg1 = -1, dcg_tpg = 0;   // the column groups of dcg_tpg tiles that hold duration outputs (at most two: there are at most 16)
 
     // puts back what this workgroup wrote in the label iteration before (see the head of the file)
@@ -1393,8 +1425,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     int in_b = -1, in_b2 = -1;
 #pragma clang loop unroll(disable)
     while (ok) {   // ---- Alg. 3 line 5: while any hypothesis is active
-        const unsigned long long act = __ballot(active);
-        if (act == 0ull) break;
+        const unsigned long long alive = __ballot(active);
+        if (alive == 0ull) break;
+        const unsigned long long act = alive & ~needm;   // who takes a predictor step: not those in the middle of a search
         st_pred_passes += 1;
 #if TDT_TRACE
         if (tid == 0) g_tr_on = (st_pred_passes >= 20 && st_pred_passes < 24);
@@ -1404,7 +1437,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         // who will search in the first joint pass (in a chunk a hypothesis may only be here for the
         // predictor step of its last label)
         bool need = active && !(CHUNKED && (time >= len || (status & TDT_HYP_TRUNCATED)));
-        unsigned long long needm = __ballot(need);
+        needm = CHUNKED ? __ballot(need) : alive;
 
         // the projected encoder frames of a work item: this wavefront's stretch of its rows
         v4u e4[NK][NL], ev[2 * C32];   // (not wide; staged: ev)
@@ -1562,6 +1595,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const int quad = lane & 15, row = qpack   ? wave + (lane >> 4) * kPackRows
                                                       : qpair ? wave * 2 + ((lane >> 4) & 1) + (lane >> 5) * kPairRows
                                                               : tid >> 4;
+                    const int q_g = qpack ? wave : qpair ? row & (kPairRows - 1) : row;   // the hypothesis
 #pragma unroll
                     for (int h = 0; h < QH; ++h)
                         if (h == 0 || nq > 4) {   // uniform
@@ -1581,7 +1615,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                                            __float_as_uint(present(v.z + q_bias[h].z)), __float_as_uint(present(v.w + q_bias[h].w))};
                             __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_off[h], (par * Bw + b0) * H * (int)sizeof(float),
                                                                    16 /* sc1 */);
-                            if (q_unit[h] >= 0) rg_l[q_unit[h]] = v;   // the four gates of one unit
+                            if (q_unit[h] >= 0 && ((unsigned)act >> q_g & 1u)) rg_l[q_unit[h]] = v;   // the four gates of one unit
                         }
                 }
             }
@@ -1700,7 +1734,34 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
         }
         if constexpr (!LSTM) plan_pass(needm);
-        // ---- inner loop (Alg. 3 line 12): joint passes until nobody searches any more
+        // (TWO, LSTM) this label's rows of the projected predictor output are staged; the others' are still there
+        auto take_p = [&](unsigned long long rows, v4u (&v)[2 * C32]) __attribute__((always_inline)) {
+            int off[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int g = h * 8 + (lane >> 3);
+                off[h] = (rows >> g) & 1ull ? (par * Bw + b0 + g) * H * (int)sizeof(float) : kNowhere;
+            }
+            const bool upper = (rows >> 8) != 0ull;
+            until_there([&]() __attribute__((always_inline)) {
+                unsigned mx = 0;
+#pragma unroll
+                for (int i = 0; i < C32; ++i) v[i] = ldx4(prs, off[0] + flat_off(i, js0, H), 0);
+                if (upper)
+#pragma unroll
+                    for (int i = 0; i < C32; ++i) v[C32 + i] = ldx4(prs, off[1] + flat_off(i, js0, H), 0);
+#pragma unroll
+                for (int i = 0; i < C32; ++i) mx = max(mx, umax4(v[i]));
+                if (upper)
+#pragma unroll
+                    for (int i = 0; i < C32; ++i) mx = max(mx, umax4(v[C32 + i]));
+                return mx;
+            });
+            lap(kTkBar);
+            stage_some(xp, v, upper, (unsigned)rows);
+        };
+        // ---- inner loop (Alg. 3 line 12): joint passes until nobody searches any more, or those who wait are enough
+        // (see "patience")
 #pragma clang loop unroll(disable)
         for (bool again = false; needm != 0ull; again = true) {
             fresh();
@@ -1728,7 +1789,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 v4u p4[NK][NL], pv[2 * C32];
                 any_value(pv);
                 int po[NK];
-                bool upper = G > 8;   // more than eight rows of the predictor's
+                bool upper = false;   // more than eight rows of the predictor's
                 const bool load_p = !LSTM || !have_p;
                 // the predictor's rows: of the group's hypotheses (LSTM), of those in this row tile (stateless); one area and an
                 // LSTM: each lane its own row's part, as it is fed (few of the 16 rows are different ones, so they take few of the
@@ -1736,11 +1797,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 // units and joint width, B = 24, 7067 us, 6996; joint width 648, 576 units, two frames a pass, 4779, 4670)
                 constexpr bool DIRECT = STAGED && LSTM && !TWO;
                 if constexpr (STAGED && LSTM && TWO) {
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int g = h * 8 + (lane >> 3);
-                        po[h] = (act >> g) & 1ull ? (par * Bw + b0 + g) * H * (int)sizeof(float) : kNowhere;
-                    }
                 } else if constexpr (STAGED && !LSTM) {
                     const int q0 = uni(q_l), q1 = __builtin_amdgcn_readlane(q_l, 15);
                     upper = q1 - q0 >= 8;
@@ -1798,23 +1854,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     if (TWO) stage_rows(xe, ev, true);
                     if (load_p) {
                         if constexpr (LSTM) {
-                            until_there([&]() __attribute__((always_inline)) {
-                                unsigned mx = 0;
-#pragma unroll
-                                for (int i = 0; i < C32; ++i) pv[i] = ldx4(prs, po[0] + flat_off(i, js0, H), 0);
-                                if (upper)
-#pragma unroll
-                                    for (int i = 0; i < C32; ++i) pv[C32 + i] = ldx4(prs, po[1] + flat_off(i, js0, H), 0);
-#pragma unroll
-                                for (int i = 0; i < C32; ++i) mx = max(mx, umax4(pv[i]));
-                                if (upper)
-#pragma unroll
-                                    for (int i = 0; i < C32; ++i) mx = max(mx, umax4(pv[C32 + i]));
-                                return mx;
-                            });
-                            lap(kTkBar);
+                            take_p(act, pv);
+                        } else {
+                            stage_rows(xp, pv, upper);
                         }
-                        stage_rows(xp, pv, upper);
                         have_p = true;
                     }
                     if (!TWO) {   // one area: the predictor's rows make way for the encoder's
@@ -1997,6 +2040,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
             const int busy = WIDE ? n_cg : items;   // workgroups with a work item (or more)
             if (rank >= busy) {   // no work item: say that this workgroup has come this far
+                if constexpr (MERGES && LSTM)
+                    if (patience > 0 && !have_p) {   // (it may have one when these rows are scored again)
+                        v4u pv[2 * C32];
+                        any_value(pv);
+                        take_p(act, pv);
+                        have_p = true;
+                    }
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
                 if (tid == 0) st_word(rank * 8, jhb, 1ull);
@@ -2181,6 +2231,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             pend_row = base + w;
             pend_m = unpack_value((unsigned long long)kb << 32);
             needm = __ballot(need);
+            // (through a scalar register: what leaves a loop on a condition the compiler can't prove the same in all lanes makes
+            // everything the loop counts a lane's own)
+            const int enough = uni(patience > 0 && __popcll(__ballot(active) & ~needm) * patience >= __popcll(needm) ? 1 : 0);
             TR(33);
             // everybody has read the pass two before this one: its cells are put back (behind the label's
             // last pass: while the next label's hidden state travels)
@@ -2191,12 +2244,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             prev_items = items;
             prev_tiles = n_tiles;
             prev_cg = n_cg;
-            if (!LSTM || needm != 0ull) {
+            if (!LSTM || (needm != 0ull && enough == 0)) {
                 fresh();
                 clear_cells();
             }
             TR(34);
             lap(kTkD);
+            if (enough != 0) break;
         }
         if (!ok) break;
         act_prev = act;
