@@ -271,10 +271,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // without 1727; float32, reductions to 64, B = 12, 448, 441) -- but for float32's longest form (1853, 1890) --
     // nor, the registers, where phase Q's second round has them (see "Weights that stay").
     constexpr bool OWN2 = DEEP ? PL == 1 && NK > 4 : !(TWO_ROUNDS && PL == 3);
-    // Hypotheses that have found a label need not wait for all that search, see "patience".  Not where the predictor's
-    // rows are read from the exchange buffers in every pass, from which they are gone a label later, and not with float32's
+    // Hypotheses that have found a label need not wait for all that search, see "patience".  Not with float32's
     // shortest reductions, whose small models have long windows (the smallest benchmark model 150 us a call, with it 155).
-    constexpr bool MERGES = !WIDE && (LAYERS == 0 || (LAYERS == 1 && TWO)) && !(PL == 1 && NK <= 4);
+    constexpr bool MERGES = !(PL == 1 && NK <= 4);
+    // Rows of the projected predictor output are read from the exchange buffers in every pass (where there are two
+    // areas they stay staged), so a row stays there until its hypothesis' next one: see "own".
+    constexpr bool OWN = LSTM && !(LAYERS == 1 && TWO);
     constexpr bool PLANES = PL == 3 && LAYERS == 1;   // few rows of the hidden state: staged as planes, see stage_planes
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
@@ -475,7 +477,12 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // as they are printed, nor with long ones, of which a search takes one.  us a call, in lock step / now: RNN-T B = 32 987 / 943,
     // B = 128 1986 / 1850, TDT B = 32 494 / 448, stateless B = 128 1979 / 1782, multi-blank B = 27 521 / 504; one or two
     // hypotheses a group, who have nobody to wait for, 235 / 237.
-    const int patience = MERGES && p.window == 0 && uni(S.plan[G].Kw) < kLongWindow ? (LSTM ? 1 : 2) : 0;
+    // Deeper LSTMs, whose predictor step is two joint passes and more: four times as many as search; twice, where the output
+    // layer is streamed and few rows are no shorter pass (two layers, 640 units, B = 32, 1761 us, with two to one 1796, four to one
+    // 1766; B = 128 3205, 3207, 3149; 8198 outputs, B = 96, 3804, 3475, three to one 3507; config 5 29489, 27752).  Reductions
+    // over 640, one layer: joint width 1024, B = 32, 1876 / 1751; TDT, B = 64, 1302 / 1128.
+    const int patience = MERGES && p.window == 0 && uni(S.plan[G].Kw) < kLongWindow ? (LSTM || WIDE ? 1 : 2) : 0;
+    constexpr int kCrowd = !DEEP ? 1 : WIDE ? 2 : 4;
 
     unsigned st_pred_passes = 0, st_joint_passes = 0;
     long long st_pred_rows = 0, st_joint_rows = 0;
@@ -964,10 +971,14 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     unsigned long long act_prev = 0ull;        // who took part in the previous label's rows
     bool first = true, ok = true;
     unsigned long long needm = 0ull;           // who searches
+    // (OWN) which of the two buffers hypothesis g's newest row of the projected predictor output is in.  The other one's is put
+    // back while the newest is made: all have read it in the pass in which the hypothesis found its label.
+    unsigned long long own = 0ull;
+    auto p_row = [&](int g, int other) __attribute__((always_inline)) { return ((int)(own >> g & 1ull) ^ other) * Bw + b0 + g; };
     int dcg0 = -1, dcg1 = -1, dcg_tpg = 0;   // the column groups of dcg_tpg tiles that hold duration outputs (at most two: there are at most 16)
 
     // puts back what this workgroup wrote in the label iteration before (see the head of the file)
-    auto clear_rows = [&]() __attribute__((always_inline)) {
+    auto clear_rows = [&](unsigned long long act) __attribute__((always_inline)) {
         const int pb = par ^ 1;
         const int hrow = Hp * (int)sizeof(float), jrow = H * (int)sizeof(float);
         if (U > 0)
@@ -990,9 +1001,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             for (int c0 = 0; c0 < nc; c0 += 64)
 #pragma clang loop unroll(disable)
                 for (int g = tid >> 4; g < G; g += THREADS / 16)
-                    if (((act_prev >> g) & 1ull) && c0 + c < nc)
-                        __builtin_amdgcn_raw_buffer_store_b128(absent, prs, (b0 + g) * jrow + (qt0 * CT + c0 + c) * (int)sizeof(float),
-                                                               pb * Bw * jrow, 16 /* sc1 */);
+                    if (((act >> g) & 1ull) && c0 + c < nc)
+                        __builtin_amdgcn_raw_buffer_store_b128(absent, prs, p_row(g, 1) * jrow + (qt0 * CT + c0 + c) * (int)sizeof(float),
+                                                               0, 16 /* sc1 */);
         }
     };
     // ... and its cells of the joint pass two before the last
@@ -1092,10 +1103,18 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // a round -- and its cell.  Offsets into the exchange buffers; beyond their end where there is
     // nothing to write, so that the stores need no branch.
     constexpr int QH = TQ > 4 ? 2 : 1;   // halves of a round: four tiles, four columns a thread
+    auto q_hyp = [&]() { return qpack ? wave : qpair ? wave * 2 + ((lane >> 4) & 1) : tid >> 4; };
     int q_off[2] = {kNowhere, kNowhere}, q_unit[2] = {-1, -1}, h_off[2] = {kNowhere, kNowhere}, c_g[2], c_u[2];
     float4 q_bias[2];
+    // ... and the place in the exchange buffers (its scalar part; OWN: in the lane's offset), of the newest row and the one before
+    auto q_base = [&](int other) { return OWN ? 0 : ((par ^ other) * Bw + b0) * H * (int)sizeof(float); };
+    auto q_at = [&](int h, unsigned long long act, int other) __attribute__((always_inline)) {
+        if (!OWN) return q_off[h];
+        const int g = q_hyp();   // (at most 16 hypotheses; q_off holds g rows already)
+        return ((unsigned)act >> g & 1u) && q_off[h] != kNowhere ? q_off[h] + (p_row(g, other) - g) * H * (int)sizeof(float) : kNowhere;
+    };
     if constexpr (LAYERS == 1) {
-        const int quad = lane & 15, g = qpack ? wave : qpair ? wave * 2 + ((lane >> 4) & 1) : tid >> 4;
+        const int quad = lane & 15, g = q_hyp();
 #pragma unroll
         for (int h = 0; h < QH; ++h) {
             const int t = h * 4 + (quad >> 2), col = (qt0 + t) * CT + (quad & 3) * 4, u = (t - na) * 4 + (quad & 3);
@@ -1169,7 +1188,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 for (int h = 0; h < 2; ++h) {   // (rows beyond the last: the last again)
                     const int g = __builtin_amdgcn_ds_bpermute(min(q0 + h * 8 + (lane >> 3), q1) * 4, slot_of) & 63;
                     if constexpr (LSTM) {
-                        po[r][h] = (par * Bw + b0 + g) * H * (int)sizeof(float);
+                        po[r][h] = p_row(g, 0) * H * (int)sizeof(float);
                     } else if (h == 0 || upper[r]) {
                         const int lab = __builtin_amdgcn_ds_bpermute(g * 4, last), lab2 = __builtin_amdgcn_ds_bpermute(g * 4, last2);
                         const float *t = p.pred_tab + (size_t)(p.pred_layers == 2 ? lab2 : lab) * H;
@@ -1428,6 +1447,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         const unsigned long long alive = __ballot(active);
         if (alive == 0ull) break;
         const unsigned long long act = alive & ~needm;   // who takes a predictor step: not those in the middle of a search
+        if (OWN) own ^= act;
         st_pred_passes += 1;
 #if TDT_TRACE
         if (tid == 0) g_tr_on = (st_pred_passes >= 20 && st_pred_passes < 24);
@@ -1542,10 +1562,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[0], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
                 if (G * U > THREADS)
                     __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[1], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
-                __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[0], pb * H * (int)sizeof(float), 16 /* sc1 */);
-                if (QH > 1 && nq > 4) __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_off[1], pb * H * (int)sizeof(float), 16 /* sc1 */);
+                __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_at(0, act, 1), q_base(1), 16 /* sc1 */);
+                if (QH > 1 && nq > 4) __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_at(1, act, 1), q_base(1), 16 /* sc1 */);
             } else {
-                clear_rows();
+                clear_rows(act);
             }
             clear_cells();
             if (needm != 0ull) {
@@ -1595,7 +1615,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const int quad = lane & 15, row = qpack   ? wave + (lane >> 4) * kPackRows
                                                       : qpair ? wave * 2 + ((lane >> 4) & 1) + (lane >> 5) * kPairRows
                                                               : tid >> 4;
-                    const int q_g = qpack ? wave : qpair ? row & (kPairRows - 1) : row;   // the hypothesis
 #pragma unroll
                     for (int h = 0; h < QH; ++h)
                         if (h == 0 || nq > 4) {   // uniform
@@ -1613,9 +1632,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             }
                             const v4u o = {__float_as_uint(present(v.x + q_bias[h].x)), __float_as_uint(present(v.y + q_bias[h].y)),
                                            __float_as_uint(present(v.z + q_bias[h].z)), __float_as_uint(present(v.w + q_bias[h].w))};
-                            __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_off[h], (par * Bw + b0) * H * (int)sizeof(float),
-                                                                   16 /* sc1 */);
-                            if (q_unit[h] >= 0 && ((unsigned)act >> q_g & 1u)) rg_l[q_unit[h]] = v;   // the four gates of one unit
+                            __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_at(h, act, 0), q_base(0), 16 /* sc1 */);
+                            if (q_unit[h] >= 0 && ((unsigned)act >> q_hyp() & 1u)) rg_l[q_unit[h]] = v;   // the four gates of one unit
                         }
                 }
             }
@@ -1683,7 +1701,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                                 if (top && t < na) {   // projected predictor output
                                     const int col = (qt0 + t) * CT + (quad & 3) * 4;
                                     if (col < H)
-                                        st_co4(px + ((size_t)par * Bw + b0 + g) * H + col,
+                                        st_co4(px + (size_t)p_row(g, 0) * H + col,
                                                make_float4(present(v.x + bias.x), present(v.y + bias.y),
                                                            present(v.z + bias.z), present(v.w + bias.w)));
                                 } else {   // the four gates of one unit
@@ -1827,7 +1845,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             for (int i = 0; i < C32; ++i) add_row(pv[C32 + i], t1[1], i);
                     }
                 } else {
-                    const int row = (par * Bw + b0 + g_l) * H * (int)sizeof(float);
+                    const int row = p_row(g_l, 0) * H * (int)sizeof(float);
 #pragma unroll
                     for (int s = 0; s < NK; ++s) po[s] = row + part_of(s, js0, H);
                 }
@@ -2040,7 +2058,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
             const int busy = WIDE ? n_cg : items;   // workgroups with a work item (or more)
             if (rank >= busy) {   // no work item: say that this workgroup has come this far
-                if constexpr (MERGES && LSTM)
+                if constexpr (MERGES && LSTM && !OWN)
                     if (patience > 0 && !have_p) {   // (it may have one when these rows are scored again)
                         v4u pv[2 * C32];
                         any_value(pv);
@@ -2233,7 +2251,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             needm = __ballot(need);
             // (through a scalar register: what leaves a loop on a condition the compiler can't prove the same in all lanes makes
             // everything the loop counts a lane's own)
-            const int enough = uni(patience > 0 && __popcll(__ballot(active) & ~needm) * patience >= __popcll(needm) ? 1 : 0);
+            const int enough = uni(patience > 0 && __popcll(__ballot(active) & ~needm) * patience >= __popcll(needm) * kCrowd ? 1 : 0);
             TR(33);
             // everybody has read the pass two before this one: its cells are put back (behind the label's
             // last pass: while the next label's hidden state travels)
