@@ -19,6 +19,7 @@ namespace tdt {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 namespace {
 
@@ -67,12 +68,12 @@ template <bool GROUPED> __device__ inline int source_column(const LinearProblem 
 // returns false (for all of them) if the tile holds no valid frame at all.  Every thread sums a
 // stretch of the utterances' lengths, the stretches' sums are scanned across the workgroup, and
 // each row finds its utterance by a search over the stretches and a walk through its stretch.
-template <int ROWS, int THREADS = GEMM_THREADS>
-__device__ inline bool valid_row_map(const int32_t *lens, int B, int T, long long m0, long long *row_of, int *scan,
-                                     int *wsum)
+// (in parts, for a workgroup that looks for the rows of several tiles: the scan, which hands out the
+// number of valid frames and ends ahead of a barrier, and the search)
+template <int THREADS>
+__device__ inline int scan_lengths(const int32_t *lens, int B, int T, int per, int *scan, int *wsum)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (B + THREADS - 1) / THREADS;
     const int b_lo = min(tid * per, B), b_hi = min(b_lo + per, B);
     int mine = 0;   // B * T < 2^31, so every sum of lengths fits an int
     for (int b = b_lo; b < b_hi; ++b) mine += min(max(lens[b], 0), T);
@@ -92,27 +93,34 @@ __device__ inline bool valid_row_map(const int32_t *lens, int B, int T, long lon
     }
     scan[tid] = base + v - mine;   // valid frames before stretch tid
     __syncthreads();
-    if (m0 >= total) return false;
-    if (tid < ROWS) {
-        const long long m = m0 + tid;
-        long long src = -1;
-        if (m < total) {
-            int lo = 0, hi = THREADS - 1;   // the last stretch that starts at or before m
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (scan[mid] <= m) lo = mid; else hi = mid - 1;
-            }
-            long long before = scan[lo];
-            int b = min(lo * per, B);
-            for (;; ++b) {   // ends, because m < total
-                const int len = min(max(lens[b], 0), T);
-                if (m < before + len) break;
-                before += len;
-            }
-            src = (long long)b * T + (m - before);
-        }
-        row_of[tid] = src;
+    return total;
+}
+template <int THREADS>   // m is less than the number of valid frames
+__device__ inline long long find_row(const int32_t *lens, int T, int B, int per, const int *scan, int m)
+{
+    int lo = 0, hi = THREADS - 1;   // the last stretch that starts at or before m
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (scan[mid] <= m) lo = mid; else hi = mid - 1;
     }
+    int before = scan[lo], b = min(lo * per, B);
+    // (stretches of one utterance: it is the one, others start later or are empty)
+    while (per > 1) {   // ends, because m is a valid frame
+        const int len = min(max(lens[b], 0), T);
+        if (m < before + len) break;
+        before += len;
+        ++b;
+    }
+    return (long long)b * T + (m - before);
+}
+template <int ROWS, int THREADS = GEMM_THREADS>
+__device__ inline bool valid_row_map(const int32_t *lens, int B, int T, long long m0, long long *row_of, int *scan,
+                                     int *wsum)
+{
+    const int tid = threadIdx.x, per = (B + THREADS - 1) / THREADS;
+    const int total = scan_lengths<THREADS>(lens, B, T, per, scan, wsum);
+    if (m0 >= total) return false;
+    if (tid < ROWS) row_of[tid] = m0 + tid < total ? find_row<THREADS>(lens, T, B, per, scan, (int)m0 + tid) : -1;
     return true;
 }
 
@@ -450,196 +458,279 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void enc_proj_bf16_small_kernel(Li
 }
 
 // ---------------------------------------------------------------------------
-// The same product for large problems: 256 x 256 output tile, 8 wavefronts, each 128 x 64
+// The same product for large problems: 256 x 256 output tile, 4 wavefronts, each 128 x 128
 // ---------------------------------------------------------------------------
-// With 64 x 64 outputs a wavefront every MFMA needs one 16-byte fragment per lane from LDS, and
-// the LDS of a compute unit (128 bytes a clock) is busy four fifths of the K loop while the
-// matrix cores are busy half of it.  At 128 x 64 outputs a wavefront six fragments feed eight
-// MFMAs, and a 256 x 256 tile stores half as many operand bytes per product.  One workgroup of
-// 8 wavefronts per compute unit (two a SIMD), two LDS buffers of 64 KB, one register set that
-// is requested during one K tile and stored to LDS during the next.
-constexpr int GM = 256, GN = 256, BIG_THREADS = 512;
-constexpr int BIG_OUT_ROWS = 64;          // rows of the output tile in LDS at a time
-constexpr int BIG_CLD = GN + 4;           // floats per row of that part
+// What bounds it is the LDS and the wait for memory.  At 128 x 128 outputs a wavefront eight fragments feed
+// sixteen MFMAs (128 x 64: six feed eight), so a K tile takes 1024 of its 2048 MFMA cycles of the LDS for fragments,
+// and the operands go straight into LDS: two buffers of a K tile, filled two steps ahead.
+//   * One workgroup of one wavefront a SIMD per compute unit, and it stays: it walks through its tiles without
+//     a pause in the requests, and the stores of a tile drain during the products of the next.
+//   * The accumulators are all 256 accumulation registers.  Products are written as assembly so that they stay
+//     there: the compiler moved them to and fro (some 500 spills).  They go to LDS from where they are.
+//   * The fragments of a k step are read during the products of the step before, also across the barrier of a K tile.
+//   * Requests are assembly, too: the compiler waits for all of them ahead of every read of LDS.  What is in
+//     flight is counted by hand where it matters, see the wait ahead of the barrier.
+//   * The L2 of the die has A's lines fetched four steps ahead, one lane a line; the workgroups that share the rows
+//     share the lines (61 x 1487 frames 187 -> 170 us, 256 x 1500 705 -> 655).
+//   * The output leaves in 128-byte pieces past the caches (non-temporal), and workgroups start apart, so that
+//     they do not all write at once: 170 -> 158 us, 655 -> 632.
+// Against 8 wavefronts of 128 x 64 that passed their operands through registers, a workgroup a tile, 1024 x 1024, us:
+// 66749 valid rows 203 -> 158, 289033 738 -> 632, 33216 117 -> 87, 31750 90 -> 74; 92759 x 1280 x 512 213 -> 162.
+constexpr int GM = 256, GN = 256, BIG_THREADS = 256;
+constexpr int BIG_MAPS = 4;               // row maps: of the tile that is multiplied and of up to two that are requested
 struct BigShared {
-    long long row_of[GM];
+    float out[BIG_THREADS / 64][32 * 32];   // a block of a wavefront's outputs
+    float bias[BIG_MAPS][GN];
+    float unused[BIG_THREADS];   // what look_ahead fetches
+    long long row_of[BIG_MAPS][GM];
     int scan[BIG_THREADS], wsum[BIG_THREADS / 64];
 };
-constexpr size_t kBigTileBytes = 2 * (size_t)(GM + GN) * BK * sizeof(uint16_t);
-static_assert((size_t)BIG_OUT_ROWS * BIG_CLD * sizeof(float) <= kBigTileBytes, "the output parts reuse the operand buffers");
-constexpr size_t kBigLdsBytes = kBigTileBytes + sizeof(BigShared);
+constexpr size_t kBigBufBytes = (size_t)(GM + GN) * BK * sizeof(uint16_t);   // one K tile of both operands
+constexpr size_t kBigLdsBytes = 2 * kBigBufBytes + sizeof(BigShared);
+constexpr int kBigGrid = 256;             // one workgroup a compute unit
+__device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
 __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(LinearProblem q)
 {
     extern __shared__ __align__(16) unsigned char big_lds[];
-    const uint16_t *__restrict__ A = static_cast<const uint16_t *>(q.A);
-    const uint16_t *__restrict__ W = static_cast<const uint16_t *>(q.W);
-    const float *__restrict__ bias = q.bias;
-    float *__restrict__ C = q.C;
-    const long long M = q.M;
-    const int N = q.N, K = q.K, ldw = q.ldw;
-    uint16_t *const As = reinterpret_cast<uint16_t *>(big_lds);                     // [2][GM * BK]
-    uint16_t *const Bs = As + 2 * GM * BK;                                          // [2][GN * BK]
-    float *const Cs = reinterpret_cast<float *>(big_lds);
-    BigShared &sh = *reinterpret_cast<BigShared *>(big_lds + kBigTileBytes);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 2, wn = wave & 3;
-    // the die-aware order of tiles of the 128 x 128 kernel
-    const unsigned block = blockIdx.x;
-    const int nt_n = (N + GN - 1) / GN;
-    const long long jb = block / kXcds;
-    const long long mt = (jb / nt_n) * kXcds + block % kXcds;
-    const long long m0 = mt * GM;
-    const int n0 = (int)(jb % nt_n) * GN;
-    if (m0 >= M) return;   // uniform over the workgroup
+    typedef __attribute__((address_space(3))) unsigned char LdsByte;
+    BigShared &sh = *reinterpret_cast<BigShared *>(big_lds + 2 * kBigBufBytes);
+    const int N = q.N, K = q.K;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const unsigned nt_n = N / GN;
+    const int nk = (K + BK - 1) / BK;
+
+    // rows of the product, and a scan of the lengths they are found by (see valid_row_map)
+    int per = 0;
+    long long rows = q.M;
     if (q.lens) {
-        if (!valid_row_map<GM, BIG_THREADS>(q.lens, q.B, q.T, m0, sh.row_of, sh.scan, sh.wsum)) return;   // uniform
-    } else if (tid < GM) {
-        sh.row_of[tid] = m0 + tid < M ? m0 + tid : -1;
+        per = (q.B + BIG_THREADS - 1) / BIG_THREADS;
+        rows = scan_lengths<BIG_THREADS>(q.lens, q.B, q.T, per, sh.scan, sh.wsum);
     }
+    // this workgroup's tiles: the die-aware order of the 128 x 128 kernel, a grid apart
+    auto tile_index = [&](int i) { return (blockIdx.x + (unsigned)i * gridDim.x) / kXcds; };
+    auto row_tile = [&](int i) { return (long long)(tile_index(i) / nt_n) * kXcds + blockIdx.x % kXcds; };
+    auto column = [&](int i) { return (int)(tile_index(i) % nt_n) * GN; };
+    auto map_rows = [&](int i) {
+        const long long m = row_tile(i) * GM + tid;
+        long long src = -1;
+        if (m < rows) src = q.lens ? find_row<BIG_THREADS>(q.lens, q.T, q.B, per, sh.scan, (int)m) : m;
+        sh.row_of[i % BIG_MAPS][tid] = src;
+    };
+    int n_tiles = 0;
+    while (row_tile(n_tiles) * GM < rows) ++n_tiles;
+    if (n_tiles == 0) return;   // uniform over the workgroup
+
+    // this lane's part of every K tile: the 16-byte chunk that lands at place lane % 8 of rows
+    // j * 32 + wave * 8 + lane / 8 (LDS takes a wavefront's 64 chunks in a row)
+    const int row0 = wave * 8 + (lane >> 3), kc = (lane & 7) ^ ((row0 >> 1) & 7);
+    const uint16_t *a_src[8], *w_src[8];
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(LdsByte *)big_lds);
+    const uint16_t *ahead;   // the line that this lane has L2 fetch ahead of the requests
+    auto sources = [&](int i) {
+        const int n0 = column(i);
+        const long long mine = sh.row_of[i % BIG_MAPS][min(GM - 1, wave * 64 + (int)(lane / nt_n * nt_n) + n0 / GN)];
+        ahead = static_cast<const uint16_t *>(q.A) + (mine >= 0 ? mine : 0) * K;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const long long ar = sh.row_of[i % BIG_MAPS][row0 + j * 32];
+            a_src[j] = static_cast<const uint16_t *>(q.A) + (ar >= 0 ? ar : 0) * K + kc * 8;
+            w_src[j] = static_cast<const uint16_t *>(q.W) + (long long)(n0 + row0 + j * 32) * q.ldw + kc * 8;
+        }
+    };
+    auto look_ahead = [&](int k) __attribute__((always_inline)) {
+        const uint16_t *src = ahead + (k < nk ? k * BK : 0);
+        const unsigned at = lds0 + (unsigned)(2 * kBigBufBytes + offsetof(BigShared, unused)) + wave * 256;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(at) : "memory");
+    };
+    auto past_the_end = [&]() {   // the last K tile, where it is not a whole one
+        if ((nk - 1) * BK + kc * 8 >= K) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a_src[j] = w_src[j] = reinterpret_cast<const uint16_t *>(&kZeroChunk);
+        }
+    };
+    const unsigned lds_wave = lds0 + wave * 8 * BK * 2;
+    auto request = [&](int idx, unsigned buf) __attribute__((always_inline)) {
+        const int j = idx & 7;
+        const uint16_t *&src = idx < 8 ? a_src[j] : w_src[j];
+        const unsigned at = lds_wave + buf + (idx < 8 ? 0 : GM * BK * 2) + j * 32 * BK * 2;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "memory");
+        src += BK;
+    };
+
+    // lane's fragments: row l % 32 of each 32 x 32 block, chunk s * 2 + l / 32
+    const int r32 = lane & 31, sw = (r32 >> 1) & 7;
+    const unsigned a_at = (wm * 128 + r32) * (BK * 2), b_at = (GM + wn * 128 + r32) * (BK * 2);
+    bf16x8 fa[2][4], fb[2][4];
+    auto fragment = [&](int set, int s, int f, unsigned buf) __attribute__((always_inline)) {   // in the order the products need them
+        const unsigned c = ((s * 2 + (lane >> 5)) ^ sw) * 16 + buf;
+        const bool is_a = f == 0 || f > 4;
+        const int i = f == 0 ? 0 : f <= 4 ? f - 1 : f - 4;
+        const bf16x8 v = *reinterpret_cast<const bf16x8 *>(big_lds + (is_a ? a_at : b_at) + c + i * 32 * BK * 2);
+        if (is_a) fa[set][i] = v; else fb[set][i] = v;
+    };
+
+    f32x16 acc[4][4];
+    auto product = [&](int x, int set) __attribute__((always_inline)) {
+        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc[x >> 2][x & 3]) : "v"(fb[set][x & 3]), "v"(fa[set][x >> 2]));
+    };
+    auto first_product = [&](int x) __attribute__((always_inline)) {
+        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=a"(acc[x >> 2][x & 3]) : "v"(fb[0][x & 3]), "v"(fa[0][x >> 2]));
+    };
+
+    const int steps = n_tiles * nk;
+    // Workgroups that write at the same time wait for each other's stores, so they start apart (where there is
+    // more than one round of tiles): up to about the time of a tile, those with most tiles first.
+    const unsigned slots = gridDim.x / kXcds, all = (unsigned)((rows + GM - 1) / GM + kXcds - 1) / kXcds * nt_n;
+    const unsigned rounds = (all + slots - 1) / slots;
+    const unsigned naps = rounds > 1 ? blockIdx.x / kXcds / 4 * nk * min(rounds - 1, 4u) : 0;   // of 128 cycles
+    for (unsigned z = 0; z < naps; ++z) __builtin_amdgcn_s_sleep(2);
+    map_rows(0);
+    if (nk == 1 && n_tiles > 1) map_rows(1);
     __syncthreads();
-
-    f32x16 acc[4][2];
+    // the tile and K tile that are requested next, two steps ahead of the products
+    int ti = 0, tk = 0;
+    auto request_bias = [&](int i) __attribute__((always_inline)) {
+        const float *src = q.bias ? q.bias + column(i) + tid : reinterpret_cast<const float *>(&kZeroChunk);
+        const unsigned at = lds0 + (unsigned)(2 * kBigBufBytes + offsetof(BigShared, bias)) + (i % BIG_MAPS) * GN * 4 + wave * 256;
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(at) : "memory");
+    };
+    auto advance = [&]() { if (++tk == nk) { tk = 0; ++ti; } };
+    auto aim = [&]() {
+        if (tk == 0) {
+            sources(ti);
+            request_bias(ti);
+        }
+        if (tk == nk - 1 && K % BK != 0) past_the_end();
+    };
+    aim();
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int idx = 0; idx < 16; ++idx) request(idx, 0);
+    advance();
+    if (steps > 1) {
+        aim();
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-
-    // this thread's part of every K tile: 16-byte chunk kc of four rows of each operand
-    // (unconditional loads, zeros by mask: see the 128 x 128 kernel)
-    const int kc = tid & 7;
-    const uint16_t *a_src[4], *w_src[4];
-    bool a_ok[4], w_ok[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int row = (tid + j * BIG_THREADS) >> 3;
-        const long long ar = sh.row_of[row];
-        const int n = n0 + row;
-        a_ok[j] = ar >= 0;
-        w_ok[j] = n < N;
-        a_src[j] = A + (a_ok[j] ? ar : 0) * K;
-        w_src[j] = W + (long long)(w_ok[j] ? n : 0) * ldw;
+        for (int idx = 0; idx < 16; ++idx) request(idx, (unsigned)kBigBufBytes);
+        advance();
+        asm volatile("s_waitcnt vmcnt(16)" : : : "memory");
+    } else {
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
     }
-    uint4 xa[4], xb[4];
-    auto keep = [](uint4 v, bool ok) {   // (a mask, not a choice: see the 128 x 128 kernel)
-        const unsigned m = ok ? 0xffffffffu : 0u;
-        return make_uint4(v.x & m, v.y & m, v.z & m, v.w & m);
-    };
-    // chunk idx (0..3 of A, 4..7 of W) of the register set: its request, and its way into LDS
-    auto request = [&](int idx, int k) __attribute__((always_inline)) {
-        if (idx < 4) xa[idx] = *reinterpret_cast<const uint4 *>(a_src[idx] + k);
-        else xb[idx - 4] = *reinterpret_cast<const uint4 *>(w_src[idx - 4] + k);
-    };
-    auto to_lds = [&](int idx, int buf, bool k_ok) __attribute__((always_inline)) {
-        const int row = (tid + (idx & 3) * BIG_THREADS) >> 3;
-        if (idx < 4) *reinterpret_cast<uint4 *>(As + buf * (GM * BK) + lds_off(row, kc)) = keep(xa[idx], a_ok[idx] && k_ok);
-        else *reinterpret_cast<uint4 *>(Bs + buf * (GN * BK) + lds_off(row, kc)) = keep(xb[idx - 4], w_ok[idx - 4] && k_ok);
-    };
-    // The products of the K tile in buffer `buf`.  Between the products of its first two k steps
-    // the register set (K tile kt + 1, requested during the tile before) goes into the other
-    // buffer, between those of its last two the set is requested again for K tile kt + 2: one
-    // LDS store or one request after every two products, so that neither the stores nor the
-    // requests stand between two K tiles, where all wavefronts would do them at the same time
-    // with the matrix cores idle.
-    auto products = [&](int buf, auto stores, auto loads, int k_store, int k_load) __attribute__((always_inline)) {
-        constexpr bool STORES = decltype(stores)::value, LOADS = decltype(loads)::value;
-        const uint16_t *const Ab = As + buf * (GM * BK), *const Bb = Bs + buf * (GN * BK);
-        const bool k_ok = k_store + kc * 8 < K;
-        const int k = min(k_load + kc * 8, K - 8);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : : : "memory");
 #pragma unroll
-        for (int s = 0; s < BK / 16; ++s) {
-            const int chunk = s * 2 + (lane >> 5);
-            bf16x8 a[4], b[2];
+    for (int f = 0; f < 8; ++f) fragment(0, 0, f, 0);
+
+    int g = 0;
+    bool stored = false;   // 64 stores of the tile before came behind the requests of the next step
+    for (int tile = 0; tile < n_tiles; ++tile) {
+        for (int kt = 0; kt < nk; ++kt, ++g) {
+            const unsigned buf = (g & 1) * (unsigned)kBigBufBytes;
+            const bool more = g + 2 < steps;
+            if (more && tk == 0) map_rows(ti);
+            if (kt == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                a[i] = *reinterpret_cast<const bf16x8 *>(Ab + lds_off(wm * 128 + i * 32 + (lane & 31), chunk));
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                b[j] = *reinterpret_cast<const bf16x8 *>(Bb + lds_off(wn * 64 + j * 32 + (lane & 31), chunk));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                acc[i][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[0], acc[i][0], 0, 0, 0);
-                acc[i][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[1], acc[i][1], 0, 0, 0);
-                if (STORES && s < 2) to_lds(s * 4 + i, buf ^ 1, k_ok);
-                if (LOADS && s >= 2) request((s - 2) * 4 + i, k);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);   // the step's six fragments from LDS
-            if ((STORES && s < 2) || (LOADS && s >= 2)) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                  // two products
-                    if (s < 2) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);       // one LDS store
-                    else __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);             // or one request
+                for (int x = 0; x < 16; ++x) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    first_product(x);
+                    if (x < 8) fragment(1, 1, x, buf);
                 }
             } else {
-                __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(x, 0);
+                    if (x < 8) fragment(1, 1, x, buf);
+                }
             }
+#pragma unroll
+            for (int s = 1; s < 3; ++s) {
+#pragma unroll
+                for (int x = 0; x < 16; ++x) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    product(x, s & 1);
+                    if (x < 8) fragment((s + 1) & 1, s + 1, x, buf);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // The next step's K tile has landed, and nobody reads this step's any more.  What may be in flight is
+            // younger: one look ahead, or the 64 stores of the tile before.
+            if (kt == 0 && stored) asm volatile("s_waitcnt vmcnt(63) lgkmcnt(0)" : : : "memory");
+            else if (kt == 0) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
+            else asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)" : : : "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" : : : "memory");
+            if (more) {
+                aim();
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a_src[j] = w_src[j] = reinterpret_cast<const uint16_t *>(&kZeroChunk);
+            }
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                __builtin_amdgcn_sched_barrier(0);
+                product(x, 1);
+                if (x < 8) fragment(0, 0, x, buf ^ (unsigned)kBigBufBytes);
+                request(x, buf);
+            }
+            look_ahead(tk + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            advance();
         }
-    };
-
-    const int nk = (K + BK - 1) / BK;
+        asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");   // the last products are written
+        // accumulator register e of lane l is row l % 32, column 8 * (e / 4) + 4 * (l / 32) + e % 4 of its block: a
+        // block passes through LDS of the wavefront's own (chunks placed as in lds_off) and leaves as 128-byte pieces
+        float *const stage = sh.out[wave];
+        const int col = lane & 7, n = column(tile) + wn * 128 + col * 4;
+        const long long *const row_of = sh.row_of[tile % BIG_MAPS] + wm * 128 + (lane >> 3);
+        auto store = [&](auto whole) __attribute__((always_inline)) {
+            constexpr bool WHOLE = decltype(whole)::value;
+            float *out[4];
+            bool ok[4];
+            f32x4 y[2][4], bn[4];
 #pragma unroll
-    for (int idx = 0; idx < 8; ++idx) request(idx, min(kc * 8, K - 8));
+            for (int j = 0; j < 4; ++j)
+                bn[j] = *reinterpret_cast<const f32x4 *>(sh.bias[tile % BIG_MAPS] + wn * 128 + j * 32 + col * 4);
 #pragma unroll
-    for (int idx = 0; idx < 8; ++idx) to_lds(idx, 0, kc * 8 < K);
-    if (nk > 1) {
+            for (int x = 0; x <= 16; ++x) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (x < 16) {
+                    const f32x16 &v = acc[x >> 2][x & 3];
 #pragma unroll
-        for (int idx = 0; idx < 8; ++idx) request(idx, min(BK + kc * 8, K - 8));
-    }
-    __syncthreads();
-    // one workgroup barrier per K tile: the buffer written during the products of tile kt was
-    // last read before the barrier that ended tile kt - 1.  The trips that store and request
-    // run without a branch.
-    const std::true_type yes{};
-    const std::false_type no{};
-    int kt = 0;
-    for (; kt + 2 < nk; ++kt) {
-        products(kt & 1, yes, yes, (kt + 1) * BK, (kt + 2) * BK);
-        __syncthreads();
-    }
-    if (kt + 1 < nk) {
-        products(kt & 1, yes, no, (kt + 1) * BK, 0);
-        __syncthreads();
-        ++kt;
-    }
-    products(kt & 1, no, no, 0, 0);
-    __syncthreads();   // the operand buffers are dead: the output tile passes through them
-
-    // accumulator register e of lane l is row 8*(e/4) + 4*(l/32) + e%4, column l%32.  The tile
-    // leaves in four parts of 64 rows, each as whole rows: a wavefront stores one 1024-byte row.
-    const int c4 = lane * 4;
-    const int n = n0 + c4;
-    float4 bn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (bias && n < N) bn = *reinterpret_cast<const float4 *>(bias + n);   // N is a multiple of 8
+                    for (int e = 0; e < 4; ++e)
+                        *reinterpret_cast<f32x4 *>(stage + r32 * 32 + (((2 * e + (lane >> 5)) ^ sw) << 2)) =
+                            f32x4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
+                    asm volatile("" : : : "memory");
 #pragma unroll
-    for (int part = 0; part < GM / BIG_OUT_ROWS; ++part) {
-        if (part > 0) __syncthreads();   // the part before has left LDS
-        if (wm == part / 2) {
+                    for (int e = 0; e < 4; ++e)
+                        y[x & 1][e] = *reinterpret_cast<const f32x4 *>(
+                            stage + (e * 8 + (lane >> 3)) * 32 + ((col ^ ((e * 4 + (lane >> 4)) & 7)) << 2));
+                    asm volatile("" : : : "memory");
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (x == 0) continue;
+                const int i = (x - 1) >> 2, j = (x - 1) & 3;
+                if (j == 0) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int r = i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
-                        Cs[r * BIG_CLD + wn * 64 + j * 32 + (lane & 31)] = acc[(part & 1) * 2 + i][j][e];
+                    for (int e = 0; e < 4; ++e) {
+                        const long long dst = row_of[i * 32 + e * 8];
+                        ok[e] = WHOLE || dst >= 0;
+                        out[e] = q.C + dst * N + n;
                     }
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int it = 0; it < BIG_OUT_ROWS / (BIG_THREADS / 64); ++it) {
-            const int r = it * (BIG_THREADS / 64) + wave;
-            const long long dst = sh.row_of[part * BIG_OUT_ROWS + r];
-            float4 v = *reinterpret_cast<const float4 *>(Cs + r * BIG_CLD + c4);
-            v.x += bn.x;
-            v.y += bn.y;
-            v.z += bn.z;
-            v.w += bn.w;
-            if (dst >= 0 && n < N) *reinterpret_cast<float4 *>(C + dst * N + n) = v;
-        }
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const f32x4 v = y[(x - 1) & 1][e] + bn[j];
+                    if (ok[e]) __builtin_nontemporal_store(v, reinterpret_cast<f32x4 *>(out[e] + j * 32));
+                }
+            }
+        };
+        stored = row_tile(tile) * GM + GM <= rows;
+        if (stored) store(std::true_type{}); else store(std::false_type{});
     }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");   // (what is still on its way into LDS)
 }
 
 // ---------------------------------------------------------------------------
@@ -878,11 +969,15 @@ static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int 
     return q;
 }
 
-// Large products with a column count that 256-column tiles divide take the 256 x 256 kernel
-// (a launch of its own: it has its own workgroup size and LDS footprint).
+// Products with a column count that 256-column tiles divide take the 256 x 256 kernel (a launch of its own: it has
+// its own workgroup size and LDS footprint) where its tiles occupy most of the chip.  The line is at 160 tiles of all
+// rows, some 120 of valid ones; valid rows x columns x inputs, us with 256 x 256 tiles / with 128 x 128: 11960 x 512 x 512
+// (94 tiles) 19.0 / 17.9, 5981 x 1280 x 640 (120) 22.4 / 20.8, 17938 x 512 x 512 (142) 21.7 / 26.0, 11960 x 1024 x 1024
+// (188) 35.1 / 42.8, 47879 x 256 x 512 (188) 26.1 / 33.8, 47879 x 1024 x 1024 (752) 114 / 162.
+constexpr long long kBigTiles = 160;
 static bool takes_big_tiles(int64_t rows, int N, int group)
 {
-    return group == 0 && N % GN == 0 && rows >= 32768;
+    return group == 0 && N % GN == 0 && (rows + GM - 1) / GM * (N / GN) >= kBigTiles;
 }
 
 static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
@@ -903,7 +998,8 @@ static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
         }
     }
     const long long row_tiles = (q.M + GM - 1) / GM, rounds = (row_tiles + kXcds - 1) / kXcds;
-    q.blocks = (unsigned)(rounds * kXcds * ((q.N + GN - 1) / GN));
+    const long long tiles = rounds * kXcds * (q.N / GN);
+    q.blocks = (unsigned)(tiles < kBigGrid ? tiles : kBigGrid);
     hipLaunchKernelGGL(enc_proj_bf16_big_kernel, dim3(q.blocks), dim3(BIG_THREADS), kBigLdsBytes, stream, q);
     return hipGetLastError();
 }

@@ -1,5 +1,5 @@
 """The encoder projection where its kernels meet: around the tile edges of the kernel for small products
-(64 x 64 output tiles, K tiles in fours), and the products just below and above the size at which the
+(64 x 64 output tiles, K tiles in fours), and the products just below and above the sizes at which the
 128 x 128 tiles take over -- against the oracle."""
 from __future__ import annotations
 
@@ -33,3 +33,42 @@ def test_projection_tiles(oracle_lib, gpu, rows, d_enc, H):   # noqa: F811
     ref = np.stack([om.enc_proj_frame(enc[0, r]) for r in range(rows)])
     np.testing.assert_allclose(got[:rows], ref, atol=2e-4, rtol=1e-5)
     assert (got[rows:] == 7.0).all(), "rows past the end were written"
+
+
+# valid frames in 256 x 256 tiles that stay in a workgroup's hands: one K tile and less, K tiles that are not whole,
+# one and several rounds of tiles, column tiles that the workgroups of a die are no multiple of, more utterances than threads
+@pytest.mark.parametrize("B,T,lo,d_enc,H", [
+    (20, 520, 520, 8, 1024), (20, 520, 300, 64, 1024), (41, 338, 0, 72, 768), (7, 2400, 1000, 136, 768), (64, 640, 0, 128, 256),
+    (300, 34, 0, 200, 1280), (530, 40, 3, 64, 1536), (23, 900, 899, 264, 1024)])
+def test_projection_large_tiles(oracle_lib, gpu, B, T, lo, d_enc, H):   # noqa: F811
+    import torch
+    cfg = synth.small_config("projlarge", dtype="bf16", d_enc=d_enc, h_joint=H, seed=48, B=B, T=T, len_lo=lo, len_hi=T)
+    assert -(-B * T // 256) * (H // 256) >= 160, "these shapes are there for the large tiles"
+    w = synth.generate_model(cfg)
+    w["b_enc"] = np.random.default_rng(9).standard_normal(H).astype(np.float32)
+    enc, _ = synth.generate_inputs(cfg)
+    ln = np.random.default_rng(10).integers(lo, T + 1, size=B).astype(np.int32)
+    ln[B // 2] = T
+    if lo == 0:
+        ln[[0, 1, B - 1]] = 0
+    parity.announce(f"tdt_encoder_projection_valid B={B} T={T} d_enc={d_enc} H={H}")
+    model = gpu.DeviceModel(cfg, w)
+    enc_d = model.upload_enc(enc)
+    valid = torch.arange(T)[None] < torch.from_numpy(ln)[:, None]
+    enc_d.view(torch.bfloat16)[~valid.to(enc_d.device)] = float("nan")
+    out = torch.full((B * T + 3, H), 7.0, dtype=torch.float32, device=model.device)
+    len_d = torch.from_numpy(ln).to(model.device)
+    gpu.tdt_encoder_projection_valid(enc_d.data_ptr(), len_d.data_ptr(), B, T, model.c,
+                                     out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    rows = np.flatnonzero(valid.numpy().reshape(-1))
+    # every frame of the first, the middle and the last utterances, a draw of the others
+    some = np.unique(np.concatenate([rows[:600], rows[-600:], np.random.default_rng(11).choice(rows, min(3000, rows.size), False)]))
+    om = oracle_lib.OracleModel(cfg, w)
+    flat = enc.reshape(B * T, d_enc)
+    ref = np.stack([om.enc_proj_frame(flat[r]) for r in some])
+    np.testing.assert_allclose(got[some], ref, atol=2e-4, rtol=1e-5)
+    assert np.isfinite(got[rows]).all()
+    rest = np.setdiff1d(np.arange(B * T + 3), rows)
+    assert (got[rest] == 7.0).all(), "rows that are no valid frame were written"
