@@ -63,13 +63,33 @@ template <bool GROUPED> __device__ inline int source_column(const LinearProblem 
     return c % kinds * q.group + c / kinds;
 }
 
+// The output tile of workgroup `block`: its row tile and its column tile.  Consecutive workgroups go to
+// consecutive XCDs, each with an L2 of its own, so the workgroups that share a row tile of `A` (all its
+// column tiles) are given to one XCD: row tiles are dealt round robin to the XCDs, and the j-th workgroup of an
+// XCD takes column tile j % nt_n of that XCD's (j / nt_n)-th row tile.  `A` then comes from HBM once instead of
+// once per XCD; `W` is small and stays in every L2.  Few row tiles would leave XCDs with half the work of others or
+// none: up to 23 are dealt in order (the table of 1025 labels, 640 inputs, 2560 columns: bfloat16, 9 row tiles,
+// 18.5 -> 14.8 us, float32, 17, 56.0 -> 45.6; from 32 on it is slower: 32 tiles of 64 x 512 x 640 8.4 -> 9.1).
+constexpr long long kFewRowTiles = 24;
+__host__ __device__ inline bool in_order(long long row_tiles) { return row_tiles < kFewRowTiles; }
+__device__ inline void tile_of(const LinearProblem &q, unsigned block, int tile, int nt_n, long long &mt, int &nt)
+{
+    if (in_order((q.M + tile - 1) / tile)) {
+        mt = block / nt_n;
+        nt = (int)(block % nt_n);
+        return;
+    }
+    const unsigned j = block / kXcds;
+    mt = (long long)(j / nt_n) * kXcds + block % kXcds;
+    nt = (int)(j % nt_n);
+}
+
 // Which frames rows m0 .. m0 + ROWS - 1 of the packed sequence of valid frames are: row_of[i] =
 // b * T + t, or -1 beyond the last valid frame.  Called by all THREADS threads of a workgroup;
 // returns false (for all of them) if the tile holds no valid frame at all.  Every thread sums a
 // stretch of the utterances' lengths, the stretches' sums are scanned across the workgroup, and
 // each row finds its utterance by a search over the stretches and a walk through its stretch.
-// (in parts, for a workgroup that looks for the rows of several tiles: the scan, which hands out the
-// number of valid frames and ends ahead of a barrier, and the search)
+// (The two halves are functions of their own for workgroups that look for the rows of several tiles.)
 template <int THREADS>
 __device__ inline int scan_lengths(const int32_t *lens, int B, int T, int per, int *scan, int *wsum)
 {
@@ -146,16 +166,12 @@ template <bool GROUPED> __device__ inline void gemm_tile_bf16(const LinearProble
     __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    // 1-D grid.  Consecutive workgroups go to consecutive XCDs, each with an L2 of its own, so
-    // the workgroups that share a row tile of `A` (all its column tiles) are given to one XCD:
-    // row tiles are dealt round robin to the XCDs, and the j-th workgroup of an XCD takes
-    // column tile j % nt_n of that XCD's (j / nt_n)-th row tile.  `A` then comes from HBM once
-    // instead of once per XCD; `W` is small and stays in every L2.
     const int nt_n = (N + BN - 1) / BN;
-    const long long j = block / kXcds;
-    const long long mt = (j / nt_n) * kXcds + block % kXcds;
+    long long mt;
+    int nt;
+    tile_of(q, block, BM, nt_n, mt, nt);
     const long long m0 = mt * BM;
-    const int n0 = (int)(j % nt_n) * BN;
+    const int n0 = nt * BN;
     if (m0 >= M) return;   // the last round of row tiles may be partial (uniform over the workgroup)
     if (q.lens) {
         if (!valid_row_map<BM>(q.lens, q.B, q.T, m0, row_of, scan, wsum)) return;   // uniform
@@ -369,9 +385,12 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void enc_proj_bf16_small_kernel(Li
     __shared__ long long row_of[SM];
     __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
-    const int nt_n = (N + SN - 1) / SN;   // die-aware order of tiles, as in gemm_tile_bf16
-    const long long j = block / kXcds, m0 = ((j / nt_n) * kXcds + block % kXcds) * SM;
-    const int n0 = (int)(j % nt_n) * SN;
+    const int nt_n = (N + SN - 1) / SN;
+    long long mt;
+    int nt;
+    tile_of(q, block, SM, nt_n, mt, nt);
+    const long long m0 = mt * SM;
+    const int n0 = nt * SN;
     if (m0 >= q.M) return;
     if (q.lens) {
         if (!valid_row_map<SM>(q.lens, q.B, q.T, m0, row_of, scan, wsum)) return;   // uniform
@@ -825,9 +844,12 @@ template <bool GROUPED> __device__ inline void gemm_tile_f32(const LinearProblem
     __shared__ long long row_of[FM];
     __shared__ int scan[GEMM_THREADS], wsum[GEMM_THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
-    const int nt_n = (N + FN - 1) / FN;   // die-aware order of tiles, as in gemm_tile_bf16
-    const long long j = block / kXcds, m0 = ((j / nt_n) * kXcds + block % kXcds) * FM;
-    const int n0 = (int)(j % nt_n) * FN;
+    const int nt_n = (N + FN - 1) / FN;
+    long long mt;
+    int nt;
+    tile_of(q, block, FM, nt_n, mt, nt);
+    const long long m0 = mt * FM;
+    const int n0 = nt * FN;
     if (m0 >= q.M) return;
     if (q.lens) {
         if (!valid_row_map<FM>(q.lens, q.B, q.T, m0, row_of, scan, wsum)) return;   // uniform
@@ -946,7 +968,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch ba
 static unsigned tile_blocks(const LinearProblem &q, int tile)   // square tiles
 {
     const long long row_tiles = (q.M + tile - 1) / tile, rounds = (row_tiles + kXcds - 1) / kXcds;
-    return (unsigned)(rounds * kXcds * ((q.N + tile - 1) / tile));
+    return (unsigned)((in_order(row_tiles) ? row_tiles : rounds * kXcds) * ((q.N + tile - 1) / tile));
 }
 
 constexpr long long kSmallTiles = 160;   // up to this many 128 x 128 tiles a product takes 64 x 64 tiles, see enc_proj_bf16_small_kernel
@@ -974,10 +996,11 @@ static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int 
 // rows, some 120 of valid ones; valid rows x columns x inputs, us with 256 x 256 tiles / with 128 x 128: 11960 x 512 x 512
 // (94 tiles) 19.0 / 17.9, 5981 x 1280 x 640 (120) 22.4 / 20.8, 17938 x 512 x 512 (142) 21.7 / 26.0, 11960 x 1024 x 1024
 // (188) 35.1 / 42.8, 47879 x 256 x 512 (188) 26.1 / 33.8, 47879 x 1024 x 1024 (752) 114 / 162.
-constexpr long long kBigTiles = 160;
+// With 256 columns they are taken from 128 tiles on: of long batches fewer rows are padding.
+constexpr long long kBigTiles = 160, kBigRows = 32768;
 static bool takes_big_tiles(int64_t rows, int N, int group)
 {
-    return group == 0 && N % GN == 0 && (rows + GM - 1) / GM * (N / GN) >= kBigTiles;
+    return group == 0 && N % GN == 0 && (rows >= kBigRows || (rows + GM - 1) / GM * (N / GN) >= kBigTiles);
 }
 
 static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
