@@ -494,7 +494,8 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void enc_proj_bf16_small_kernel(Li
 //   * The output leaves in 128-byte pieces past the caches (non-temporal), and workgroups start apart, so that
 //     they do not all write at once: 170 -> 158 us, 655 -> 632.
 // Against 8 wavefronts of 128 x 64 that passed their operands through registers, a workgroup a tile, 1024 x 1024, us:
-// 66749 valid rows 203 -> 158, 289033 738 -> 632, 33216 117 -> 87, 31750 90 -> 74; 92759 x 1280 x 512 213 -> 162.
+// 66749 valid rows 203 -> 156, 289033 738 -> 640, 33216 117 -> 87, 31750 90 -> 73; 92759 x 1280 x 512 213 -> 163.
+// Halving the tiles of a last round that leaves half the workgroups idle was no better (156 -> 162, 33216 rows the same).
 constexpr int GM = 256, GN = 256, BIG_THREADS = 256;
 constexpr int BIG_MAPS = 4;               // row maps: of the tile that is multiplied and of up to two that are requested
 struct BigShared {
