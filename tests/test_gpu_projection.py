@@ -35,6 +35,29 @@ def test_projection_tiles(oracle_lib, gpu, rows, d_enc, H):   # noqa: F811
     assert (got[rows:] == 7.0).all(), "rows past the end were written"
 
 
+# where row tiles stop being dealt to the dies in order: 23 and 24 of 64 rows (bfloat16's small products, float32) and of 128
+@pytest.mark.parametrize("dtype,rows,d_enc,H", [
+    ("bf16", 1472, 72, 72), ("bf16", 1473, 72, 72), ("bf16", 2944, 40, 1000), ("bf16", 2945, 40, 1000),
+    ("fp32", 1472, 24, 200), ("fp32", 1473, 24, 200)])
+def test_projection_of_few_row_tiles(oracle_lib, gpu, dtype, rows, d_enc, H):   # noqa: F811
+    import torch
+    cfg = synth.small_config("projfew", dtype=dtype, d_enc=d_enc, h_joint=H, seed=49, B=1, T=rows, len_lo=rows, len_hi=rows)
+    w = synth.generate_model(cfg)
+    w["b_enc"] = np.random.default_rng(12).standard_normal(H).astype(np.float32)
+    enc, _ = synth.generate_inputs(cfg)
+    parity.announce(f"tdt_encoder_projection dtype={dtype} rows={rows} d_enc={d_enc} H={H}")
+    model = gpu.DeviceModel(cfg, w)
+    enc_d = model.upload_enc(enc[0])
+    out = torch.full((rows + 3, H), 7.0, dtype=torch.float32, device=model.device)
+    gpu.tdt_encoder_projection(enc_d.data_ptr(), rows, model.c, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    om = oracle_lib.OracleModel(cfg, w)
+    ref = np.stack([om.enc_proj_frame(enc[0, r]) for r in range(rows)])
+    np.testing.assert_allclose(got[:rows], ref, atol=2e-4, rtol=1e-5)
+    assert (got[rows:] == 7.0).all(), "rows past the end were written"
+
+
 # valid frames in 256 x 256 tiles that stay in a workgroup's hands: one K tile and less, K tiles that are not whole,
 # one and several rounds of tiles, column tiles that the workgroups of a die are no multiple of, more utterances than threads
 @pytest.mark.parametrize("B,T,lo,d_enc,H", [
