@@ -510,6 +510,20 @@ constexpr size_t kBigLdsBytes = 2 * kBigBufBytes + sizeof(BigShared);
 constexpr int kBigGrid = 256;             // one workgroup a compute unit
 __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
 
+// Requests BYTES bytes a lane from `src`: lane l's land at byte `at` + l * BYTES of LDS.  (The compiler reserves m0, so it
+// warns of a statement that says it changes it; saying so keeps it from relying on a value that it put there itself.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+template <int BYTES> __device__ inline void into_lds(const void *src, unsigned at)
+{
+    static_assert(BYTES == 4 || BYTES == 16, "");
+    if constexpr (BYTES == 16)
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "m0", "memory");
+    else
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(at) : "m0", "memory");
+}
+#pragma clang diagnostic pop
+
 __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(LinearProblem q)
 {
     extern __shared__ __align__(16) unsigned char big_lds[];
@@ -563,7 +577,7 @@ __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(Linea
     auto look_ahead = [&](int k) __attribute__((always_inline)) {
         const uint16_t *src = ahead + (k < nk ? k * BK : 0);
         const unsigned at = lds0 + (unsigned)(2 * kBigBufBytes + offsetof(BigShared, unused)) + wave * 256;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(at) : "memory");
+        into_lds<4>(src, at);
     };
     auto past_the_end = [&]() {   // the last K tile, where it is not a whole one
         if ((nk - 1) * BK + kc * 8 >= K) {
@@ -576,7 +590,7 @@ __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(Linea
         const int j = idx & 7;
         const uint16_t *&src = idx < 8 ? a_src[j] : w_src[j];
         const unsigned at = lds_wave + buf + (idx < 8 ? 0 : GM * BK * 2) + j * 32 * BK * 2;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "memory");
+        into_lds<16>(src, at);
         src += BK;
     };
 
@@ -615,7 +629,7 @@ __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(Linea
     auto request_bias = [&](int i) __attribute__((always_inline)) {
         const float *src = q.bias ? q.bias + column(i) + tid : reinterpret_cast<const float *>(&kZeroChunk);
         const unsigned at = lds0 + (unsigned)(2 * kBigBufBytes + offsetof(BigShared, bias)) + (i % BIG_MAPS) * GN * 4 + wave * 256;
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(src), "s"(at) : "memory");
+        into_lds<4>(src, at);
     };
     auto advance = [&]() { if (++tk == nk) { tk = 0; ++ti; } };
     auto aim = [&]() {
@@ -700,6 +714,9 @@ __global__ __launch_bounds__(BIG_THREADS, 1) void enc_proj_bf16_big_kernel(Linea
             advance();
         }
         asm volatile("s_nop 15\n\ts_nop 15" : : : "memory");   // the last products are written
+        // (the compiler does not see that a product takes so long: what reads one has to stay behind the wait)
+#pragma unroll
+        for (int x = 0; x < 16; ++x) asm volatile("" : "+a"(acc[x >> 2][x & 3]));
         // accumulator register e of lane l is row l % 32, column 8 * (e / 4) + 4 * (l / 32) + e % 4 of its block: a
         // block passes through LDS of the wavefront's own (chunks placed as in lds_off) and leaves as 128-byte pieces
         float *const stage = sh.out[wave];

@@ -1,0 +1,78 @@
+"""What the compiler cannot see in hand-written assembly: registers that it changes, and products whose results take
+longer than an instruction.  The first is looked for in the sources, the second in the code the compiler makes of them."""
+from __future__ import annotations
+
+import glob
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2406_06220_amd import build
+
+CSRC = os.path.join(build.PKG, "csrc")
+
+
+def asm_statements():
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):
+        src = open(path).read()
+        for m in re.finditer(r"\basm\s+volatile\s*\((.*?)\);", src, flags=re.S):
+            yield os.path.basename(path), m.group(1)
+
+
+def test_assembly_that_writes_m0_says_so():
+    writes = [(f, s) for f, s in asm_statements() if re.search(r"\bs_\w+ m0\b", s)]
+    assert writes
+    for f, s in writes:
+        assert re.search(r':[^:]*"m0"[^:]*$', s), f"{f}: {s}"
+
+
+@pytest.fixture(scope="module")
+def big_kernel(tmp_path_factory):
+    """The instructions of the 256 x 256 projection kernel, in order: (mnemonic, operands)."""
+    out = str(tmp_path_factory.mktemp("asm") / "enc_proj.s")
+    flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
+    subprocess.run(["hipcc", *flags, "-I", os.path.join(build.ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
+                    os.path.join(CSRC, "enc_proj.hip"), "-o", out], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    code, inside = [], False
+    for line in open(out):
+        line = line.split(";")[0].strip()
+        if re.match(r"_ZN\w*enc_proj_bf16_big_kernel\w*:", line):
+            inside = True
+        elif inside and line and not line.startswith(".") and not line.endswith(":"):
+            op, _, rest = line.partition(" ")
+            code.append((op, [o.strip() for o in rest.split(",")]))
+            if op == "s_endpgm":
+                return code
+    raise AssertionError("the kernel was not found")
+
+
+def registers(operand):
+    m = re.match(r"([va])\[(\d+):(\d+)\]$", operand)
+    if m:
+        return {f"{m[1]}{i}" for i in range(int(m[2]), int(m[3]) + 1)}
+    return {operand} if re.match(r"[va]\d+$", operand) else set()
+
+
+def test_products_are_read_behind_their_wait(big_kernel):
+    """Sixteen cycles a product and more: nothing but another product touches an accumulator from the first product to the
+    wait behind the last."""
+    products = [i for i, (op, _) in enumerate(big_kernel) if op.startswith("v_mfma")]
+    waits = [i for i, (op, o) in enumerate(big_kernel) if op == "s_nop" and o == ["15"]]
+    assert len(products) == 80 and len(waits) == 2 and waits[1] == waits[0] + 1 and products[-1] < waits[0]
+    for op, operands in big_kernel[products[0]:waits[0]]:
+        if not op.startswith("v_mfma"):
+            assert not any(r[0] == "a" for o in operands for r in registers(o)), (op, operands)
+    assert any(r[0] == "a" for op, operands in big_kernel[waits[1]:] for o in operands for r in registers(o))
+
+
+def test_products_do_not_follow_what_makes_their_operands(big_kernel):
+    """A product may read a vector register two instructions after the vector ALU wrote it: fragments come from LDS, and no
+    copy of one stands that close in front of a product."""
+    for i, (op, operands) in enumerate(big_kernel):
+        if op.startswith("v_mfma"):
+            needs = registers(operands[1]) | registers(operands[2])
+            for before, o in big_kernel[max(0, i - 2):i]:
+                if before.startswith("v_") and not before.startswith("v_mfma"):
+                    assert not registers(o[0]) & needs, (before, o, op, operands)
