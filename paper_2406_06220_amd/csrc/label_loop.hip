@@ -379,7 +379,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     float *const hx = p.hbuf;         // [2][L][Bw][Hp]
     float *const px = p.pred_proj;    // [2][Bw][H]
     const int cells = p.cells_per_cluster;   // joint cells of one buffer (work items x 16)
-    // The words of the joint exchanges lie behind one another (label_layout, two megabytes at most) and are reached through
+    // The words of the joint exchanges lie behind one another (label_words, some eight megabytes at most) and are reached through
     // one descriptor: a lane offset and a scalar offset instead of 64-bit sums of pointers, of which a pass needed some
     // twenty.  Byte offsets of this group's, and the bytes of one of their kRowBufs buffers:
     auto behind = [&](const unsigned long long *q) { return (int)((q - p.row_lab) * sizeof(unsigned long long)); };

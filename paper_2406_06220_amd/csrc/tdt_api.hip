@@ -112,26 +112,19 @@ LabelLayout label_layout(const tdt_weights_t *w, bool wide, int n_clusters, int 
     LabelLayout L{};
     const bool lstm = w->pred_kind == TDT_PRED_LSTM;
     const size_t rows = (size_t)n_clusters * hyps_per_cluster;
-    L.rows_per_cluster = hyps_per_cluster * kMaxWindow < kLabelRowsPerPass ? hyps_per_cluster * kMaxWindow
-                                                                         : kLabelRowsPerPass;
-    const int tiles = L.rows_per_cluster / 16;   // row tiles of a joint pass
-    // one cell a row for every work item: a workgroup has one, or more where there are more row tiles than
-    // workgroups; wide: one for every row tile
-    L.cells_per_cluster = 16 * (wide ? tiles * C : tiles > C ? tiles : C);
+    const LabelWords words = label_words(wide, w->n_dur > 0 && !w->multi_blank, n_clusters, hyps_per_cluster, C);
+    L.rows_per_cluster = words.rows;
+    L.cells_per_cluster = words.cells;
     size_t off = 0;
     L.ones_begin = L.hx = off;
     if (lstm) off = align_up(off + 2 * (size_t)w->pred_layers * rows * w->h_pred * sizeof(float), 256);
     L.px = off;
     if (lstm) off = align_up(off + 2 * rows * w->h_joint * sizeof(float), 256);
     L.ones_end = L.zero_begin = L.row_lab = off;
-    off = align_up(off + (size_t)n_clusters * kRowBufs * L.cells_per_cluster * sizeof(unsigned long long), 256);
-    L.row_lse = off;
-    off = align_up(off + (size_t)n_clusters * kRowBufs * L.cells_per_cluster * sizeof(unsigned long long), 256);
-    L.row_dur = off;
-    if (w->n_dur > 0 && !w->multi_blank)
-        off = align_up(off + (size_t)n_clusters * kRowBufs * 2 * L.rows_per_cluster * sizeof(unsigned long long), 256);
-    L.present = off;
-    off = align_up(off + (size_t)n_clusters * (kRowBufs + 1) * C * sizeof(unsigned long long), 256);
+    L.row_lse = off + words.lse;
+    L.row_dur = off + words.dur;
+    L.present = off + words.present;
+    off += words.end;
     L.abort_flag = off;
     off += 256;
     L.zero_end = off;

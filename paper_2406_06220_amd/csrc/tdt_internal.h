@@ -18,19 +18,16 @@ namespace tdt {
 
 constexpr int kThreads = 512;                 // threads per workgroup of the decode kernel
 constexpr int kWaves = kThreads / 64;         // 64-wide wavefronts per workgroup
-constexpr int kMaxGrid = 256;                 // one workgroup per compute unit
 constexpr int kMaxRowsPerPass = 1024;         // (hypothesis, frame) rows of one joint pass
 constexpr int kMaxColGroups = 64;             // output-column slices of one joint pass
 constexpr int kPartialEntries = kMaxRowsPerPass * kMaxGrid;  // per partial buffer
 constexpr int kBarrierStride = 32;            // uint32 slots between two workgroups' barrier flags
 constexpr int kMaxRankedBatch = 1024;          // largest batch whose hypotheses are dealt to the clusters by length
 constexpr int kMaxDuration = 1 << 20;          // largest frame increment of a duration class
-constexpr int kRowBufs = 4;                   // rotating per-row argmax buffers
 constexpr size_t kLdsBytes = 160 * 1024;      // LDS of a compute unit
-// label_loop.hip: hypotheses a group can hold (one lane each), (hypothesis, frame) rows of a joint pass
+// label_loop.hip: hypotheses a group can hold (one lane each)
 constexpr int kLabelThreads = 256;
 constexpr int kLabelMaxHyps = 64;
-constexpr int kLabelRowsPerPass = 256;
 
 // Softmax-denominator share of one slice of label columns for one joint row.
 struct __align__(8) LsePartial {

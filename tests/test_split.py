@@ -39,6 +39,12 @@ extern "C" void nowhere_c(int *out)
     const int v[3] = {kNowhere, kLabelLongest, label_nk(true, kLabelLongest) > 0 && label_nk(true, kLabelLongest + 1) == 0};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
+extern "C" void words_c(int wide, int durations, int n_clusters, int hpc, int C, long long *out)
+{
+    const LabelWords w = label_words(wide != 0, durations != 0, n_clusters, hpc, C);
+    const long long v[7] = {w.rows, w.cells, w.lse, w.dur, w.present, w.end, kLabelWordsMost};
+    for (int i = 0; i < 7; ++i) out[i] = v[i];
+}
 extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
 {
     return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
@@ -237,3 +243,23 @@ def test_group_counts_of_stateless_models(split):
                 for asked in ({}, dict(window=1), dict(window=64), dict(joint_tiles=1)):
                     n = label_groups(split, B, kind=kind, n_out=n_out, **asked)
                     assert max(1, -(-B // 256)) <= n <= max(64, -(-B // 256)) and (n <= B or B == 1), (kind, n_out, B, asked)
+
+
+def test_words_of_the_joint_passes_are_reached_by_32_bit_offsets(split):
+    """Arrays that do not overlap and hold every word, and no split of the chip's workgroups has more than the bound."""
+    out, most = (C.c_longlong * 7)(), 0
+    for n in range(1, 257):
+        for c in sorted({1, 2, 3, 15, 16, 17, 64, 128, 255, 256, 256 // n}):
+            if n * c > 256:
+                continue
+            for hpc in (1, 3, 4, 16, 64, 256):
+                for wide in (0, 1):
+                    for dur in (0, 1):
+                        split.words_c(wide, dur, n, hpc, c, out)
+                        rows, cells, lse, durs, present, end, bound = out
+                        assert rows == min(64 * hpc, 256) and cells >= max(rows, 16 * c) and cells % 16 == 0
+                        assert lse >= n * 4 * cells * 8 and durs >= lse + n * 4 * cells * 8
+                        assert present >= durs + dur * n * 4 * 2 * rows * 8 and end >= present + n * 5 * c * 8
+                        assert all(x % 256 == 0 for x in (lse, durs, present, end)) and end <= bound
+                        most = max(most, end)
+    assert most > 0.99 * bound and bound < 2**31 - 2**16
