@@ -44,9 +44,12 @@ struct LinearProblem {
     const float *bias;
     float *C;
     long long M;
-    int N, K, ldw, group;
+    int N, K, ldw;
+    // row tiles are dealt to 1 << deal_shift dies: all of them, or one (tiles in order).  (Among the first 64 bytes, which every kernel
+    // loads: behind them the first tile waits for a second line of arguments, 28 x 10 tiles of 64 x 64 9.0 us, not 8.8.)
+    int deal_shift;
     const int32_t *lens;
-    int B, T;
+    int B, T, group;
     unsigned blocks;
 };
 constexpr int kMaxProblems = 3;   // products one preparation launch can hold
@@ -67,20 +70,11 @@ template <bool GROUPED> __device__ inline int source_column(const LinearProblem 
 // consecutive XCDs, each with an L2 of its own, so the workgroups that share a row tile of `A` (all its
 // column tiles) are given to one XCD: row tiles are dealt round robin to the XCDs, and the j-th workgroup of an
 // XCD takes column tile j % nt_n of that XCD's (j / nt_n)-th row tile.  `A` then comes from HBM once instead of
-// once per XCD; `W` is small and stays in every L2.  Few row tiles would leave XCDs with half the work of others or
-// none: up to 23 are dealt in order (the table of 1025 labels, 640 inputs, 2560 columns: bfloat16, 9 row tiles,
-// 18.5 -> 14.8 us, float32, 17, 56.0 -> 45.6; from 32 on it is slower: 32 tiles of 64 x 512 x 640 8.4 -> 9.1).
-constexpr long long kFewRowTiles = 24;
-__host__ __device__ inline bool in_order(long long row_tiles) { return row_tiles < kFewRowTiles; }
-__device__ inline void tile_of(const LinearProblem &q, unsigned block, int tile, int nt_n, long long &mt, int &nt)
+// once per XCD; `W` is small and stays in every L2.  Few row tiles may be taken in order (tiles_in_order).
+__device__ inline void tile_of(const LinearProblem &q, unsigned block, int nt_n, long long &mt, int &nt)
 {
-    if (in_order((q.M + tile - 1) / tile)) {
-        mt = block / nt_n;
-        nt = (int)(block % nt_n);
-        return;
-    }
-    const unsigned j = block / kXcds;
-    mt = (long long)(j / nt_n) * kXcds + block % kXcds;
+    const unsigned j = block >> q.deal_shift;
+    mt = ((long long)(j / nt_n) << q.deal_shift) + (block & ((1u << q.deal_shift) - 1u));
     nt = (int)(j % nt_n);
 }
 
@@ -169,7 +163,7 @@ template <bool GROUPED> __device__ inline void gemm_tile_bf16(const LinearProble
     const int nt_n = (N + BN - 1) / BN;
     long long mt;
     int nt;
-    tile_of(q, block, BM, nt_n, mt, nt);
+    tile_of(q, block, nt_n, mt, nt);
     const long long m0 = mt * BM;
     const int n0 = nt * BN;
     if (m0 >= M) return;   // the last round of row tiles may be partial (uniform over the workgroup)
@@ -388,7 +382,7 @@ __global__ __launch_bounds__(GEMM_THREADS, 4) void enc_proj_bf16_small_kernel(Li
     const int nt_n = (N + SN - 1) / SN;
     long long mt;
     int nt;
-    tile_of(q, block, SM, nt_n, mt, nt);
+    tile_of(q, block, nt_n, mt, nt);
     const long long m0 = mt * SM;
     const int n0 = nt * SN;
     if (m0 >= q.M) return;
@@ -865,7 +859,7 @@ template <bool GROUPED> __device__ inline void gemm_tile_f32(const LinearProblem
     const int nt_n = (N + FN - 1) / FN;
     long long mt;
     int nt;
-    tile_of(q, block, FM, nt_n, mt, nt);
+    tile_of(q, block, nt_n, mt, nt);
     const long long m0 = mt * FM;
     const int n0 = nt * FN;
     if (m0 >= q.M) return;
@@ -983,10 +977,15 @@ __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch ba
 
 }  // namespace
 
-static unsigned tile_blocks(const LinearProblem &q, int tile)   // square tiles
+// the order of a problem's square tiles, and the workgroups that makes
+static void order_tiles(LinearProblem &q, int tile, TileLaunch launch)
 {
-    const long long row_tiles = (q.M + tile - 1) / tile, rounds = (row_tiles + kXcds - 1) / kXcds;
-    return (unsigned)((in_order(row_tiles) ? row_tiles : rounds * kXcds) * ((q.N + tile - 1) / tile));
+    const long long row_tiles = (q.M + tile - 1) / tile, column_tiles = (q.N + tile - 1) / tile;
+    const long long rounds = (row_tiles + kXcds - 1) / kXcds;
+    const bool in_order = tiles_in_order(launch, row_tiles, column_tiles);
+    static_assert(kXcds == 1 << 3, "a power of two");
+    q.deal_shift = in_order ? 0 : 3;
+    q.blocks = (unsigned)((in_order ? row_tiles : rounds * kXcds) * column_tiles);
 }
 
 constexpr long long kSmallTiles = 160;   // up to this many 128 x 128 tiles a product takes 64 x 64 tiles, see enc_proj_bf16_small_kernel
@@ -1005,7 +1004,6 @@ static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int 
     q.K = K;
     q.ldw = ldw;
     q.group = group;
-    q.blocks = tile_blocks(q, dtype == 1 ? BM : FM);
     return q;
 }
 
@@ -1058,10 +1056,10 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
     batch.q[n].lens = enc_len;
     batch.q[n].B = B;
     batch.q[n].T = T;
-    if (bf16 && takes_big_tiles((int64_t)B * T, w->h_joint, 0)) {
+    const bool apart = bf16 && takes_big_tiles((int64_t)B * T, w->h_joint, 0);   // not part of the launch below
+    if (apart) {
         const hipError_t e = launch_big_tiles(batch.q[n], stream);
         if (e != hipSuccess) return e;
-        batch.q[n].blocks = 0;   // not part of the launch below
     }
     ++n;
     if (w->pred_kind == TDT_PRED_LSTM) {   // stored [label][unit][gate]
@@ -1077,7 +1075,10 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
                                           pred_tab + c * rows_tab * w->h_joint);
     }
     unsigned blocks = 0;
-    for (int i = 0; i < n; ++i) blocks += batch.q[i].blocks;
+    for (int i = apart ? 1 : 0; i < n; ++i) {
+        order_tiles(batch.q[i], bf16 ? BM : FM, TileLaunch::kPrepare);
+        blocks += batch.q[i].blocks;
+    }
     const size_t n16 = clear.zero_bytes / 16, n16_ones = clear.ones_bytes / 16;
     size_t zb = ((n16 > n16_ones ? n16 : n16_ones) + GEMM_THREADS - 1) / GEMM_THREADS;
     if (zb > 256) zb = 256;
@@ -1099,10 +1100,15 @@ static hipError_t launch_problem(int dtype, LinearProblem q, hipStream_t stream)
     if (q.M <= 0) return hipSuccess;
     if (dtype == 1 && takes_big_tiles(q.M, q.N, q.group)) return launch_big_tiles(q, stream);
     if (dtype == 1 && tiles_of(q) <= kSmallTiles) {
-        q.blocks = tile_blocks(q, SM);
+        order_tiles(q, SM, TileLaunch::kSmall);
         hipLaunchKernelGGL(enc_proj_bf16_small_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
-    } else if (dtype == 1) hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
-    else hipLaunchKernelGGL(enc_proj_f32_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    } else if (dtype == 1) {
+        order_tiles(q, BM, TileLaunch::kOwn);
+        hipLaunchKernelGGL(enc_proj_bf16_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    } else {
+        order_tiles(q, FM, TileLaunch::kOwn);
+        hipLaunchKernelGGL(enc_proj_f32_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);
+    }
     return hipGetLastError();
 }
 

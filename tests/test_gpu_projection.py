@@ -35,10 +35,13 @@ def test_projection_tiles(oracle_lib, gpu, rows, d_enc, H):   # noqa: F811
     assert (got[rows:] == 7.0).all(), "rows past the end were written"
 
 
-# where row tiles stop being dealt to the dies in order: 23 and 24 of 64 rows (bfloat16's small products, float32) and of 128
+# few row tiles, on both sides of where they are given to the dies in order: bfloat16's 64 x 64 tiles, 128 x 128 tiles, float32's
 @pytest.mark.parametrize("dtype,rows,d_enc,H", [
     ("bf16", 1472, 72, 72), ("bf16", 1473, 72, 72), ("bf16", 2944, 40, 1000), ("bf16", 2945, 40, 1000),
-    ("fp32", 1472, 24, 200), ("fp32", 1473, 24, 200)])
+    ("fp32", 1472, 24, 200), ("fp32", 1473, 24, 200),
+    ("bf16", 128, 72, 200), ("bf16", 129, 72, 200), ("bf16", 512, 40, 1272), ("bf16", 513, 40, 1272), ("bf16", 768, 40, 1272),
+    ("bf16", 769, 40, 1272), ("bf16", 1535, 40, 2040), ("bf16", 2944, 24, 2040), ("bf16", 2945, 24, 2040),
+    ("fp32", 100, 40, 2040), ("fp32", 600, 40, 1272), ("fp32", 1472, 24, 2040), ("fp32", 1473, 24, 2040)])
 def test_projection_of_few_row_tiles(oracle_lib, gpu, dtype, rows, d_enc, H):   # noqa: F811
     import torch
     cfg = synth.small_config("projfew", dtype=dtype, d_enc=d_enc, h_joint=H, seed=49, B=1, T=rows, len_lo=rows, len_hi=rows)

@@ -45,6 +45,11 @@ extern "C" void words_c(int wide, int durations, int n_clusters, int hpc, int C,
     const long long v[7] = {w.rows, w.cells, w.lse, w.dur, w.present, w.end, kLabelWordsMost};
     for (int i = 0; i < 7; ++i) out[i] = v[i];
 }
+extern "C" int in_order_c(int launch, long long row_tiles, long long column_tiles)
+{
+    return tiles_in_order(launch == 0 ? TileLaunch::kPrepare : launch == 1 ? TileLaunch::kOwn : TileLaunch::kSmall, row_tiles,
+                          column_tiles);
+}
 extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
 {
     return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
@@ -263,3 +268,22 @@ def test_words_of_the_joint_passes_are_reached_by_32_bit_offsets(split):
                         assert all(x % 256 == 0 for x in (lse, durs, present, end)) and end <= bound
                         most = max(most, end)
     assert most > 0.99 * bound and bound < 2**31 - 2**16
+
+
+def test_order_of_a_projections_tiles(split):
+    """Row tiles are given out in order only where it was measured to pay: in the preparation launch, and elsewhere where
+    dealing them fills a die's compute units before the others'; never from 24 row tiles on."""
+    order = lambda launch, r, c: split.in_order_c(launch, C.c_longlong(r), C.c_longlong(c)) != 0   # noqa: E731
+    prepare, own, small = 0, 1, 2
+    for r in range(1, 40):
+        for c in (1, 5, 20, 40):
+            assert order(prepare, r, c) == (r < 24)
+    for r, c in ((1, 4), (2, 10), (1, 16), (6, 16), (12, 16), (21, 16), (23, 16), (1, 32), (8, 32), (16, 32)):
+        assert order(own, r, c)
+    for r, c in ((21, 8), (23, 8), (3, 10), (17, 10), (23, 10), (23, 4), (24, 16), (32, 32)):
+        assert not order(own, r, c)
+    for r, c in ((1, 2), (1, 10), (1, 16), (2, 16), (1, 20), (2, 20), (2, 32), (9, 20), (12, 20)):
+        assert order(small, r, c)
+    for r, c in ((6, 10), (8, 10), (9, 10), (16, 10), (20, 10), (23, 10), (28, 10), (3, 16), (8, 16), (16, 16), (23, 16), (23, 2), (9, 4), (23, 4),
+                 (6, 8), (16, 8), (23, 8), (3, 20), (8, 20), (13, 20), (16, 20), (23, 20), (8, 32), (16, 32)):
+        assert not order(small, r, c)
