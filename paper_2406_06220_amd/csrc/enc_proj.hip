@@ -943,8 +943,9 @@ __global__ __launch_bounds__(GEMM_THREADS) void enc_proj_f32_kernel(LinearProble
 // Everything a decode call needs before its decode kernel, in one launch: the encoder
 // projection, the per-label tables of the predictor side (a product with blocks == 0 is
 // absent), and the clearing of the workspace's zero region and of the statistics.  The tasks
-// are independent; a workgroup takes its task from its index.  Every product's workgroup count
-// is a multiple of the number of dies, so each keeps its die-aware order of tiles.
+// are independent; a workgroup takes its task from its index.  A product's die-aware order of tiles takes no more
+// than that local indexes which are alike modulo the dies run on one die; which die that is depends on the
+// workgroups ahead, whose number is any (products in order have no whole rounds of the dies).
 template <bool BF16>
 __global__ __launch_bounds__(GEMM_THREADS, 2) void prepare_kernel(LinearBatch batch, PackBatch pack, unsigned pack_blocks,
                                                               uint4 *zero, size_t n16, uint4 *ones, size_t n16_ones,

@@ -8,7 +8,7 @@ import pytest
 
 import parity
 from paper_2406_06220_amd import synth
-from test_gpu_parity import gpu  # noqa: F401  (the fixture)
+from test_gpu_parity import check, gpu  # noqa: F401  (gpu: the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -98,3 +98,20 @@ def test_projection_large_tiles(oracle_lib, gpu, B, T, lo, d_enc, H):   # noqa: 
     assert np.isfinite(got[rows]).all()
     rest = np.setdiff1d(np.arange(B * T + 3), rows)
     assert (got[rest] == 7.0).all(), "rows that are no valid frame were written"
+
+
+# the preparation launch: a projection of 17 or 18 row tiles in order, whose workgroups are no multiple of the dies, ahead of
+# per-label tables of 24 row tiles, which are dealt -- one of an LSTM (grouped columns), two of a stateless predictor
+@pytest.mark.parametrize("kw", [
+    dict(dtype="bf16", pred_kind="lstm", h_pred=160, emb_dim=24, h_joint=640, vocab=3071, B=7, T=311),
+    dict(dtype="bf16", pred_kind="stateless", pred_layers=2, h_pred=48, emb_dim=24, h_joint=640, vocab=3071, B=7, T=311),
+    dict(dtype="fp32", pred_kind="lstm", h_pred=80, emb_dim=24, h_joint=320, vocab=1535, B=4, T=260),
+    dict(dtype="fp32", pred_kind="stateless", pred_layers=2, h_pred=48, emb_dim=24, h_joint=320, vocab=1535, B=4, T=260)])
+def test_tiles_in_order_ahead_of_tiles_that_are_dealt(oracle_lib, gpu, kw):   # noqa: F811
+    tile = 128 if kw["dtype"] == "bf16" else 64
+    ahead = -(-kw["B"] * kw["T"] // tile) * (kw["h_joint"] // tile)
+    assert ahead % 8 != 0 and -(-kw["B"] * kw["T"] // tile) in (17, 18) and (kw["vocab"] + 1) // tile == 24
+    cfg = synth.small_config("projahead", d_enc=32, len_lo=kw["T"] // 2, len_hi=kw["T"], seed=50, default_blank_bias=4.0, **kw)
+    w = synth.generate_model(cfg)
+    enc, ln = synth.generate_inputs(cfg)
+    check(oracle_lib, gpu, cfg, w, enc, ln, max_replayed_frac=0.2)
