@@ -1008,16 +1008,10 @@ static LinearProblem linear_problem(int dtype, const void *a, int64_t rows, int 
     return q;
 }
 
-// Products with a column count that 256-column tiles divide take the 256 x 256 kernel (a launch of its own: it has
-// its own workgroup size and LDS footprint) where its tiles occupy most of the chip.  The line is at 160 tiles of all
-// rows, some 120 of valid ones; valid rows x columns x inputs, us with 256 x 256 tiles / with 128 x 128: 11960 x 512 x 512
-// (94 tiles) 19.0 / 17.9, 5981 x 1280 x 640 (120) 22.4 / 20.8, 17938 x 512 x 512 (142) 21.7 / 26.0, 11960 x 1024 x 1024
-// (188) 35.1 / 42.8, 47879 x 256 x 512 (188) 26.1 / 33.8, 47879 x 1024 x 1024 (752) 114 / 162.
-// With 256 columns they are taken from 128 tiles on: of long batches fewer rows are padding.
-constexpr long long kBigTiles = 160, kBigRows = 32768;
-static bool takes_big_tiles(int64_t rows, int N, int group)
+// Products that take the 256 x 256 kernel (a launch of its own: it has its own workgroup size and LDS footprint)
+static bool takes_big_tiles(const LinearProblem &q)
 {
-    return group == 0 && N % GN == 0 && (rows >= kBigRows || (rows + GM - 1) / GM * (N / GN) >= kBigTiles);
+    return q.group == 0 && q.N % GN == 0 && big_tiles(q.lens != nullptr, q.M, q.N / GN);
 }
 
 static hipError_t launch_big_tiles(LinearProblem q, hipStream_t stream)
@@ -1057,7 +1051,7 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
     batch.q[n].lens = enc_len;
     batch.q[n].B = B;
     batch.q[n].T = T;
-    const bool apart = bf16 && takes_big_tiles((int64_t)B * T, w->h_joint, 0);   // not part of the launch below
+    const bool apart = bf16 && takes_big_tiles(batch.q[n]);   // not part of the launch below
     if (apart) {
         const hipError_t e = launch_big_tiles(batch.q[n], stream);
         if (e != hipSuccess) return e;
@@ -1099,7 +1093,7 @@ hipError_t launch_prepare(const void *enc, const int32_t *enc_len, int B, int T,
 static hipError_t launch_problem(int dtype, LinearProblem q, hipStream_t stream)
 {
     if (q.M <= 0) return hipSuccess;
-    if (dtype == 1 && takes_big_tiles(q.M, q.N, q.group)) return launch_big_tiles(q, stream);
+    if (dtype == 1 && takes_big_tiles(q)) return launch_big_tiles(q, stream);
     if (dtype == 1 && tiles_of(q) <= kSmallTiles) {
         order_tiles(q, SM, TileLaunch::kSmall);
         hipLaunchKernelGGL(enc_proj_bf16_small_kernel, dim3(q.blocks), dim3(GEMM_THREADS), 0, stream, q);

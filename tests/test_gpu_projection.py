@@ -64,12 +64,12 @@ def test_projection_of_few_row_tiles(oracle_lib, gpu, dtype, rows, d_enc, H):   
 # valid frames in 256 x 256 tiles that stay in a workgroup's hands: one K tile and less, K tiles that are not whole,
 # one and several rounds of tiles, column tiles that the workgroups of a die are no multiple of, more utterances than threads
 @pytest.mark.parametrize("B,T,lo,d_enc,H", [
-    (20, 520, 520, 8, 1024), (20, 520, 300, 64, 1024), (41, 338, 0, 72, 768), (7, 2400, 1000, 136, 768), (64, 640, 0, 128, 256),
-    (300, 34, 0, 200, 1280), (530, 40, 3, 64, 1536), (23, 900, 899, 264, 1024)])
+    (20, 820, 820, 8, 1024), (20, 820, 300, 64, 1024), (41, 534, 0, 72, 768), (7, 3200, 1000, 136, 768), (64, 640, 0, 128, 256),
+    (300, 44, 0, 200, 1280), (530, 40, 3, 64, 1536), (23, 900, 899, 264, 1024)])
 def test_projection_large_tiles(oracle_lib, gpu, B, T, lo, d_enc, H):   # noqa: F811
     import torch
     cfg = synth.small_config("projlarge", dtype="bf16", d_enc=d_enc, h_joint=H, seed=48, B=B, T=T, len_lo=lo, len_hi=T)
-    assert -(-B * T // 256) * (H // 256) >= 160, "these shapes are there for the large tiles"
+    assert B * T >= 32768 or -(-B * T // 256) * (H // 256) >= 256, "these shapes are there for the large tiles"
     w = synth.generate_model(cfg)
     w["b_enc"] = np.random.default_rng(9).standard_normal(H).astype(np.float32)
     enc, _ = synth.generate_inputs(cfg)
@@ -98,6 +98,39 @@ def test_projection_large_tiles(oracle_lib, gpu, B, T, lo, d_enc, H):   # noqa: 
     assert np.isfinite(got[rows]).all()
     rest = np.setdiff1d(np.arange(B * T + 3), rows)
     assert (got[rest] == 7.0).all(), "rows that are no valid frame were written"
+
+
+# on both sides of where 256 x 256 tiles begin: all rows (40 and 39 row tiles, four column tiles), and half-padded utterances (64 and
+# 63), one column tile of 32768 rows and one less
+@pytest.mark.parametrize("B,T,lo,d_enc,H", [
+    (1, 9985, None, 40, 1024), (1, 9984, None, 40, 1024), (16, 1023, 100, 40, 1024), (16, 1008, 100, 40, 1024), (32, 1024, 100, 40, 256),
+    (7, 4681, 400, 40, 256)])
+def test_projection_where_large_tiles_begin(oracle_lib, gpu, B, T, lo, d_enc, H):   # noqa: F811
+    import torch
+    cfg = synth.small_config("projbegin", dtype="bf16", d_enc=d_enc, h_joint=H, seed=51, B=B, T=T, len_lo=T, len_hi=T)
+    w = synth.generate_model(cfg)
+    w["b_enc"] = np.random.default_rng(13).standard_normal(H).astype(np.float32)
+    enc, _ = synth.generate_inputs(cfg)
+    ln = np.random.default_rng(14).integers(lo or T, T + 1, size=B).astype(np.int32)
+    parity.announce(f"projection B={B} T={T} d_enc={d_enc} H={H} lengths from {lo}")
+    model = gpu.DeviceModel(cfg, w)
+    enc_d, len_d = model.upload_enc(enc), torch.from_numpy(ln).to(model.device)
+    out = torch.full((B * T + 3, H), 7.0, dtype=torch.float32, device=model.device)
+    stream = torch.cuda.current_stream().cuda_stream
+    if lo is None:
+        gpu.tdt_encoder_projection(enc_d.data_ptr(), B * T, model.c, out.data_ptr(), stream)
+    else:
+        gpu.tdt_encoder_projection_valid(enc_d.data_ptr(), len_d.data_ptr(), B, T, model.c, out.data_ptr(), stream)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    valid = np.append((np.arange(T)[None] < ln[:, None]).reshape(-1), [False] * 3)
+    rows = np.flatnonzero(valid)
+    some = np.unique(np.concatenate([rows[:300], rows[-300:], np.random.default_rng(15).choice(rows, min(2000, rows.size), False)]))
+    om = oracle_lib.OracleModel(cfg, w)
+    flat = enc.reshape(B * T, d_enc)
+    ref = np.stack([om.enc_proj_frame(flat[r]) for r in some])
+    np.testing.assert_allclose(got[some], ref, atol=2e-4, rtol=1e-5)
+    assert np.isfinite(got[rows]).all() and (got[~valid] == 7.0).all()
 
 
 # the preparation launch: a projection of 17 or 18 row tiles in order, whose workgroups are no multiple of the dies, ahead of

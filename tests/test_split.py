@@ -50,6 +50,7 @@ extern "C" int in_order_c(int launch, long long row_tiles, long long column_tile
     return tiles_in_order(launch == 0 ? TileLaunch::kPrepare : launch == 1 ? TileLaunch::kOwn : TileLaunch::kSmall, row_tiles,
                           column_tiles);
 }
+extern "C" int big_tiles_c(int ragged, long long rows, long long column_tiles) { return big_tiles(ragged != 0, rows, column_tiles); }
 extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
 {
     return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
@@ -287,3 +288,21 @@ def test_order_of_a_projections_tiles(split):
     for r, c in ((6, 10), (8, 10), (9, 10), (16, 10), (20, 10), (23, 10), (28, 10), (3, 16), (8, 16), (16, 16), (23, 16), (23, 2), (9, 4), (23, 4),
                  (6, 8), (16, 8), (23, 8), (3, 20), (8, 20), (13, 20), (16, 20), (23, 20), (8, 32), (16, 32)):
         assert not order(small, r, c)
+
+
+def test_large_tiles_where_neither_full_nor_half_padded_batches_lose(split):
+    """129 tiles of valid rows are where 256 x 256 tiles begin to pay.  Batches whose lengths nobody knows on the host take
+    them where lengths even over a tenth to the whole fill as many."""
+    big = lambda ragged, rows, c: split.big_tiles_c(ragged, C.c_longlong(rows), C.c_longlong(c)) != 0   # noqa: E731
+    for c in (2, 3, 4, 5, 8):
+        for tiles in range(100, 400):
+            rows = tiles * 256 // c
+            if rows < 32768:
+                assert big(0, rows, c) == (-(-rows // 256) * c >= 160)
+                if big(1, rows, c):
+                    assert 0.55 * rows / 256 * c > 129
+                elif -(-rows // 256) * c >= 260:
+                    raise AssertionError((rows, c))
+            else:
+                assert big(0, rows, c) and big(1, rows, c)
+    assert big(1, 32768, 1) and not big(1, 32767, 1) and not big(0, 32512, 1)
