@@ -118,6 +118,22 @@ __device__ inline void st_co64(unsigned long long *p, unsigned long long v)
     __hip_atomic_store((TDT_GLOBAL unsigned long long *)p, v, __ATOMIC_RELAXED, TDT_AGENT);
 }
 
+// The same for an array that is reached through one buffer descriptor (a lane offset and a scalar offset, multiples of 8): the
+// access an agent-scope relaxed atomic of 8 bytes compiles to, one dwordx2 instruction with the scope bit sc1, in its buffer form --
+// which LLVM's memory model of this architecture lists beside the global form for these atomics.  So the two halves of a word arrive
+// together, and a word that is not zero is whole.  The compiler may move these accesses like plain ones, so a loop that
+// waits needs a memory clobber in it, and it does not drop a half of one of which both halves are used.
+typedef unsigned WordHalves __attribute__((ext_vector_type(2)));
+__device__ inline __attribute__((always_inline)) unsigned long long ld_word64(__amdgpu_buffer_rsrc_t rs, int lane_off, int off)
+{
+    const WordHalves x = __builtin_amdgcn_raw_buffer_load_b64(rs, lane_off, off, 16 /* sc1 */);
+    return (unsigned long long)x.x | ((unsigned long long)x.y << 32);
+}
+__device__ inline __attribute__((always_inline)) void st_word64(__amdgpu_buffer_rsrc_t rs, int lane_off, int off, unsigned long long v)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(WordHalves{(unsigned)v, (unsigned)(v >> 32)}, rs, lane_off, off, 16 /* sc1 */);
+}
+
 // (logit, index) packed so that an unsigned 64-bit maximum is "largest logit,
 // lowest index on ties"; zero is below every packed value
 __device__ inline unsigned long long pack_best(float v, int idx)

@@ -389,14 +389,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     const int jd = behind(p.row_dur) + cl * kRowBufs * jd_n;      // packed (logit, ~duration class)
     const int jh = behind(p.present) + cl * (kRowBufs + 1) * jh_n;   // workgroups without a work item (the last: state has been read)
     const __amdgpu_buffer_rsrc_t crs = buffer_of(p.row_lab, (size_t)behind(p.present) + (size_t)ncl * (kRowBufs + 1) * jh_n);
-    typedef unsigned v2u __attribute__((ext_vector_type(2)));
-    auto ld_word = [&](int lane_off, int off) __attribute__((always_inline)) {
-        const v2u x = __builtin_amdgcn_raw_buffer_load_b64(crs, lane_off, off, 16 /* sc1 */);
-        return (unsigned long long)x.x | ((unsigned long long)x.y << 32);
-    };
-    auto st_word = [&](int lane_off, int off, unsigned long long v) __attribute__((always_inline)) {
-        __builtin_amdgcn_raw_buffer_store_b64(v2u{(unsigned)v, (unsigned)(v >> 32)}, crs, lane_off, off, 16 /* sc1 */);
-    };
+    auto ld_word = [&](int lane_off, int off) __attribute__((always_inline)) { return ld_word64(crs, lane_off, off); };
+    auto st_word = [&](int lane_off, int off, unsigned long long v) __attribute__((always_inline)) { st_word64(crs, lane_off, off, v); };
 
     // ---- Alg. 3 lines 3-4.  Lane g of every wavefront holds hypothesis g of the group
     __syncthreads();

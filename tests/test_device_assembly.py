@@ -28,17 +28,15 @@ def test_assembly_that_writes_m0_says_so():
         assert re.search(r':[^:]*"m0"[^:]*$', s), f"{f}: {s}"
 
 
-@pytest.fixture(scope="module")
-def big_kernel(tmp_path_factory):
-    """The instructions of the 256 x 256 projection kernel, in order: (mnemonic, operands)."""
-    out = str(tmp_path_factory.mktemp("asm") / "enc_proj.s")
+def instructions(source, kernel, out):
+    """The instructions of one kernel of a file, in order: (mnemonic, operands)."""
     flags = [f for f in build.HIPCC_FLAGS if f != "-shared"]
-    subprocess.run(["hipcc", *flags, "-I", os.path.join(build.ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only",
-                    os.path.join(CSRC, "enc_proj.hip"), "-o", out], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    subprocess.run(["hipcc", *flags, "-I", os.path.join(build.ROOT, "include"), "-I", CSRC, "-S", "--cuda-device-only", source,
+                    "-o", out], check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     code, inside = [], False
     for line in open(out):
         line = line.split(";")[0].strip()
-        if re.match(r"_ZN\w*enc_proj_bf16_big_kernel\w*:", line):
+        if re.match(rf"\w*{kernel}\w*:", line):
             inside = True
         elif inside and line and not line.startswith(".") and not line.endswith(":"):
             op, _, rest = line.partition(" ")
@@ -46,6 +44,39 @@ def big_kernel(tmp_path_factory):
             if op == "s_endpgm":
                 return code
     raise AssertionError("the kernel was not found")
+
+
+@pytest.fixture(scope="module")
+def big_kernel(tmp_path_factory):
+    return instructions(os.path.join(CSRC, "enc_proj.hip"), "enc_proj_bf16_big_kernel", str(tmp_path_factory.mktemp("asm") / "enc_proj.s"))
+
+
+WORDS = r"""
+#include "exchange.h"
+using namespace tdt;
+__global__ void words_kernel(const unsigned long long *a, unsigned long long *b, int n)
+{
+    const int lane = threadIdx.x * 8;
+    const __amdgpu_buffer_rsrc_t in = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned long long *>(a), 0, n, 0x00020000);
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(b, 0, n, 0x00020000);
+    const unsigned long long x = ld_co64(a + threadIdx.x);
+    const unsigned long long y = ld_word64(in, lane, 4096);
+    st_co64(b + 64 + threadIdx.x, y);
+    st_word64(out, lane, 0, x);
+}
+"""
+
+
+def test_words_move_like_atomics(tmp_path):
+    """An 8-byte word through a buffer descriptor is one access of the width and the scope that an agent-scope atomic of 8
+    bytes is."""
+    src = tmp_path / "words.hip"
+    src.write_text(WORDS)
+    code = instructions(str(src), "words_kernel", str(tmp_path / "words.s"))
+    moves = {op: o for op, o in code if re.match(r"(global|flat|buffer)_(load|store|atomic)", op)}
+    assert sorted(moves) == ["buffer_load_dwordx2", "buffer_store_dwordx2", "global_load_dwordx2", "global_store_dwordx2"]
+    scope = lambda op: [w for w in moves[op][-1].split() if w in ("sc0", "sc1", "nt")]   # noqa: E731
+    assert all(scope(op) == ["sc1"] for op in moves)
 
 
 def registers(operand):
