@@ -121,7 +121,11 @@ typedef struct {
  *               for its next non-blank label (the inner loop of Algorithm 3
  *               advances one frame per pass; since the predictor output is fixed
  *               during that loop, several upcoming frames can be scored at once
- *               and the first non-blank taken).  0 = automatic.
+ *               and the first non-blank taken).  0 = automatic.  With a window of the
+ *               caller's, the loops are Algorithm 3's as printed: every hypothesis of a
+ *               group that has found a label waits until all of them have.  With the
+ *               automatic one it may take its predictor step while others still search:
+ *               the same hypotheses, fewer joint passes, more predictor steps (out_stats).
  *   n_clusters  the batch is split into this many groups of hypotheses that are
  *               decoded by disjoint sets of workgroups without waiting for each
  *               other.  0 = automatic (by batch size and model shape; see the design notes).

@@ -20,7 +20,8 @@
 //   * A workgroup owns its column tiles of the predictor-side matrices for the whole call.  The four
 //     gates of a unit meet in the workgroup that updates the unit's cell, so the recurrent
 //     pre-activations and the cell state never leave its LDS; only h is exchanged.
-//   * A group's hypotheses wait for each other's searches only until half of them do (see "patience").
+//   * A group's hypotheses wait for each other's searches only until enough of them do: half, without a predictor a third, with
+//     deeper LSTMs two thirds or four fifths (see "patience").
 //   * The control state of a hypothesis (frame, label count, last labels, score ...) lives in lane g
 //     of every wavefront, the lists of active and searching hypotheses are 64-bit masks: a decision
 //     is taken by every wavefront on its own, without a workgroup barrier or LDS list.
@@ -41,12 +42,20 @@
 // Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
 // exchange (a workgroup without work item: a word of its own that everybody waits for), after it
 // has finished reading all earlier exchanges.  So a workgroup that has read joint exchange j knows
-// that all others have read the h and projection rows of this label, and the cells of joint exchange
-// j - 2 (those of j - 1 not for certain: the score terms found in it are summed while j's cells
-// travel): it puts its own words of those back.  The stores complete before it publishes joint
+// what all others have read, and puts its own words of that back.  The stores complete before it publishes joint
 // exchange j + 1 (every wavefront waits for its stores before the workgroup barrier that precedes
-// publishing), and the next readers of those words come only behind that exchange: rows alternate
-// between two buffers by label, cells rotate through four.
+// publishing), and the next readers of those words come only behind that exchange.  What is known to have been read:
+//   * Cells: those of joint exchange j - 2 (those of j - 1 not for certain: the score terms found in it are summed while
+//     j's cells travel).  They rotate through four buffers.
+//   * Rows of the hidden state: this predictor step's.  They alternate between two buffers by step.
+//   * Projected rows where LDS has two areas (one layer, not OWN): this step's, which alternate by step as well.  Every workgroup
+//     stages the rows of those who took the step before it publishes the step's first joint exchange -- a workgroup without a work item,
+//     too, though it has no use for them in that pass: a hypothesis that goes on searching is scored behind later steps,
+//     with the row it has, by workgroups that may have had no item until then, and by that time the row is put back.  (Where
+//     nobody goes on early, `patience` zero, every row belongs to the step at hand and stays until it ends.)
+//   * Projected rows of the other LSTM forms (OWN), which are read in every pass: a hypothesis' own last one.  It stays through
+//     as many steps of others as the hypothesis searches; which of the two buffers it is in is kept per hypothesis (`own`), and
+//     it is put back while the hypothesis' next one is made, since all have read it in the pass that found the label.
 #include <math.h>
 
 #include <mutex>
@@ -462,7 +471,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     __syncthreads();
 
     // ---- Algorithm 3's inner loop ends when nobody searches any more: a group's label takes as many joint passes as its
-    // longest search, and who has found one waits.  Here it ends, from the second pass of a search on, as soon as those
+    // longest search, and who has found one waits.  Here it ends, after any pass, as soon as those
     // who wait are as many as those who search (no predictor: half as many): they take their predictor step, and
     // the next pass scores both.  A hypothesis' own sequence of steps is the same; the group's joint passes are fewer, for more
     // predictor steps of fewer hypotheses.  Replays of decoded hypotheses (7 to 16 of a group; labels in bursts, and drawn on 3 to 60
