@@ -76,7 +76,6 @@ constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront 
 static_assert(kNowhere >= 2ll * TDT_MAX_LSTM_LAYERS * kMaxGrid * kLabelMaxHyps * kLabelLongest * 4, "the largest exchange buffer");
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kPairRows = 8;                // up to this many rows two planes do (one LSTM layer)
-constexpr int kLongWindow = 16;             // frames of a pass of which a search seldom takes a second one
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -479,7 +478,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // one 0.82 to 1.24 (predictor and joint pass at their measured times).  Not with a caller's window, which asks for the steps
     // as they are printed, nor with long ones, of which a search takes one.  us a call, in lock step / now: RNN-T B = 32 987 / 943,
     // B = 128 1986 / 1850, TDT B = 32 494 / 448, stateless B = 128 1979 / 1782, multi-blank B = 27 521 / 504; one or two
-    // hypotheses a group, who have nobody to wait for, 235 / 237.
+    // hypotheses a group 235 / 237.  (One has nobody to wait for and a long window: a pass has a row tile at least.)
     // Deeper LSTMs, whose predictor step is two joint passes and more: four times as many as search; twice, where the output
     // layer is streamed and few rows are no shorter pass (two layers, 640 units, B = 32, 1761 us, with two to one 1796, four to one
     // 1766; B = 128 3205, 3207, 3149; 8198 outputs, B = 96, 3804, 3475, three to one 3507; config 5 29489, 27752).  Reductions

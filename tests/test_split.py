@@ -51,6 +51,7 @@ extern "C" int in_order_c(int launch, long long row_tiles, long long column_tile
                           column_tiles);
 }
 extern "C" int big_tiles_c(int ragged, long long rows, long long column_tiles) { return big_tiles(ragged != 0, rows, column_tiles); }
+extern "C" int long_window_c() { return kLongWindow; }
 extern "C" int item_c(int C, int nt, int hpc, int window, int joint_tiles)
 {
     return usual_item(C, nt, hpc, window, joint_tiles, hpc * 64 < 256 ? hpc * 64 : 256);
@@ -306,3 +307,12 @@ def test_large_tiles_where_neither_full_nor_half_padded_batches_lose(split):
             else:
                 assert big(0, rows, c) and big(1, rows, c)
     assert big(1, 32768, 1) and not big(1, 32767, 1) and not big(0, 32512, 1)
+
+
+def test_a_hypothesis_of_its_own_has_a_long_window(split):
+    """Whether hypotheses go on before all of their group have found a label is decided by the window that all of them would
+    search with.  One alone never does: it has nobody to wait for."""
+    for C_ in (1, 2, 3, 7, 15, 16, 17, 32, 51, 64, 128, 256):
+        for nt in (1, 4, 5, 9, 33, 65, 129, 513, 2048):
+            for hpc in (1, 2, 5, 16, 64):
+                assert split.window_c(0, C_, nt, hpc, hpc, 1, 0, min(64 * hpc, 256), 64) >= split.long_window_c()
