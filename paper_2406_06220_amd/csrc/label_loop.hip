@@ -254,7 +254,8 @@ struct LabelShared {
 // group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
 // NW: wavefronts.  Four, or (WIDE) eight for output layers of many thousands of columns, see wide_rows.
 // TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round.
-template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW, int TQ>
+// QROWS: most rows of the hidden state that are multiplied at once (kPairRows: see few_products).
+template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW, int TQ, int QROWS>
 __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 {
     typedef Frags<WT> F;
@@ -286,6 +287,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // areas they stay staged), so a row stays there until its hypothesis' next one: see "own".
     constexpr bool OWN = LSTM && !(LAYERS == 1 && TWO);
     constexpr bool PLANES = PL == 3 && LAYERS == 1;   // few rows of the hidden state: staged as planes, see stage_planes
+    constexpr bool FEW = QROWS < RT;                  // ... float32: see few_products
+    static_assert(!FEW || (PL == 1 && LAYERS == 1 && QROWS == kPairRows), "few_products");
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
 
@@ -770,7 +773,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
         }
     };
-    const bool qpack = PL == 3 && (DEEP || PLANES) && hpc <= kPackRows, qpair = PLANES && !qpack && hpc <= kPairRows;
+    const bool qpack = PL == 3 && (DEEP || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
     // One layer, up to eight rows: the wavefront that loads a row's stretch splits it where it is, four inputs a lane and
     // none for rows that are not there, and stages the planes.  Up to four rows they are the rows of one tile (plane
     // pl of row i is row pl * 4 + i), up to eight those of a tile and a half (rows 0 .. 7 the first terms, 8 .. 15 the
@@ -826,6 +829,51 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             for (int t = 0; t < N; ++t) c[t] = F::mma(a[i], b[t][i % NK], c[t]);
 #pragma unroll
         for (int t = 0; t < N; ++t) *reinterpret_cast<f32x4 *>(pw + t * CT) = c[t];
+    };
+
+    // float32, one layer, up to eight rows: sixteen products of four columns and four rows at a time (v_mfma_f32_4x4x1_16b_f32,
+    // 8 cycles) instead of one of sixteen and sixteen over four inputs (32 cycles, four a step and tile, whatever
+    // rows there are).  A lane's part of a fragment is column l % 16 and inputs l / 16 * 4 .. + 3 of the step, so the
+    // products are those of four columns with four rows over one input in four, and every lane ends with its four
+    // neighbouring columns of row l % 4 over a quarter of the wavefront's inputs.  Quarters are added up in pairs, and lie
+    // in the partial sums as planes of up to eight rows do: half q of row i is row q * 8 + i.  Four rows at a time; a form of its
+    // own, because rows for both kinds of products were 22 registers more than there are.  What bounds it are the matrix cores: four
+    // tiles and 160 inputs a wavefront took 5120 cycles, now 1280 per four rows.  Config 2's model in float32, B = 16, four
+    // rows a group, 1305 / 1179 us.  Error of 640 products against 64 bits, rms for a result of 1: 1.69e-7 / 1.27e-7 (shorter chains).
+    auto few_products = [&](const auto &b0, const auto &b1, auto tiles, float *part) __attribute__((always_inline)) {
+        constexpr int PLD = decltype(tiles)::value * CT + 4, N = TWO_ROUNDS ? 2 * TR : TR;
+#pragma clang loop unroll(disable)
+        for (int r = 0; r < hpc; r += 4) {   // uniform
+            float *const pw = part + (size_t)wave * RT * PLD + (r + (lane & 3) + ((lane >> 4) & 1) * kPairRows) * PLD + ((lane >> 2) & 3) * 4;
+            constexpr int AHEAD = 3;   // steps of the rows on their way (registers)
+            float4 x[AHEAD];
+#pragma unroll
+            for (int s = 0; s < AHEAD; ++s) x[s] = staged(xe, r + (lane & 3), s, 0);
+            f32x4 c[N];
+#pragma unroll
+            for (int t = 0; t < N; ++t) c[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int s = 0; s < NK; ++s) {
+                const float4 y4 = x[s % AHEAD];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < N; ++t) {
+                        const float y = e == 0 ? y4.x : e == 1 ? y4.y : e == 2 ? y4.z : y4.w;
+                        const float w = __uint_as_float(t < TR ? b0[t % TR][s][e] : b1[t % TR][s][e]);
+                        c[t] = __builtin_amdgcn_mfma_f32_4x4x1f32(w, y, c[t], 0, 0, 0);
+                    }
+                if (s + AHEAD < NK) x[s % AHEAD] = staged(xe, r + (lane & 3), s + AHEAD, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                f32x4 sum;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[e] = sum_over_halves(c[t][e]);
+                if (lane < 32) *reinterpret_cast<f32x4 *>(pw + t * CT) = sum;
+            }
+        }
     };
 
     // byte offsets of this workgroup's predictor-side tiles (the fragment-major copies)
@@ -920,7 +968,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 } else {
                     stage_rows(xe, v, upper);
                 }
-                if constexpr (PL == 1)
+                if constexpr (PL == 1 && !FEW)
 #pragma unroll
                     for (int s = 0; s < NK; ++s) {
                         float x[F::E];
@@ -1589,7 +1637,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     fresh();
                     TR(14);
                     const std::integral_constant<int, (TR + 1) / 2> half{};
-                    if (PLANES && qpack) {
+                    if constexpr (FEW) {
+                        few_products(bq, bq2, q_tiles, part_q);
+                    } else if (PLANES && qpack) {
                         if (TWO_ROUNDS || nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
                         else plane_products(full_rows, half, bq, q_tiles, part_q);
                         if (TWO_ROUNDS && nq > TR) plane_products(full_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
@@ -2359,14 +2409,18 @@ int label_kseg(const tdt_weights_t *w)
     return w->pred_kind == TDT_PRED_LSTM && w->h_pred > w->h_joint ? w->h_pred : w->h_joint;
 }
 
-template <typename WT, int LAYERS, int NK, int NW, int TQ> const void *label_form_of(bool chunked)
+template <typename WT, int LAYERS, int NK, int NW, int TQ, int QROWS = RT> const void *label_form_of(bool chunked)
 {
-    return chunked ? (const void *)label_kernel<WT, LAYERS, true, NK, NW, TQ> : (const void *)label_kernel<WT, LAYERS, false, NK, NW, TQ>;
+    return chunked ? (const void *)label_kernel<WT, LAYERS, true, NK, NW, TQ, QROWS>
+                   : (const void *)label_kernel<WT, LAYERS, false, NK, NW, TQ, QROWS>;
 }
-template <typename WT, int NK> const void *label_fn(int layers, int tq, bool chunked)
+template <typename WT, int NK> const void *label_fn(int layers, int tq, bool chunked, int hyps_per_cluster)
 {
     constexpr int TR = label_tiles(NK);
     if (layers > 1) return label_form_of<WT, 2, NK, 4, TR>(chunked);
+    if constexpr (Frags<WT>::PL == 1)
+        if (layers == 1 && hyps_per_cluster <= kPairRows)
+            return tq > TR ? label_form_of<WT, 1, NK, 4, 2 * TR, kPairRows>(chunked) : label_form_of<WT, 1, NK, 4, TR, kPairRows>(chunked);
     if (layers == 1) return tq > TR ? label_form_of<WT, 1, NK, 4, 2 * TR>(chunked) : label_form_of<WT, 1, NK, 4, TR>(chunked);
     if constexpr (first_tiles(Frags<WT>::PL == 3, NK) > TR)
         if (tq > TR) return label_form_of<WT, 0, NK, 4, first_tiles(true, NK)>(chunked);
@@ -2408,9 +2462,10 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
             if (per_wg > f.tq) f.tq *= 2;
         }
     }
+    const int hpc = hyps_per_cluster;
     if (w->dtype == 1)
-        f.fn = f.nk == 5 ? label_fn<uint16_t, 5>(f.layers, f.tq, chunked) : label_fn<uint16_t, 8>(f.layers, f.tq, chunked);
-    else f.fn = f.nk == 4 ? label_fn<float, 4>(f.layers, f.tq, chunked) : label_fn<float, 10>(f.layers, f.tq, chunked);
+        f.fn = f.nk == 5 ? label_fn<uint16_t, 5>(f.layers, f.tq, chunked, hpc) : label_fn<uint16_t, 8>(f.layers, f.tq, chunked, hpc);
+    else f.fn = f.nk == 4 ? label_fn<float, 4>(f.layers, f.tq, chunked, hpc) : label_fn<float, 10>(f.layers, f.tq, chunked, hpc);
     return f;
 }
 
@@ -2463,7 +2518,7 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
 {
     // the LDS limit of a compiled form is raised once per device (to all a workgroup can have)
     static std::mutex mu;
-    static const void *ready[64][40];
+    static const void *ready[64][48];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -2477,12 +2532,12 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     {
         std::lock_guard<std::mutex> lock(mu);
         int i = 0;
-        while (i < 40 && ready[dev][i] && ready[dev][i] != fn) ++i;
-        if (i == 40 || !ready[dev][i]) {
+        while (i < 48 && ready[dev][i] && ready[dev][i] != fn) ++i;
+        if (i == 48 || !ready[dev][i]) {
             e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)kLabelDynLds);
             if (e != hipSuccess) return e;
-            if (i < 40) ready[dev][i] = fn;
+            if (i < 48) ready[dev][i] = fn;
         }
     }
     DecodeParams pc = p;

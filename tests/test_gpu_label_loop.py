@@ -102,6 +102,11 @@ CASES = [
     *[(config(f"ll_planes_k{h}_{hp}_{B}", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
       for h, hp, B, c in ((8, 8, 1, 1), (40, 616, 3, 1), (640, 632, 4, 1), (104, 640, 5, 1), (616, 24, 7, 1), (640, 640, 8, 1),
                           (1024, 1000, 8, 1), (648, 1024, 2, 1), (320, 320, 15, 2), (600, 640, 30, 4))],
+    # float32, few rows of the hidden state, four at a time: one to eight, reductions of both lengths that end inside a step
+    # and that leave wavefronts without one, one round of phase Q and two
+    *[(config(f"ll_few_f32_k{h}_{hp}_{B}_{c}", dtype="fp32", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
+      for h, hp, B, c in ((8, 8, 1, 1), (40, 616, 3, 1), (640, 632, 4, 1), (104, 640, 5, 1), (616, 24, 8, 1), (640, 640, 28, 4), (632, 640, 12, 4),
+                          (256, 248, 8, 1), (48, 248, 80, 16), (240, 200, 128, 16))],
     # a stateless group of one workgroup by the size of the output layer, and one column beyond
     *[(config(f"ll_one_wg{v}", dtype="fp32", pred_kind="stateless", h_pred=24, vocab=v, B=300), {}) for v in (63, 64)],
     # the form of eight wavefronts: row tiles in pairs and one left over, columns that are no multiple of a
@@ -125,9 +130,9 @@ def test_label_loop(oracle_lib, gpu, cfg, opts):   # noqa: F811
     check(oracle_lib, gpu, cfg, max_replayed_frac=0.1, **opts)
 
 
-@pytest.mark.parametrize("kw", [dict(B=6), dict(B=40, pred_layers=2), dict(B=9, pred_kind="stateless", h_pred=24),
+@pytest.mark.parametrize("kw", [dict(B=6), dict(B=6, dtype="fp32"), dict(B=40, pred_layers=2), dict(B=9, pred_kind="stateless", h_pred=24),
                                 dict(B=20, pred_kind="stateless", h_pred=24, vocab=1000)],
-                         ids=["one_layer", "two_layers", "stateless", "stateless_items"])
+                         ids=["one_layer", "one_layer_f32", "two_layers", "stateless", "stateless_items"])
 def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
     from test_gpu_chunks import check_chunks
     cfg = config("ll_chunks", durations=(0, 1, 5), **kw)
