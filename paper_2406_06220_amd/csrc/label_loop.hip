@@ -58,6 +58,7 @@
 //     it is put back while the hypothesis' next one is made, since all have read it in the pass that found the label.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -72,7 +73,10 @@ namespace tdt {
 namespace {
 
 constexpr unsigned kAbsent = 0xffffffffu;   // an exchanged float that is not there yet (a NaN no result is stored as)
-constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront and row of a tile in the partial sums (all uses)
+constexpr int kWidePart = 2 * (4 * CT + 8);       // WIDE: floats per wavefront and row of a tile in the partial sums, at least (all uses)
+constexpr int kWideTiles = 16;                    // ... column tiles of the predictor side with a place there, at most
+constexpr int wide_part(int tiles) { return tiles * CT + 4 > kWidePart ? tiles * CT + 4 : kWidePart; }
+constexpr int wide_tiles(int part) { return (part - 4) / CT; }
 static_assert(kNowhere >= 2ll * TDT_MAX_LSTM_LAYERS * kMaxGrid * kLabelMaxHyps * kLabelLongest * 4, "the largest exchange buffer");
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kPairRows = 8;                // up to this many rows two planes do (one LSTM layer)
@@ -253,7 +257,8 @@ struct LabelShared {
 // LAYERS: 0: stateless predictor; 1: one LSTM layer, a workgroup's column tiles fit one round and the
 // group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
 // NW: wavefronts.  Four, or (WIDE) eight for output layers of many thousands of columns, see wide_rows.
-// TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round.
+// TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round; eight wavefronts: steps
+// of the predictor's reduction.
 // QROWS: most rows of the hidden state that are multiplied at once (kPairRows: see few_products).
 template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW, int TQ, int QROWS>
 __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
@@ -268,7 +273,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr int TJ = LAYERS == 0 && !WIDE ? TQ : TR;        // ... per its first round
     constexpr int JH = TJ > 4 ? 2 : 1;                        // which is looked at four tiles, four columns a thread, at a time
     constexpr int QPR = THREADS / RT;                         // threads that share a row of a round, four columns each
-    static_assert(!WIDE || (LAYERS != 1 && TQ * CT <= QPR * 4), "eight wavefronts: a round is one pass of the threads");
+    static_assert(!WIDE || LAYERS != 1, "eight wavefronts: any LSTM or none");
+    constexpr int NQ = WIDE ? TQ : NK;                        // steps of the predictor's reduction
     constexpr int PLQ = TQ * CT + 4, PLJ = TJ * CT + 4;   // floats per row of the partial sums (padded: 16 rows, 64 banks)
     constexpr int KI = (NK * NW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
     constexpr bool STAGED = stages_rows(LAYERS, NW);          // rows go through LDS, see stage_rows
@@ -365,7 +371,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
-    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PLANES && hpc <= kPairRows ? NK * 64 : PL == 3 && DEEP && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
+    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PLANES && hpc <= kPairRows ? NK * 64 : PL == 3 && DEEP && !WIDE && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
     float *const part_j = part_q + (LSTM && !WIDE ? NW * RT * PLQ : 0);                                              // [NW][16][PLJ]
     for (int i = tid; i < p.lds_bytes / 16; i += THREADS)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
@@ -379,7 +385,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     const int u0 = share.u0, U = share.U, QT = (NT_A + NT_B + C - 1) / C;
     const int Upad = (DEEP ? (NT_B + C - 1) / C : QT) * 4;
     const int xp_rows = STAGED && TWO ? pred_area_rows(LAYERS, hpc) : 0;
-    float *const xs = part_j + NW * RT * (WIDE ? kWidePart : PLJ);             // staged rows: [NW][16 + xp_rows][LDX]
+    float *const xs = part_j + NW * RT * (WIDE ? p.wide_part : PLJ);             // staged rows: [NW][16 + xp_rows][LDX]
     static_assert(!WIDE || RT * LDX <= RT * kWidePart, "wide: a wavefront's rows lie over its share of the partial sums");
     float *const xe = WIDE ? part_q + wave * RT * LDX : xs + wave * (RT + xp_rows) * LDX, *const xp = xe + (TWO ? RT * LDX : 0);
     float4 *const rg_l = reinterpret_cast<float4 *>(xs + (STAGED ? NW * (RT + xp_rows) * LDX : 0));               // [L][hpc][Upad]
@@ -564,22 +570,6 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         constexpr int PLD = decltype(tiles)::value * CT + 4;
         constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED || N < 4 ? 2 : 1;   // chains per tile
         float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
-        if constexpr (WIDE) {   // (half the registers a lane: two tiles at a time; the other wavefront of the SIMD fills the gaps)
-#pragma unroll
-            for (int t = 0; t < N; t += 2) {
-                f32x4 c[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
-#pragma unroll
-                for (int s = 0; s < NK; ++s)
-#pragma unroll
-                    for (int pl = PACKED ? 0 : PL - 1; pl >= 0; --pl)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u) c[u] = F::mma(a[s][pl], b[t + u][s], c[u]);
-#pragma unroll
-                for (int u = 0; u < 2; ++u) *reinterpret_cast<f32x4 *>(pw + (t + u) * CT) = c[u];
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            return;
-        }
         f32x4 c[N][NC];
 #pragma unroll
         for (int t = 0; t < N; ++t)
@@ -603,7 +593,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     };
     auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n, auto tiles, int sn, float *part) __attribute__((always_inline)) {
         constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
-        constexpr int H2 = WIDE ? (TT + 2) / 4 * 2 : TT / 2;   // (wide: pairs)
+        constexpr int H2 = TT / 2;
         const std::integral_constant<int, H2> half{};
         const std::integral_constant<int, TT> all{};
         if (n <= H2) products_of(packed_tag, half, a, b, tiles, sn, part);
@@ -773,7 +763,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
         }
     };
-    const bool qpack = PL == 3 && (DEEP || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
+    const bool qpack = PL == 3 && ((DEEP && !WIDE) || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
     // One layer, up to eight rows: the wavefront that loads a row's stretch splits it where it is, four inputs a lane and
     // none for rows that are not there, and stages the planes.  Up to four rows they are the rows of one tile (plane
     // pl of row i is row pl * 4 + i), up to eight those of a tile and a half (rows 0 .. 7 the first terms, 8 .. 15 the
@@ -912,10 +902,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // Row tile tq of this label iteration's hidden state (row0: the group's first row in the exchange
     // buffer): loads, waits, splits.  For a row without an active hypothesis nothing is loaded where rows are
     // staged, elsewhere it repeats one that has (nobody looks at its results).
-    auto stage_h = [&](AFrag (&a)[NK][PL], int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
+    auto stage_h = [&](auto &a, int row0, int tq, unsigned long long in_tile) __attribute__((always_inline)) {
+        constexpr int NA = sizeof(a) / sizeof(a[0]);   // (steps: NQ)
         const int any = __ffsll((long long)in_tile) - 1;
         if (DEEP && qpack) {   // a wavefront takes a row
-            if constexpr (PL == 3 && DEEP) {
+            if constexpr (PL == 3 && DEEP && !WIDE) {
                 v4u v[KI];
                 const bool row = wave < kPackRows;   // uniform
                 const int off = (row0 + (row && ((in_tile >> wave) & 1ull) ? wave : any)) * Hp * (int)sizeof(float);
@@ -977,27 +968,27 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     }
                 return;
             }
-            v4u v[NK][NL];
-            int off[NK];
+            v4u v[NA][NL];
+            int off[NA];
             const int g = (in_tile >> (lane & 15)) & 1ull ? lane & 15 : any;
             const int row = (row0 + tq * RT + g) * Hp * (int)sizeof(float);
 #pragma unroll
-            for (int s = 0; s < NK; ++s) off[s] = row + part_of(s, hs0, Hp);
+            for (int s = 0; s < NA; ++s) off[s] = WIDE && s >= hsn ? kNowhere : row + part_of(s, hs0, Hp);
             until_there([&]() __attribute__((always_inline)) {
                 unsigned mx = 0;
 #pragma unroll
-                for (int s = 0; s < NK; ++s)
+                for (int s = 0; s < NA; ++s)
 #pragma unroll
                     for (int l = 0; l < NL; ++l) v[s][l] = ldx4(hrs, off[s] + l * 16, 0);
 #pragma unroll
-                for (int s = 0; s < NK; ++s)
+                for (int s = 0; s < NA; ++s)
 #pragma unroll
                     for (int l = 0; l < NL; ++l) mx = max(mx, umax4(v[s][l]));
                 return mx;
             });
             TR(11);
 #pragma unroll
-            for (int s = 0; s < NK; ++s) {
+            for (int s = 0; s < NA; ++s) {
                 float x[F::E];
 #pragma unroll
                 for (int e = 0; e < F::E; ++e) x[e] = __uint_as_float(v[s][e / 4][e % 4]);
@@ -1690,8 +1681,191 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 }
             }
             const int ntq = (G + RT - 1) / RT;
+            // ---- eight wavefronts: the column tiles that a row tile of a layer's h is multiplied by are two lists, what somebody waits
+            // for -- the next layer's input product with its cells, at the top W_pred -- and the recurrent product for the
+            // next label, which is formed while the first one's results travel.  What bounds a list is the stream of its
+            // weights (64 bytes a clock, at some 1.7 GHz: ten tiles of 640 inputs 1.9 us, the list takes 2.5) and, with all
+            // sixteen rows, nearly as many cycles of the matrix cores.  So the weights run through registers of two tiles from
+            // list to list, requested step by step where they have been multiplied, steps that a wavefront has not are left out,
+            // and a list has one look at its sums.  Rounds of six tiles, fetched, multiplied and looked at one after the other, took a
+            // label of two layers 30 us where it now takes 20: 8198 outputs, 640 units, B = 256, 27.7 / 25.4 ms; B = 110, 7.76
+            // / 6.84 ms; B = 32, 3.53 / 3.40 ms; B = 1, 418 / 415 us.  Registers of four tiles are no faster (B = 256 25.6 ms, two
+            // 25.5; B = 32 3.56, 3.41), nor is a compiled reduction of four steps where there are three (25.9).
+            if constexpr (WIDE && LSTM) {
+                constexpr int TS = 2;
+                const int room = wide_tiles(p.wide_part), PLW = room * CT + 4;
+                v4u b[TS][NQ];
+                auto request = [&](int u, int s, int n, int base) __attribute__((always_inline)) {   // tile u of the n that start at base, or nothing
+                    const int w = base + (u < n ? u : 0) * hbytes + (hs0 + (s < hsn ? s : 0)) * 1024;
+                    b[u][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, u < n && s < hsn ? lane * 16 : ~0xff, w, 0);
+                };
+                auto request_all = [&](int n, int base) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int u = 0; u < TS; ++u)
+#pragma unroll
+                        for (int s = 0; s < NQ; ++s) request(u, s, n, base);
+                };
+                // One list, and which tiles follow it, of a tile of `rows` rows.  pre(t, i, j): what use(t, i, j, sums, pre, out, off) takes beside
+                // the sums of row i's columns j * 4 .. + 3 of tile t (rows and tiles that are not there as well); publish(out, off)
+                // takes place in all lanes: behind a branch its stores would be waited for with the weights.
+                auto list = [&](const AFrag (&a)[NQ][PL], int rows, int n, int base, int n_next, int base_next, auto pre, auto use, auto publish) __attribute__((always_inline)) {
+                    if (n == 0) request_all(n_next, base_next);
+#pragma clang loop unroll(disable)
+                    for (int t1 = 0; t1 < n; t1 += room) {   // as many tiles as there is room for
+                        const int np = min(room, n - t1), n4 = np * 4;
+                        const int rn1 = t1 + room < n ? n - t1 - room : n_next, rat1 = t1 + room < n ? base + (t1 + room) * hbytes : base_next;
+                        fresh();
+                        TR(14);
+                        // a thread looks at four columns of a row, or two times four: idx / n4 and the rest
+                        const int rcp = uni((int)(1048576.0f * __builtin_amdgcn_rcpf((float)n4)) + 2);
+                        int row[2], quad[2];
+                        float4 extra[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const int idx = h * THREADS + tid;
+                            row[h] = (idx * rcp) >> 20;
+                            quad[h] = idx - row[h] * n4;
+                            extra[h] = pre(t1 + (quad[h] >> 2), row[h], quad[h] & 3);
+                        }
+                        float *const pw = part_q + (size_t)wave * RT * PLW + (lane & 15) * PLW + (lane >> 4) * 4;
+#pragma clang loop unroll(disable)
+                        for (int t0 = 0; t0 < np; t0 += TS) {
+                            const int rn = t0 + TS < np ? np - t0 - TS : rn1, rat = t0 + TS < np ? base + (t1 + t0 + TS) * hbytes : rat1;
+                            f32x4 c[TS];
+#pragma unroll
+                            for (int u = 0; u < TS; ++u) c[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                            for (int s = 0; s < NQ; ++s) {
+                                if (s < NK / 2 || s < hsn)   // uniform
+#pragma unroll
+                                    for (int pl = PL - 1; pl >= 0; --pl)
+#pragma unroll
+                                        for (int u = 0; u < TS; ++u) c[u] = F::mma(a[s][pl], b[u][s], c[u]);
+#pragma unroll
+                                for (int u = 0; u < TS; ++u) request(u, s, rn, rat);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            if (t0 == 0) __syncthreads();   // the partial sums before are not read any more
+#pragma unroll
+                            for (int u = 0; u < TS; ++u)
+                                if (t0 + u < np) *reinterpret_cast<f32x4 *>(pw + (t0 + u) * CT) = c[u];
+                        }
+                        TR(15);
+                        __syncthreads();
+                        TR(16);
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            v4u out = {0u, 0u, 0u, 0u};
+                            int off = kNowhere;
+                            if (h == 0 || rows * n4 > THREADS) {   // uniform
+                                const float *q = part_q + (size_t)min(row[h], RT - 1) * PLW + quad[h] * 4;
+                                f32x4 v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                                for (int w0 = 0; w0 < NW; w0 += NW / 2) {   // (registers: half of them at a time)
+                                    f32x4 x[NW / 2];
+#pragma unroll
+                                    for (int w = 0; w < NW / 2; ++w) x[w] = *reinterpret_cast<const f32x4 *>(q + (size_t)(w0 + w) * RT * PLW);
+#pragma unroll
+                                    for (int w = 0; w < NW / 2; ++w) v = w0 + w == 0 ? x[0] : v + x[w];
+                                    __builtin_amdgcn_sched_barrier(0);
+                                }
+                                use(t1 + (quad[h] >> 2), row[h], quad[h] & 3, make_float4(v.x, v.y, v.z, v.w), extra[h], out, off);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            publish(out, off);
+                        }
+                    }
+                };
+                auto first_of = [&](int l, int &n, int &base) __attribute__((always_inline)) {   // what layer l's h is multiplied by first
+                    const bool top = l == L - 1;
+                    n = top ? na : nr;
+                    base = here((top ? p.off_w_pred + qt0 * hbytes : p.off_w_ih[l + 1] + r0 * hbytes));
+                };
+                int n0, base0;
+                first_of(0, n0, base0);
+                request_all(n0, base0);
+#pragma clang loop unroll(disable)
+                for (int l = 0; l < L; ++l) {
+                    const bool top = l == L - 1;
+                    first_of(l, n0, base0);
+                    int n_up = 0, base_up = 0;
+                    if (!top) first_of(l + 1, n_up, base_up);
+                    const int base1 = here(p.off_w_hh[l] + r0 * hbytes);
+#pragma clang loop unroll(disable)
+                    for (int tq = 0; tq < ntq; ++tq) {
+                        const unsigned long long in_tile = act >> (tq * RT) & 0xffffull;
+                        if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
+                        const bool more = tq + 1 < ntq && act >> (tq * RT + RT) != 0ull;   // another row tile of this layer
+                        AFrag a[NQ][PL];
+                        stage_h(a, (par * L + l) * Bw + b0, tq, in_tile);
+                        lap(kTkBar);
+                        const int rows = min(RT, G - tq * RT);
+                        auto of_row = [&](int i, int &g) __attribute__((always_inline)) {   // row i is that of an active hypothesis, g
+                            g = tq * RT + min(i, RT - 1);
+                            return i < RT && g < G && ((act >> g) & 1ull);
+                        };
+                        if (!top) {
+                            const float *const bl = p.b_lstm[l + 1] + u0;
+                            list(a, rows, n0, base0, nr, base1,
+                                 [&](int t, int, int j) __attribute__((always_inline)) {
+                                     const int u = min(t * 4 + j, max(U - 1, 0));
+                                     return make_float4(bl[u], bl[Hp + u], bl[2 * Hp + u], bl[3 * Hp + u]);
+                                 },
+                                 [&](int t, int i, int j, float4 v, float4 bias, v4u &out, int &off) __attribute__((always_inline)) {
+                                     const int u = t * 4 + j;
+                                     int g;
+                                     const bool there = of_row(i, g) && u < U;
+                                     const int o = there ? ((l + 1) * hpc + g) * Upad + u : 0;
+                                     const float4 r4 = rg_l[o];
+                                     float cn, hn;
+                                     cell(make_float4(v.x + r4.x + bias.x, v.y + r4.y + bias.y, v.z + r4.z + bias.z, v.w + r4.w + bias.w),
+                                          c_l[o], cn, hn);
+                                     if (CHUNKED && first && there && ((carried >> g) & 1ull)) {
+                                         const size_t at = ((size_t)(l + 1) * B + S.gid[g]) * Hp + u0 + u;
+                                         hn = p.st_h[at];
+                                         cn = p.st_c[at];
+                                     }
+                                     if (there) {
+                                         c_l[o] = cn;
+                                         if (CHUNKED) h_l[o] = hn;
+                                     }
+                                     out.x = __float_as_uint(present(hn));
+                                     off = there ? (((par * L + l + 1) * Bw + b0 + g) * Hp + u0 + u) * (int)sizeof(float) : kNowhere;
+                                 },
+                                 [&](const v4u &out, int off) __attribute__((always_inline)) {
+                                     __builtin_amdgcn_raw_buffer_store_b32(out.x, hrs, off, 0, 16 /* sc1 */);
+                                 });
+                        } else {
+                            list(a, rows, n0, base0, nr, base1,
+                                 [&](int t, int, int j) __attribute__((always_inline)) {
+                                     return *reinterpret_cast<const float4 *>(p.b_pred + min((qt0 + t) * CT + j * 4, H - 4));
+                                 },
+                                 [&](int t, int i, int j, float4 v, float4 bias, v4u &out, int &off) __attribute__((always_inline)) {
+                                     const int col = (qt0 + t) * CT + j * 4;
+                                     int g;
+                                     const bool there = of_row(i, g) && t < na && col < H;
+                                     out = v4u{__float_as_uint(present(v.x + bias.x)), __float_as_uint(present(v.y + bias.y)),
+                                               __float_as_uint(present(v.z + bias.z)), __float_as_uint(present(v.w + bias.w))};
+                                     off = there ? (p_row(g, 0) * H + col) * (int)sizeof(float) : kNowhere;
+                                 },
+                                 [&](const v4u &out, int off) __attribute__((always_inline)) {
+                                     __builtin_amdgcn_raw_buffer_store_b128(out, prs, off, 0, 16 /* sc1 */);
+                                 });
+                        }
+                        list(a, rows, nr, base1, more ? n0 : n_up, more ? base0 : base_up,
+                             [](int, int, int) __attribute__((always_inline)) { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); },
+                             [&](int t, int i, int j, float4 v, float4, v4u &, int &) __attribute__((always_inline)) {
+                                 const int u = t * 4 + j;
+                                 int g;
+                                 if (of_row(i, g) && u < U) rg_l[(l * hpc + g) * Upad + u] = v;
+                             },
+                             [](const v4u &, int) __attribute__((always_inline)) {});
+                        lap(kTkQ);   // (behind every wait what followed it: the next one starts here)
+                    }
+                }
+            }
             // ---- deeper layers: W_ih . [h of the layer below] + what W_hh . h left here
-            if constexpr (DEEP)
+            if constexpr (DEEP && !WIDE)
 #pragma clang loop unroll(disable)
             for (int l = 0; l < L; ++l) {
                 const int row0 = (par * L + l) * Bw + b0;
@@ -1715,7 +1889,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const unsigned long long in_tile = act >> (tq * RT) & 0xffffull;
                     if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
                     if (!loaded) fetch_round(0, 0);   // while the rows are on their way
-                    loaded = !WIDE && top && n_all <= TQ;
+                    loaded = top && n_all <= TQ;
                     AFrag a[NK][PL];
                     any_value(a);
                     stage_h(a, row0, tq, in_tile);
@@ -2426,9 +2600,10 @@ template <typename WT, int NK> const void *label_fn(int layers, int tq, bool chu
         if (tq > TR) return label_form_of<WT, 0, NK, 4, first_tiles(true, NK)>(chunked);
     return label_form_of<WT, 0, NK, 4, TR>(chunked);
 }
-const void *label_wide_fn(bool lstm, bool chunked)   // (bfloat16)
+const void *label_wide_fn(bool lstm, int pred_steps, bool chunked)   // (bfloat16)
 {
-    return lstm ? label_form_of<uint16_t, 2, 4, 8, 6>(chunked) : label_form_of<uint16_t, 0, 4, 8, 6>(chunked);
+    if (!lstm) return label_form_of<uint16_t, 0, 4, 8, 4>(chunked);
+    return pred_steps <= 3 ? label_form_of<uint16_t, 2, 4, 8, 3>(chunked) : label_form_of<uint16_t, 2, 4, 8, 4>(chunked);
 }
 struct LabelForm {
     const void *fn;   // null: none
@@ -2447,7 +2622,7 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     const int kseg = label_kseg(w);
     if (wide) {
         f.nk = 4;
-        if (w->dtype == 1 && label_steps(true, kseg, f.nw) <= f.nk) f.fn = label_wide_fn(lstm, chunked);
+        if (w->dtype == 1 && label_steps(true, kseg, f.nw) <= f.nk) f.fn = label_wide_fn(lstm, label_steps(true, w->h_pred, f.nw), chunked);
         return f;
     }
     f.nk = label_nk(w->dtype == 1, kseg);
@@ -2471,14 +2646,15 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
 
 }  // namespace
 
-static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C)
+// wide (f.nw == 8): with room for as many column tiles of partial sums as wide_part floats hold
+static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C, int wide_part = kWidePart)
 {
     size_t n = 0;
     if (w->dtype == 1 && f.layers == 1 && hyps_per_cluster <= kPairRows) n = (size_t)f.nk * 64;
-    else if (w->dtype == 1 && f.layers > 1 && hyps_per_cluster <= kPackRows)
+    else if (w->dtype == 1 && f.layers > 1 && f.nw < 8 && hyps_per_cluster <= kPackRows)
         n = (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t);
     if (f.nw == 8) {
-        n += (size_t)f.nw * RT * kWidePart * sizeof(float);
+        n += (size_t)f.nw * RT * wide_part * sizeof(float);
     } else {
         if (w->pred_kind == TDT_PRED_LSTM) n += (size_t)f.nw * RT * (f.tq * CT + 4) * sizeof(float);
         n += (size_t)f.nw * RT * ((f.layers == 0 ? f.tq : label_tiles(f.nk)) * CT + 4) * sizeof(float);
@@ -2542,7 +2718,15 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     }
     DecodeParams pc = p;
     pc.kseg_max = label_kseg(w);
-    pc.lds_bytes = (int)label_lds_bytes(w, f, chunked, p.hyps_per_cluster, C);
+    // (wide: the most column tiles a workgroup has of one matrix, or as many as LDS has room for)
+    int tiles = 0;
+    if (f.nw == 8 && f.layers > 0) {
+        tiles = std::max(((w->h_joint + CT - 1) / CT + C - 1) / C, ((w->h_pred + 3) / 4 + C - 1) / C);
+        tiles = std::min(tiles, kWideTiles);
+        while (tiles > 0 && label_lds_bytes(w, f, chunked, p.hyps_per_cluster, C, wide_part(tiles)) > kLabelDynLds) --tiles;
+    }
+    pc.wide_part = wide_part(tiles);
+    pc.lds_bytes = (int)label_lds_bytes(w, f, chunked, p.hyps_per_cluster, C, pc.wide_part);
     void *args[] = {&pc};
     // A group of one workgroup waits for nobody, so its workgroups need not all be resident.  A cooperative launch, which
     // sees to that, goes through another queue: 11 us from the kernel before to this one and 11 to the next (the

@@ -47,6 +47,7 @@ struct DecodeParams {
     int joint_tiles;       // column tiles per joint work item the automatic window aims at (0 = automatic: 4 to 12)
     int kseg_max;          // longest K segment staged at once (set by launch_decode)
     int lds_bytes;         // dynamic LDS of the launch, a multiple of 16 (set by launch_decode)
+    int wide_part;         // label_loop.hip, eight wavefronts: floats per wavefront and row of the partial sums
     int n_clusters, hyps_per_cluster;
     int frame_loop;        // non-zero: batched frame-looping (Algorithm 2) instead of label-looping
     int selftest_stall;    // non-zero: rank 0 of cluster 0 withholds its first barrier arrival

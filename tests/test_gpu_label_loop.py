@@ -119,6 +119,12 @@ CASES = [
        dict(n_clusters=4, window=w, joint_kernel=2))
       for k, n, hp, v, h, w in (("lstm", 1, 40, 120, 1000, 1), ("lstm", 2, 104, 700, 72, 2), ("stateless", 2, 48, 3000, 616, 1),
                                 ("lstm", 1, 40, 2000, 1024, 1), ("stateless", 1, 24, 4090, 104, 3))],
+    # ... the predictor's column tiles as lists: as many as there is room for and more, some workgroups without any, one layer to
+    # four, reductions of three steps a wavefront and of four, one row tile and several
+    *[(config(f"ll_wide_lists_{hp}_{n}_{B}_{c}", h_pred=hp, pred_layers=n, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2)),
+       dict(n_clusters=c, joint_kernel=2))
+      for hp, n, B, c in ((640, 2, 64, 16), (768, 1, 40, 32), (776, 2, 40, 32), (1024, 3, 24, 16), (1000, 1, 70, 4), (40, 4, 150, 4),
+                          (648, 2, 100, 32), (16, 1, 3, 4))],
     (config("ll_wide_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, vocab=700, B=40), dict(n_clusters=4, joint_kernel=2)),
     # deeper LSTMs on several row tiles
     (config("ll_deep", pred_layers=3, B=40), dict(n_clusters=2)),
