@@ -19,7 +19,8 @@
 //     "Reuse of the exchange buffers" below.
 //   * A workgroup owns its column tiles of the predictor-side matrices for the whole call.  The four
 //     gates of a unit meet in the workgroup that updates the unit's cell, so the recurrent
-//     pre-activations and the cell state never leave its LDS; only h is exchanged.
+//     pre-activations and the cell state never leave its LDS; only h is exchanged (bfloat16, one layer: as the three terms its
+//     readers multiply, split once by whoever updates the cell).
 //   * A group's hypotheses wait for each other's searches only until enough of them do: half, without a predictor a third, with
 //     deeper LSTMs two thirds or four fifths (see "patience").
 //   * The control state of a hypothesis (frame, label count, last labels, score ...) lives in lane g
@@ -80,6 +81,7 @@ constexpr int wide_tiles(int part) { return (part - 4) / CT; }
 static_assert(kNowhere >= 2ll * TDT_MAX_LSTM_LAYERS * kMaxGrid * kLabelMaxHyps * kLabelLongest * 4, "the largest exchange buffer");
 constexpr int kPackRows = 4;                // up to this many rows the three planes of a tile share its 16 rows
 constexpr int kPairRows = 8;                // up to this many rows two planes do (one LSTM layer)
+static_assert(plane_rows(kPackRows) == kPackRows && plane_rows(kPairRows) == kPairRows, "planes");
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // Rows of the projected predictor output are read from the exchange buffers in every pass (where there are two
     // areas they stay staged), so a row stays there until its hypothesis' next one: see "own".
     constexpr bool OWN = LSTM && !(LAYERS == 1 && TWO);
-    constexpr bool PLANES = PL == 3 && LAYERS == 1;   // few rows of the hidden state: staged as planes, see stage_planes
+    constexpr bool PLANES = PL == 3 && LAYERS == 1;   // the hidden state travels as its terms, see plane_base
     constexpr bool FEW = QROWS < RT;                  // ... float32: see few_products
     static_assert(!FEW || (PL == 1 && LAYERS == 1 && QROWS == kPairRows), "few_products");
     extern __shared__ __align__(16) unsigned char dyn_lds[];
@@ -364,14 +366,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     }
     const int Hp = p.h_pred, L = DEEP ? p.pred_layers : 1;
 
-    // ---- LDS: in deeper LSTMs of few hypotheses the tile of packed rows, with planes the zeros that stand for the rows
-    // of their second tile (bfloat16); the partial sums of a round -- of the predictor side and of a joint
+    // ---- LDS: in deeper LSTMs of few hypotheses the tile of packed rows (bfloat16); the partial sums of a round -- of the predictor side and of a joint
     // pass, which may start while the former are still read; every wavefront's staged rows (STAGED; eight
     // wavefronts: over the partial sums); and what this workgroup keeps of its own units: recurrent
     // pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
-    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PLANES && hpc <= kPairRows ? NK * 64 : PL == 3 && DEEP && !WIDE && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
+    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 && DEEP && !WIDE && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
     float *const part_j = part_q + (LSTM && !WIDE ? NW * RT * PLQ : 0);                                              // [NW][16][PLJ]
     for (int i = tid; i < p.lds_bytes / 16; i += THREADS)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
@@ -764,59 +765,32 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         }
     };
     const bool qpack = PL == 3 && ((DEEP && !WIDE) || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
-    // One layer, up to eight rows: the wavefront that loads a row's stretch splits it where it is, four inputs a lane and
-    // none for rows that are not there, and stages the planes.  Up to four rows they are the rows of one tile (plane
-    // pl of row i is row pl * 4 + i), up to eight those of a tile and a half (rows 0 .. 7 the first terms, 8 .. 15 the
-    // first remainders; a second tile's rows 0 .. 7 the second ones, its others zeros): one or two products a step
-    // instead of three.  One label's phase Q up to its partial sums, microseconds: 7 rows 1.45 -> 1.20, 1 row 1.35 -> 0.87; a
-    // call with two rounds, 648 units and joint width, B = 12, 2185 -> 2110.
-    constexpr int LDP = NK * 32 + 8;   // elements of a plane's row (padded: 16 rows start in 16 different banks)
-    auto stage_planes = [&](const v4u (&v)[2 * C32]) __attribute__((always_inline)) {
-        uint16_t *const at = reinterpret_cast<uint16_t *>(xe) + (lane >> 3) * LDP + (lane & 7) * 4;
-        const int plane = (qpack ? kPackRows : kPairRows) * LDP;
-        lds_order();
-        if (lane < (qpack ? kPackRows * 8 : 64))
-#pragma unroll
-            for (int i = 0; i < C32; ++i) {
-                float x[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(v[i][e]);
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    const unsigned lo = top_halves(x[0], x[1]), hi = top_halves(x[2], x[3]);
-                    *reinterpret_cast<uint2 *>(at + pl * plane + i * 32) = make_uint2(lo, hi);
-                    if (pl < 2) {
-                        x[0] = less_term(lo, minus.low, x[0]);
-                        x[1] = less_term(lo, minus.high, x[1]);
-                        x[2] = less_term(hi, minus.low, x[2]);
-                        x[3] = less_term(hi, minus.high, x[3]);
-                    }
-                }
-            }
-        lds_order();
-    };
-    auto plane_products = [&](auto pair_tag, auto count, const auto &b, auto tiles, float *part) __attribute__((always_inline)) {
+    // bfloat16, one layer: the hidden state travels as the three terms of its values, in the order in which the matrix cores
+    // take them.  Whoever updates a cell splits it, once, and a reader of the exchange buffers has its operands in
+    // registers as soon as they are there: no rows to change lanes, no split.  Plane row `pl * RP + g` is term pl of hypothesis g,
+    // RP the rows of a plane: with up to four hypotheses four, and all terms are rows of one tile of sixteen; up to eight eight, a tile
+    // and a half; else sixteen.  A step of 32 inputs is 64 bytes a plane row: a lane's eight inputs of plane row r are the 16 bytes
+    // at (lane / 16 * 3 RP + r) * 16.  Absent is a pair of terms that are all ones, which no two terms are: a NaN is stored as the one of
+    // which they are not.  Before, every reader had rows of float32 change lanes through LDS and split them, and ten
+    // workgroups of 51 had all of W_pred (see pred_share).  Both with the encoder's rows staged early (planes_of), and the table
+    // rows requested early (request_gates), us a call: config 2 at B = 1 528 / 503, B = 32 847 / 814, B = 128 2017 / 1942,
+    // 32 chunked streams 1811 / 1732, TDT B = 7 289 / 274, B = 32 454 / 441.
+    const int RP = plane_rows(hpc), plane_step = 3 * RP * 64, plane_buffer = plane_bytes(Hp, hpc);
+    auto plane_base = [&](int buffer) { return (buffer * ncl + cl) * plane_buffer; };
+    // Products of the first `count` tiles that `b` holds with the plane rows `v` (NT tiles of them), smallest terms first
+    auto plane_products = [&](auto count, const auto &v, const auto &b, auto tiles, float *part) __attribute__((always_inline)) {
         constexpr int PLD = decltype(tiles)::value * CT + 4, N = decltype(count)::value;
+        constexpr int NT = sizeof(v) / sizeof(v[0]);
         float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
-        const uint16_t *const rows = reinterpret_cast<const uint16_t *>(xe) + (lane & 15) * LDP + (lane >> 4) * 8;
-        constexpr int NA = decltype(pair_tag)::value ? 2 * NK : NK;
-        AFrag a[NA];   // (all on their way before the first product)
-        if constexpr (decltype(pair_tag)::value) {   // (the second remainders first)
-            const uint16_t *const more = (lane & 15) < kPairRows ? rows + 2 * kPairRows * LDP
-                                                                 : reinterpret_cast<const uint16_t *>(dyn_lds) + (lane >> 4) * 8;
-#pragma unroll
-            for (int s = 0; s < NK; ++s) a[s] = *reinterpret_cast<const AFrag *>(more + s * 32);
-        }
-#pragma unroll
-        for (int s = 0; s < NK; ++s) a[NA - NK + s] = *reinterpret_cast<const AFrag *>(rows + s * 32);
-        __builtin_amdgcn_sched_barrier(0);
         f32x4 c[N];
 #pragma unroll
         for (int t = 0; t < N; ++t) c[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int i = 0; i < NA; ++i)
+        for (int i = NT - 1; i >= 0; --i)
 #pragma unroll
-            for (int t = 0; t < N; ++t) c[t] = F::mma(a[i], b[t][i % NK], c[t]);
+            for (int s = 0; s < NK; ++s)
+#pragma unroll
+                for (int t = 0; t < N; ++t) c[t] = F::mma(*reinterpret_cast<const AFrag *>(&v[i][s]), b[t][s], c[t]);
 #pragma unroll
         for (int t = 0; t < N; ++t) *reinterpret_cast<f32x4 *>(pw + t * CT) = c[t];
     };
@@ -886,7 +860,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 
     // what lane l reads of a whole row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
     auto hoff = [&](int kk) { return min(lane * 4 + kk * 256, Hp - 4) * (int)sizeof(float); };
-    const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, (size_t)2 * L * Bw * Hp * sizeof(float));
+    const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, PLANES ? (size_t)2 * ncl * plane_buffer : (size_t)2 * L * Bw * Hp * sizeof(float));
     const __amdgpu_buffer_rsrc_t prs = buffer_of(px, (size_t)2 * Bw * H * sizeof(float));
     const __amdgpu_buffer_rsrc_t brs = buffer_of(p.b_out, (size_t)O * sizeof(float));
     auto h_source = [&](int s, float (&x)[F::E]) __attribute__((always_inline)) {
@@ -953,13 +927,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     return mx;
                 });
                 TR(11);
-                if constexpr (PLANES) {
-                    if (qpack || qpair) stage_planes(v);
-                    else stage_rows(xe, v, upper);
-                } else {
-                    stage_rows(xe, v, upper);
-                }
-                if constexpr (PL == 1 && !FEW)
+                stage_rows(xe, v, upper);
+                if constexpr (!FEW)
 #pragma unroll
                     for (int s = 0; s < NK; ++s) {
                         float x[F::E];
@@ -1145,7 +1114,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // nothing to write, so that the stores need no branch.
     constexpr int QH = TQ > 4 ? 2 : 1;   // halves of a round: four tiles, four columns a thread
     auto q_hyp = [&]() { return qpack ? wave : qpair ? wave * 2 + ((lane >> 4) & 1) : tid >> 4; };
-    int q_off[2] = {kNowhere, kNowhere}, q_unit[2] = {-1, -1}, h_off[2] = {kNowhere, kNowhere}, c_g[2], c_u[2];
+    int q_off[2] = {kNowhere, kNowhere}, q_unit[2] = {-1, -1}, h_off[2] = {kNowhere, kNowhere}, h_off2[2] = {kNowhere, kNowhere}, c_g[2], c_u[2];
     float4 q_bias[2];
     // ... and the place in the exchange buffers (its scalar part; OWN: in the lane's offset), of the newest row and the one before
     auto q_base = [&](int other) { return OWN ? 0 : ((par ^ other) * Bw + b0) * H * (int)sizeof(float); };
@@ -1169,7 +1138,15 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             const int idx = tid + h * THREADS;
             c_g[h] = U > 0 ? min(idx / max(U, 1), kLabelMaxHyps - 1) : kLabelMaxHyps - 1;
             c_u[h] = U > 0 ? idx - idx / max(U, 1) * U : 0;
-            if (U > 0 && idx < G * U) h_off[h] = (c_g[h] * Hp + u0 + c_u[h]) * (int)sizeof(float);
+            if (U > 0 && idx < G * U) {
+                if constexpr (PLANES) {   // (of two neighbours the one stores the pairs of first and of last terms, the other those between)
+                    const int k = u0 + c_u[h], odd = k & 1;
+                    h_off[h] = (k >> 5) * plane_step + ((k >> 3 & 3) * 3 * RP + odd * RP + c_g[h]) * 16 + (k & 6) * 2;
+                    if (!odd) h_off2[h] = h_off[h] + 2 * RP * 16;
+                } else {
+                    h_off[h] = (c_g[h] * Hp + u0 + c_u[h]) * (int)sizeof(float);
+                }
+            }
         }
     }
     // ---- WIDE: R row tiles from tile tb on against this workgroup's columns.  What bounds a pass over
@@ -1483,6 +1460,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     v4u b2[TR][NK];   // ... and those of later rounds
     v4u bias0[JH], bias1[1];
     int in_b = -1, in_b2 = -1;
+    // LAYERS == 1: the table rows of this thread's cells, by the last labels of their hypotheses.  They are requested as soon as a
+    // pass is known to be the label's last, ahead of what else is left to do of it.
+    v4u t4[2];
+    any_value(t4);
+    auto request_gates = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (h == 0 || G * U > THREADS) {   // uniform
+                const int lab = __builtin_amdgcn_ds_bpermute(c_g[h] * 4, last);
+                t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + c_u[h]) * 4);
+            }
+    };
+    if constexpr (LAYERS == 1) request_gates();
 #pragma clang loop unroll(disable)
     while (ok) {   // ---- Alg. 3 line 5: while any hypothesis is active
         const unsigned long long alive = __ballot(active);
@@ -1524,17 +1514,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         v4u bq2_now[TR][NK];
         auto &bq2 = KEEPQ2 ? bq2_kept : bq2_now;
         if constexpr (LAYERS == 1) {
-            // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, W_hh * h was formed by this
-            // workgroup when h was new.
+            // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, requested behind the decision
+            // (request_gates); W_hh * h was formed by this workgroup when h was new.
             const bool two_cells = G * U > THREADS;   // uniform
-            v4u t4[2];
-            any_value(t4);
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                if (h == 0 || two_cells) {
-                    const int lab = __builtin_amdgcn_ds_bpermute(c_g[h] * 4, last);
-                    t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + c_u[h]) * 4);
-                }
             __builtin_amdgcn_sched_barrier(0);
             if (TWO_ROUNDS && !KEEPQ2) fetch_second(bq2);   // (they take about as long to leave as the row to arrive)
             __builtin_amdgcn_sched_barrier(0);
@@ -1543,21 +1525,39 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             asm volatile("" ::"v"(t4[0]), "v"(t4[1]));
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                if ((h == 0 || two_cells) && h_off[h] != kNowhere && ((act >> c_g[h]) & 1ull)) {
-                    const int o = c_g[h] * Upad + c_u[h];
-                    float cn, hn;
-                    if (CHUNKED && first && ((carried >> c_g[h]) & 1ull)) {
-                        const size_t src = (size_t)S.gid[c_g[h]] * Hp + u0 + c_u[h];
-                        hn = p.st_h[src];
-                        cn = p.st_c[src];
-                    } else {
-                        const float4 r4 = rg_l[o], x = as_float4(t4[h]);
-                        cell(make_float4(r4.x + x.x, r4.y + x.y, r4.z + x.z, r4.w + x.w), c_l[o], cn, hn);
+                if (h == 0 || two_cells) {
+                    const bool there = h_off[h] != kNowhere && ((act >> c_g[h]) & 1ull);
+                    float hn = 0.0f;
+                    if (there) {
+                        const int o = c_g[h] * Upad + c_u[h];
+                        float cn;
+                        if (CHUNKED && first && ((carried >> c_g[h]) & 1ull)) {
+                            const size_t src = (size_t)S.gid[c_g[h]] * Hp + u0 + c_u[h];
+                            hn = p.st_h[src];
+                            cn = p.st_c[src];
+                        } else {
+                            const float4 r4 = rg_l[o], x = as_float4(t4[h]);
+                            cell(make_float4(r4.x + x.x, r4.y + x.y, r4.z + x.z, r4.w + x.w), c_l[o], cn, hn);
+                        }
+                        c_l[o] = cn;
+                        if (CHUNKED) h_l[o] = hn;
                     }
-                    c_l[o] = cn;
-                    if (CHUNKED) h_l[o] = hn;
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(present(hn)), hrs, h_off[h],
-                                                          (par * Bw + b0) * Hp * (int)sizeof(float), 16 /* sc1 */);
+                    if constexpr (PLANES) {
+                        // (in all lanes: neighbours exchange terms.  A NaN becomes the one whose terms are not all ones.)
+                        hn = hn == hn ? hn : __uint_as_float(0x7fc00000u);
+                        const float r = hn - __uint_as_float(__float_as_uint(hn) & 0xffff0000u);
+                        const float r2 = r - __uint_as_float(__float_as_uint(r) & 0xffff0000u);
+                        auto neighbour = [](float x) { return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0xb1, 0xf, 0xf, false)); };   // quad_perm 1 0 3 2
+                        const bool odd = tid & 1;
+                        const float from = neighbour(odd ? hn : r), from2 = neighbour(r2);
+                        const unsigned w0 = top_halves(odd ? from : hn, odd ? r : from), w1 = top_halves(r2, from2);
+                        const int at = plane_base(par);
+                        __builtin_amdgcn_raw_buffer_store_b32(w0, hrs, there ? h_off[h] : kNowhere, at, 16 /* sc1 */);
+                        __builtin_amdgcn_raw_buffer_store_b32(w1, hrs, there ? h_off2[h] : kNowhere, at, 16 /* sc1 */);
+                    } else {
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(present(hn)), hrs, there ? h_off[h] : kNowhere,
+                                                              (par * Bw + b0) * Hp * (int)sizeof(float), 16 /* sc1 */);
+                    }
                 }
         }
         if constexpr (DEEP) {
@@ -1600,9 +1600,13 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             if constexpr (LAYERS == 1) {
                 const v4u absent = {kAbsent, kAbsent, kAbsent, kAbsent};
                 const int pb = (par ^ 1) * Bw + b0;
-                __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[0], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
-                if (G * U > THREADS)
-                    __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[1], pb * Hp * (int)sizeof(float), 16 /* sc1 */);
+                const int h_at = PLANES ? plane_base(par ^ 1) : pb * Hp * (int)sizeof(float);
+                __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[0], h_at, 16 /* sc1 */);
+                if (PLANES) __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off2[0], h_at, 16 /* sc1 */);
+                if (G * U > THREADS) {
+                    __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off[1], h_at, 16 /* sc1 */);
+                    if (PLANES) __builtin_amdgcn_raw_buffer_store_b32(kAbsent, hrs, h_off2[1], h_at, 16 /* sc1 */);
+                }
                 __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_at(0, act, 1), q_base(1), 16 /* sc1 */);
                 if (QH > 1 && nq > 4) __builtin_amdgcn_raw_buffer_store_b128(absent, prs, q_at(1, act, 1), q_base(1), 16 /* sc1 */);
             } else {
@@ -1621,63 +1625,102 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             lap(kTkP);
             if constexpr (LAYERS == 1) {
                 // ---- Q
-                if (nq > 0) {
+                // What a thread takes of the sums of half h, four columns of a row.
+                // Planes: a wavefront takes a row, or two, its lanes one tile row each, and the planes are added up.
+                auto look = [&](int h) __attribute__((always_inline)) {
+                    const int quad = lane & 15, row = qpack   ? wave + (lane >> 4) * kPackRows
+                                                      : qpair ? wave * 2 + ((lane >> 4) & 1) + (lane >> 5) * kPairRows
+                                                              : tid >> 4;
+                    float4 v = gather(q_tiles, part_q, row, h * 16 + quad);
+                    if (qpack) {   // (rows 12 .. 15 of a packed tile are nobody's)
+                        v.x = sum_over_rows(lane < 48 ? v.x : 0.0f);
+                        v.y = sum_over_rows(lane < 48 ? v.y : 0.0f);
+                        v.z = sum_over_rows(lane < 48 ? v.z : 0.0f);
+                        v.w = sum_over_rows(lane < 48 ? v.w : 0.0f);
+                    } else if (qpair) {
+                        v.x = sum_over_halves(v.x);
+                        v.y = sum_over_halves(v.y);
+                        v.z = sum_over_halves(v.z);
+                        v.w = sum_over_halves(v.w);
+                    }
+                    const v4u o = {__float_as_uint(present(v.x + q_bias[h].x)), __float_as_uint(present(v.y + q_bias[h].y)),
+                                   __float_as_uint(present(v.z + q_bias[h].z)), __float_as_uint(present(v.w + q_bias[h].w))};
+                    __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_at(h, act, 0), q_base(0), 16 /* sc1 */);
+                    if (q_unit[h] >= 0 && ((unsigned)act >> q_hyp() & 1u)) rg_l[q_unit[h]] = v;   // the four gates of one unit
+                };
+                if constexpr (PLANES) {
+                    // The encoder's rows are staged behind the first look for the hidden state, ahead of which they were requested: a wait
+                    // for it is a wait for them, and behind phase Q staging them was 1.5 % of a call.
+                    bool rows_wait = needm != 0ull && rank < items;
+                    // (A copy of everything up to the published results for each number of tiles: with one behind them that all three lead to,
+                    // which needs no more than their tags, calls were 3.5 % slower.)
+                    auto planes_of = [&](auto nt) __attribute__((always_inline)) {
+                        constexpr int NT = decltype(nt)::value;
+                        v4u v[NT][NK];
+                        int off[NT][NK];
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            const int r = t * RT + (lane & 15), g = r & (RP - 1);
+                            const bool row = r < 3 * RP && ((unsigned)act >> g & 1u);
+#pragma unroll
+                            for (int s = 0; s < NK; ++s)   // (zeros where there is nothing)
+                                off[t][s] = row && s < hsn && (hs0 + s) * 32 + (lane >> 4) * 8 < Hp ? ((lane >> 4) * 3 * RP + r) * 16 : kNowhere;
+                        }
+                        const int at = plane_base(par) + hs0 * plane_step;
+                        until_there([&]() __attribute__((always_inline)) {
+                            unsigned mx = 0;
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                                for (int s = 0; s < NK; ++s) v[t][s] = ldx4(hrs, off[t][s], at + s * plane_step);
+                            if (rows_wait) {   // uniform
+                                stage_rows(xe, ev, true);
+                                rows_wait = false;
+                            }
+#pragma unroll
+                            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                                for (int s = 0; s < NK; ++s) mx = max(mx, umax4(v[t][s]));
+                            return mx;
+                        });
+                        TR(11);
+                        lap(kTkBar);
+                        plane_products(r_tiles, v, bq, q_tiles, part_q);
+                        if (TWO_ROUNDS && nq > TR) plane_products(r_tiles, v, bq2, q_tiles, part_q + TR * CT);   // uniform
+                        TR(14);
+                        __syncthreads();
+                        look(0);
+                        if (QH > 1 && nq > 4) look(1);
+                        TR(16);
+                    };
+                    if (nq > 0) {
+                        if (qpack) planes_of(std::integral_constant<int, 1>{});
+                        else if (qpair) planes_of(std::integral_constant<int, 2>{});
+                        else planes_of(std::integral_constant<int, 3>{});
+                    } else if (rows_wait) {
+                        stage_rows(xe, ev, true);
+                    }
+                } else if (nq > 0) {
                     AFrag a[NK][PL];
                     stage_h(a, par * Bw + b0, 0, act);
                     lap(kTkBar);
                     fresh();
                     TR(14);
-                    const std::integral_constant<int, (TR + 1) / 2> half{};
                     if constexpr (FEW) {
                         few_products(bq, bq2, q_tiles, part_q);
-                    } else if (PLANES && qpack) {
-                        if (TWO_ROUNDS || nq > TR / 2) plane_products(full_rows, r_tiles, bq, q_tiles, part_q);
-                        else plane_products(full_rows, half, bq, q_tiles, part_q);
-                        if (TWO_ROUNDS && nq > TR) plane_products(full_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
-                    } else if (PLANES && qpair) {
-                        plane_products(packed_rows, r_tiles, bq, q_tiles, part_q);
-                        if (TWO_ROUNDS && nq > TR) plane_products(packed_rows, r_tiles, bq2, q_tiles, part_q + TR * CT);
-                    } else if constexpr (PL == 3) {
-                        if (TQ > TR || nq > TR / 2) split_and_multiply(r_tiles, h_source, a, bq, q_tiles, part_q);
-                        else split_and_multiply(half, h_source, a, bq, q_tiles, part_q);
-                        if (TQ > TR && nq > TR) products_of(full_rows, r_tiles, a, bq2, q_tiles, hsn, part_q + TR * CT);
+                    } else if constexpr (TQ == TR) {
+                        products(full_rows, a, bq, nq, q_tiles, hsn, part_q);
                     } else {
-                        if constexpr (TQ == TR) {
-                            products(full_rows, a, bq, nq, q_tiles, hsn, part_q);
-                        } else {
-                            products_of(full_rows, r_tiles, a, bq, q_tiles, hsn, part_q);
-                            if (nq > TR) products_of(full_rows, r_tiles, a, bq2, q_tiles, hsn, part_q + TR * CT);
-                        }
+                        products_of(full_rows, r_tiles, a, bq, q_tiles, hsn, part_q);
+                        if (nq > TR) products_of(full_rows, r_tiles, a, bq2, q_tiles, hsn, part_q + TR * CT);
                     }
                     TR(15);
                     __syncthreads();
                     TR(16);
                     fresh();
-                    // a thread takes four columns of a row; staged as planes: a wavefront takes a row, or two, its
-                    // lanes one tile row each, and the planes are added up
-                    const int quad = lane & 15, row = qpack   ? wave + (lane >> 4) * kPackRows
-                                                      : qpair ? wave * 2 + ((lane >> 4) & 1) + (lane >> 5) * kPairRows
-                                                              : tid >> 4;
 #pragma unroll
                     for (int h = 0; h < QH; ++h)
-                        if (h == 0 || nq > 4) {   // uniform
-                            float4 v = gather(q_tiles, part_q, row, h * 16 + quad);
-                            if (qpack) {   // (rows 12 .. 15 of a packed tile are nobody's)
-                                v.x = sum_over_rows(lane < 48 ? v.x : 0.0f);
-                                v.y = sum_over_rows(lane < 48 ? v.y : 0.0f);
-                                v.z = sum_over_rows(lane < 48 ? v.z : 0.0f);
-                                v.w = sum_over_rows(lane < 48 ? v.w : 0.0f);
-                            } else if (qpair) {
-                                v.x = sum_over_halves(v.x);
-                                v.y = sum_over_halves(v.y);
-                                v.z = sum_over_halves(v.z);
-                                v.w = sum_over_halves(v.w);
-                            }
-                            const v4u o = {__float_as_uint(present(v.x + q_bias[h].x)), __float_as_uint(present(v.y + q_bias[h].y)),
-                                           __float_as_uint(present(v.z + q_bias[h].z)), __float_as_uint(present(v.w + q_bias[h].w))};
-                            __builtin_amdgcn_raw_buffer_store_b128(o, prs, q_at(h, act, 0), q_base(0), 16 /* sc1 */);
-                            if (q_unit[h] >= 0 && ((unsigned)act >> q_hyp() & 1u)) rg_l[q_unit[h]] = v;   // the four gates of one unit
-                        }
+                        if (h == 0 || nq > 4) look(h);   // uniform
                 }
             }
             const int ntq = (G + RT - 1) / RT;
@@ -2094,8 +2137,9 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     in_b2 = key(TJ, TR);
                 }
                 TR(20);
+                const bool to_stage = !PLANES || again || it != rank;   // (else phase Q has)
                 if constexpr (STAGED && !DIRECT) {
-                    if (TWO) stage_rows(xe, ev, true);
+                    if (TWO && to_stage) stage_rows(xe, ev, true);
                     if (load_p) {
                         if constexpr (LSTM) {
                             take_p(act, pv);
@@ -2116,7 +2160,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                         stage_rows(xe, ev, true);
                     }
                 } else {
-                    if (DIRECT) stage_rows(xe, ev, true);
+                    if (DIRECT && to_stage) stage_rows(xe, ev, true);
                     until_there([&]() __attribute__((always_inline)) {
                         unsigned mx = 0;
 #pragma unroll
@@ -2302,7 +2346,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             fresh();
             if (C > 1 && (!LSTM || again)) {   // (an LSTM's first pass: summed while the hidden state travelled)
                 --jpass;   // (finish_scores looks at the last pass)
-                if (wave == NW - 1) finish_scores();
+                    if (wave == NW - 1) finish_scores();
                 ++jpass;
             }
             // ---- gather the cells: a wavefront takes one row tile, or a share of its column groups;
@@ -2497,6 +2541,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             if (enough != 0) break;
         }
         if (!ok) break;
+        if constexpr (LAYERS == 1) request_gates();
         act_prev = act;
         first = false;
         par ^= 1;
@@ -2630,11 +2675,10 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     f.tq = label_tiles(f.nk);
     if (!lstm && item > f.tq) f.tq = first_tiles(w->dtype == 1, f.nk);
     if (lstm && w->pred_layers == 1) {
-        const int tiles = (w->h_joint + CT - 1) / CT + (w->h_pred + 3) / 4, per_wg = (tiles + C - 1) / C;
-        // one round, one row tile, one or two cells a thread
-        if (per_wg <= 2 * label_tiles(f.nk) && hyps_per_cluster <= RT && hyps_per_cluster * per_wg * 4 <= 2 * kLabelThreads) {
+        const int nt_a = (w->h_joint + CT - 1) / CT, nt_b = (w->h_pred + 3) / 4;
+        if (one_layer_form(f.nk, nt_a, nt_b, C, hyps_per_cluster, kLabelThreads)) {
             f.layers = 1;
-            if (per_wg > f.tq) f.tq *= 2;
+            if ((nt_a + nt_b + C - 1) / C > f.tq) f.tq *= 2;
         }
     }
     const int hpc = hyps_per_cluster;
@@ -2650,8 +2694,7 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
 static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C, int wide_part = kWidePart)
 {
     size_t n = 0;
-    if (w->dtype == 1 && f.layers == 1 && hyps_per_cluster <= kPairRows) n = (size_t)f.nk * 64;
-    else if (w->dtype == 1 && f.layers > 1 && f.nw < 8 && hyps_per_cluster <= kPackRows)
+    if (w->dtype == 1 && f.layers > 1 && f.nw < 8 && hyps_per_cluster <= kPackRows)
         n = (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t);
     if (f.nw == 8) {
         n += (size_t)f.nw * RT * wide_part * sizeof(float);

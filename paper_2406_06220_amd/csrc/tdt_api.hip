@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument checks, workspace layout, launches.
 #include <string.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "tdt_internal.h"
@@ -92,7 +93,7 @@ WorkspaceLayout workspace_layout(const tdt_weights_t *w, int B, int T)
     size_t cells = 16 * (4 * rows > (size_t)kMaxGrid ? 4 * rows : (size_t)kMaxGrid);
     if (cells < 16 * 16 * (size_t)kMaxGrid) cells = 16 * 16 * (size_t)kMaxGrid;
     size_t lab = L.partials;
-    lab = align_up(lab + 2 * lstm_layers * rows * w->h_pred * sizeof(float), 256);
+    lab = align_up(lab + std::max(2 * lstm_layers * rows * w->h_pred * sizeof(float), (size_t)(lstm_layers == 1 ? kPlanesMost : 0)), 256);
     if (lstm_layers > 0) lab = align_up(lab + 2 * rows * w->h_joint * sizeof(float), 256);
     lab = align_up(lab + 2 * kRowBufs * cells * sizeof(unsigned long long), 256);
     lab = align_up(lab + kRowBufs * 2 * 64 * rows * sizeof(unsigned long long), 256);
@@ -117,7 +118,11 @@ LabelLayout label_layout(const tdt_weights_t *w, bool wide, int n_clusters, int 
     L.cells_per_cluster = words.cells;
     size_t off = 0;
     L.ones_begin = L.hx = off;
-    if (lstm) off = align_up(off + 2 * (size_t)w->pred_layers * rows * w->h_pred * sizeof(float), 256);
+    const bool planes = lstm && w->dtype == 1 && w->pred_layers == 1 && !wide &&
+                        one_layer_form(label_nk(true, std::max(w->h_pred, w->h_joint)), (w->h_joint + 15) / 16, (w->h_pred + 3) / 4, C,
+                                       hyps_per_cluster, kLabelThreads);
+    if (planes) off = align_up(off + 2 * (size_t)n_clusters * plane_bytes(w->h_pred, hyps_per_cluster), 256);
+    else if (lstm) off = align_up(off + 2 * (size_t)w->pred_layers * rows * w->h_pred * sizeof(float), 256);
     L.px = off;
     if (lstm) off = align_up(off + 2 * rows * w->h_joint * sizeof(float), 256);
     L.ones_end = L.zero_begin = L.row_lab = off;

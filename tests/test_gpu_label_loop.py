@@ -272,6 +272,39 @@ def test_values_that_are_no_numbers(oracle_lib, gpu, kind):   # noqa: F811
         assert (a["labels"][b, :n] == g["labels"][b, :n]).all() and (a["frames"][b, :n] == g["frames"][b, :n]).all()
 
 
+@pytest.mark.parametrize("B,ncl", [(3, 1), (7, 1), (12, 1), (9, 3)])
+def test_a_carried_state_of_all_ones(gpu, B, ncl):   # noqa: F811
+    """The bit pattern that stands for what is not there yet, as the hidden state a caller hands in (a NaN): nobody waits
+    for it, and the other hypotheses' results are what they are without it."""
+    import torch
+    from paper_2406_06220_amd import binding
+    cfg = config(f"ll_ones_{B}_{ncl}", B=B, h_pred=72, T=12, len_lo=12, len_hi=12)
+    w = synth.generate_model(cfg)
+    enc, _ = synth.generate_inputs(cfg)
+    model = gpu.DeviceModel(cfg, w)
+    enc_d = model.upload_enc(enc)
+    ln = torch.full((B,), 6, dtype=torch.int32, device=model.device)
+    outs = []
+    for poisoned in (False, True):
+        state = binding.StreamState(model, B)
+        dec = binding.ChunkDecoder(model, B, 6, 6 * cfg.max_symbols, state, n_clusters=ncl)
+        dec(enc_d[:, :6].contiguous(), ln)
+        torch.cuda.synchronize()
+        if poisoned:
+            at = state.ptr - state.buf.data_ptr() + 4 * (-(-4 * B // 256) * 256)
+            h = state.buf[at:at + 4 * B * cfg.h_pred].view(torch.int32).view(B, cfg.h_pred)
+            h[B // 2] = -1
+            h[B - 1, 5:8] = -1
+        dec(enc_d[:, 6:].contiguous(), ln)
+        outs.append(dec.results())
+    clean, out = outs
+    assert out["stats"]["abort"] == 0 and not (out["status"] & gpu.TDT_HYP_ABORTED).any()
+    for b in range(B):
+        if b not in (B // 2, B - 1):
+            n = out["len"][b]
+            assert n == clean["len"][b] and (out["labels"][b, :n] == clean["labels"][b, :n]).all()
+
+
 # ------------------------------------------------------------------ waits that run out
 @pytest.mark.parametrize("kind,blank_bias,T", [("stateless", 1e4, 15), ("stateless", 1.0, 40), ("lstm", 1.0, 20)])
 def test_a_wait_of_the_label_loop_that_runs_out(oracle_lib, gpu, kind, blank_bias, T):   # noqa: F811
