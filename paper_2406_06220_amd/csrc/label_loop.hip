@@ -6,9 +6,9 @@
 // lengths (label_form), and is built for the length of the chain: an exchange between workgroups is about
 // 1.4 us whatever it carries, so what matters is how many dependent steps there are between them and how
 // few instructions each takes.  Config 2 at B = 32, a label with one joint pass, microseconds by a time line
-// of one workgroup: P 0.4; the pass set up while the hidden state travels 0.8, and 0.5 until it is there; Q
-// 1.7; on to the joint pass 0.4, and 0.8 until the projected output is there; J 2.8; cells gathered 1.2; D 1.4
-// with the top of the next label (10.1 with the time stamps; about 8 a label without).
+// of one workgroup: P 0.7; the pass set up while the hidden state travels 0.9, and 0.8 until it is there; Q
+// 1.1; on to the joint pass 0.5, and 0.6 until the projected output is there; J 2.9; cells gathered 1.1; D 1.6
+// with the top of the next label (10.2 with the time stamps; about 8 a label without).
 //
 //   * No barriers between workgroups.  Every exchanged word says itself whether it is there: rows
 //     of the hidden state and of the projected predictor output start out as a bit pattern that no
