@@ -775,7 +775,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // workgroups of 51 had all of W_pred (see pred_share).  Both with the encoder's rows staged early (planes_of), and the table
     // rows requested early (request_gates), us a call: config 2 at B = 1 528 / 503, B = 32 847 / 814, B = 128 2017 / 1942,
     // 32 chunked streams 1811 / 1732, TDT B = 7 289 / 274, B = 32 454 / 441.
-    const int RP = plane_rows(hpc), plane_step = 3 * RP * 64, plane_buffer = plane_bytes(Hp, hpc);
+    const int RP = plane_rows(hpc), hstep = plane_step(hpc), plane_buffer = plane_bytes(Hp, hpc);
     auto plane_base = [&](int buffer) { return (buffer * ncl + cl) * plane_buffer; };
     // Products of the first `count` tiles that `b` holds with the plane rows `v` (NT tiles of them), smallest terms first
     auto plane_products = [&](auto count, const auto &v, const auto &b, auto tiles, float *part) __attribute__((always_inline)) {
@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             if (U > 0 && idx < G * U) {
                 if constexpr (PLANES) {   // (of two neighbours the one stores the pairs of first and of last terms, the other those between)
                     const int k = u0 + c_u[h], odd = k & 1;
-                    h_off[h] = (k >> 5) * plane_step + ((k >> 3 & 3) * 3 * RP + odd * RP + c_g[h]) * 16 + (k & 6) * 2;
+                    h_off[h] = (k >> 5) * hstep + ((k >> 3 & 3) * 3 * RP + odd * RP + c_g[h]) * 16 + (k & 6) * 2;
                     if (!odd) h_off2[h] = h_off[h] + 2 * RP * 16;
                 } else {
                     h_off[h] = (c_g[h] * Hp + u0 + c_u[h]) * (int)sizeof(float);
@@ -1666,13 +1666,17 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             for (int s = 0; s < NK; ++s)   // (zeros where there is nothing)
                                 off[t][s] = row && s < hsn && (hs0 + s) * 32 + (lane >> 4) * 8 < Hp ? ((lane >> 4) * 3 * RP + r) * 16 : kNowhere;
                         }
-                        const int at = plane_base(par) + hs0 * plane_step;
+                        // (formed ahead of the loop that polls: in it they are a selection a step and turn, config 2 at B = 1 500 / 495 us)
+                        const int first_at = plane_base(par) + hs0 * hstep;
+                        int at[NK];
+#pragma unroll
+                        for (int s = 0; s < NK; ++s) at[s] = here(first_at + plane_step_at(hstep, hsn, s));
                         until_there([&]() __attribute__((always_inline)) {
                             unsigned mx = 0;
 #pragma unroll
                             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                                for (int s = 0; s < NK; ++s) v[t][s] = ldx4(hrs, off[t][s], at + s * plane_step);
+                                for (int s = 0; s < NK; ++s) v[t][s] = ldx4(hrs, off[t][s], at[s]);
                             if (rows_wait) {   // uniform
                                 stage_rows(xe, ev, true);
                                 rows_wait = false;

@@ -39,6 +39,11 @@ extern "C" void nowhere_c(int *out)
     const int v[3] = {kNowhere, kLabelLongest, label_nk(true, kLabelLongest) > 0 && label_nk(true, kLabelLongest + 1) == 0};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
+extern "C" void planes_c(int h_pred, int hpc, int steps, int s, int *out)
+{
+    const int v[3] = {plane_step(hpc), plane_bytes(h_pred, hpc), plane_step_at(plane_step(hpc), steps, s)};
+    for (int i = 0; i < 3; ++i) out[i] = v[i];
+}
 extern "C" void words_c(int wide, int durations, int n_clusters, int hpc, int C, long long *out)
 {
     const LabelWords w = label_words(wide != 0, durations != 0, n_clusters, hpc, C);
@@ -188,6 +193,30 @@ def test_usual_items(split):
             for hpc in (1, 2, 16, 63, 64):
                 for window in (0, 1, 8, 64):
                     assert -(-nt // C_) <= split.item_c(C_, nt, hpc, window, 0) <= nt
+
+
+@pytest.mark.parametrize("hpc", [1, 4, 5, 8, 9, 16])
+def test_no_step_of_the_hidden_state_lies_beyond_its_buffer(split, hpc):
+    """The scalar offset of every load of the hidden state's terms, over all widths, of steps that a wavefront has and of those
+    that are only compiled: never past the buffer's end, which the last buffer shares with the descriptor; and the steps that
+    wavefronts have are all there are, each once."""
+    out = (C.c_int * 3)()
+    for h_pred in range(8, 1025, 8):
+        steps = -(-h_pred // 32)
+        for nk in (5, 8):
+            if steps > 4 * nk:
+                continue
+            seen = []
+            for wave in range(4):
+                have = steps // 4 + (wave < steps % 4)
+                first = wave * (steps // 4) + min(wave, steps % 4)
+                for s in range(nk):
+                    split.planes_c(h_pred, hpc, have, s, out)
+                    step, size, at = out[0], out[1], first * out[0] + out[2]
+                    assert 0 <= at <= size, (h_pred, nk, wave, s)
+                    if s < have:
+                        seen.append(at)
+            assert seen == [i * step for i in range(steps)] and size == steps * step
 
 
 def label_groups(split, B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025, **asked):
