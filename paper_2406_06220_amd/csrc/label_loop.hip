@@ -795,15 +795,15 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         for (int t = 0; t < N; ++t) *reinterpret_cast<f32x4 *>(pw + t * CT) = c[t];
     };
 
-    // float32, one layer, up to eight rows: sixteen products of four columns and four rows at a time (v_mfma_f32_4x4x1_16b_f32,
+    // float32, one layer, few rows: sixteen products of four columns and four rows at a time (v_mfma_f32_4x4x1_16b_f32,
     // 8 cycles) instead of one of sixteen and sixteen over four inputs (32 cycles, four a step and tile, whatever
     // rows there are).  A lane's part of a fragment is column l % 16 and inputs l / 16 * 4 .. + 3 of the step, so the
     // products are those of four columns with four rows over one input in four, and every lane ends with its four
     // neighbouring columns of row l % 4 over a quarter of the wavefront's inputs.  Quarters are added up in pairs, and lie
     // in the partial sums as planes of up to eight rows do: half q of row i is row q * 8 + i.  Four rows at a time; a form of its
     // own, because rows for both kinds of products were 22 registers more than there are.  What bounds it are the matrix cores: four
-    // tiles and 160 inputs a wavefront took 5120 cycles, now 1280 per four rows.  Config 2's model in float32, B = 16, four
-    // rows a group, 1305 / 1179 us.  Error of 640 products against 64 bits, rms for a result of 1: 1.69e-7 / 1.27e-7 (shorter chains).
+    // tiles and 160 inputs a wavefront took 5120 cycles, now 1280 per four rows (see few_rows for which groups).  Config 2's model in
+    // float32, B = 16, four rows a group, 1305 / 1179 us.  Error of 640 products against 64 bits, rms for a result of 1: 1.69e-7 / 1.27e-7 (shorter chains).
     auto few_products = [&](const auto &b0, const auto &b1, auto tiles, float *part) __attribute__((always_inline)) {
         constexpr int PLD = decltype(tiles)::value * CT + 4, N = TWO_ROUNDS ? 2 * TR : TR;
 #pragma clang loop unroll(disable)
@@ -2637,12 +2637,12 @@ template <typename WT, int LAYERS, int NK, int NW, int TQ, int QROWS = RT> const
     return chunked ? (const void *)label_kernel<WT, LAYERS, true, NK, NW, TQ, QROWS>
                    : (const void *)label_kernel<WT, LAYERS, false, NK, NW, TQ, QROWS>;
 }
-template <typename WT, int NK> const void *label_fn(int layers, int tq, bool chunked, int hyps_per_cluster)
+template <typename WT, int NK> const void *label_fn(int layers, int tq, bool few, bool chunked)
 {
     constexpr int TR = label_tiles(NK);
     if (layers > 1) return label_form_of<WT, 2, NK, 4, TR>(chunked);
     if constexpr (Frags<WT>::PL == 1)
-        if (layers == 1 && hyps_per_cluster <= kPairRows)
+        if (layers == 1 && few)
             return tq > TR ? label_form_of<WT, 1, NK, 4, 2 * TR, kPairRows>(chunked) : label_form_of<WT, 1, NK, 4, TR, kPairRows>(chunked);
     if (layers == 1) return tq > TR ? label_form_of<WT, 1, NK, 4, 2 * TR>(chunked) : label_form_of<WT, 1, NK, 4, TR>(chunked);
     if constexpr (first_tiles(Frags<WT>::PL == 3, NK) > TR)
@@ -2676,19 +2676,21 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     }
     f.nk = label_nk(w->dtype == 1, kseg);
     if (f.nk == 0) return f;
+    bool few = false;
     f.tq = label_tiles(f.nk);
     if (!lstm && item > f.tq) f.tq = first_tiles(w->dtype == 1, f.nk);
     if (lstm && w->pred_layers == 1) {
         const int nt_a = (w->h_joint + CT - 1) / CT, nt_b = (w->h_pred + 3) / 4;
         if (one_layer_form(f.nk, nt_a, nt_b, C, hyps_per_cluster, kLabelThreads)) {
             f.layers = 1;
-            if ((nt_a + nt_b + C - 1) / C > f.tq) f.tq *= 2;
+            const int per_wg = (nt_a + nt_b + C - 1) / C;
+            few = few_rows(f.nk, per_wg, hyps_per_cluster);   // (float32)
+            if (per_wg > f.tq) f.tq *= 2;
         }
     }
-    const int hpc = hyps_per_cluster;
     if (w->dtype == 1)
-        f.fn = f.nk == 5 ? label_fn<uint16_t, 5>(f.layers, f.tq, chunked, hpc) : label_fn<uint16_t, 8>(f.layers, f.tq, chunked, hpc);
-    else f.fn = f.nk == 4 ? label_fn<float, 4>(f.layers, f.tq, chunked, hpc) : label_fn<float, 10>(f.layers, f.tq, chunked, hpc);
+        f.fn = f.nk == 5 ? label_fn<uint16_t, 5>(f.layers, f.tq, few, chunked) : label_fn<uint16_t, 8>(f.layers, f.tq, few, chunked);
+    else f.fn = f.nk == 4 ? label_fn<float, 4>(f.layers, f.tq, few, chunked) : label_fn<float, 10>(f.layers, f.tq, few, chunked);
     return f;
 }
 

@@ -107,6 +107,11 @@ CASES = [
     *[(config(f"ll_few_f32_k{h}_{hp}_{B}_{c}", dtype="fp32", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
       for h, hp, B, c in ((8, 8, 1, 1), (40, 616, 3, 1), (640, 632, 4, 1), (104, 640, 5, 1), (616, 24, 8, 1), (640, 640, 28, 4), (632, 640, 12, 4),
                           (256, 248, 8, 1), (48, 248, 80, 16), (240, 200, 128, 16))],
+    # ... the shorter reductions, three column tiles a workgroup, four and two rounds, one row to four; and what sixteen rows at a
+    # time stay for, two tiles and five rows
+    *[(config(f"ll_few_f32_short_k{h}_{hp}_{B}_{c}", dtype="fp32", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
+      for h, hp, B, c in ((192, 192, 12, 12), (192, 184, 48, 12), (184, 192, 34, 17), (48, 248, 64, 16), (16, 200, 42, 21), (192, 192, 24, 8),
+                          (192, 192, 60, 12))],
     # a stateless group of one workgroup by the size of the output layer, and one column beyond
     *[(config(f"ll_one_wg{v}", dtype="fp32", pred_kind="stateless", h_pred=24, vocab=v, B=300), {}) for v in (63, 64)],
     # the form of eight wavefronts: row tiles in pairs and one left over, columns that are no multiple of a

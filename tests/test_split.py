@@ -39,6 +39,7 @@ extern "C" void nowhere_c(int *out)
     const int v[3] = {kNowhere, kLabelLongest, label_nk(true, kLabelLongest) > 0 && label_nk(true, kLabelLongest + 1) == 0};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
+extern "C" int few_rows_c(bool bf16, int k, int per_wg, int hpc) { return few_rows(label_nk(bf16, k), per_wg, hpc); }
 extern "C" void planes_c(int h_pred, int hpc, int steps, int s, int *out)
 {
     const int v[3] = {plane_step(hpc), plane_bytes(h_pred, hpc), plane_step_at(plane_step(hpc), steps, s)};
@@ -217,6 +218,15 @@ def test_no_step_of_the_hidden_state_lies_beyond_its_buffer(split, hpc):
                     if s < have:
                         seen.append(at)
             assert seen == [i * step for i in range(steps)] and size == steps * step
+
+
+def test_rows_that_are_multiplied_four_at_a_time(split):
+    """float32, one LSTM layer: up to eight rows with the longer reductions; with the shorter ones, whose products of sixteen rows
+    are soon done, up to four and where they take more than half a round of column tiles."""
+    for k in (264, 640):
+        assert [split.few_rows_c(0, k, per, hpc) for per in (1, 4) for hpc in (1, 4, 5, 8, 9, 16)] == [1, 1, 1, 1, 0, 0] * 2
+    for k in (8, 120, 256):
+        assert [[split.few_rows_c(0, k, per, hpc) for hpc in (1, 4, 5, 8, 9)] for per in (1, 2, 3, 4, 5, 8)] == [[0] * 5] * 2 + [[1, 1, 0, 0, 0]] * 4
 
 
 def label_groups(split, B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025, **asked):
