@@ -1742,8 +1742,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 constexpr int TS = 2;
                 const int room = wide_tiles(p.wide_part), PLW = room * CT + 4;
                 v4u b[TS][NQ];
+                // (The scalar offset is made uniform by hand: the compiler does not see that it is, and put a loop over the wavefront's different
+                // values, of which there is one, around every request.  Joint width 1024, B = 32, one layer of 640 units 682 / 666 us, two 1110
+                // / 1074, in chunks 1863 / 1794; 1024 units, two layers, in chunks, where four registers were in scratch memory, 1970 / 1842.)
                 auto request = [&](int u, int s, int n, int base) __attribute__((always_inline)) {   // tile u of the n that start at base, or nothing
-                    const int w = base + (u < n ? u : 0) * hbytes + (hs0 + (s < hsn ? s : 0)) * 1024;
+                    const int w = uni(base + (u < n ? u : 0) * hbytes + (hs0 + (s < hsn ? s : 0)) * 1024);
                     b[u][s] = __builtin_amdgcn_raw_buffer_load_b128(wrs, u < n && s < hsn ? lane * 16 : ~0xff, w, 0);
                 };
                 auto request_all = [&](int n, int base) __attribute__((always_inline)) {

@@ -5,6 +5,7 @@ from __future__ import annotations
 import glob
 import os
 import re
+import struct
 import subprocess
 
 import pytest
@@ -107,3 +108,37 @@ def test_products_do_not_follow_what_makes_their_operands(big_kernel):
             for before, o in big_kernel[max(0, i - 2):i]:
                 if before.startswith("v_") and not before.startswith("v_mfma"):
                     assert not registers(o[0]) & needs, (before, o, op, operands)
+
+
+def scratch_bytes(library, directory):
+    """Bytes of scratch memory a lane of every kernel of a library takes, as its code objects say."""
+    data, magic, found, at = open(library, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}, -1
+    while (at := data.find(magic, at + 1)) >= 0:
+        n, = struct.unpack_from("<Q", data, at + len(magic))
+        entry = at + len(magic) + 8
+        for _ in range(n if n < 16 else 0):   # (more: the name alone, not a bundle)
+            off, size, length = struct.unpack_from("<QQQ", data, entry)
+            target = data[entry + 24:entry + 24 + length]
+            entry += 24 + length
+            if b"gfx950" in target and size:
+                path = directory / "code.o"
+                path.write_bytes(data[at + off:at + off + size])
+                notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(path)], check=True,
+                                       stdout=subprocess.PIPE, text=True).stdout
+                names = re.findall(r"^ +\.name: +(_Z\S+)$", notes, re.M)
+                sizes = re.findall(r"^ +\.private_segment_fixed_size: +(\d+)$", notes, re.M)
+                assert len(names) == len(sizes)
+                found.update(zip(names, map(int, sizes)))
+    return found
+
+
+def test_scratch_memory_of_the_label_loop(tmp_path):
+    """A value in scratch memory is a trip to memory in the middle of a label, so the forms of the kernel that have any are
+    known: chunks in float32 of larger groups with two rounds, and of one bfloat16 layer to 1024."""
+    if not os.path.exists(build.LIB):
+        pytest.skip("the library has not been built")
+    label = {n: b for n, b in scratch_bytes(build.LIB, tmp_path).items() if "label_kernel" in n}
+    assert len(label) > 40
+    known = ("IfLi1ELb1ELi10ELi4ELi4ELi16E", "ItLi1ELb1ELi8ELi4ELi2ELi16E")
+    for name, size in label.items():
+        assert size == 0 or (size <= 64 and any(k in name for k in known)), (name, size)
