@@ -259,8 +259,8 @@ struct LabelShared {
 // LAYERS: 0: stateless predictor; 1: one LSTM layer, a workgroup's column tiles fit one round and the
 // group one row tile (every thread then has fixed places to write its results to); 2: any LSTM.
 // NW: wavefronts.  Four, or (WIDE) eight for output layers of many thousands of columns, see wide_rows.
-// TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round; eight wavefronts: steps
-// of the predictor's reduction.
+// TQ: column tiles of a round of the predictor-side products; stateless: of a joint pass's first round; eight wavefronts: those of the
+// one round of one layer (wide_round), or the steps of the predictor's reduction, whose column tiles then are lists.
 // QROWS: most rows of the hidden state that are multiplied at once (kPairRows: see few_products).
 template <typename WT, int LAYERS, bool CHUNKED, int NK, int NW, int TQ, int QROWS>
 __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
@@ -275,8 +275,10 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr int TJ = LAYERS == 0 && !WIDE ? TQ : TR;        // ... per its first round
     constexpr int JH = TJ > 4 ? 2 : 1;                        // which is looked at four tiles, four columns a thread, at a time
     constexpr int QPR = THREADS / RT;                         // threads that share a row of a round, four columns each
-    static_assert(!WIDE || LAYERS != 1, "eight wavefronts: any LSTM or none");
-    constexpr int NQ = WIDE ? TQ : NK;                        // steps of the predictor's reduction
+    constexpr bool LISTS = WIDE && LSTM && TQ <= NK;          // eight wavefronts, the predictor's column tiles as lists
+    static_assert(!WIDE || (LAYERS != 1 && (!LSTM || LISTS || TQ * CT <= QPR * 4)), "eight wavefronts: any LSTM or none, a round is one pass of the threads");
+    constexpr bool ONE_ROUND = WIDE && LSTM && !LISTS;        // ... one layer and one round of them (wide_round)
+    constexpr int NQ = LISTS ? TQ : NK;                       // steps of the predictor's reduction
     constexpr int PLQ = TQ * CT + 4, PLJ = TJ * CT + 4;   // floats per row of the partial sums (padded: 16 rows, 64 banks)
     constexpr int KI = (NK * NW * KS + 255) / 256;  // 16-byte loads per lane for a whole row
     constexpr bool STAGED = stages_rows(LAYERS, NW);          // rows go through LDS, see stage_rows
@@ -364,7 +366,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     } else {
         if (tid < G) S.gid[tid] = b0 + tid;
     }
-    const int Hp = p.h_pred, L = DEEP ? p.pred_layers : 1;
+    const int Hp = p.h_pred, L = DEEP && !ONE_ROUND ? p.pred_layers : 1;
 
     // ---- LDS: in deeper LSTMs of few hypotheses the tile of packed rows (bfloat16); the partial sums of a round -- of the predictor side and of a joint
     // pass, which may start while the former are still read; every wavefront's staged rows (STAGED; eight
@@ -372,7 +374,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // pre-activations, cell state, (chunks) hidden state
     const int ldb = ActTile<WT>::row_elems(p.kseg_max);
     WT *const planes = reinterpret_cast<WT *>(dyn_lds);
-    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 && DEEP && !WIDE && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
+    float *const part_q = reinterpret_cast<float *>(dyn_lds + (PL == 3 && DEEP && !LISTS && hpc <= kPackRows ? RT * ldb * sizeof(WT) : 0));   // [NW][16][PLQ]
     float *const part_j = part_q + (LSTM && !WIDE ? NW * RT * PLQ : 0);                                              // [NW][16][PLJ]
     for (int i = tid; i < p.lds_bytes / 16; i += THREADS)
         reinterpret_cast<uint4 *>(dyn_lds)[i] = make_uint4(0, 0, 0, 0);
@@ -571,6 +573,22 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         constexpr int PLD = decltype(tiles)::value * CT + 4;
         constexpr int N = decltype(count)::value, NC = PL == 1 || PACKED || N < 4 ? 2 : 1;   // chains per tile
         float *const pw = part + (size_t)wave * RT * PLD + (lane & 15) * PLD + (lane >> 4) * 4;
+        if constexpr (WIDE) {   // (half the registers a lane: two tiles at a time; the other wavefront of the SIMD fills the gaps)
+#pragma unroll
+            for (int t = 0; t < N; t += 2) {
+                f32x4 c[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+                for (int s = 0; s < NK; ++s)
+#pragma unroll
+                    for (int pl = PACKED ? 0 : PL - 1; pl >= 0; --pl)
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) c[u] = F::mma(a[s][pl], b[t + u][s], c[u]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) *reinterpret_cast<f32x4 *>(pw + (t + u) * CT) = c[u];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
         f32x4 c[N][NC];
 #pragma unroll
         for (int t = 0; t < N; ++t)
@@ -594,7 +612,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     };
     auto products = [&](auto packed_tag, const AFrag (&a)[NK][PL], const auto &b, int n, auto tiles, int sn, float *part) __attribute__((always_inline)) {
         constexpr int TT = sizeof(b) / (NK * sizeof(v4u));
-        constexpr int H2 = TT / 2;
+        constexpr int H2 = WIDE ? (TT + 2) / 4 * 2 : TT / 2;   // (wide: pairs)
         const std::integral_constant<int, H2> half{};
         const std::integral_constant<int, TT> all{};
         if (n <= H2) products_of(packed_tag, half, a, b, tiles, sn, part);
@@ -764,7 +782,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             }
         }
     };
-    const bool qpack = PL == 3 && ((DEEP && !WIDE) || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
+    const bool qpack = PL == 3 && ((DEEP && !LISTS) || PLANES) && hpc <= kPackRows, qpair = FEW || (PLANES && !qpack && hpc <= kPairRows);
     // bfloat16, one layer: the hidden state travels as the three terms of its values, in the order in which the matrix cores
     // take them.  Whoever updates a cell splits it, once, and a reader of the exchange buffers has its operands in
     // registers as soon as they are there: no rows to change lanes, no split.  Plane row `pl * RP + g` is term pl of hypothesis g,
@@ -880,7 +898,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
         constexpr int NA = sizeof(a) / sizeof(a[0]);   // (steps: NQ)
         const int any = __ffsll((long long)in_tile) - 1;
         if (DEEP && qpack) {   // a wavefront takes a row
-            if constexpr (PL == 3 && DEEP && !WIDE) {
+            if constexpr (PL == 3 && DEEP && !LISTS) {
                 v4u v[KI];
                 const bool row = wave < kPackRows;   // uniform
                 const int off = (row0 + (row && ((in_tile >> wave) & 1ull) ? wave : any)) * Hp * (int)sizeof(float);
@@ -942,7 +960,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             const int g = (in_tile >> (lane & 15)) & 1ull ? lane & 15 : any;
             const int row = (row0 + tq * RT + g) * Hp * (int)sizeof(float);
 #pragma unroll
-            for (int s = 0; s < NA; ++s) off[s] = WIDE && s >= hsn ? kNowhere : row + part_of(s, hs0, Hp);
+            for (int s = 0; s < NA; ++s) off[s] = LISTS && s >= hsn ? kNowhere : row + part_of(s, hs0, Hp);
             until_there([&]() __attribute__((always_inline)) {
                 unsigned mx = 0;
 #pragma unroll
@@ -1738,7 +1756,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // label of two layers 30 us where it now takes 20: 8198 outputs, 640 units, B = 256, 27.7 / 25.4 ms; B = 110, 7.76
             // / 6.84 ms; B = 32, 3.53 / 3.40 ms; B = 1, 418 / 415 us.  Registers of four tiles are no faster (B = 256 25.6 ms, two
             // 25.5; B = 32 3.56, 3.41), nor is a compiled reduction of four steps where there are three (25.9).
-            if constexpr (WIDE && LSTM) {
+            if constexpr (LISTS) {
                 constexpr int TS = 2;
                 const int room = wide_tiles(p.wide_part), PLW = room * CT + 4;
                 v4u b[TS][NQ];
@@ -1915,7 +1933,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 }
             }
             // ---- deeper layers: W_ih . [h of the layer below] + what W_hh . h left here
-            if constexpr (DEEP && !WIDE)
+            if constexpr (DEEP && !LISTS)
 #pragma clang loop unroll(disable)
             for (int l = 0; l < L; ++l) {
                 const int row0 = (par * L + l) * Bw + b0;
@@ -1939,7 +1957,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                     const unsigned long long in_tile = act >> (tq * RT) & 0xffffull;
                     if (in_tile == 0ull) continue;   // nobody active here (uniform over the group)
                     if (!loaded) fetch_round(0, 0);   // while the rows are on their way
-                    loaded = top && n_all <= TQ;
+                    loaded = !WIDE && top && n_all <= TQ;
                     AFrag a[NK][PL];
                     any_value(a);
                     stage_h(a, row0, tq, in_tile);
@@ -2652,9 +2670,10 @@ template <typename WT, int NK> const void *label_fn(int layers, int tq, bool few
         if (tq > TR) return label_form_of<WT, 0, NK, 4, first_tiles(true, NK)>(chunked);
     return label_form_of<WT, 0, NK, 4, TR>(chunked);
 }
-const void *label_wide_fn(bool lstm, int pred_steps, bool chunked)   // (bfloat16)
+const void *label_wide_fn(bool lstm, int round, int pred_steps, bool chunked)   // (bfloat16)
 {
     if (!lstm) return label_form_of<uint16_t, 0, 4, 8, 4>(chunked);
+    if (round > 0) return label_form_of<uint16_t, 2, 4, 8, kWideRound>(chunked);
     return pred_steps <= 3 ? label_form_of<uint16_t, 2, 4, 8, 3>(chunked) : label_form_of<uint16_t, 2, 4, 8, 4>(chunked);
 }
 struct LabelForm {
@@ -2674,7 +2693,8 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
     const int kseg = label_kseg(w);
     if (wide) {
         f.nk = 4;
-        if (w->dtype == 1 && label_steps(true, kseg, f.nw) <= f.nk) f.fn = label_wide_fn(lstm, label_steps(true, w->h_pred, f.nw), chunked);
+        if (lstm && wide_round(w->pred_layers, (w->h_joint + CT - 1) / CT, (w->h_pred + 3) / 4, C)) f.tq = kWideRound;
+        if (w->dtype == 1 && label_steps(true, kseg, f.nw) <= f.nk) f.fn = label_wide_fn(lstm, f.tq, label_steps(true, w->h_pred, f.nw), chunked);
         return f;
     }
     f.nk = label_nk(w->dtype == 1, kseg);
@@ -2699,11 +2719,11 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
 
 }  // namespace
 
-// wide (f.nw == 8): with room for as many column tiles of partial sums as wide_part floats hold
+// lists of column tiles (f.nw == 8, f.tq == 0): with room for as many column tiles of partial sums as wide_part floats hold
 static size_t label_lds_bytes(const tdt_weights_t *w, const LabelForm &f, bool chunked, int hyps_per_cluster, int C, int wide_part = kWidePart)
 {
     size_t n = 0;
-    if (w->dtype == 1 && f.layers > 1 && f.nw < 8 && hyps_per_cluster <= kPackRows)
+    if (w->dtype == 1 && f.layers > 1 && (f.nw < 8 || f.tq > 0) && hyps_per_cluster <= kPackRows)
         n = (size_t)RT * ActTile<uint16_t>::row_elems(label_kseg(w)) * sizeof(uint16_t);
     if (f.nw == 8) {
         n += (size_t)f.nw * RT * wide_part * sizeof(float);
@@ -2746,7 +2766,7 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
 {
     // the LDS limit of a compiled form is raised once per device (to all a workgroup can have)
     static std::mutex mu;
-    static const void *ready[64][48];
+    static const void *ready[64][64];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
@@ -2760,19 +2780,19 @@ hipError_t launch_label(const DecodeParams &p, const tdt_weights_t *w, bool chun
     {
         std::lock_guard<std::mutex> lock(mu);
         int i = 0;
-        while (i < 48 && ready[dev][i] && ready[dev][i] != fn) ++i;
-        if (i == 48 || !ready[dev][i]) {
+        while (i < 64 && ready[dev][i] && ready[dev][i] != fn) ++i;
+        if (i == 64 || !ready[dev][i]) {
             e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)kLabelDynLds);
             if (e != hipSuccess) return e;
-            if (i < 48) ready[dev][i] = fn;
+            if (i < 64) ready[dev][i] = fn;
         }
     }
     DecodeParams pc = p;
     pc.kseg_max = label_kseg(w);
-    // (wide: the most column tiles a workgroup has of one matrix, or as many as LDS has room for)
+    // (lists: the most column tiles a workgroup has of one matrix, or as many as LDS has room for)
     int tiles = 0;
-    if (f.nw == 8 && f.layers > 0) {
+    if (f.nw == 8 && f.layers > 0 && f.tq == 0) {
         tiles = std::max(((w->h_joint + CT - 1) / CT + C - 1) / C, ((w->h_pred + 3) / 4 + C - 1) / C);
         tiles = std::min(tiles, kWideTiles);
         while (tiles > 0 && label_lds_bytes(w, f, chunked, p.hyps_per_cluster, C, wide_part(tiles)) > kLabelDynLds) --tiles;

@@ -128,8 +128,12 @@ CASES = [
     # four, reductions of three steps a wavefront and of four, one row tile and several
     *[(config(f"ll_wide_lists_{hp}_{n}_{B}_{c}", h_pred=hp, pred_layers=n, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2)),
        dict(n_clusters=c, joint_kernel=2))
-      for hp, n, B, c in ((640, 2, 64, 16), (768, 1, 40, 32), (776, 2, 40, 32), (1024, 3, 24, 16), (1000, 1, 70, 4), (40, 4, 150, 4),
-                          (648, 2, 100, 32), (16, 1, 3, 4))],
+      for hp, n, B, c in ((640, 2, 64, 16), (768, 1, 40, 32), (776, 2, 40, 32), (1024, 3, 24, 16), (1000, 1, 140, 8), (40, 4, 150, 4),
+                          (648, 2, 100, 32), (264, 1, 60, 16))],
+    # ... one layer and one round of them: six tiles a workgroup and one, workgroups without any, packed rows, one row tile and several
+    *[(config(f"ll_wide_round_k{h}_{hp}_{B}_{c}", h_joint=h, h_pred=hp, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2)),
+       dict(n_clusters=c, joint_kernel=2))
+      for h, hp, B, c in ((48, 640, 3, 8), (48, 640, 40, 8), (1024, 1000, 70, 4), (1000, 776, 4, 4), (48, 16, 3, 4), (264, 72, 250, 4), (640, 264, 130, 8))],
     (config("ll_wide_stateless", pred_kind="stateless", pred_layers=2, h_pred=48, vocab=700, B=40), dict(n_clusters=4, joint_kernel=2)),
     # deeper LSTMs on several row tiles
     (config("ll_deep", pred_layers=3, B=40), dict(n_clusters=2)),
@@ -224,6 +228,7 @@ KINDS = {
     "deep": (dict(B=9, pred_layers=3), {}),
     "fp32": (dict(B=9, dtype="fp32"), {}),
     "wide": (dict(B=20, vocab=600, durations=(0, 1, 2)), dict(n_clusters=4, joint_kernel=2)),
+    "wide_lists": (dict(B=20, pred_layers=2, vocab=600, durations=(0, 1, 2)), dict(n_clusters=4, joint_kernel=2)),
     "stateless": (dict(B=9, pred_kind="stateless", pred_layers=2, h_pred=48), {}),
     "stateless_items": (dict(B=12, pred_kind="stateless", pred_layers=2, h_pred=48, vocab=300), dict(n_clusters=1)),
     "stateless_eight": (dict(B=12, pred_kind="stateless", pred_layers=2, h_pred=48, vocab=1000), dict(n_clusters=12, joint_tiles=8)),

@@ -40,6 +40,7 @@ extern "C" void nowhere_c(int *out)
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
 extern "C" int few_rows_c(bool bf16, int k, int per_wg, int hpc) { return few_rows(label_nk(bf16, k), per_wg, hpc); }
+extern "C" int wide_round_c(int layers, int nt_a, int nt_b, int C) { return wide_round(layers, nt_a, nt_b, C) ? kWideRound : 0; }
 extern "C" void planes_c(int h_pred, int hpc, int steps, int s, int *out)
 {
     const int v[3] = {plane_step(hpc), plane_bytes(h_pred, hpc), plane_step_at(plane_step(hpc), steps, s)};
@@ -227,6 +228,26 @@ def test_rows_that_are_multiplied_four_at_a_time(split):
         assert [split.few_rows_c(0, k, per, hpc) for per in (1, 4) for hpc in (1, 4, 5, 8, 9, 16)] == [1, 1, 1, 1, 0, 0] * 2
     for k in (8, 120, 256):
         assert [[split.few_rows_c(0, k, per, hpc) for hpc in (1, 4, 5, 8, 9)] for per in (1, 2, 3, 4, 5, 8)] == [[0] * 5] * 2 + [[1, 1, 0, 0, 0]] * 4
+
+
+def test_one_round_of_eight_wavefronts(split):
+    """Where a workgroup's column tiles are said to be one round, no workgroup has more; with as many groups as batches of one
+    layer get by themselves that is four groups of 640 or of 1024 units, and not more of them."""
+    out = (C.c_int * 6)()
+    rounds = 0
+    for H in range(8, 1025, 72):
+        for Hp in range(8, 1025, 56):
+            for n in (1, 2, 7, 16, 32, 64, 128, 256):
+                nt_a, nt_b = -(-H // 16), -(-Hp // 4)
+                most = split.wide_round_c(1, nt_a, nt_b, n)
+                assert not split.wide_round_c(2, nt_a, nt_b, n)
+                rounds += most > 0
+                for rank in range(n if most else 0):
+                    split.pred_share_c(1, nt_a, nt_b, Hp, n, rank, out)
+                    assert out[1] + out[3] <= most, (H, Hp, n, rank)
+    assert rounds > 100
+    assert [split.wide_round_c(1, 40, 160, n) > 0 for n in (128, 64, 32, 16)] == [True, True, False, False]
+    assert [split.wide_round_c(1, 64, 256, n) > 0 for n in (128, 64, 32, 16)] == [True, True, False, False]
 
 
 def label_groups(split, B, dtype="bf16", kind="lstm", layers=1, H=640, Hp=640, n_out=1025, **asked):
