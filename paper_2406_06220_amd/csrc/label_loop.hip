@@ -2707,7 +2707,7 @@ LabelForm label_form(const tdt_weights_t *w, bool chunked, bool wide, int hyps_p
         if (one_layer_form(f.nk, nt_a, nt_b, C, hyps_per_cluster, kLabelThreads)) {
             f.layers = 1;
             const int per_wg = (nt_a + nt_b + C - 1) / C;
-            few = few_rows(f.nk, per_wg, hyps_per_cluster);   // (float32)
+            few = few_rows(f.nk, per_wg, hyps_per_cluster, w->h_pred);   // (float32)
             if (per_wg > f.tq) f.tq *= 2;
         }
     }

@@ -39,7 +39,7 @@ extern "C" void nowhere_c(int *out)
     const int v[3] = {kNowhere, kLabelLongest, label_nk(true, kLabelLongest) > 0 && label_nk(true, kLabelLongest + 1) == 0};
     for (int i = 0; i < 3; ++i) out[i] = v[i];
 }
-extern "C" int few_rows_c(bool bf16, int k, int per_wg, int hpc) { return few_rows(label_nk(bf16, k), per_wg, hpc); }
+extern "C" int few_rows_c(bool bf16, int k, int per_wg, int hpc, int h_pred) { return few_rows(label_nk(bf16, k), per_wg, hpc, h_pred); }
 extern "C" int wide_round_c(int layers, int nt_a, int nt_b, int C) { return wide_round(layers, nt_a, nt_b, C) ? kWideRound : 0; }
 extern "C" void planes_c(int h_pred, int hpc, int steps, int s, int *out)
 {
@@ -223,11 +223,13 @@ def test_no_step_of_the_hidden_state_lies_beyond_its_buffer(split, hpc):
 
 def test_rows_that_are_multiplied_four_at_a_time(split):
     """float32, one LSTM layer: up to eight rows with the longer reductions; with the shorter ones, whose products of sixteen rows
-    are soon done, up to four and where they take more than half a round of column tiles."""
-    for k in (264, 640):
-        assert [split.few_rows_c(0, k, per, hpc) for per in (1, 4) for hpc in (1, 4, 5, 8, 9, 16)] == [1, 1, 1, 1, 0, 0] * 2
-    for k in (8, 120, 256):
-        assert [[split.few_rows_c(0, k, per, hpc) for hpc in (1, 4, 5, 8, 9)] for per in (1, 2, 3, 4, 5, 8)] == [[0] * 5] * 2 + [[1, 1, 0, 0, 0]] * 4
+    are soon done, up to four, where they take more than half a round of column tiles and three steps or four a wavefront."""
+    for k, hp in ((264, 264), (264, 8), (640, 128), (640, 640)):
+        assert [split.few_rows_c(0, k, per, hpc, hp) for per in (1, 4) for hpc in (1, 4, 5, 8, 9, 16)] == [1, 1, 1, 1, 0, 0] * 2
+    for k, hp in ((136, 129), (256, 136), (256, 256)):
+        assert [[split.few_rows_c(0, k, per, hpc, hp) for hpc in (1, 4, 5, 8, 9)] for per in (1, 2, 3, 4, 5, 8)] == [[0] * 5] * 2 + [[1, 1, 0, 0, 0]] * 4
+    for k, hp in ((8, 8), (120, 120), (256, 128), (256, 64)):
+        assert not any(split.few_rows_c(0, k, per, hpc, hp) for hpc in (1, 4, 8) for per in (1, 3, 4, 8))
 
 
 def test_one_round_of_eight_wavefronts(split):
