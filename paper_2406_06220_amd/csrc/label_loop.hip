@@ -299,6 +299,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     constexpr bool PLANES = PL == 3 && LAYERS == 1;   // the hidden state travels as its terms, see plane_base
     constexpr bool FEW = QROWS < RT;                  // ... float32: see few_products
     static_assert(!FEW || (PL == 1 && LAYERS == 1 && QROWS == kPairRows), "few_products");
+    constexpr bool EARLY_GATES = LAYERS == 1 && (PL == 3 || FEW || !CHUNKED);   // see request_gates
     extern __shared__ __align__(16) unsigned char dyn_lds[];
     __shared__ LabelShared S;
 
@@ -1479,7 +1480,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     v4u bias0[JH], bias1[1];
     int in_b = -1, in_b2 = -1;
     // LAYERS == 1: the table rows of this thread's cells, by the last labels of their hypotheses.  They are requested as soon as a
-    // pass is known to be the label's last, ahead of what else is left to do of it.
+    // pass is known to be the label's last, ahead of what else is left to do of it -- but for chunks in float32 with more than few rows,
+    // where they are registers too many (640 units and joint width, B = 64, 1820 / 1809 us; 256, 1470 / 1455).
     v4u t4[2];
     any_value(t4);
     auto request_gates = [&]() __attribute__((always_inline)) {
@@ -1490,7 +1492,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                 t4[h] = *(const TDT_GLOBAL v4u *)(p.emb_gates + ((size_t)lab * Hp + u0 + c_u[h]) * 4);
             }
     };
-    if constexpr (LAYERS == 1) request_gates();
+    if constexpr (EARLY_GATES) request_gates();
 #pragma clang loop unroll(disable)
     while (ok) {   // ---- Alg. 3 line 5: while any hypothesis is active
         const unsigned long long alive = __ballot(active);
@@ -1535,6 +1537,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             // ---- P: the cell update (one or two units a thread).  W_ih * emb[label] + b is a table row, requested behind the decision
             // (request_gates); W_hh * h was formed by this workgroup when h was new.
             const bool two_cells = G * U > THREADS;   // uniform
+            if constexpr (!EARLY_GATES) request_gates();
             __builtin_amdgcn_sched_barrier(0);
             if (TWO_ROUNDS && !KEEPQ2) fetch_second(bq2);   // (they take about as long to leave as the row to arrive)
             __builtin_amdgcn_sched_barrier(0);
@@ -2566,7 +2569,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             if (enough != 0) break;
         }
         if (!ok) break;
-        if constexpr (LAYERS == 1) request_gates();
+        if constexpr (EARLY_GATES) request_gates();
         act_prev = act;
         first = false;
         par ^= 1;
