@@ -34,11 +34,12 @@
 //     for two rounds in bfloat16).  Scalar registers are short: 100 to 400 scalar values of a form are
 //     kept in lanes of vector registers and moved back where they are used.
 //   * Every wavefront multiplies its own quarter of the reduction for all column tiles.  So no two
-//     wavefronts need the same activation: each loads, waits for and splits its quarter of the rows, and
+//     wavefronts need the same activation: each loads and waits for its quarter of the rows, and
 //     only the partial sums are shared (rows staged in LDS for all wavefronts, with the barrier that
 //     takes: config 2 at B = 1 648 us against 610; stateless at B = 128 3.11 ms against 2.70).  Where there is
-//     one LSTM layer or none, a wavefront's rows change lanes through LDS of its own (stages_rows) and are
-//     split between the products of the step before (split_and_multiply).
+//     one LSTM layer or none, a wavefront's rows of a joint pass change lanes through LDS of its own (stages_rows) and are
+//     split between the products of the step before (split_and_multiply); so do rows of the hidden state in float32, while in
+//     bfloat16 with one layer they arrive as the operands they are multiplied as (plane_base).
 //
 // Reuse of the exchange buffers.  Every workgroup of a group publishes something in every joint
 // exchange (a workgroup without work item: a word of its own that everybody waits for), after it
@@ -226,7 +227,7 @@ __device__ inline float sigmoid(float x)
 // multiplies its own stretch of the reduction of all 16 rows, and lane l feeds part l / 16 of row l % 16.
 // Loaded like that, 16 lanes in a row ask for 16 different rows, and a compute unit takes in one 64-byte
 // piece a clock: 1.1 us for the 40 KB of 16 rows of 640 floats, twice or three times in every pass (rows
-// of the encoder, of the projected predictor output, of the hidden state).  Eight lanes on 128 bytes of a row
+// of the encoder, of the projected predictor output, in float32 of the hidden state).  Eight lanes on 128 bytes of a row
 // are four times as fast (0.33 us; 4 wavefronts x 10 loads of 16 bytes a lane, 256 workgroups, all from L2).
 // So rows are loaded that way and change lanes through LDS, in an area of the wavefront's own: no barrier.
 // With the split between the products below, one case timed alone on both sides: stateless at B = 128 2.74 -> 2.42
@@ -2374,7 +2375,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
             fresh();
             if (C > 1 && (!LSTM || again)) {   // (an LSTM's first pass: summed while the hidden state travelled)
                 --jpass;   // (finish_scores looks at the last pass)
-                    if (wave == NW - 1) finish_scores();
+                if (wave == NW - 1) finish_scores();
                 ++jpass;
             }
             // ---- gather the cells: a wavefront takes one row tile, or a share of its column groups;
