@@ -112,6 +112,10 @@ CASES = [
     *[(config(f"ll_few_f32_short_k{h}_{hp}_{B}_{c}", dtype="fp32", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
       for h, hp, B, c in ((192, 192, 12, 12), (192, 184, 48, 12), (184, 192, 34, 17), (48, 248, 64, 16), (16, 200, 42, 21), (192, 192, 24, 8),
                           (192, 192, 60, 12))],
+    # float32, nine to sixteen hypotheses a group and two rounds of phase Q: reductions of both lengths, a second round of one tile and of all
+    *[(config(f"ll_f32_rows_k{h}_{hp}_{B}_{c}", dtype="fp32", h_joint=h, h_pred=hp, B=B), dict(n_clusters=c))
+      for h, hp, B, c in ((640, 640, 40, 4), (640, 632, 64, 4), (584, 328, 45, 5), (48, 248, 150, 16), (256, 256, 208, 16), (40, 200, 230, 20),
+                          (240, 192, 300, 32))],
     # a stateless group of one workgroup by the size of the output layer, and one column beyond
     *[(config(f"ll_one_wg{v}", dtype="fp32", pred_kind="stateless", h_pred=24, vocab=v, B=300), {}) for v in (63, 64)],
     # the form of eight wavefronts: row tiles in pairs and one left over, columns that are no multiple of a
@@ -162,13 +166,28 @@ def test_label_loop_chunks(oracle_lib, gpu, kw):   # noqa: F811
     # the longer reductions: one round and two
     (dict(B=15, h_pred=648, h_joint=648), 2), (dict(B=9, h_pred=648, h_joint=648), 3),
     # a row tile of five to eight hypotheses, staged as planes, and a full one
-    (dict(B=8, h_pred=96), 1), (dict(B=13, h_pred=96), 1), (dict(B=16, h_pred=640, h_joint=640), 2)],
-    ids=["two_rounds", "fp32_two_rounds", "fp32_two_rounds_long", "long", "long_two_rounds", "planes", "full_tile", "planes_640"])
+    (dict(B=8, h_pred=96), 1), (dict(B=13, h_pred=96), 1), (dict(B=16, h_pred=640, h_joint=640), 2),
+    # float32, more than eight hypotheses a group: two rounds with reductions of both lengths, and one round
+    (dict(B=40, h_pred=640, h_joint=640, dtype="fp32"), 4), (dict(B=64, h_pred=640, h_joint=640, dtype="fp32"), 4),
+    (dict(B=150, h_pred=248, dtype="fp32"), 16), (dict(B=26, h_pred=328, h_joint=328, dtype="fp32"), 2), (dict(B=13, h_pred=96, dtype="fp32"), 1)],
+    ids=["two_rounds", "fp32_two_rounds", "fp32_two_rounds_long", "long", "long_two_rounds", "planes", "full_tile", "planes_640",
+         "fp32_rows_long", "fp32_rows_long_full", "fp32_rows", "fp32_rows_long_one_round", "fp32_rows_one_round"])
 def test_label_loop_chunks_of_one_layer(oracle_lib, gpu, kw, ncl):   # noqa: F811
     """The state that a chunk takes up and leaves, in the forms of one LSTM layer."""
     from test_gpu_chunks import check_chunks
     cfg = config("ll_chunks1", durations=(0, 1, 5), T=20, len_hi=20, **kw)
     check_chunks(oracle_lib, gpu, cfg, "random", 3, n_clusters=ncl)
+
+
+@pytest.mark.parametrize("hp,n,B,ncl", [(640, 2, 64, 16), (1024, 3, 24, 16), (1000, 1, 140, 8), (776, 2, 40, 32),   # lists
+                                         (1000, 1, 70, 4), (640, 1, 24, 8), (16, 1, 3, 4)])                          # one round
+def test_label_loop_chunks_of_eight_wavefronts(oracle_lib, gpu, hp, n, B, ncl):   # noqa: F811
+    """The state that a chunk takes up and leaves where the predictor's column tiles are lists -- of more tiles than there is room
+    for, reductions of three steps a wavefront and of four, one row tile and several -- and where they are one round, packed rows
+    and workgroups without tiles among them."""
+    from test_gpu_chunks import check_chunks
+    cfg = config(f"ll_wide_chunks_{hp}_{n}_{B}", h_pred=hp, pred_layers=n, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2))
+    check_chunks(oracle_lib, gpu, cfg, "random", 3, n_clusters=ncl, joint_kernel=2)
 
 
 # ------------------------------------------------------------------ hypotheses that do not wait for all searches
@@ -282,37 +301,63 @@ def test_values_that_are_no_numbers(oracle_lib, gpu, kind):   # noqa: F811
         assert (a["labels"][b, :n] == g["labels"][b, :n]).all() and (a["frames"][b, :n] == g["frames"][b, :n]).all()
 
 
-@pytest.mark.parametrize("B,ncl", [(3, 1), (7, 1), (12, 1), (9, 3)])
-def test_a_carried_state_of_all_ones(gpu, B, ncl):   # noqa: F811
+ONES = {
+    # one layer in bfloat16, whose hidden state travels as terms: packed, pairs, a full tile, several groups; reductions beyond 640
+    **{f"B{B}_{c}": (dict(B=B), dict(n_clusters=c)) for B, c in ((3, 1), (7, 1), (12, 1), (9, 3))},
+    "long": (dict(B=7, h_joint=648), dict(n_clusters=1)),
+    # float32: rows four at a time, sixteen
+    "fp32_few": (dict(B=7, dtype="fp32", h_joint=264), dict(n_clusters=1)),
+    "fp32": (dict(B=12, dtype="fp32", h_joint=264), dict(n_clusters=1)),
+    # deeper LSTMs, packed rows and not; eight wavefronts
+    "deep_packed": (dict(B=4, pred_layers=2), dict(n_clusters=1)),
+    "deep": (dict(B=20, pred_layers=2), dict(n_clusters=1)),
+    "wide": (dict(B=20, pred_layers=2), dict(n_clusters=4, joint_kernel=2)),
+    "wide_round": (dict(B=20), dict(n_clusters=4, joint_kernel=2)),
+    "wide_round_packed": (dict(B=6), dict(n_clusters=4, joint_kernel=2)),
+}
+
+
+@pytest.mark.parametrize("kind", ONES)
+def test_a_carried_state_of_all_ones(gpu, kind):   # noqa: F811
     """The bit pattern that stands for what is not there yet, as the hidden state a caller hands in (a NaN): nobody waits
-    for it, and the other hypotheses' results are what they are without it."""
+    for it, the hypotheses it was handed to keep a NaN, and the other hypotheses' results are what they are without it."""
     import torch
     from paper_2406_06220_amd import binding
-    cfg = config(f"ll_ones_{B}_{ncl}", B=B, h_pred=72, T=12, len_lo=12, len_hi=12)
+    kw, opts = ONES[kind]
+    cfg = config(f"ll_ones_{kind}", h_pred=72, T=12, len_lo=12, len_hi=12, **kw)
+    B = cfg.B
     w = synth.generate_model(cfg)
     enc, _ = synth.generate_inputs(cfg)
     model = gpu.DeviceModel(cfg, w)
     enc_d = model.upload_enc(enc)
     ln = torch.full((B,), 6, dtype=torch.int32, device=model.device)
-    outs = []
+    hit = (B // 2, B - 1)
+    outs, ends = [], []
     for poisoned in (False, True):
         state = binding.StreamState(model, B)
-        dec = binding.ChunkDecoder(model, B, 6, 6 * cfg.max_symbols, state, n_clusters=ncl)
+        dec = binding.ChunkDecoder(model, B, 6, 6 * cfg.max_symbols, state, **opts)
         dec(enc_d[:, :6].contiguous(), ln)
         torch.cuda.synchronize()
         if poisoned:
             at = state.ptr - state.buf.data_ptr() + 4 * (-(-4 * B // 256) * 256)
-            h = state.buf[at:at + 4 * B * cfg.h_pred].view(torch.int32).view(B, cfg.h_pred)
-            h[B // 2] = -1
-            h[B - 1, 5:8] = -1
+            h = state.buf[at:at + 4 * cfg.pred_layers * B * cfg.h_pred].view(torch.int32).view(cfg.pred_layers, B, cfg.h_pred)
+            before = state.download()
+            assert (h.cpu().numpy() == before["h"].view(np.int32)).all() and before["h"].any()
+            assert before["started"].all() and (before["time"] < 6).all()   # all of them bring their state along
+            h[:, hit[0]] = -1
+            h[:, hit[1], 5:8] = -1
         dec(enc_d[:, 6:].contiguous(), ln)
         outs.append(dec.results())
+        ends.append(state.download())
     clean, out = outs
     assert out["stats"]["abort"] == 0 and not (out["status"] & gpu.TDT_HYP_ABORTED).any()
+    lost = np.isnan(ends[1]["h"]).any(axis=2).any(axis=0)
     for b in range(B):
-        if b not in (B // 2, B - 1):
+        assert lost[b] == (b in hit) and not np.isnan(ends[0]["h"][:, b]).any(), b
+        if b not in hit:
             n = out["len"][b]
             assert n == clean["len"][b] and (out["labels"][b, :n] == clean["labels"][b, :n]).all()
+            assert (ends[1]["h"][:, b] == ends[0]["h"][:, b]).all() and (ends[1]["c"][:, b] == ends[0]["c"][:, b]).all()
 
 
 # ------------------------------------------------------------------ waits that run out
