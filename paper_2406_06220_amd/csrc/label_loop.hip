@@ -880,7 +880,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
 
     // what lane l reads of a whole row: inputs l*4 + kk*256 .. + 3, or the row's last ones again
     auto hoff = [&](int kk) { return min(lane * 4 + kk * 256, Hp - 4) * (int)sizeof(float); };
-    const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, PLANES ? (size_t)2 * ncl * plane_buffer : (size_t)2 * L * Bw * Hp * sizeof(float));
+    const __amdgpu_buffer_rsrc_t hrs = buffer_of(hx, PLANES ? (size_t)planes_covered(ncl, Hp, hpc, NK) : (size_t)2 * L * Bw * Hp * sizeof(float));
     const __amdgpu_buffer_rsrc_t prs = buffer_of(px, (size_t)2 * Bw * H * sizeof(float));
     const __amdgpu_buffer_rsrc_t brs = buffer_of(p.b_out, (size_t)O * sizeof(float));
     auto h_source = [&](int s, float (&x)[F::E]) __attribute__((always_inline)) {
@@ -1688,17 +1688,20 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
                             for (int s = 0; s < NK; ++s)   // (zeros where there is nothing)
                                 off[t][s] = row && s < hsn && (hs0 + s) * 32 + (lane >> 4) * 8 < Hp ? ((lane >> 4) * 3 * RP + r) * 16 : kNowhere;
                         }
-                        // (formed ahead of the loop that polls: in it they are a selection a step and turn, config 2 at B = 1 500 / 495 us)
+                        // (reductions to 640: formed ahead of the loop that polls; in it they are a selection a step and turn, config 2 at B = 1
+                        // 500 / 495 us.  Longer ones: see planes_covered.)
                         const int first_at = plane_base(par) + hs0 * hstep;
                         int at[NK];
+                        any_value(at);
+                        if constexpr (NK <= 5)
 #pragma unroll
-                        for (int s = 0; s < NK; ++s) at[s] = here(first_at + plane_step_at(hstep, hsn, s));
+                            for (int s = 0; s < NK; ++s) at[s] = here(first_at + plane_step_at(hstep, hsn, s));
                         until_there([&]() __attribute__((always_inline)) {
                             unsigned mx = 0;
 #pragma unroll
                             for (int t = 0; t < NT; ++t)
 #pragma unroll
-                                for (int s = 0; s < NK; ++s) v[t][s] = ldx4(hrs, off[t][s], at[s]);
+                                for (int s = 0; s < NK; ++s) v[t][s] = ldx4(hrs, off[t][s], NK <= 5 ? at[s] : first_at + s * hstep);
                             if (rows_wait) {   // uniform
                                 stage_rows(xe, ev, true);
                                 rows_wait = false;

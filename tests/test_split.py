@@ -41,6 +41,7 @@ extern "C" void nowhere_c(int *out)
 }
 extern "C" int few_rows_c(bool bf16, int k, int per_wg, int hpc, int h_pred) { return few_rows(label_nk(bf16, k), per_wg, hpc, h_pred); }
 extern "C" int wide_round_c(int layers, int nt_a, int nt_b, int C) { return wide_round(layers, nt_a, nt_b, C) ? kWideRound : 0; }
+extern "C" long long planes_covered_c(int n_clusters, int h_pred, int hpc, int nk) { return planes_covered(n_clusters, h_pred, hpc, nk); }
 extern "C" void planes_c(int h_pred, int hpc, int steps, int s, int *out)
 {
     const int v[3] = {plane_step(hpc), plane_bytes(h_pred, hpc), plane_step_at(plane_step(hpc), steps, s)};
@@ -219,6 +220,23 @@ def test_no_step_of_the_hidden_state_lies_beyond_its_buffer(split, hpc):
                     if s < have:
                         seen.append(at)
             assert seen == [i * step for i in range(steps)] and size == steps * step
+
+
+@pytest.mark.parametrize("hpc", [1, 4, 5, 8, 9, 16])
+def test_what_the_descriptor_of_the_terms_covers(split, hpc):
+    """Reductions over 640 leave the scalar offset of a compiled step that a wavefront does not have where it falls: always before the end
+    of what the descriptor covers, in the last group's second buffer as well.  Up to 640 it covers the buffers and nothing else."""
+    split.planes_covered_c.restype = C.c_longlong
+    out = (C.c_int * 3)()
+    for h_pred in range(8, 1025, 8):
+        steps, n = -(-h_pred // 32), 64 // hpc
+        split.planes_c(h_pred, hpc, steps, 0, out)
+        step, size = out[0], out[1]
+        covered = split.planes_covered_c(n, h_pred, hpc, 8)
+        for wave in range(4):
+            first = wave * (steps // 4) + min(wave, steps % 4)
+            assert (2 * n - 1) * size + (first + 7) * step < covered <= 2 * n * size + 8 * step
+        assert split.planes_covered_c(n, h_pred, hpc, 5) == 2 * n * size
 
 
 def test_rows_that_are_multiplied_four_at_a_time(split):
