@@ -132,8 +132,8 @@ CASES = [
     # four, reductions of three steps a wavefront and of four, one row tile and several
     *[(config(f"ll_wide_lists_{hp}_{n}_{B}_{c}", h_pred=hp, pred_layers=n, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2)),
        dict(n_clusters=c, joint_kernel=2))
-      for hp, n, B, c in ((640, 2, 64, 16), (768, 1, 40, 32), (776, 2, 40, 32), (1024, 3, 24, 16), (1000, 1, 140, 8), (40, 4, 150, 4),
-                          (648, 2, 100, 32), (264, 1, 60, 16))],
+      for hp, n, B, c in ((640, 2, 64, 16), (768, 1, 40, 32), (776, 2, 40, 32), (1024, 3, 24, 16), (1000, 1, 70, 4), (40, 4, 150, 4),
+                          (648, 2, 100, 32), (16, 1, 3, 4), (1000, 1, 140, 8), (264, 1, 60, 16))],
     # ... one layer and one round of them: six tiles a workgroup and one, workgroups without any, packed rows, one row tile and several
     *[(config(f"ll_wide_round_k{h}_{hp}_{B}_{c}", h_joint=h, h_pred=hp, vocab=700, B=B, T=14, len_hi=14, durations=(0, 1, 2)),
        dict(n_clusters=c, joint_kernel=2))
@@ -301,6 +301,39 @@ def test_values_that_are_no_numbers(oracle_lib, gpu, kind):   # noqa: F811
         assert (a["labels"][b, :n] == g["labels"][b, :n]).all() and (a["frames"][b, :n] == g["frames"][b, :n]).all()
 
 
+@pytest.mark.parametrize("B,ncl", [(3, 1), (7, 1), (12, 1), (9, 3)])
+def test_a_carried_state_of_all_ones(gpu, B, ncl):   # noqa: F811
+    """The bit pattern that stands for what is not there yet, as the hidden state a caller hands in (a NaN): nobody waits
+    for it, and the other hypotheses' results are what they are without it."""
+    import torch
+    from paper_2406_06220_amd import binding
+    cfg = config(f"ll_ones_{B}_{ncl}", B=B, h_pred=72, T=12, len_lo=12, len_hi=12)
+    w = synth.generate_model(cfg)
+    enc, _ = synth.generate_inputs(cfg)
+    model = gpu.DeviceModel(cfg, w)
+    enc_d = model.upload_enc(enc)
+    ln = torch.full((B,), 6, dtype=torch.int32, device=model.device)
+    outs = []
+    for poisoned in (False, True):
+        state = binding.StreamState(model, B)
+        dec = binding.ChunkDecoder(model, B, 6, 6 * cfg.max_symbols, state, n_clusters=ncl)
+        dec(enc_d[:, :6].contiguous(), ln)
+        torch.cuda.synchronize()
+        if poisoned:
+            at = state.ptr - state.buf.data_ptr() + 4 * (-(-4 * B // 256) * 256)
+            h = state.buf[at:at + 4 * B * cfg.h_pred].view(torch.int32).view(B, cfg.h_pred)
+            h[B // 2] = -1
+            h[B - 1, 5:8] = -1
+        dec(enc_d[:, 6:].contiguous(), ln)
+        outs.append(dec.results())
+    clean, out = outs
+    assert out["stats"]["abort"] == 0 and not (out["status"] & gpu.TDT_HYP_ABORTED).any()
+    for b in range(B):
+        if b not in (B // 2, B - 1):
+            n = out["len"][b]
+            assert n == clean["len"][b] and (out["labels"][b, :n] == clean["labels"][b, :n]).all()
+
+
 ONES = {
     # one layer in bfloat16, whose hidden state travels as terms: packed, pairs, a full tile, several groups; reductions beyond 640
     **{f"B{B}_{c}": (dict(B=B), dict(n_clusters=c)) for B, c in ((3, 1), (7, 1), (12, 1), (9, 3))},
@@ -318,7 +351,7 @@ ONES = {
 
 
 @pytest.mark.parametrize("kind", ONES)
-def test_a_carried_state_of_all_ones(gpu, kind):   # noqa: F811
+def test_a_carried_state_of_all_ones_is_taken_up(gpu, kind):   # noqa: F811
     """The bit pattern that stands for what is not there yet, as the hidden state a caller hands in (a NaN): nobody waits
     for it, the hypotheses it was handed to keep a NaN, and the other hypotheses' results are what they are without it."""
     import torch
