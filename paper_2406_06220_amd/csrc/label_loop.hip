@@ -793,7 +793,7 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // at (lane / 16 * 3 RP + r) * 16.  Absent is a pair of terms that are all ones, which no two terms are: a NaN is stored as the one of
     // which they are not.  Before, every reader had rows of float32 change lanes through LDS and split them, and ten
     // workgroups of 51 had all of W_pred (see pred_share).  Both with the encoder's rows staged early (planes_of), and the table
-    // rows requested early (request_gates), us a call: config 2 at B = 1 528 / 503, B = 32 847 / 814, B = 128 2017 / 1942,
+    // rows requested early (request_gates), us a call on the same utterances: config 2 at B = 1 528 / 503, B = 32 847 / 814, B = 128 2017 / 1942,
     // 32 chunked streams 1811 / 1732, TDT B = 7 289 / 274, B = 32 454 / 441.
     const int RP = plane_rows(hpc), hstep = plane_step(hpc), plane_buffer = plane_bytes(Hp, hpc);
     auto plane_base = [&](int buffer) { return (buffer * ncl + cl) * plane_buffer; };
@@ -823,7 +823,8 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void label_kernel(DecodeParams p)
     // in the partial sums as planes of up to eight rows do: half q of row i is row q * 8 + i.  Four rows at a time; a form of its
     // own, because rows for both kinds of products were 22 registers more than there are.  What bounds it are the matrix cores: four
     // tiles and 160 inputs a wavefront took 5120 cycles, now 1280 per four rows (see few_rows for which groups).  Config 2's model in
-    // float32, B = 16, four rows a group, 1305 / 1179 us.  Error of 640 products against 64 bits, rms for a result of 1: 1.69e-7 / 1.27e-7 (shorter chains).
+    // float32, B = 16, four rows a group, 1305 / 1179 us.  Error of 640 products against 64 bits, rms for a result of 1: 1.69e-7 / 1.27e-7 (shorter
+    // chains: tests/test_sum_orders.py forms both sums).
     auto few_products = [&](const auto &b0, const auto &b1, auto tiles, float *part) __attribute__((always_inline)) {
         constexpr int PLD = decltype(tiles)::value * CT + 4, N = TWO_ROUNDS ? 2 * TR : TR;
 #pragma clang loop unroll(disable)
